@@ -148,7 +148,7 @@ struct gsc_ctx {
     uint32_t cache_tiles = 0, cache_pairs = 0;
     uint64_t cache_items = 0;
     // device scratch
-    DevBuf views, views_all, cov, keys, vals, keys_alt, vals_alt, counts, offsets, rec0, rec1, rec2,
+    DevBuf views, views_all, cov, keys, vals, keys_alt, vals_alt, counts, offsets, rec,
         sort_scratch, pkeys, pvals, pkeys_alt, pvals_alt, ranges, vs, gamma, bbar, misc, order, queues,
         coef_t, factor, img, stat, wbuf, post, vsdet, chk, obs;
     bool order_valid = false;  // `order` holds the tile order of the current binning
@@ -171,9 +171,9 @@ struct gsc_ctx {
     size_t ev_used = 0;
     struct Mark { int stage; hipEvent_t a, b; uint32_t launches; };
     std::vector<Mark> marks;
-    std::array<DevBuf*, 33> bufs() {
+    std::array<DevBuf*, 31> bufs() {
         return {&views, &views_all, &cov, &keys, &vals, &keys_alt, &vals_alt, &counts,
-                &offsets, &rec0, &rec1, &rec2, &sort_scratch, &pkeys, &pvals, &pkeys_alt,
+                &offsets, &rec, &sort_scratch, &pkeys, &pvals, &pkeys_alt,
                 &pvals_alt, &ranges, &vs, &gamma, &bbar, &misc, &order, &queues, &coef_t,
                 &factor, &img, &stat, &wbuf, &post, &vsdet, &chk, &obs};
     }
@@ -417,6 +417,13 @@ const uint32_t* tile_order(const gsc_ctx* ctx, uint32_t n_tiles) {
     return ctx->order.as<uint32_t>() + n_tiles;
 }
 
+// The tile lists left by the current binning of nv views.
+TileLists tile_lists(const gsc_ctx* ctx, int nv, const Binned& bn) {
+    return TileLists{ctx->views.as<ViewInfo>(), nv,  bn.n_tiles, ctx->bin, ctx->ranges.as<uint2>(),
+                     ctx->pvals.as<uint32_t>(), ctx->rec.as<float4>(), ctx->vals.as<uint32_t>(),
+                     tile_order(ctx, bn.n_tiles)};
+}
+
 // Project, depth-sort, emit and tile-sort the views [v0, v0+nv) of `all`.
 // The batch's ViewInfo table is uploaded to ctx->views (tile_base local to
 // the batch).  Synchronises `s` once to read the pair count.
@@ -457,9 +464,7 @@ gsc_status bin_views(gsc_ctx* ctx, const ViewInfo* all, int v0, int nv,
     GSC_HIP(ctx->vals_alt.ensure(4 * items + 4));
     GSC_HIP(ctx->counts.ensure(4 * items + 4));
     GSC_HIP(ctx->offsets.ensure(4 * items + 4));
-    GSC_HIP(ctx->rec0.ensure(16 * items + 16));
-    GSC_HIP(ctx->rec1.ensure(16 * items + 16));
-    GSC_HIP(ctx->rec2.ensure(8 * items + 8));
+    GSC_HIP(ctx->rec.ensure(32 * items + 32));
     GSC_HIP(ctx->ranges.ensure(sizeof(uint2) * (tiles + 1)));
     const ViewInfo* dviews = ctx->views.as<ViewInfo>();
     {
@@ -480,8 +485,7 @@ gsc_status bin_views(gsc_ctx* ctx, const ViewInfo* all, int v0, int nv,
         // projection in depth order: records and counts land at the depth rank
         StageTimer t(ctx, s, GSC_STAGE_PROJECT);
         launch_project(dviews, nv, ni, ctx->vals.as<uint32_t>(), ctx->cov.as<float>(), bp,
-                       ctx->counts.as<uint32_t>(), ctx->rec0.as<float4>(), ctx->rec1.as<float4>(),
-                       ctx->rec2.as<uint2>(), ctx->bin, s);
+                       ctx->counts.as<uint32_t>(), ctx->rec.as<float4>(), ctx->bin, s);
         GSC_LAUNCHED("project");
     }
     StageTimer* scan_t = new StageTimer(ctx, s, GSC_STAGE_SCAN);
@@ -512,8 +516,7 @@ gsc_status bin_views(gsc_ctx* ctx, const ViewInfo* all, int v0, int nv,
     {
         StageTimer t(ctx, s, GSC_STAGE_EMIT);
         launch_emit(dviews, nv, ctx->vals.as<uint32_t>(), ctx->offsets.as<uint32_t>(),
-                    ctx->counts.as<uint32_t>(), ctx->rec0.as<float4>(),
-                    ctx->rec1.as<float4>(), bp, ni, (uint32_t)tiles, ctx->pkeys.as<uint32_t>(),
+                    ctx->counts.as<uint32_t>(), ctx->rec.as<float4>(), bp, ni, (uint32_t)tiles, ctx->pkeys.as<uint32_t>(),
                     ctx->pvals.as<uint32_t>(), ctx->bin, s);
         GSC_LAUNCHED("emit");
     }
@@ -719,11 +722,11 @@ struct gsc_plan {
     bool acc_persistent = false;      // persistent work-queue accumulate
     float tune_ms[8] = {};
     int tune_variant[8] = {};
-    DevBuf d_views, cov, keys, vals, keys_alt, vals_alt, counts, offsets, rec0, rec1,
-        rec2, sort_scratch, pkeys, pvals, pkeys_alt, pvals_alt, ranges, vs, misc, queues, order, obs;
+    DevBuf d_views, cov, keys, vals, keys_alt, vals_alt, counts, offsets, rec,
+        sort_scratch, pkeys, pvals, pkeys_alt, pvals_alt, ranges, vs, misc, queues, order, obs;
     ~gsc_plan() {
         DevBuf* all[] = {&d_views, &cov, &keys, &vals, &keys_alt, &vals_alt, &counts,
-                         &offsets, &rec0, &rec1, &rec2, &sort_scratch, &pkeys, &pvals, &pkeys_alt,
+                         &offsets, &rec, &sort_scratch, &pkeys, &pvals, &pkeys_alt,
                          &pvals_alt, &ranges, &vs, &misc, &queues, &order, &obs};
         for (DevBuf* b : all) b->release();
     }
@@ -744,8 +747,7 @@ gsc_status validate_cameras(const gsc_camera* cams, int32_t n_cams) {
 gsc_status plan_count_pairs(gsc_plan* P, const gsc_plan::Batch& b, hipStream_t s, uint64_t* pairs) {
     const ViewInfo* dv = P->d_views.as<ViewInfo>() + b.v0;
     launch_project(dv, b.nv, b.n_items, nullptr, P->cov.as<float>(), P->bp,
-                   P->counts.as<uint32_t>(), P->rec0.as<float4>(), P->rec1.as<float4>(),
-                   P->rec2.as<uint2>(), P->bin, s);
+                   P->counts.as<uint32_t>(), P->rec.as<float4>(), P->bin, s);
     GSC_LAUNCHED("project");
     unsigned long long* d64 = reinterpret_cast<unsigned long long*>(P->misc.as<char>() + 24);
     launch_fill_u32(reinterpret_cast<uint32_t*>(d64), 0u, 2, s);
@@ -780,14 +782,12 @@ void plan_number_views(gsc_plan* P) {
 
 gsc_status plan_accumulate(gsc_plan* P, const gsc_plan::Batch& b, const void* targets, int tdtype,
                            int chunk, bool persistent, hipStream_t s) {
-    const ViewInfo* dv = P->d_views.as<ViewInfo>() + b.v0;
     unsigned long long* d_counter = reinterpret_cast<unsigned long long*>(P->misc.p);
-    launch_accumulate_chunked(dv, b.nv, b.n_tiles, P->ranges.as<uint2>(), P->pvals.as<uint32_t>(),
-                              P->rec0.as<float4>(), P->rec1.as<float4>(), P->rec2.as<uint2>(),
-                              P->bin, targets, tdtype, P->C,
-                              P->per_view, P->bp, P->vs.as<float>(), d_counter, nullptr, chunk, s,
-                              persistent ? P->queues.as<uint32_t>() : nullptr,
-                              P->order.as<uint32_t>() + b.n_tiles);
+    const TileLists tl{P->d_views.as<ViewInfo>() + b.v0, b.nv, b.n_tiles, P->bin, P->ranges.as<uint2>(),
+                       P->pvals.as<uint32_t>(), P->rec.as<float4>(), P->vals.as<uint32_t>(),
+                       P->order.as<uint32_t>() + b.n_tiles};
+    launch_accumulate(tl, targets, tdtype, P->C, P->per_view, P->bp, P->vs.as<float>(), d_counter, nullptr,
+                      chunk, s, persistent ? P->queues.as<uint32_t>() : nullptr);
     GSC_LAUNCHED("accumulate");
     return GSC_OK;
 }
@@ -813,8 +813,7 @@ gsc_status plan_bin_batch(gsc_plan* P, const gsc_plan::Batch& b, hipStream_t s) 
     {
         StageTimer t(ctx, s, GSC_STAGE_PROJECT);
         launch_project(dv, b.nv, b.n_items, P->vals.as<uint32_t>(), P->cov.as<float>(),
-                       P->bp, P->counts.as<uint32_t>(), P->rec0.as<float4>(), P->rec1.as<float4>(),
-                       P->rec2.as<uint2>(), P->bin, s);
+                       P->bp, P->counts.as<uint32_t>(), P->rec.as<float4>(), P->bin, s);
         GSC_LAUNCHED("project");
     }
     {
@@ -826,7 +825,7 @@ gsc_status plan_bin_batch(gsc_plan* P, const gsc_plan::Batch& b, hipStream_t s) 
     {
         StageTimer t(ctx, s, GSC_STAGE_EMIT);
         launch_emit(dv, b.nv, P->vals.as<uint32_t>(), P->offsets.as<uint32_t>(),
-                    P->counts.as<uint32_t>(), P->rec0.as<float4>(), P->rec1.as<float4>(), P->bp,
+                    P->counts.as<uint32_t>(), P->rec.as<float4>(), P->bp,
                     b.n_items, b.n_tiles, P->pkeys.as<uint32_t>(), P->pvals.as<uint32_t>(), P->bin, s,
                     b.pair_cap, d_drop);
         GSC_LAUNCHED("emit");
@@ -1060,7 +1059,7 @@ gsc_status colorize_core(gsc_ctx* ctx, const float* means, const float* scales,
     if (det) {
         GSC_HIP(ctx->vsdet.ensure(8 * vs_words));
         launch_fill_u32(ctx->vsdet.as<uint32_t>(), 0u, 2 * vs_words, s);
-        acc_vs = ctx->vsdet.as<float>();  // 64-bit words, see launch_accumulate_chunked
+        acc_vs = ctx->vsdet.as<float>();  // 64-bit words, see launch_accumulate
     } else {
         launch_fill_u32(ctx->vs.as<uint32_t>(), 0u, vs_words, s);
     }
@@ -1076,15 +1075,13 @@ gsc_status colorize_core(gsc_ctx* ctx, const float* means, const float* scales,
         // blocks in index order), the matrix-core form as a persistent grid
         // taking tiles from a work queue (each measured the faster for it).
         uint32_t* queues = nullptr;
-        const uint32_t* order = tile_order(ctx, bn.n_tiles);
-        if (order != nullptr && (chunk & kChunkMfma)) {
+        const TileLists tl = tile_lists(ctx, nv, bn);
+        if (tl.order != nullptr && (chunk & kChunkMfma)) {
             GSC_HIP(ctx->queues.ensure(4 * (size_t)(kMaxC + 1)));
             queues = ctx->queues.as<uint32_t>();
         }
-        launch_accumulate_chunked(ctx->views.as<ViewInfo>(), nv, bn.n_tiles, ctx->ranges.as<uint2>(),
-                                  ctx->pvals.as<uint32_t>(), ctx->rec0.as<float4>(), ctx->rec1.as<float4>(),
-                                  ctx->rec2.as<uint2>(), ctx->bin, targets, tdtype, C, per_view, bp,
-                                  acc_vs, d_counter, x_cnt, chunk, s, queues, order, det ? &dsc : nullptr);
+        launch_accumulate(tl, targets, tdtype, C, per_view, bp, acc_vs, d_counter, x_cnt, chunk, s, queues,
+                          det ? &dsc : nullptr);
         GSC_LAUNCHED("accumulate");
         return GSC_OK;
     });
@@ -1328,25 +1325,19 @@ gsc_status gsc_colorize_refine(gsc_ctx* ctx, const float* means, const float* sc
             GSC_HIP(ctx->gamma.ensure(4 * (size_t)nv * (size_t)N * (size_t)C));
             int max_px = 0;
             for (int k = 0; k < nv; ++k) max_px = std::max(max_px, all[v0 + k].width * all[v0 + k].height);
-            const uint32_t* order = tile_order(ctx, bn.n_tiles);
+            const TileLists tl = tile_lists(ctx, nv, bn);
             StageTimer t(ctx, s, GSC_STAGE_BLEND);
             launch_view_colors(ctx->views.as<ViewInfo>(), nv, (uint32_t)bn.n_items, means,
                                ctx->coef_t.as<float>(), N, C, sh_deg, ctx->gamma.as<float>(), s);
-            launch_render(ctx->views.as<ViewInfo>(), nv, bn.n_tiles, ctx->ranges.as<uint2>(),
-                          ctx->pvals.as<uint32_t>(), ctx->rec0.as<float4>(), ctx->rec1.as<float4>(),
-                          ctx->rec2.as<uint2>(), ctx->bin, ctx->gamma.as<float>(), C, bp,
-                          ctx->img.as<float>(), d_pass_counter, s, order);
+            launch_render(tl, ctx->gamma.as<float>(), C, bp, ctx->img.as<float>(), d_pass_counter, s);
             launch_residual(ctx->views.as<ViewInfo>(), nv, max_px, targets, tdtype, C, ctx->img.as<float>(), s);
             uint32_t* queues = nullptr;
-            if (order != nullptr && (chunk & kChunkMfma)) {
+            if (tl.order != nullptr && (chunk & kChunkMfma)) {
                 GSC_HIP(ctx->queues.ensure(4 * (size_t)(kMaxC + 1)));
                 queues = ctx->queues.as<uint32_t>();
             }
-            launch_accumulate_chunked(ctx->views.as<ViewInfo>(), nv, bn.n_tiles, ctx->ranges.as<uint2>(),
-                                      ctx->pvals.as<uint32_t>(), ctx->rec0.as<float4>(),
-                                      ctx->rec1.as<float4>(), ctx->rec2.as<uint2>(), ctx->bin,
-                                      ctx->img.as<float>(), GSC_F32, C, per_view, bp, ctx->vs.as<float>(),
-                                      d_pass_counter, nullptr, chunk, s, queues, order);
+            launch_accumulate(tl, ctx->img.as<float>(), GSC_F32, C, per_view, bp, ctx->vs.as<float>(),
+                              d_pass_counter, nullptr, chunk, s, queues);
             GSC_LAUNCHED("refinement pass");
             (void)v0;
             return GSC_OK;
@@ -1401,9 +1392,7 @@ gsc_status gsc_render(gsc_ctx* ctx, const float* means, const float* scales, con
         launch_view_colors(ctx->views.as<ViewInfo>(), nv, (uint32_t)bn.n_items, means,
                            ctx->coef_t.as<float>(), N, C, sh_deg, ctx->gamma.as<float>(), s);
         GSC_LAUNCHED("view colors");
-        launch_render(ctx->views.as<ViewInfo>(), nv, bn.n_tiles, ctx->ranges.as<uint2>(),
-                      ctx->pvals.as<uint32_t>(), ctx->rec0.as<float4>(), ctx->rec1.as<float4>(), ctx->rec2.as<uint2>(), ctx->bin,
-                      ctx->gamma.as<float>(), C, bp, images, d_counter, s, tile_order(ctx, bn.n_tiles));
+        launch_render(tile_lists(ctx, nv, bn), ctx->gamma.as<float>(), C, bp, images, d_counter, s);
         GSC_LAUNCHED("render");
         return GSC_OK;
     });
@@ -1455,10 +1444,7 @@ gsc_status gsc_colorize_backward(gsc_ctx* ctx, const float* means, const float* 
                           [&](int v0, int nv, const Binned& bn) -> gsc_status {
         StageTimer t(ctx, s, GSC_STAGE_BLEND);
         (void)v0;
-        launch_accumulate_weights(ctx->views.as<ViewInfo>(), nv, bn.n_tiles, ctx->ranges.as<uint2>(),
-                                  ctx->pvals.as<uint32_t>(), ctx->rec0.as<float4>(),
-                                  ctx->rec1.as<float4>(), ctx->rec2.as<uint2>(), ctx->bin, per_view, bp, ctx->vs.as<float>(),
-                                  d_counter, s, tile_order(ctx, bn.n_tiles));
+        launch_accumulate_weights(tile_lists(ctx, nv, bn), per_view, bp, ctx->vs.as<float>(), d_counter, s);
         GSC_LAUNCHED("accumulate weights");
         last = bn;
         return GSC_OK;
@@ -1493,10 +1479,8 @@ gsc_status gsc_colorize_backward(gsc_ctx* ctx, const float* means, const float* 
         launch_view_adjoint(ctx->views.as<ViewInfo>(), nv, (uint32_t)bn.n_items, means, d_coef_t,
                             d_bbar_t, N, d_rho, C, sh_deg, false, ctx->gamma.as<float>(), s);
         GSC_LAUNCHED("view adjoint");
-        launch_blend_adjoint(ctx->views.as<ViewInfo>(), nv, bn.n_tiles, ctx->ranges.as<uint2>(),
-                             ctx->pvals.as<uint32_t>(), ctx->rec0.as<float4>(), ctx->rec1.as<float4>(), ctx->rec2.as<uint2>(), ctx->bin,
-                             targets, tdtype, C, ctx->gamma.as<float>(), bp, grad_targets,
-                             grad_opacities, s, tile_order(ctx, bn.n_tiles));
+        launch_blend_adjoint(tile_lists(ctx, nv, bn), targets, tdtype, C, ctx->gamma.as<float>(), bp,
+                             grad_targets, grad_opacities, s);
         GSC_LAUNCHED("blend adjoint");
         return GSC_OK;
     };
@@ -1559,10 +1543,8 @@ gsc_status gsc_render_backward(gsc_ctx* ctx, const float* means, const float* sc
             // forward accumulate with dL/dimages in place of the targets
             StageTimer t(ctx, s, GSC_STAGE_BLEND);
             (void)v0;
-            launch_accumulate(ctx->views.as<ViewInfo>(), nv, bn.n_tiles, ctx->ranges.as<uint2>(),
-                              ctx->pvals.as<uint32_t>(), ctx->rec0.as<float4>(), ctx->rec1.as<float4>(), ctx->rec2.as<uint2>(), ctx->bin,
-                              grad_images, GSC_F32, C, per_view, bp, ctx->vs.as<float>(),
-                              d_counter, nullptr, s, tile_order(ctx, bn.n_tiles));
+            launch_accumulate(tile_lists(ctx, nv, bn), grad_images, GSC_F32, C, per_view, bp, ctx->vs.as<float>(),
+                              d_counter, nullptr, 0, s);
             GSC_LAUNCHED("accumulate");
         }
         if (grad_opacities) {
@@ -1572,11 +1554,8 @@ gsc_status gsc_render_backward(gsc_ctx* ctx, const float* means, const float* sc
                                 ctx->coef_t.as<float>(), nullptr, N, nullptr, C, sh_deg, true,
                                 ctx->gamma.as<float>(), s);
             GSC_LAUNCHED("view colours");
-            launch_blend_adjoint(ctx->views.as<ViewInfo>(), nv, bn.n_tiles, ctx->ranges.as<uint2>(),
-                                 ctx->pvals.as<uint32_t>(), ctx->rec0.as<float4>(),
-                                 ctx->rec1.as<float4>(), ctx->rec2.as<uint2>(), ctx->bin, grad_images, GSC_F32, C,
-                                 ctx->gamma.as<float>(), bp, nullptr, grad_opacities, s,
-                                 tile_order(ctx, bn.n_tiles));
+            launch_blend_adjoint(tile_lists(ctx, nv, bn), grad_images, GSC_F32, C, ctx->gamma.as<float>(), bp,
+                                 nullptr, grad_opacities, s);
             GSC_LAUNCHED("blend adjoint");
         }
         return GSC_OK;
@@ -1694,9 +1673,7 @@ gsc_status gsc_plan_create(gsc_ctx* ctx, const gsc_scene* scenes, int32_t n_scen
     GSC_HIP(P->vals_alt.ensure(4 * mi + 4));
     GSC_HIP(P->counts.ensure(4 * mi + 4));
     GSC_HIP(P->offsets.ensure(4 * mi + 4));
-    GSC_HIP(P->rec0.ensure(16 * mi + 16));
-    GSC_HIP(P->rec1.ensure(16 * mi + 16));
-    GSC_HIP(P->rec2.ensure(8 * mi + 8));
+    GSC_HIP(P->rec.ensure(32 * mi + 32));
     GSC_HIP(P->d_views.ensure(sizeof(ViewInfo) * std::max<size_t>(P->views.size(), 1)));
     if (!P->views.empty())
         GSC_HIP(hipMemcpyAsync(P->d_views.p, P->views.data(), sizeof(ViewInfo) * P->views.size(),
@@ -1970,10 +1947,7 @@ gsc_status gsc_select_views(gsc_ctx* ctx, const float* means, const float* scale
                                 [&](int v0, int nv, const Binned& bn) -> gsc_status {
             StageTimer t(ctx, s, GSC_STAGE_BLEND);
             (void)v0;
-            launch_accumulate_weights(ctx->views.as<ViewInfo>(), nv, bn.n_tiles, ctx->ranges.as<uint2>(),
-                                      ctx->pvals.as<uint32_t>(), ctx->rec0.as<float4>(),
-                                      ctx->rec1.as<float4>(), ctx->rec2.as<uint2>(), ctx->bin, true, bp,
-                                      ctx->vs.as<float>(), d_counter, s, tile_order(ctx, bn.n_tiles));
+            launch_accumulate_weights(tile_lists(ctx, nv, bn), true, bp, ctx->vs.as<float>(), d_counter, s);
             GSC_LAUNCHED("accumulate weights");
             return GSC_OK;
         });

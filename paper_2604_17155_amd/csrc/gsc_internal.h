@@ -81,18 +81,20 @@ struct BlendParams {
     float alpha_min, alpha_max, t_min, cut2, dilation, znear;
 };
 
-// Splat record of one (view, Gaussian) item i = v * N + g, two float4:
+// Splat record of the item of depth rank k, two float4 at rec[2k], rec[2k+1]
+// (one 32-byte access per random gather):
 //   r0 = (u_hi, v_hi, u_lo, v_lo)   projected mean as FP32 hi/lo pairs
 //   r1 = (K*cxx, 2*K*cxy, K*cyy, opacity) with the conic (cxx, cxy, cyy) =
 //        Sigma_2D^{-1} pre-scaled by K = -log2(e)/2, so that
 //        q2 = K*q = r1.x dx^2 + r1.y dx dy + r1.z dy^2 and exp(-q/2) = exp2(q2).
 constexpr double kExp2Scale = -0.72134752044448170368;  // -0.5 * log2(e)
 
-// Bin pairs carry the item index in the low 26 bits and a 4-bit mask above:
-// 16-pixel bins: which 16x4 pixel bands (rows 4k..4k+3 of the tile) the
-// footprint reaches; 32-pixel bins: which of the bin's four 16x16 tiles
-// (bit 2 * row half + column half).  The tile kernels run one wave per
-// 16x16 tile: (bin / 16)^2 waves per bin.
+// Bin pairs carry the depth rank in the low 26 bits and a 4-bit mask above:
+// which quadrants of the bin the footprint reaches (bit 2 * row half + column
+// half).  The tile kernels run one wave per 16x16 tile, which takes its pixels
+// in four blocks of 8x8: for 16-pixel bins the bin is the tile and the mask
+// names its blocks; for 32-pixel bins it names the bin's four tiles, and the
+// blocks are found when the records are gathered (entry_blocks).
 constexpr uint32_t kItemBits = 26;
 constexpr uint32_t kItemMask = (1u << kItemBits) - 1u;
 
@@ -115,20 +117,35 @@ void launch_depth_keys(const ViewInfo* views, int n_views, uint32_t n_items, con
                        hipStream_t s);
 
 // Projection in depth order: position k handles item i = order[k] (k if order
-// is null) and writes counts[k] and, when counts[k] > 0, rec0/rec1[k] and
-// rec2[k] = (first | last << 16, i): the pixel rows of the footprint and the
-// item (records are only ever read through tile pairs).
+// is null) and writes counts[k] and, when counts[k] > 0, the record rec[2k],
+// rec[2k + 1] (records are only ever read through tile pairs).
 void launch_project(const ViewInfo* views, int n_views, uint32_t n_items, const uint32_t* order,
-                    const float* geo, BlendParams bp, uint32_t* counts, float4* rec0, float4* rec1,
-                    uint2* rec2, int bin, hipStream_t s);
+                    const float* geo, BlendParams bp, uint32_t* counts, float4* rec, int bin,
+                    hipStream_t s);
 
 // Pairs of the depth-ordered records: pair values carry the depth rank k.
 // Pairs at offsets >= cap are dropped and counted in *overflow (if given).
 void launch_emit(const ViewInfo* views, int n_views, const uint32_t* sorted_vals,
-                 const uint32_t* offsets, const uint32_t* counts, const float4* rec0,
-                 const float4* rec1, BlendParams bp, uint32_t n_items, uint32_t n_tiles,
-                 uint32_t* pair_keys, uint32_t* pair_vals, int bin, hipStream_t s,
-                 uint32_t cap = 0xFFFFFFFFu, uint32_t* overflow = nullptr);
+                 const uint32_t* offsets, const uint32_t* counts, const float4* rec, BlendParams bp,
+                 uint32_t n_items, uint32_t n_tiles, uint32_t* pair_keys, uint32_t* pair_vals,
+                 int bin, hipStream_t s, uint32_t cap = 0xFFFFFFFFu, uint32_t* overflow = nullptr);
+
+// The tile lists of a view batch, as the tile kernels read them: bin b's
+// entries are pair_vals[ranges[b].x .. ranges[b].y), front to back; an entry
+// names depth rank k, whose record is rec[2k], rec[2k + 1] and whose batch
+// item is items[k].  order (optional): the bins in the order their tiles are
+// taken (launch_tile_order).
+struct TileLists {
+    const ViewInfo* views;
+    int n_views;
+    uint32_t n_bins;
+    int bin;  // bin size in pixels
+    const uint2* ranges;
+    const uint32_t* pair_vals;
+    const float4* rec;
+    const uint32_t* items;
+    const uint32_t* order;
+};
 
 // Sum of n uint32 counts into *out (u64, must be zeroed).
 void launch_sum_u64(const uint32_t* counts, uint32_t n, unsigned long long* out, hipStream_t s);
@@ -185,32 +202,21 @@ int resolve_chunk(int requested, int C, int tdtype);
 
 // Accumulate V_gj and S_gj into slot (view.vs_base + g) when per_view, else
 // into slot (view.g_offset + g), summed over views; slots hold C+1 floats.
-void launch_accumulate(const ViewInfo* views, int n_views, uint32_t n_tiles, const uint2* ranges,
-                       const uint32_t* pair_vals, const float4* rec0, const float4* rec1, const uint2* rec2, int bin,
-                       const void* targets, int tdtype, int C, bool per_view, BlendParams bp,
-                       float* VS, unsigned long long* counter, uint32_t* gcount, hipStream_t s,
-                       const uint32_t* order = nullptr);
-
-// As launch_accumulate with accumulate variant `chunk` (1, 2, 3, 4, 8 or 16
-// channels per launch, or kChunkMfma | 16, 32 or 64 for BF16 targets;
-// anything else picks accumulate_chunk(C, tdtype)).  queues (device, one word per
-// channel pass, zeroed here by a fill kernel): persistent launches of
-// kPersistentBlocks blocks that take tiles from a counter; nullptr: one
-// block per four tiles.  order (device, optional, with queues): the bins in
-// the order their tiles are taken (launch_tile_order).
-constexpr uint32_t kPersistentBlocks = 2048;  // 8 blocks of 4 waves per CU
-bool accumulate_chunk_valid(int chunk, int tdtype);
-void launch_accumulate_chunked(const ViewInfo* views, int n_views, uint32_t n_tiles,
-                               const uint2* ranges, const uint32_t* pair_vals, const float4* rec0,
-                               const float4* rec1, const uint2* rec2, int bin, const void* targets, int tdtype, int C,
-                               bool per_view, BlendParams bp, float* VS,
-                               unsigned long long* counter, uint32_t* gcount, int chunk,
-                               hipStream_t s, uint32_t* queues = nullptr,
-                               const uint32_t* order = nullptr, const float2* det = nullptr);
+// chunk: the accumulate variant (1, 2, 3, 4, 8 or 16 channels per launch, or
+// kChunkMfma | 16, 32 or 64 for BF16 targets; anything else picks
+// accumulate_chunk(C, tdtype)).  queues (device, one word per channel pass,
+// zeroed here by a fill kernel): persistent launches of kPersistentBlocks
+// blocks that take tiles from a counter; nullptr: one block per four tiles.
 // det (non-null): deterministic form.  VS holds 64-bit fixed-point words
 // (zero before the first launch); each tile's share is scaled by det->x
 // (visibility column) or det->y (channel columns), powers of two, and added
 // with integer atomics.  Vector form only (a matrix-core chunk falls back).
+constexpr uint32_t kPersistentBlocks = 2048;  // 8 blocks of 4 waves per CU
+bool accumulate_chunk_valid(int chunk, int tdtype);
+void launch_accumulate(const TileLists& tl, const void* targets, int tdtype, int C, bool per_view,
+                       BlendParams bp, float* VS, unsigned long long* counter, uint32_t* gcount,
+                       int chunk, hipStream_t s, uint32_t* queues = nullptr,
+                       const float2* det = nullptr);
 
 // out[k][r] = in[r][k] (rows x K row-major in, K x rows row-major out).
 void launch_transpose(const float* in, int64_t rows, int K, float* out, hipStream_t s);
@@ -223,11 +229,8 @@ void launch_view_colors(const ViewInfo* views, int n_views, uint32_t n_items, co
                         const float* coeffs_t, int64_t ldn, int C, int sh_deg, float* gamma,
                         hipStream_t s);
 
-void launch_render(const ViewInfo* views, int n_views, uint32_t n_tiles, const uint2* ranges,
-                   const uint32_t* pair_vals, const float4* rec0, const float4* rec1, const uint2* rec2, int bin,
-                   const float* gamma, int C, BlendParams bp, float* images,
-                   unsigned long long* counter, hipStream_t s,
-                       const uint32_t* order = nullptr);
+void launch_render(const TileLists& tl, const float* gamma, int C, BlendParams bp, float* images,
+                   unsigned long long* counter, hipStream_t s);
 
 // Fold the per-view sums into the regularised normal equations and solve.
 // per_view: VS holds [n_views][N][C+1] (else [N][C+1] summed over views).
@@ -269,11 +272,8 @@ void launch_residual(const ViewInfo* views, int n_views, int max_pixels, const v
                      int C, float* img, hipStream_t s);
 
 // Weights-only accumulate: V[slot] += sum_p w (stride 1; slots as in launch_accumulate).
-void launch_accumulate_weights(const ViewInfo* views, int n_views, uint32_t n_tiles,
-                               const uint2* ranges, const uint32_t* pair_vals, const float4* rec0,
-                               const float4* rec1, const uint2* rec2, int bin, bool per_view, BlendParams bp, float* V,
-                               unsigned long long* counter, hipStream_t s,
-                       const uint32_t* order = nullptr);
+void launch_accumulate_weights(const TileLists& tl, bool per_view, BlendParams bp, float* V,
+                               unsigned long long* counter, hipStream_t s);
 
 // Adjoint solve: bbar = (A_g + w_g Lambda)^{-1} grad_coeffs and
 // rho_g = sum lambda_m bbar[m][c] coeffs[m][c].  V holds per-view
@@ -294,11 +294,8 @@ void launch_view_adjoint(const ViewInfo* views, int n_views, uint32_t n_items, c
 
 // Blend adjoint over the binned tiles: grad_y[row][c] = sum_g w beta (every
 // pixel of every view written, if grad_y) and grad_o[g] += dL/do (atomics, if grad_o).
-void launch_blend_adjoint(const ViewInfo* views, int n_views, uint32_t n_tiles, const uint2* ranges,
-                          const uint32_t* pair_vals, const float4* rec0, const float4* rec1, const uint2* rec2, int bin,
-                          const void* ypix, int ydtype, int C, const float* beta, BlendParams bp,
-                          float* grad_y, float* grad_o, hipStream_t s,
-                       const uint32_t* order = nullptr);
+void launch_blend_adjoint(const TileLists& tl, const void* ypix, int ydtype, int C, const float* beta,
+                          BlendParams bp, float* grad_y, float* grad_o, hipStream_t s);
 
 // grad_coeffs[g][m][c] = sum_j phi_gj[m] S_gj[c] from per-view sums [n_views][N][C+1].
 void launch_fold_rhs(const ViewInfo* views, int n_views, const float* means, const float* VS,

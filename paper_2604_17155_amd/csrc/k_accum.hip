@@ -1,13 +1,13 @@
 // Fused per-tile blend + accumulate (the hot loop).
 //
-// One wave64 owns one 16x16 tile; lane l handles the four pixels
-// (l%16, l/16 + 4k), k = 0..3.  The tile's Gaussians arrive in front-to-back
+// One wave64 owns one 16x16 tile; lane l handles pixel (l%8, l/8) of each of
+// its four 8x8 blocks.  The tile's Gaussians arrive in front-to-back
 // order (eq. 2).  Each lane blends its pixels in FP32; per Gaussian the wave
 // reduces sum_p w and sum_p w*y_p over the tile (the per-view visibility V_gj
 // of eq. 5 and the numerator of eq. 6) with DPP row reductions, and one
 // atomic per value adds the tile's share to the (view, Gaussian) slot.
-// Splat records for the next 64 list entries are loaded one per lane and
-// broadcast with v_readlane, so the loop needs no LDS and no barriers.
+// Splat records for the next 64 list entries are loaded one per lane and read
+// back from the wave's own LDS slots, so the loop needs no block barrier.
 #include <type_traits>
 
 #include "gsc_internal.h"
@@ -38,16 +38,14 @@ __device__ __forceinline__ void vs_add(float* VS, float* p, float v, float scale
 // Gaussian's tile share of V and S (channels [c_off, c_off + CC) of C) to its
 // slot.  Returns the wave's accepted contributions (uniform).
 //
-// A pixel that stopped has T < t_min (outside the image it starts at kOutsideT).  Bands of
-// four pixel rows are skipped when the Gaussian's footprint misses them (bits
-// of the pair value) or when none of their pixels is live; the wave ends when
-// no band is live.
+// A pixel that stopped has T < t_min (outside the image it starts at
+// kOutsideT).  Blocks are skipped when the Gaussian's footprint misses them or
+// when none of their pixels is live; the wave ends when no block is live.
 template <int CC, bool BF16, int BIN, bool DET>
 __device__ __forceinline__ uint32_t accumulate_tile(
     uint32_t tile, uint32_t lane, const ViewInfo* __restrict__ views, int n_views,
     const uint2* __restrict__ ranges, const uint32_t* __restrict__ pair_vals,
-    const float4* __restrict__ rec0, const float4* __restrict__ rec1,
-    const uint2* __restrict__ rec2,
+    const float4* __restrict__ rec, const uint32_t* __restrict__ items,
     const void* __restrict__ targets, int C, int c_off, int per_view, const BlendParams& bp,
     float* __restrict__ VS, float2 dsc, uint32_t* __restrict__ gcount, float4* __restrict__ lrec1,
     float2* __restrict__ lrec0) {
@@ -57,16 +55,14 @@ __device__ __forceinline__ uint32_t accumulate_tile(
     // view fields read once (plain values: the conditions below need no branch)
     const int vw = V.width, vh = V.height;
     const int64_t poff = V.pixel_offset;
-    const int ix = tg.x0 + (int)(lane & 15);
-    const int iy0 = tg.y0 + (int)(lane >> 4);
     const int stride = C + 1;
 
     float T[4];
     float y[4][CCA];
-    uint32_t alive = 0;  // bit k: band k has a live pixel (wave-uniform)
+    uint32_t alive = 0;  // bit k: block k has a live pixel (wave-uniform)
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-        const int iy = iy0 + 4 * k;
+        const int ix = tg.x0 + block_px(lane, k), iy = tg.y0 + block_py(lane, k);
         const bool inside = (ix < vw) & (iy < vh);
         T[k] = inside ? 1.0f : kOutsideT;
         alive |= (__builtin_amdgcn_ballot_w64(inside) != 0 ? 1u : 0u) << k;
@@ -94,11 +90,9 @@ __device__ __forceinline__ uint32_t accumulate_tile(
     const float qlim = uniform_in_vgpr((float)(kExp2Scale * (double)bp.cut2));  // q <= cut2  <=>  q2 >= qlim
     const float amax = uniform_in_vgpr(bp.alpha_max), amin = uniform_in_vgpr(bp.alpha_min),
                 tmin = uniform_in_vgpr(bp.t_min);
-    // the lane's pixel column and rows within the tile
-    const float lx = tile_offset_col(lane);
-    float lyk[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) lyk[k] = tile_offset_row(lane, k);
+    // the lane's pixel offsets from the tile's centre point
+    const float lx[2] = {tile_offset_col(lane, 0), tile_offset_col(lane, 1)};
+    const float ly[2] = {tile_offset_row(lane, 0), tile_offset_row(lane, 1)};
 
     // The list is walked in chunks of 64 entries.  A chunk's records are
     // gathered at once, one entry per lane, and broadcast entry by entry with
@@ -112,13 +106,13 @@ __device__ __forceinline__ uint32_t accumulate_tile(
     // offset is then that plus its pixel's offset from the point
     // (tile_offset_col / tile_offset_row).
     const float ox = tile_centre(tg.x0), oy = tile_centre(tg.y0);
-    auto gather = [&](uint32_t pv, uint32_t b, float2& R0, float4& R1, uint2& R2) {
+    auto gather = [&](uint32_t pv, uint32_t b, float2& R0, float4& R1, uint32_t& gi) {
         const uint32_t it = pv & kItemMask;
-        const bool own = b + lane < rg.y;
-        const float4 r = own ? rec0[it] : make_float4(0.f, 0.f, 0.f, 0.f);
+        const bool own = b + lane < rg.y && pair_reaches<BIN>(pv, tg.quad, 15u);
+        const float4 r = own ? rec[2 * (size_t)it] : make_float4(0.f, 0.f, 0.f, 0.f);
         R0 = make_float2((ox - r.x) - r.z, (oy - r.y) - r.w);
-        R1 = own ? rec1[it] : make_float4(0.f, 0.f, 0.f, 0.f);
-        R2 = own ? rec2[it] : make_uint2(0u, 0u);
+        R1 = own ? rec[2 * (size_t)it + 1] : make_float4(0.f, 0.f, 0.f, 0.f);
+        gi = own ? items[it] : 0u;
     };
     // (wide channel chunks have no registers to spare for the second buffer:
     // there the next chunk is gathered when the current one is done)
@@ -126,20 +120,20 @@ __device__ __forceinline__ uint32_t accumulate_tile(
     uint32_t pv = load_pv(rg.x), pvn = load_pv(rg.x + 64);
     float2 R0;
     float4 R1;
-    uint2 R2;
-    gather(pv, rg.x, R0, R1, R2);
+    uint32_t gi;  // the entry's item
+    gather(pv, rg.x, R0, R1, gi);
     for (uint32_t b = rg.x; b < rg.y && alive != 0u; b += 64) {
         const uint32_t nb = min(64u, rg.y - b);
         float2 Q0;
         float4 Q1;
-        uint2 Q2;
-        if constexpr (kDouble) gather(pvn, b + 64, Q0, Q1, Q2);
+        uint32_t qi;
+        if constexpr (kDouble) gather(pvn, b + 64, Q0, Q1, qi);
         const uint32_t pvnn = load_pv(b + 128);
-        // the chunk's entries that can reach a live band, one bit per lane in
+        // the chunk's entries that can reach a live block, one bit per lane in
         // list order: the walk visits only these
-        // each lane forms its entry's band mask: taking an entry then costs
+        // each lane forms its entry's block mask: taking an entry then costs
         // one broadcast of it
-        const uint32_t BL = lane < nb ? entry_bands<BIN>(pv, tg.quad, R2.x, tg.y0) : 0u;
+        const uint32_t BL = lane < nb && pair_reaches<BIN>(pv, tg.quad, alive) ? entry_blocks<BIN>(pv, R0, R1, bp) : 0u;
         uint64_t todo = __builtin_amdgcn_ballot_w64((BL & alive) != 0u);
         // the chunk's records go through LDS (this wave's 64 slots): an entry
         // reads them back with two broadcast loads instead of six readlanes
@@ -162,21 +156,20 @@ __device__ __forceinline__ uint32_t accumulate_tile(
                     const bool any = todo != 0u;
                     const uint32_t j = any ? (uint32_t)__builtin_ctzll(todo) : 0u;
                     todo &= todo - 1u;
-                    const uint32_t gid = bcast_u(R2.y, j);  // the entry's item
-                    const uint32_t bands = any ? bcast_u(BL, j) & alive : 0u;
+                    const uint32_t gid = bcast_u(gi, j);  // the entry's item
+                    const uint32_t blocks = any ? bcast_u(BL, j) & alive : 0u;
                     float sv = 0.0f, s0 = 0.0f, s1 = 0.0f, s2 = 0.0f;
                     uint32_t nh = 0;
-                    if (bands != 0u) {
+                    if (blocks != 0u) {
                         const float2 c0 = lrec0[j];
                         const float4 c1 = lrec1[j];
-                        const float dx = c0.x + lx;
-                        const float a0 = c1.x * dx * dx;
-                        const float b0 = c1.y * dx;
+                        const float dx[2] = {c0.x + lx[0], c0.x + lx[1]}, dy[2] = {c0.y + ly[0], c0.y + ly[1]};
+                        const float a0[2] = {c1.x * dx[0] * dx[0], c1.x * dx[1] * dx[1]};
+                        const float b0[2] = {c1.y * dx[0], c1.y * dx[1]};
 #pragma unroll
                         for (int k = 0; k < 4; ++k) {
-                            if (!((bands >> k) & 1u)) continue;  // uniform
-                            const float dy = c0.y + lyk[k];
-                            const float q2 = fmaf(dy, fmaf(c1.z, dy, b0), a0);
+                            if (!((blocks >> k) & 1u)) continue;  // uniform
+                            const float q2 = fmaf(dy[k >> 1], fmaf(c1.z, dy[k >> 1], b0[k & 1]), a0[k & 1]);
                             uint64_t taken, kept;
                             const float w = pixel_step(q2, c1.w, T[k], qlim, amin, amax, tmin, taken, kept);
                             sv += w;
@@ -217,14 +210,14 @@ __device__ __forceinline__ uint32_t accumulate_tile(
             while (todo != 0u) {
                 const uint32_t j = (uint32_t)__builtin_ctzll(todo);
                 todo &= todo - 1u;
-                const uint32_t bands = bcast_u(BL, j) & alive;
-                if (bands == 0u) continue;
-                const uint32_t gid = bcast_u(R2.y, j);  // the entry's item
+                const uint32_t blocks = bcast_u(BL, j) & alive;
+                if (blocks == 0u) continue;
+                const uint32_t gid = bcast_u(gi, j);  // the entry's item
                 const float2 c0 = lrec0[j];
                 const float4 c1 = lrec1[j];
-                const float dx = c0.x + lx;
-                const float a0 = c1.x * dx * dx;
-                const float b0 = c1.y * dx;
+                const float dx[2] = {c0.x + lx[0], c0.x + lx[1]}, dy[2] = {c0.y + ly[0], c0.y + ly[1]};
+                const float a0[2] = {c1.x * dx[0] * dx[0], c1.x * dx[1] * dx[1]};
+                const float b0[2] = {c1.y * dx[0], c1.y * dx[1]};
                 float sv = 0.0f;
                 float ss[CCA];
 #pragma unroll
@@ -232,9 +225,8 @@ __device__ __forceinline__ uint32_t accumulate_tile(
                 uint32_t nh = 0;    // contributions of this entry (wave total)
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
-                    if (!((bands >> k) & 1u)) continue;  // uniform
-                    const float dy = c0.y + lyk[k];
-                    const float q2 = fmaf(dy, fmaf(c1.z, dy, b0), a0);
+                    if (!((blocks >> k) & 1u)) continue;  // uniform
+                    const float q2 = fmaf(dy[k >> 1], fmaf(c1.z, dy[k >> 1], b0[k & 1]), a0[k & 1]);
                     uint64_t taken, kept;
                     const float w = pixel_step(q2, c1.w, T[k], qlim, amin, amax, tmin, taken, kept);
                     sv += w;
@@ -243,7 +235,7 @@ __device__ __forceinline__ uint32_t accumulate_tile(
                     nh += (uint32_t)__popcll(taken);
                     if (kept == 0) alive &= ~(1u << k);
                 }
-                // keep the band mask and the count in scalar registers
+                // keep the block mask and the count in scalar registers
                 alive = (uint32_t)__builtin_amdgcn_readfirstlane((int)alive);
                 nh = (uint32_t)__builtin_amdgcn_readfirstlane((int)nh);
                 cnt += nh;
@@ -284,9 +276,9 @@ __device__ __forceinline__ uint32_t accumulate_tile(
         if constexpr (kDouble) {
             R0 = Q0;
             R1 = Q1;
-            R2 = Q2;
+            gi = qi;
         } else {
-            gather(pvn, b + 64, R0, R1, R2);
+            gather(pvn, b + 64, R0, R1, gi);
         }
         pv = pvn;
         pvn = pvnn;
@@ -309,8 +301,8 @@ template <int CC, bool BF16, int BIN, bool DET>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(acc_waves_per_simd<CC>()))) void k_accumulate(
     const ViewInfo* __restrict__ views, int n_views, uint32_t n_tiles, const uint2* __restrict__ ranges,
     const uint32_t* __restrict__ pair_vals,
-    const float4* __restrict__ rec0, const float4* __restrict__ rec1,
-    const uint2* __restrict__ rec2, const void* __restrict__ targets, int C, int c_off,
+    const float4* __restrict__ rec, const uint32_t* __restrict__ items,
+    const void* __restrict__ targets, int C, int c_off,
     int per_view, BlendParams bp, float* __restrict__ VS, float2 dsc,
     unsigned long long* __restrict__ counter, uint32_t* __restrict__ gcount,
     uint32_t* __restrict__ queue, const uint32_t* __restrict__ order) {
@@ -323,7 +315,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(acc_waves_p
         if (wi >= n_tiles) return;  // whole wave
         const uint32_t tile = queued_tile<BIN>(wi, order);  // blocks start in index order
         cnt = accumulate_tile<CC, BF16, BIN, DET>(tile, lane, views, n_views, ranges, pair_vals,
-                                                  rec0, rec1, rec2, targets, C, c_off, per_view, bp,
+                                                  rec, items, targets, C, c_off, per_view, bp,
                                                   VS, dsc, gcount, srec1[w], srec0[w]);
     } else {
         for (;;) {
@@ -333,7 +325,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(acc_waves_p
             if (tq >= n_tiles) break;  // uniform: every wave ends here
             const uint32_t tile = queued_tile<BIN>(tq, order);
             cnt += accumulate_tile<CC, BF16, BIN, DET>(tile, lane, views, n_views, ranges, pair_vals,
-                                                       rec0, rec1, rec2, targets, C, c_off,
+                                                       rec, items, targets, C, c_off,
                                                        per_view, bp, VS, dsc, gcount, srec1[w], srec0[w]);
         }
     }
@@ -344,46 +336,37 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(acc_waves_p
 static inline uint32_t wave_tiles(uint32_t n_bins, int bin) { return bin == 32 ? 4u * n_bins : n_bins; }
 
 template <int CC, bool BF16, int BIN, bool DET = false>
-static void launch_acc_k(const ViewInfo* views, int n_views, uint32_t n_wt, const uint2* ranges,
-                         const uint32_t* pair_vals, const float4* rec0,
-                         const float4* rec1,
-                         const uint2* rec2, const void* targets, int C, bool per_view,
-                         BlendParams bp, float* VS, unsigned long long* counter, uint32_t* gcount,
-                         uint32_t* queues, const uint32_t* order, hipStream_t s,
-                         float2 dsc = make_float2(0.f, 0.f)) {
+static void launch_acc_k(const TileLists& tl, const void* targets, int C, bool per_view, BlendParams bp,
+                         float* VS, unsigned long long* counter, uint32_t* gcount, uint32_t* queues,
+                         hipStream_t s, float2 dsc = make_float2(0.f, 0.f)) {
+    const uint32_t n_wt = wave_tiles(tl.n_bins, BIN);
     const uint32_t full = (n_wt + 3) / 4;
     dim3 grid(queues ? std::min(full, kPersistentBlocks) : full), block(256);
     int pass = 0;
     const int step = CC > 0 ? CC : C + 1;
     for (int c_off = 0; c_off < std::max(C, 1); c_off += step, ++pass) {
         uint32_t* q = queues ? queues + pass : nullptr;
-        hipLaunchKernelGGL((k_accumulate<CC, BF16, BIN, DET>), grid, block, 0, s, views, n_views, n_wt,
-                           ranges, pair_vals, rec0, rec1, rec2, targets, C, c_off,
-                           (int)per_view, bp, VS, dsc, counter, gcount, q, order);
+        hipLaunchKernelGGL((k_accumulate<CC, BF16, BIN, DET>), grid, block, 0, s, tl.views, tl.n_views,
+                           n_wt, tl.ranges, tl.pair_vals, tl.rec, tl.items, targets, C, c_off,
+                           (int)per_view, bp, VS, dsc, counter, gcount, q, tl.order);
     }
 }
 
 template <int CC>
-static void launch_acc_cc(const ViewInfo* views, int n_views, uint32_t n_bins, const uint2* ranges,
-                          const uint32_t* pair_vals, const float4* rec0,
-                          const float4* rec1,
-                          const uint2* rec2, int bin, const void* targets, int tdtype, int C,
-                          bool per_view, BlendParams bp, float* VS, unsigned long long* counter,
-                          uint32_t* gcount, uint32_t* queues, const uint32_t* order, hipStream_t s,
-                          const float2* det) {
-    const uint32_t n_wt = wave_tiles(n_bins, bin);
+static void launch_acc_cc(const TileLists& tl, const void* targets, int tdtype, int C, bool per_view,
+                          BlendParams bp, float* VS, unsigned long long* counter, uint32_t* gcount,
+                          uint32_t* queues, hipStream_t s, const float2* det) {
     const bool bf = tdtype == GSC_BF16;
-#define GSC_ACCK(BFV, BINV, DETV)                                                                  \
-    launch_acc_k<CC, BFV, BINV, DETV>(views, n_views, n_wt, ranges, pair_vals, rec0, rec1, rec2,    \
-                                      targets, C, per_view, bp, VS, counter, gcount, queues, order, s, \
+#define GSC_ACCK(BFV, BINV, DETV)                                                             \
+    launch_acc_k<CC, BFV, BINV, DETV>(tl, targets, C, per_view, bp, VS, counter, gcount, queues, s, \
                                       det ? *det : make_float2(0.f, 0.f))
     if (det) {
-        if (bin == 32) {
+        if (tl.bin == 32) {
             if (bf) GSC_ACCK(true, 32, true); else GSC_ACCK(false, 32, true);
         } else {
             if (bf) GSC_ACCK(true, 16, true); else GSC_ACCK(false, 16, true);
         }
-    } else if (bin == 32) {
+    } else if (tl.bin == 32) {
         if (bf) GSC_ACCK(true, 32, false); else GSC_ACCK(false, 32, false);
     } else {
         if (bf) GSC_ACCK(true, 16, false); else GSC_ACCK(false, 16, false);
@@ -403,8 +386,9 @@ static void launch_acc_cc(const ViewInfo* views, int n_views, uint32_t n_bins, c
 // registers for the whole tile, give S, and a block of ones gives
 // V = sum_p w from the same split weights.  (Groups of 8 entries put W_hi in
 // rows 0..7 of the A operand and W_lo in rows 8..15: one product per K-step.)
-// K index k = 32 s + 8 (lane / 16) + i of K-step s is tile pixel k (row k/16,
-// column k%16); the blend's lane l owns pixels l + 64 j, j = 0..3.
+// K index 64 j + l is the blend's pixel of lane l in block j, so index
+// 32 s + 8 q + i of K-step s (q = lane / 16) is the pixel in row 4 (s & 1) + q
+// and column i of block s / 2: eight neighbours of a pixel row per lane.
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float floatx4_t __attribute__((ext_vector_type(4)));
@@ -443,7 +427,7 @@ template <int NBLK, int BIN, int YM>
 __device__ __forceinline__ uint32_t accumulate_tile_mfma(
     uint32_t tile, uint32_t lane, MfmaLds<mfma_rows<NBLK>()>& L, const ViewInfo* __restrict__ views, int n_views,
     const uint2* __restrict__ ranges, const uint32_t* __restrict__ pair_vals,
-    const float4* __restrict__ rec0, const float4* __restrict__ rec1, const uint2* __restrict__ rec2,
+    const float4* __restrict__ rec, const uint32_t* __restrict__ items,
     const void* __restrict__ targets, int C, int c_off, int per_view, const BlendParams& bp,
     float* __restrict__ VS, uint32_t* __restrict__ gcount) {
     const TileGeom tg = tile_geom<BIN>(tile, views, n_views);
@@ -451,14 +435,12 @@ __device__ __forceinline__ uint32_t accumulate_tile_mfma(
     // view fields read once (plain values: the conditions below need no branch)
     const int vw = V.width, vh = V.height;
     const int64_t poff = V.pixel_offset;
-    const int ix = tg.x0 + (int)(lane & 15);
-    const int iy0 = tg.y0 + (int)(lane >> 4);
     const int stride = C + 1;
     const uint32_t n16 = lane & 15, q4 = lane >> 4;
     constexpr int ROWS = mfma_rows<NBLK>();
 
-    // targets of the tile as B operands: Y[s][b] holds pixels 32 s + 8 q4 + i
-    // (tile row 2 s + q4/2, columns 8 (q4&1) + i) of channel c_off + 16 b + n16
+    // targets of the tile as B operands: Y[s][b] holds the eight pixels of
+    // row 4 (s & 1) + q4 of block s / 2, channel c_off + 16 b + n16
     bf16x8_t Y[8][NBLK];
     // packed forms: the channel this lane's column reads, and its role
     const int pc = YM == 2 ? ((int)n16 < C ? (int)n16 : (int)n16 - C) : (int)n16;
@@ -475,8 +457,8 @@ __device__ __forceinline__ uint32_t accumulate_tile_mfma(
         TY xv[8][NBLK][8];
 #pragma unroll
         for (int s = 0; s < 8; ++s) {
-            const int gy = tg.y0 + 2 * s + (int)(q4 >> 1);
-            const int gx0 = tg.x0 + 8 * (int)(q4 & 1u);
+            const int gy = tg.y0 + 8 * (s >> 2) + 4 * (s & 1) + (int)q4;
+            const int gx0 = tg.x0 + 8 * ((s >> 1) & 1);
 #pragma unroll
             for (int b = 0; b < NBLK; ++b) {
                 const int c = YM == 0 ? c_off + 16 * b + (int)n16 : pc;
@@ -488,8 +470,8 @@ __device__ __forceinline__ uint32_t accumulate_tile_mfma(
         }
 #pragma unroll
         for (int s = 0; s < 8; ++s) {
-            const int gy = tg.y0 + 2 * s + (int)(q4 >> 1);
-            const int gx0 = tg.x0 + 8 * (int)(q4 & 1u);
+            const int gy = tg.y0 + 8 * (s >> 2) + 4 * (s & 1) + (int)q4;
+            const int gx0 = tg.x0 + 8 * ((s >> 1) & 1);
 #pragma unroll
             for (int b = 0; b < NBLK; ++b) {
                 const int c = YM == 0 ? c_off + 16 * b + (int)n16 : pc;
@@ -513,8 +495,8 @@ __device__ __forceinline__ uint32_t accumulate_tile_mfma(
         // a 64-bit element index per load
 #pragma unroll
         for (int s = 0; s < 8; ++s) {
-            const int gy = tg.y0 + 2 * s + (int)(q4 >> 1);
-            const int gx0 = tg.x0 + 8 * (int)(q4 & 1u);
+            const int gy = tg.y0 + 8 * (s >> 2) + 4 * (s & 1) + (int)q4;
+            const int gx0 = tg.x0 + 8 * ((s >> 1) & 1);
 #pragma unroll
             for (int b = 0; b < NBLK; ++b) {
                 const int c = YM == 0 ? c_off + 16 * b + (int)n16 : pc;
@@ -549,13 +531,13 @@ __device__ __forceinline__ uint32_t accumulate_tile_mfma(
         ones = __builtin_bit_cast(bf16x8_t, o4);
     }
 
-    // transmittance of the lane's pixel in each band: four scalars (as an
-    // array the compiler rebuilt it in new registers on every band update)
+    // transmittance of the lane's pixel in each block: four scalars (as an
+    // array the compiler rebuilt it in new registers on every block update)
     float T0, T1, T2, T3;
     uint32_t alive = 0;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-        const bool inside = (ix < vw) & (iy0 + 4 * k < vh);
+        const bool inside = (tg.x0 + block_px(lane, k) < vw) & (tg.y0 + block_py(lane, k) < vh);
         const float t = inside ? 1.0f : kOutsideT;
         if (k == 0) T0 = t;
         if (k == 1) T1 = t;
@@ -578,15 +560,13 @@ __device__ __forceinline__ uint32_t accumulate_tile_mfma(
                 tmin = uniform_in_vgpr(bp.t_min);
     // the lane's pixel offsets from the tile's centre point; R0 below keeps,
     // per entry, the offset of that point from the projected centre
-    const float lx = tile_offset_col(lane);
-    float lyk[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) lyk[k] = tile_offset_row(lane, k);
+    const float lx[2] = {tile_offset_col(lane, 0), tile_offset_col(lane, 1)};
+    const float ly[2] = {tile_offset_row(lane, 0), tile_offset_row(lane, 1)};
     const float ox = tile_centre(tg.x0), oy = tile_centre(tg.y0);
 
     // Rows are never cleared: rows past a group's count feed only output rows
-    // that the flush does not use, and an entry writes zeros in the bands its
-    // footprint misses (measured faster than per-row band masks that zero
+    // that the flush does not use, and an entry writes zeros in the blocks its
+    // footprint misses (measured faster than per-row masks that zero
     // the operand in the flush, for one and for two channel blocks).
 
     // one matrix product over the group's `rows` entries, then the atomics.
@@ -655,9 +635,9 @@ __device__ __forceinline__ uint32_t accumulate_tile_mfma(
     };
 
     // list walk: chunks of 64 entries gathered one per lane; each lane also
-    // forms its entry's band mask (the live bands its footprint rows reach),
+    // forms its entry's block mask (the live blocks its footprint reaches),
     // so taking an entry costs one broadcast of that mask; the entries that
-    // reach a live band are taken in order
+    // reach a live block are taken in order
     constexpr bool kLdsCentre = NBLK == 1;
     uint32_t rows = 0;
     for (uint32_t b = rg.x; b < rg.y && alive != 0u; b += 64) {
@@ -665,12 +645,11 @@ __device__ __forceinline__ uint32_t accumulate_tile_mfma(
         const uint32_t pv = in_list ? pair_vals[b + lane] : 0u;
         const uint32_t it = pv & kItemMask;
         const bool own = in_list && pair_reaches<BIN>(pv, tg.quad, alive);
-        const float4 r = own ? rec0[it] : make_float4(0.f, 0.f, 0.f, 0.f);
+        const float4 r = own ? rec[2 * (size_t)it] : make_float4(0.f, 0.f, 0.f, 0.f);
         const float2 R0 = make_float2((ox - r.x) - r.z, (oy - r.y) - r.w);
-        const float4 R1 = own ? rec1[it] : make_float4(0.f, 0.f, 0.f, 0.f);
-        const uint2 r2 = own ? rec2[it] : make_uint2(0u, 0u);
-        const uint32_t gid = r2.y;  // the entry's item (geometry slot) index
-        const uint32_t BL = own ? (entry_bands<BIN>(pv, tg.quad, r2.x, tg.y0) & alive) : 0u;
+        const float4 R1 = own ? rec[2 * (size_t)it + 1] : make_float4(0.f, 0.f, 0.f, 0.f);
+        const uint32_t gid = own ? items[it] : 0u;  // the entry's item
+        const uint32_t BL = own ? (entry_blocks<BIN>(pv, R0, R1, bp) & alive) : 0u;
         uint64_t sm = __builtin_amdgcn_ballot_w64(BL != 0u);  // entries still to take
         // the records go through LDS: an entry then reads them with one
         // broadcast load each instead of a readlane per value (measured:
@@ -684,24 +663,23 @@ __device__ __forceinline__ uint32_t accumulate_tile_mfma(
         while (sm != 0u) {
             const uint32_t j = (uint32_t)__builtin_ctzll(sm);
             sm &= sm - 1;
-            const uint32_t bands = bcast_u(BL, j) & alive;
-            if (bands == 0u) continue;
+            const uint32_t blocks = bcast_u(BL, j) & alive;
+            if (blocks == 0u) continue;
             const float2 c0 = kLdsCentre ? L.crec0[j] : make_float2(bcast(R0.x, j), bcast(R0.y, j));
             const float4 c1 = L.crec1[j];
-            const float dx = c0.x + lx;
-            const float a0 = c1.x * dx * dx;
-            const float b0 = c1.y * dx;
+            const float dx[2] = {c0.x + lx[0], c0.x + lx[1]}, dy[2] = {c0.y + ly[0], c0.y + ly[1]};
+            const float a0[2] = {c1.x * dx[0] * dx[0], c1.x * dx[1] * dx[1]};
+            const float b0[2] = {c1.y * dx[0], c1.y * dx[1]};
             uint32_t nh = 0;
             __bf16* wrow_h = &L.whi[rows * kWRow];
             __bf16* wrow_l = &L.wlo[rows * kWRow];
-            auto band = [&](const int k, float& Tk) {
-                if (!((bands >> k) & 1u)) {  // uniform: no weight in this band
+            auto step = [&](const int k, float& Tk) {
+                if (!((blocks >> k) & 1u)) {  // uniform: no weight in this block
                     wrow_h[lane + 64 * k] = (__bf16)0.0f;
                     wrow_l[lane + 64 * k] = (__bf16)0.0f;
                     return;
                 }
-                const float dy = c0.y + lyk[k];
-                const float q2 = fmaf(dy, fmaf(c1.z, dy, b0), a0);
+                const float q2 = fmaf(dy[k >> 1], fmaf(c1.z, dy[k >> 1], b0[k & 1]), a0[k & 1]);
                 uint64_t taken, kept;
                 const float w = pixel_step(q2, c1.w, Tk, qlim, amin, amax, tmin, taken, kept);
                 // hi: w's upper half (truncated), lo: the exact remainder rounded
@@ -714,10 +692,10 @@ __device__ __forceinline__ uint32_t accumulate_tile_mfma(
                 nh += (uint32_t)__popcll(taken);
                 if (kept == 0) alive &= ~(1u << k);
             };
-            band(0, T0);
-            band(1, T1);
-            band(2, T2);
-            band(3, T3);
+            step(0, T0);
+            step(1, T1);
+            step(2, T2);
+            step(3, T3);
             alive = (uint32_t)__builtin_amdgcn_readfirstlane((int)alive);
             nh = (uint32_t)__builtin_amdgcn_readfirstlane((int)nh);
             cnt += nh;
@@ -740,8 +718,8 @@ template <int NBLK, int BIN, int YM>
 __global__ __launch_bounds__(64 * kMfmaWaves)
 __attribute__((amdgpu_waves_per_eu(mfma_waves_per_simd<NBLK>()))) void k_accumulate_mfma(
     const ViewInfo* __restrict__ views, int n_views, uint32_t n_tiles, const uint2* __restrict__ ranges,
-    const uint32_t* __restrict__ pair_vals, const float4* __restrict__ rec0,
-    const float4* __restrict__ rec1, const uint2* __restrict__ rec2,
+    const uint32_t* __restrict__ pair_vals, const float4* __restrict__ rec,
+    const uint32_t* __restrict__ items,
     const void* __restrict__ targets, int C, int c_off, int per_view, BlendParams bp,
     float* __restrict__ VS, unsigned long long* __restrict__ counter, uint32_t* __restrict__ gcount,
     uint32_t* __restrict__ queue, const uint32_t* __restrict__ order) {
@@ -753,7 +731,7 @@ __attribute__((amdgpu_waves_per_eu(mfma_waves_per_simd<NBLK>()))) void k_accumul
         if (wi >= n_tiles) return;  // whole wave
         const uint32_t tile = queued_tile<BIN>(wi, order);  // blocks start in index order
         cnt = accumulate_tile_mfma<NBLK, BIN, YM>(tile, lane, lds[w], views, n_views, ranges, pair_vals,
-                                              rec0, rec1, rec2, targets, C, c_off, per_view, bp, VS,
+                                              rec, items, targets, C, c_off, per_view, bp, VS,
                                               gcount);
     } else {
         for (;;) {
@@ -763,7 +741,7 @@ __attribute__((amdgpu_waves_per_eu(mfma_waves_per_simd<NBLK>()))) void k_accumul
             if (tq >= n_tiles) break;  // uniform: every wave ends here
             const uint32_t tile = queued_tile<BIN>(tq, order);
             cnt += accumulate_tile_mfma<NBLK, BIN, YM>(tile, lane, lds[w], views, n_views, ranges,
-                                                   pair_vals, rec0, rec1, rec2, targets, C, c_off,
+                                                   pair_vals, rec, items, targets, C, c_off,
                                                    per_view, bp, VS, gcount);
         }
     }
@@ -771,37 +749,30 @@ __attribute__((amdgpu_waves_per_eu(mfma_waves_per_simd<NBLK>()))) void k_accumul
 }
 
 template <int NBLK, int BIN, int YM>
-static void launch_acc_mfma(const ViewInfo* views, int n_views, uint32_t n_wt, const uint2* ranges,
-                            const uint32_t* pair_vals, const float4* rec0, const float4* rec1,
-                            const uint2* rec2, const void* targets, int C, bool per_view,
-                            BlendParams bp, float* VS, unsigned long long* counter, uint32_t* gcount,
-                            uint32_t* queues, const uint32_t* order, hipStream_t s) {
+static void launch_acc_mfma(const TileLists& tl, const void* targets, int C, bool per_view, BlendParams bp,
+                            float* VS, unsigned long long* counter, uint32_t* gcount, uint32_t* queues,
+                            hipStream_t s) {
+    const uint32_t n_wt = wave_tiles(tl.n_bins, BIN);
     const uint32_t full = (n_wt + kMfmaWaves - 1) / kMfmaWaves;
     dim3 grid(queues ? std::min(full, 2 * kPersistentBlocks) : full), block(64 * kMfmaWaves);
     int pass = 0;
     const int step = YM == 0 ? 16 * NBLK : C;  // packed forms: one launch
     for (int c_off = 0; c_off < C; c_off += step, ++pass) {
         uint32_t* q = queues ? queues + pass : nullptr;
-        hipLaunchKernelGGL((k_accumulate_mfma<NBLK, BIN, YM>), grid, block, 0, s, views, n_views, n_wt,
-                           ranges, pair_vals, rec0, rec1, rec2, targets, C, c_off,
-                           (int)per_view, bp, VS, counter, gcount, q, order);
+        hipLaunchKernelGGL((k_accumulate_mfma<NBLK, BIN, YM>), grid, block, 0, s, tl.views, tl.n_views,
+                           n_wt, tl.ranges, tl.pair_vals, tl.rec, tl.items, targets, C, c_off,
+                           (int)per_view, bp, VS, counter, gcount, q, tl.order);
     }
 }
 
 template <int NBLK, int YM>
-static void launch_acc_mfma_bin(const ViewInfo* views, int n_views, uint32_t n_bins, const uint2* ranges,
-                                const uint32_t* pair_vals, const float4* rec0, const float4* rec1,
-                                const uint2* rec2, int bin, const void* targets, int C, bool per_view,
-                                BlendParams bp, float* VS, unsigned long long* counter,
-                                uint32_t* gcount, uint32_t* queues, const uint32_t* order,
-                                hipStream_t s) {
-    const uint32_t n_wt = wave_tiles(n_bins, bin);
-    if (bin == 32)
-        launch_acc_mfma<NBLK, 32, YM>(views, n_views, n_wt, ranges, pair_vals, rec0, rec1, rec2, targets, C,
-                                  per_view, bp, VS, counter, gcount, queues, order, s);
+static void launch_acc_mfma_bin(const TileLists& tl, const void* targets, int C, bool per_view,
+                                BlendParams bp, float* VS, unsigned long long* counter, uint32_t* gcount,
+                                uint32_t* queues, hipStream_t s) {
+    if (tl.bin == 32)
+        launch_acc_mfma<NBLK, 32, YM>(tl, targets, C, per_view, bp, VS, counter, gcount, queues, s);
     else
-        launch_acc_mfma<NBLK, 16, YM>(views, n_views, n_wt, ranges, pair_vals, rec0, rec1, rec2, targets, C,
-                                  per_view, bp, VS, counter, gcount, queues, order, s);
+        launch_acc_mfma<NBLK, 16, YM>(tl, targets, C, per_view, bp, VS, counter, gcount, queues, s);
 }
 
 int accumulate_chunk(int C, int tdtype) {
@@ -827,33 +798,16 @@ bool accumulate_chunk_valid(int chunk, int tdtype) {
     return chunk == 1 || chunk == 2 || chunk == 3 || chunk == 4 || chunk == 8 || chunk == 16;
 }
 
-void launch_accumulate(const ViewInfo* views, int n_views, uint32_t n_tiles, const uint2* ranges,
-                       const uint32_t* pair_vals, const float4* rec0,
-                       const float4* rec1,
-                       const uint2* rec2, int bin, const void* targets, int tdtype, int C,
-                       bool per_view, BlendParams bp, float* VS, unsigned long long* counter,
-                       uint32_t* gcount, hipStream_t s, const uint32_t* order) {
-    launch_accumulate_chunked(views, n_views, n_tiles, ranges, pair_vals, rec0, rec1, rec2, bin,
-                              targets, tdtype, C, per_view, bp, VS, counter, gcount, 0, s, nullptr, order,
-                              nullptr);
-}
-
-void launch_accumulate_chunked(const ViewInfo* views, int n_views, uint32_t n_tiles,
-                               const uint2* ranges, const uint32_t* pair_vals,
-                               const float4* rec0,
-                               const float4* rec1, const uint2* rec2, int bin,
-                               const void* targets, int tdtype, int C, bool per_view,
-                               BlendParams bp, float* VS, unsigned long long* counter,
-                               uint32_t* gcount, int chunk, hipStream_t s, uint32_t* queues,
-                               const uint32_t* order, const float2* det) {
-    if (n_tiles == 0) return;
+void launch_accumulate(const TileLists& tl, const void* targets, int tdtype, int C, bool per_view,
+                       BlendParams bp, float* VS, unsigned long long* counter, uint32_t* gcount,
+                       int chunk, hipStream_t s, uint32_t* queues, const float2* det) {
+    if (tl.n_bins == 0) return;
     chunk = resolve_chunk(chunk, C, tdtype);
     if (det && (chunk & kChunkMfma)) chunk = accumulate_chunk(C, GSC_F32);  // vector form only
     if (queues) launch_fill_u32(queues, 0u, (uint64_t)accumulate_launches(C, chunk), s);
     if (chunk & kChunkMfma) {
-#define GSC_ACCM(NB, YMV)                                                                          \
-    launch_acc_mfma_bin<NB, YMV>(views, n_views, n_tiles, ranges, pair_vals, rec0, rec1, rec2, bin, \
-                                 targets, C, per_view, bp, VS, counter, gcount, queues, order, s)
+#define GSC_ACCM(NB, YMV) \
+    launch_acc_mfma_bin<NB, YMV>(tl, targets, C, per_view, bp, VS, counter, gcount, queues, s)
         switch (chunk_channels(chunk)) {
             case 1:
                 if (tdtype == GSC_BF16) GSC_ACCM(1, 1); else GSC_ACCM(1, 2);
@@ -865,9 +819,8 @@ void launch_accumulate_chunked(const ViewInfo* views, int n_views, uint32_t n_ti
 #undef GSC_ACCM
         return;
     }
-#define GSC_ACC(CCV)                                                                                \
-    launch_acc_cc<CCV>(views, n_views, n_tiles, ranges, pair_vals, rec0, rec1, rec2, bin, targets, \
-                       tdtype, C, per_view, bp, VS, counter, gcount, queues, order, s, det)
+#define GSC_ACC(CCV) \
+    launch_acc_cc<CCV>(tl, targets, tdtype, C, per_view, bp, VS, counter, gcount, queues, s, det)
     switch (chunk) {
         case 1: GSC_ACC(1); break;
         case 2: GSC_ACC(2); break;
@@ -879,20 +832,13 @@ void launch_accumulate_chunked(const ViewInfo* views, int n_views, uint32_t n_ti
 #undef GSC_ACC
 }
 
-void launch_accumulate_weights(const ViewInfo* views, int n_views, uint32_t n_tiles,
-                               const uint2* ranges, const uint32_t* pair_vals,
-                               const float4* rec0,
-                               const float4* rec1, const uint2* rec2, int bin, bool per_view,
-                               BlendParams bp, float* V, unsigned long long* counter, hipStream_t s,
-                               const uint32_t* order) {
-    if (n_tiles == 0) return;
-    const uint32_t n_wt = wave_tiles(n_tiles, bin);
-    if (bin == 32)
-        launch_acc_k<0, false, 32>(views, n_views, n_wt, ranges, pair_vals, rec0, rec1, rec2, nullptr,
-                                   0, per_view, bp, V, counter, nullptr, nullptr, order, s);
+void launch_accumulate_weights(const TileLists& tl, bool per_view, BlendParams bp, float* V,
+                               unsigned long long* counter, hipStream_t s) {
+    if (tl.n_bins == 0) return;
+    if (tl.bin == 32)
+        launch_acc_k<0, false, 32>(tl, nullptr, 0, per_view, bp, V, counter, nullptr, nullptr, s);
     else
-        launch_acc_k<0, false, 16>(views, n_views, n_wt, ranges, pair_vals, rec0, rec1, rec2, nullptr,
-                                   0, per_view, bp, V, counter, nullptr, nullptr, order, s);
+        launch_acc_k<0, false, 16>(tl, nullptr, 0, per_view, bp, V, counter, nullptr, nullptr, s);
 }
 
 }  // namespace gsc

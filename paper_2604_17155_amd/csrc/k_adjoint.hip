@@ -142,8 +142,7 @@ template <int CC, bool BF16, bool GY, int BIN>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(adj_waves_per_simd<CC>()))) void k_blend_adjoint(
     const ViewInfo* __restrict__ views, int n_views, uint32_t n_wt, const uint2* __restrict__ ranges,
     const uint32_t* __restrict__ pair_vals,
-    const float4* __restrict__ rec0, const float4* __restrict__ rec1,
-    const uint2* __restrict__ rec2, const void* __restrict__ ypix, int C, int c_off,
+    const float4* __restrict__ rec, const uint32_t* __restrict__ items, const void* __restrict__ ypix, int C, int c_off,
     const float* __restrict__ beta, BlendParams bp, float* __restrict__ grad_y,
     float* __restrict__ grad_o, const uint32_t* __restrict__ order) {
     // the chunk's records and, for up to three channels, the entry's adjoint
@@ -158,8 +157,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(adj_waves_p
     const uint32_t wt = queued_tile<BIN>(wi, order);  // blocks start in index order
     const TileGeom tg = tile_geom<BIN>(wt, views, n_views);
     const ViewInfo& V = views[tg.vloc];
-    const int ix = tg.x0 + (int)(lane & 15);
-    const int iy0 = tg.y0 + (int)(lane >> 4);
     const int stride = C + 1;
     const bool first_chunk = c_off == 0;
     // dL/do of an entry goes to Gaussian g_offset + (item - item_base), the
@@ -176,14 +173,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(adj_waves_p
     float yv[4][CC];  // pixel values (read only when dL/do is wanted)
     // the lane's pixel offsets from the tile's centre point; R0 below keeps,
     // per entry, the offset of that point from the projected centre
-    const float lx = tile_offset_col(lane);
-    float lyk[4];
+    const float lx[2] = {tile_offset_col(lane, 0), tile_offset_col(lane, 1)};
+    const float ly[2] = {tile_offset_row(lane, 0), tile_offset_row(lane, 1)};
     const float ox = tile_centre(tg.x0), oy = tile_centre(tg.y0);
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-        const int iy = iy0 + 4 * k;
+        const int ix = tg.x0 + block_px(lane, k), iy = tg.y0 + block_py(lane, k);
         inside[k] = ix < V.width && iy < V.height;
-        lyk[k] = tile_offset_row(lane, k);
         const int64_t row = V.pixel_offset + (int64_t)iy * V.width + ix;
 #pragma unroll
         for (int c = 0; c < CC; ++c)
@@ -197,11 +193,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(adj_waves_p
     // decisions.  A chunk of 64 entries is gathered at once, one entry per
     // lane (records and the entry's adjoint colours), and staged in LDS, from
     // which an entry reads them back with broadcast loads (adjoint colours of
-    // wider chunks by readlane); each lane forms its entry's band mask, and
-    // only entries reaching a band with a live pixel are visited.  A
+    // wider chunks by readlane); each lane forms its entry's block mask, and
+    // only entries reaching a block with a live pixel are visited.  A
     // pixel that stopped adds nothing in either pass, so the skipped entries
-    // and bands change no sum.
-    uint32_t alive0 = 0;  // bands holding a pixel of the image
+    // and blocks change no sum.
+    uint32_t alive0 = 0;  // blocks holding a pixel of the image
 #pragma unroll
     for (int k = 0; k < 4; ++k) alive0 |= (__builtin_amdgcn_ballot_w64(inside[k]) != 0 ? 1u : 0u) << k;
     alive0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)alive0);
@@ -216,19 +212,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(adj_waves_p
         uint32_t alive = alive0;
         for (uint32_t b = rg.x; b < rg.y && alive != 0u; b += 64) {
             const uint32_t nb = min(64u, rg.y - b);
-            const bool own = lane < nb;
-            const uint32_t pv = own ? pair_vals[b + lane] : 0u;
+            const uint32_t pv = lane < nb ? pair_vals[b + lane] : 0u;
+            const bool own = lane < nb && pair_reaches<BIN>(pv, tg.quad, alive);
             const uint32_t it = pv & kItemMask;
-            const float4 r = own ? rec0[it] : make_float4(0.f, 0.f, 0.f, 0.f);
+            const float4 r = own ? rec[2 * (size_t)it] : make_float4(0.f, 0.f, 0.f, 0.f);
             const float2 R0 = make_float2((ox - r.x) - r.z, (oy - r.y) - r.w);
-            const float4 R1 = own ? rec1[it] : make_float4(0.f, 0.f, 0.f, 0.f);
-            const uint2 R2 = own ? rec2[it] : make_uint2(0u, 0u);
-            const float* bl = beta + (int64_t)R2.y * stride;  // the record names the item
+            const float4 R1 = own ? rec[2 * (size_t)it + 1] : make_float4(0.f, 0.f, 0.f, 0.f);
+            const uint32_t gid = own ? items[it] : 0u;
+            const float* bl = beta + (int64_t)gid * stride;
             float RB[CC];
 #pragma unroll
             for (int c = 0; c < CC; ++c) RB[c] = (own && c_off + c < C) ? bl[c_off + c] : 0.0f;
             const float RD = (own && first_chunk) ? bl[C] : 0.0f;
-            const uint32_t BL = own ? (entry_bands<BIN>(pv, tg.quad, R2.x, tg.y0) & alive) : 0u;
+            const uint32_t BL = own ? (entry_blocks<BIN>(pv, R0, R1, bp) & alive) : 0u;
             uint64_t todo = __builtin_amdgcn_ballot_w64(BL != 0u);
             srec1[w][lane] = R1;
             srec0[w][lane] = R0;
@@ -240,9 +236,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(adj_waves_p
             while (todo != 0u) {
                 const uint32_t j = (uint32_t)__builtin_ctzll(todo);
                 todo &= todo - 1u;
-                const uint32_t bands = bcast_u(BL, j) & alive;
-                if (bands == 0u) continue;
-                const uint2 e2 = make_uint2(0u, bcast_u(R2.y, j));  // the item
+                const uint32_t blocks = bcast_u(BL, j) & alive;
+                if (blocks == 0u) continue;
+                const uint32_t item = bcast_u(gid, j);
                 const float2 c0 = srec0[w][j];
                 const float4 c1 = srec1[w][j];
                 float bet[CC];
@@ -258,10 +254,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(adj_waves_p
                     for (int c = 0; c < CC; ++c) bet[c] = bcast(RB[c], j);
                     del = bcast(RD, j);
                 }
-                body(bands, c0, c1, e2, bet, del);
+                body(blocks, c0, c1, item, bet, del);
 #pragma unroll
                 for (int k = 0; k < 4; ++k)
-                    if (((bands >> k) & 1u) && __builtin_amdgcn_ballot_w64(live[k]) == 0) alive &= ~(1u << k);
+                    if (((blocks >> k) & 1u) && __builtin_amdgcn_ballot_w64(live[k]) == 0) alive &= ~(1u << k);
                 alive = (uint32_t)__builtin_amdgcn_readfirstlane((int)alive);
                 if (alive == 0u) break;
             }
@@ -278,16 +274,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(adj_waves_p
 #pragma unroll
         for (int c = 0; c < (GY ? CC : 1); ++c) gy[k][c] = 0.0f;
     }
-    walk([&](uint32_t bands, const float2& c0, const float4& c1, const uint2& e2, const float (&bet)[CC],
+    walk([&](uint32_t blocks, const float2& c0, const float4& c1, uint32_t item, const float (&bet)[CC],
              float del) {
-        const float dx = c0.x + lx;
-        const float a0 = c1.x * dx * dx;
-        const float b0 = c1.y * dx;
+        const float dx[2] = {c0.x + lx[0], c0.x + lx[1]}, dy[2] = {c0.y + ly[0], c0.y + ly[1]};
+        const float a0[2] = {c1.x * dx[0] * dx[0], c1.x * dx[1] * dx[1]};
+        const float b0[2] = {c1.y * dx[0], c1.y * dx[1]};
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            if (!((bands >> k) & 1u)) continue;  // uniform
-            const float dy = c0.y + lyk[k];
-            const float q2 = fmaf(dy, fmaf(c1.z, dy, b0), a0);
+            if (!((blocks >> k) & 1u)) continue;  // uniform
+            const float q2 = fmaf(dy[k >> 1], fmaf(c1.z, dy[k >> 1], b0[k & 1]), a0[k & 1]);
             const Step st = blend_step(T[k], live[k], q2, c1.w, qlim, bpv);
             float u = -del;
 #pragma unroll
@@ -303,7 +298,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(adj_waves_p
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             if (!inside[k]) continue;
-            const int64_t row = V.pixel_offset + (int64_t)(iy0 + 4 * k) * V.width + ix;
+            const int64_t row = V.pixel_offset + (int64_t)(tg.y0 + block_py(lane, k)) * V.width + tg.x0 + block_px(lane, k);
 #pragma unroll
             for (int c = 0; c < CC; ++c)
                 if (c_off + c < C) grad_y[row * C + c_off + c] = gy[k][c];
@@ -315,18 +310,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(adj_waves_p
     double P[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) P[k] = 0.0;
-    walk([&](uint32_t bands, const float2& c0, const float4& c1, const uint2& e2, const float (&bet)[CC],
+    walk([&](uint32_t blocks, const float2& c0, const float4& c1, uint32_t item, const float (&bet)[CC],
              float del) {
-        const float dx = c0.x + lx;
-        const float a0 = c1.x * dx * dx;
-        const float b0 = c1.y * dx;
+        const float dx[2] = {c0.x + lx[0], c0.x + lx[1]}, dy[2] = {c0.y + ly[0], c0.y + ly[1]};
+        const float a0[2] = {c1.x * dx[0] * dx[0], c1.x * dx[1] * dx[1]};
+        const float b0[2] = {c1.y * dx[0], c1.y * dx[1]};
         float go = 0.0f;
         uint32_t any = 0;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            if (!((bands >> k) & 1u)) continue;  // uniform
-            const float dy = c0.y + lyk[k];
-            const float q2 = fmaf(dy, fmaf(c1.z, dy, b0), a0);
+            if (!((blocks >> k) & 1u)) continue;  // uniform
+            const float q2 = fmaf(dy[k >> 1], fmaf(c1.z, dy[k >> 1], b0[k & 1]), a0[k & 1]);
             const Step st = blend_step(T[k], live[k], q2, c1.w, qlim, bpv);
             float u = -del;
 #pragma unroll
@@ -340,25 +334,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(adj_waves_p
         }
         if (__ballot(any != 0) != 0) {
             const float t = wave_sum(go);
-            if (lane == 0) unsafeAtomicAdd(grad_o + ((int64_t)e2.y + g_shift), t);
+            if (lane == 0) unsafeAtomicAdd(grad_o + ((int64_t)item + g_shift), t);
         }
     });
 }
 
 template <int CC, bool GY>
-static void launch_badj_cc(const ViewInfo* views, int n_views, uint32_t n_bins, const uint2* ranges,
-                           const uint32_t* pair_vals, const float4* rec0,
-                           const float4* rec1, const uint2* rec2, int bin, const void* ypix,
-                           int ydtype, int C, const float* beta, BlendParams bp, float* grad_y,
-                           float* grad_o, const uint32_t* order, hipStream_t s) {
-    const uint32_t n_wt = bin == 32 ? 4u * n_bins : n_bins;
+static void launch_badj_cc(const TileLists& tl, const void* ypix, int ydtype, int C, const float* beta,
+                           BlendParams bp, float* grad_y, float* grad_o, hipStream_t s) {
+    const uint32_t n_wt = tl.bin == 32 ? 4u * tl.n_bins : tl.n_bins;
     dim3 grid((n_wt + 3) / 4), block(256);
-#define GSC_BADJ(BFV, BINV)                                                                         \
-    hipLaunchKernelGGL((k_blend_adjoint<CC, BFV, GY, BINV>), grid, block, 0, s, views, n_views, n_wt, \
-                       ranges, pair_vals, rec0, rec1, rec2, ypix, C, c_off, beta, bp, grad_y, grad_o, order)
+#define GSC_BADJ(BFV, BINV)                                                                          \
+    hipLaunchKernelGGL((k_blend_adjoint<CC, BFV, GY, BINV>), grid, block, 0, s, tl.views, tl.n_views, \
+                       n_wt, tl.ranges, tl.pair_vals, tl.rec, tl.items, ypix, C, c_off, beta, bp,     \
+                       grad_y, grad_o, tl.order)
     for (int c_off = 0; c_off < C; c_off += CC) {
         const bool bf = ydtype == GSC_BF16;
-        if (bin == 32) {
+        if (tl.bin == 32) {
             if (bf) GSC_BADJ(true, 32); else GSC_BADJ(false, 32);
         } else {
             if (bf) GSC_BADJ(true, 16); else GSC_BADJ(false, 16);
@@ -368,15 +360,9 @@ static void launch_badj_cc(const ViewInfo* views, int n_views, uint32_t n_bins, 
 }
 
 template <bool GY>
-static void launch_badj(const ViewInfo* views, int n_views, uint32_t n_tiles, const uint2* ranges,
-                        const uint32_t* pair_vals, const float4* rec0,
-                        const float4* rec1,
-                        const uint2* rec2, int bin, const void* ypix, int ydtype, int C,
-                        const float* beta, BlendParams bp, float* grad_y, float* grad_o,
-                        const uint32_t* order, hipStream_t s) {
-#define GSC_BA(CCV)                                                                                \
-    launch_badj_cc<CCV, GY>(views, n_views, n_tiles, ranges, pair_vals, rec0, rec1, rec2, bin, ypix, \
-                            ydtype, C, beta, bp, grad_y, grad_o, order, s)
+static void launch_badj(const TileLists& tl, const void* ypix, int ydtype, int C, const float* beta,
+                        BlendParams bp, float* grad_y, float* grad_o, hipStream_t s) {
+#define GSC_BA(CCV) launch_badj_cc<CCV, GY>(tl, ypix, ydtype, C, beta, bp, grad_y, grad_o, s)
     switch (accumulate_chunk(C, GSC_F32)) {  // vector-lane channel chunks
         case 1: GSC_BA(1); break;
         case 2: GSC_BA(2); break;
@@ -388,19 +374,13 @@ static void launch_badj(const ViewInfo* views, int n_views, uint32_t n_tiles, co
 #undef GSC_BA
 }
 
-void launch_blend_adjoint(const ViewInfo* views, int n_views, uint32_t n_tiles, const uint2* ranges,
-                          const uint32_t* pair_vals, const float4* rec0,
-                          const float4* rec1,
-                          const uint2* rec2, int bin, const void* ypix, int ydtype, int C,
-                          const float* beta, BlendParams bp, float* grad_y, float* grad_o,
-                          hipStream_t s, const uint32_t* order) {
-    if (n_tiles == 0 || (!grad_y && !grad_o)) return;
+void launch_blend_adjoint(const TileLists& tl, const void* ypix, int ydtype, int C, const float* beta,
+                          BlendParams bp, float* grad_y, float* grad_o, hipStream_t s) {
+    if (tl.n_bins == 0 || (!grad_y && !grad_o)) return;
     if (grad_y)
-        launch_badj<true>(views, n_views, n_tiles, ranges, pair_vals, rec0, rec1, rec2, bin, ypix,
-                          ydtype, C, beta, bp, grad_y, grad_o, order, s);
+        launch_badj<true>(tl, ypix, ydtype, C, beta, bp, grad_y, grad_o, s);
     else
-        launch_badj<false>(views, n_views, n_tiles, ranges, pair_vals, rec0, rec1, rec2, bin, ypix,
-                           ydtype, C, beta, bp, grad_y, grad_o, order, s);
+        launch_badj<false>(tl, ypix, ydtype, C, beta, bp, grad_y, grad_o, s);
 }
 
 // grad_coeffs[g][m][c] = sum_j phi_gj[m] S_gj[c] from the per-view sums

@@ -6,6 +6,7 @@
 // front-to-back order of eq. 2 keyed on the camera-space depth of the mean.
 #include <algorithm>
 
+#include "footprint.h"
 #include "gsc_internal.h"
 
 namespace gsc {
@@ -80,163 +81,6 @@ void launch_geometry_stats(const float* means, const float* scales, int64_t N, d
     hipLaunchKernelGGL(k_geometry_stats, dim3((unsigned)blocks), dim3(256), 0, s, means, scales, N, out);
 }
 
-// Largest q at which a pixel can still pass both the footprint test
-// (q <= cut2) and the alpha floor (o exp(-q/2) >= alpha_min), with a margin
-// covering the FP32 evaluation in the blend; negative when nothing passes.
-__device__ inline float reach_q(float o, const BlendParams& bp) {
-    if (!(o >= bp.alpha_min)) return -1.0f;
-    const float qa = 2.0f * __logf(o / bp.alpha_min);
-    const float q = fminf(bp.cut2, qa);
-    return q * (1.0f + 1e-4f) + 1e-3f;
-}
-
-// Walks a record's footprint {q <= qmax} band by band (four pixel rows) and
-// calls visit(ty, lo, hi) once per 16-row tile row, where [lo[k], hi[k]] is a
-// range of 16-column blocks covering every pixel centre of band k (rows
-// 4k..4k+3 of the tile row) inside the footprint (lo > hi: none).  The x
-// extent of a band is taken over the continuous span of its row centres: the
-// left edge of the ellipse is convex and the right edge concave in y, so the
-// extremes lie at the span's ends or at the ellipse's leftmost / rightmost
-// point when that falls inside the span.  Extents are widened by 0.01 pixel
-// (and 1e-4 relative), so the walk is conservative with respect to the
-// blend's FP32 test (and cover the ~1 ulp of the hardware square root used
-// here).  *rows (optional) receives the first and last pixel row walked.
-// Used identically for counting and emitting.
-// STEP = 16 walks whole tile rows instead of bands (only [lo[0], hi[0]] is
-// then set): the extent over a tile row's span is the union of its bands'.
-template <int STEP = 4, typename Visit>
-__device__ inline void footprint_rows(float4 r0, float4 r1, float qmax, int W, int H,
-                                      Visit&& visit, int* rows = nullptr) {
-    static_assert(STEP == 4 || STEP == 16, "steps of a band or of a tile row");
-    constexpr float kInvK = (float)(1.0 / kExp2Scale);
-    const float a = r1.x * kInvK, b = 0.5f * r1.y * kInvK, c = r1.z * kInvK;
-    const float det = a * c - b * b;
-    if (!(a > 0.0f && det > 0.0f && qmax > 0.0f)) return;
-    const float ia = 1.0f / a, cq = det * ia;  // q = a (dx + b dy / a)^2 + cq dy^2
-    const float ry = __builtin_amdgcn_sqrtf(qmax / cq) * 1.0001f + 0.01f;
-    const float vc = r0.y - 0.5f + r0.w;  // row index whose centre is the mean
-    const float fy0 = fmaxf(ceilf(vc - ry), 0.0f);
-    const float fy1 = fminf(floorf(vc + ry), (float)(H - 1));
-    if (!(fy0 <= fy1)) return;
-    const int y0 = (int)fy0, y1 = (int)fy1;
-    if (rows) {
-        rows[0] = y0;
-        rows[1] = y1;
-    }
-    const float cx = r0.x - 0.5f + r0.z;  // column index whose centre is the mean
-    // leftmost / rightmost point of the ellipse: dx = -+ sqrt(qmax Sxx) at
-    // dy = -+ sqrt(qmax / Sxx) Sxy, with Sxx = c / det, Sxy = -b / det
-    const float sxx = c / det, sxy = -b / det;
-    const float xr = __builtin_amdgcn_sqrtf(qmax * sxx) * 1.0001f + 0.01f;
-    const float dyl = -__builtin_amdgcn_sqrtf(qmax / sxx) * sxy;  // row offset of the leftmost point (rightmost: -dyl)
-    auto edges = [&](int y, float& l, float& r) {
-        const float dy = ((float)y + 0.5f - r0.y) - r0.w;
-        const float disc = fmaxf(qmax - cq * dy * dy, 0.0f);
-        const float half = __builtin_amdgcn_sqrtf(disc * ia) * 1.0001f + 0.01f;
-        const float mid = cx - b * dy * ia;
-        l = mid - half;
-        r = mid + half;
-    };
-    int lo[4], hi[4];
-    int cur = y0 >> kTileShift;
-    for (int k = 0; k < 4; ++k) { lo[k] = 1 << 30; hi[k] = -1; }
-    for (int ya = y0; ya <= y1; ya = (ya | (STEP - 1)) + 1) {
-        const int yb = min(ya | (STEP - 1), y1);  // rows [ya, yb] of one band (tile row)
-        const int ty = ya >> kTileShift;
-        if (ty != cur) {
-            visit(cur, lo, hi);
-            for (int k = 0; k < 4; ++k) { lo[k] = 1 << 30; hi[k] = -1; }
-            cur = ty;
-        }
-        float la, ra, lb, rb;
-        edges(ya, la, ra);
-        edges(yb, lb, rb);
-        float l = fminf(la, lb), r = fmaxf(ra, rb);
-        const float sa = ((float)ya + 0.5f - r0.y) - r0.w, sb = ((float)yb + 0.5f - r0.y) - r0.w;
-        if (sa <= dyl && dyl <= sb) l = cx - xr;
-        if (sa <= -dyl && -dyl <= sb) r = cx + xr;
-        const float xf = fmaxf(ceilf(l), 0.0f);
-        const float xl = fminf(floorf(r), (float)(W - 1));
-        if (!(xf <= xl)) continue;
-        const int band = STEP == 4 ? (ya >> 2) & 3 : 0;
-        const int t0 = (int)xf >> kTileShift, t1 = (int)xl >> kTileShift;
-        for (int k = 0; k < 4; ++k)
-            if (k == band) {
-                lo[k] = min(lo[k], t0);
-                hi[k] = max(hi[k], t1);
-            }
-    }
-    visit(cur, lo, hi);
-}
-
-// Footprint per bin row.  BIN = 16: the bin is the 16x16 tile and its 4-bit
-// mask marks the bands (rows 4k..4k+3) the footprint reaches.  BIN = 32: the
-// bin is a 32x32 block of four 16x16 tiles and bit 2h + c marks the tile in
-// row half h and column half c.  visit(bin_row, t0, t1, mask_of, n, h) is
-// called per bin row with the bin columns [t0, t1], a function giving a bin
-// column's mask (0: not reached), n, the number of columns in [t0, t1] whose
-// mask is not 0, and (BIN = 32) h = the first and last 16-pixel tile column
-// reached in each row half (lo0, hi0, lo1, hi1; lo > hi: none).
-template <int BIN, typename Visit>
-__device__ inline void footprint_bins(float4 r0, float4 r1, float qmax, int W, int H,
-                                      Visit&& visit, int* rows = nullptr) {
-    if constexpr (BIN == 16) {
-        footprint_rows(r0, r1, qmax, W, H, [&](int ty, const int* lo, const int* hi) {
-            int t0 = 1 << 30, t1 = -1;
-            for (int k = 0; k < 4; ++k) {
-                t0 = min(t0, lo[k]);
-                t1 = max(t1, hi[k]);
-            }
-            auto mask_of = [&](int t) {
-                uint32_t m = 0;
-                for (int k = 0; k < 4; ++k) m |= (lo[k] <= t && t <= hi[k]) ? (1u << k) : 0u;
-                return m;
-            };
-            int n = 0;
-            for (int t = t0; t <= t1; ++t) n += mask_of(t) != 0u;
-            visit(ty, t0, t1, mask_of, n, make_int4(0, -1, 0, -1));
-        }, rows);
-    } else {
-        static_assert(BIN == 32, "bins are 16 or 32 pixels");
-        // 16-column block ranges of the two tile rows of the current bin row
-        int cur = -1, lo[2] = {1 << 30, 1 << 30}, hi[2] = {-1, -1};
-        auto flush = [&]() {
-            if (cur < 0) return;
-            const int b0 = min(lo[0], lo[1]), b1 = max(hi[0], hi[1]);
-            if (b0 <= b1) {
-                // a bin column t has a tile of row half h reached exactly when
-                // lo[h] >> 1 <= t <= hi[h] >> 1 (tile columns are >= 0; an
-                // unreached half has lo > hi and gives an empty range), so the
-                // reached columns are the union of two ranges
-                const int a0 = lo[0] >> 1, a1 = hi[0] >> 1, c0 = lo[1] >> 1, c1 = hi[1] >> 1;
-                const int na = max(a1 - a0 + 1, 0), nc = max(c1 - c0 + 1, 0);
-                const int nboth = max(min(a1, c1) - max(a0, c0) + 1, 0);
-                visit(cur, b0 >> 1, b1 >> 1, [&](int t) {
-                    uint32_t m = 0;
-                    for (int h = 0; h < 2; ++h)
-                        for (int c = 0; c < 2; ++c)
-                            m |= (lo[h] <= 2 * t + c && 2 * t + c <= hi[h]) ? (1u << (2 * h + c)) : 0u;
-                    return m;
-                }, na + nc - nboth, make_int4(lo[0], hi[0], lo[1], hi[1]));
-            }
-        };
-        footprint_rows<16>(r0, r1, qmax, W, H, [&](int ty, const int* l4, const int* h4) {
-            const int br = ty >> 1, h = ty & 1;
-            if (br != cur) {
-                flush();
-                cur = br;
-                lo[0] = lo[1] = 1 << 30;
-                hi[0] = hi[1] = -1;
-            }
-            for (int k = 0; k < 4; ++k) {
-                lo[h] = min(lo[h], l4[k]);
-                hi[h] = max(hi[h], h4[k]);
-            }
-        }, rows);
-        flush();
-    }
-}
-
 // a2, first step: the depth key of every (view, Gaussian) item of the batch,
 // keys[i] = bits of the camera-space depth of the mean computed in binary32
 // (positive floats order like their bit patterns), 0xFFFFFFFF for items culled
@@ -277,15 +121,12 @@ void launch_depth_keys(const ViewInfo* views, int n_views, uint32_t n_items, con
 // enough to move alpha by ~1e-4 relative at the footprint edge.
 // A tile is binned only if its pixel centres come within the footprint
 // reach (3-sigma ellipse, shrunk by the alpha floor for faint splats).
-// rec2[k] = (first | last << 16, i): the pixel rows the footprint walk covers
-// and the item.
 template <int BIN>
 __global__ __launch_bounds__(256) void k_project(const ViewInfo* __restrict__ views, int n_views,
                                                  uint32_t n_items, const uint32_t* __restrict__ order,
                                                  const float* __restrict__ geo,
                                                  BlendParams bp, uint32_t* __restrict__ counts,
-                                                 float4* __restrict__ rec0, float4* __restrict__ rec1,
-                                                 uint2* __restrict__ rec2) {
+                                                 float4* __restrict__ rec) {
     __shared__ uint32_t sbase[kViewLds];
     const bool vlds = stage_view_bases(views, n_views, sbase);
     const uint32_t k = blockIdx.x * blockDim.x + threadIdx.x;
@@ -301,7 +142,6 @@ __global__ __launch_bounds__(256) void k_project(const ViewInfo* __restrict__ vi
     float mx = ga.x, my = ga.y, mz = ga.z;
     float key = __fmaf_rn(V.R[6], mx, __fmaf_rn(V.R[7], my, __fmaf_rn(V.R[8], mz, V.t[2])));
     uint32_t cnt = 0;
-    int rows[2] = {1, 0};
     float4 r0 = make_float4(0.f, 0.f, 0.f, 0.f), r1 = r0;
     const float og = ga.w;
     const float qmax = reach_q(og, bp);
@@ -341,29 +181,28 @@ __global__ __launch_bounds__(256) void k_project(const ViewInfo* __restrict__ vi
                              (float)(kExp2Scale * sxx * inv), og);
             footprint_bins<BIN>(r0, r1, qmax, V.width, V.height, [&](int, int, int, auto&&, int n, int4) {
                 cnt += (uint32_t)n;
-            }, rows);
+            });
         }
     }
     counts[k] = cnt;
     // records are read only through tile pairs: an item with none keeps its
     // slot unwritten
     if (cnt != 0) {
-        rec0[k] = r0;
-        rec1[k] = r1;
-        rec2[k] = make_uint2((uint32_t)(rows[0] & 0xFFFF) | ((uint32_t)(rows[1] & 0xFFFF) << 16), i);
+        rec[2 * (size_t)k] = r0;
+        rec[2 * (size_t)k + 1] = r1;
     }
 }
 
 void launch_project(const ViewInfo* views, int n_views, uint32_t n_items, const uint32_t* order,
-                    const float* geo, BlendParams bp, uint32_t* counts, float4* rec0, float4* rec1,
-                    uint2* rec2, int bin, hipStream_t s) {
+                    const float* geo, BlendParams bp, uint32_t* counts, float4* rec, int bin,
+                    hipStream_t s) {
     if (n_items == 0 || n_views <= 0) return;
     if (bin == 32)
         hipLaunchKernelGGL(k_project<32>, dim3((n_items + 255) / 256), dim3(256), 0, s, views, n_views,
-                           n_items, order, geo, bp, counts, rec0, rec1, rec2);
+                           n_items, order, geo, bp, counts, rec);
     else
         hipLaunchKernelGGL(k_project<16>, dim3((n_items + 255) / 256), dim3(256), 0, s, views, n_views,
-                           n_items, order, geo, bp, counts, rec0, rec1, rec2);
+                           n_items, order, geo, bp, counts, rec);
 }
 
 // a3: emit (global bin id, k | mask) pairs in depth order, k being the depth
@@ -376,8 +215,7 @@ __global__ __launch_bounds__(256) void k_emit(const ViewInfo* __restrict__ views
                                               const uint32_t* __restrict__ sorted_vals,
                                               const uint32_t* __restrict__ offsets,
                                               const uint32_t* __restrict__ counts,
-                                              const float4* __restrict__ rec0,
-                                              const float4* __restrict__ rec1, BlendParams bp,
+                                              const float4* __restrict__ rec, BlendParams bp,
                                               uint32_t n_items, uint32_t sentinel, uint32_t cap,
                                               uint32_t* __restrict__ overflow,
                                               uint32_t* __restrict__ pair_keys,
@@ -397,7 +235,7 @@ __global__ __launch_bounds__(256) void k_emit(const ViewInfo* __restrict__ views
         const uint32_t cnt = counts[k];
         if (cnt != 0) {
             const ViewInfo& V = views[find_view_item(views, n_views, sorted_vals[k])];
-            const float4 r0 = rec0[k], r1 = rec1[k];
+            const float4 r0 = rec[2 * (size_t)k], r1 = rec[2 * (size_t)k + 1];
             uint32_t off = offsets[k];
             uint32_t end = off + cnt;
             if (end > cap || end < off) {  // capacity exceeded: keep what fits, report the rest
@@ -461,8 +299,7 @@ __global__ __launch_bounds__(256) void k_emit32(const ViewInfo* __restrict__ vie
                                                 const uint32_t* __restrict__ sorted_vals,
                                                 const uint32_t* __restrict__ offsets,
                                                 const uint32_t* __restrict__ counts,
-                                                const float4* __restrict__ rec0,
-                                                const float4* __restrict__ rec1, BlendParams bp,
+                                                const float4* __restrict__ rec, BlendParams bp,
                                                 uint32_t n_items, uint32_t sentinel, uint32_t cap,
                                                 uint32_t* __restrict__ overflow,
                                                 uint32_t* __restrict__ pair_keys,
@@ -489,8 +326,8 @@ __global__ __launch_bounds__(256) void k_emit32(const ViewInfo* __restrict__ vie
         cnt = counts[k];
         if (cnt != 0) {
             V = &views[view_of(views, n_views, sbase, vlds, sorted_vals[k])];
-            r0 = rec0[k];
-            r1 = rec1[k];
+            r0 = rec[2 * (size_t)k];
+            r1 = rec[2 * (size_t)k + 1];
             off = offsets[k];
             end = off + cnt;
             if (end > cap || end < off) {  // capacity exceeded: keep what fits, report the rest
@@ -615,18 +452,17 @@ __global__ __launch_bounds__(256) void k_emit32(const ViewInfo* __restrict__ vie
 }
 
 void launch_emit(const ViewInfo* views, int n_views, const uint32_t* sorted_vals,
-                 const uint32_t* offsets, const uint32_t* counts, const float4* rec0,
-                 const float4* rec1, BlendParams bp, uint32_t n_items, uint32_t n_tiles,
-                 uint32_t* pair_keys, uint32_t* pair_vals, int bin, hipStream_t s, uint32_t cap,
-                 uint32_t* overflow) {
+                 const uint32_t* offsets, const uint32_t* counts, const float4* rec, BlendParams bp,
+                 uint32_t n_items, uint32_t n_tiles, uint32_t* pair_keys, uint32_t* pair_vals,
+                 int bin, hipStream_t s, uint32_t cap, uint32_t* overflow) {
     if (n_items == 0) return;
     if (bin == 32)
         hipLaunchKernelGGL(k_emit32, dim3((n_items + 255) / 256), dim3(256), 0, s, views, n_views,
-                           sorted_vals, offsets, counts, rec0, rec1, bp, n_items, n_tiles, cap,
+                           sorted_vals, offsets, counts, rec, bp, n_items, n_tiles, cap,
                            overflow, pair_keys, pair_vals);
     else
         hipLaunchKernelGGL(k_emit<16>, dim3((n_items + 255) / 256), dim3(256), 0, s, views, n_views,
-                           sorted_vals, offsets, counts, rec0, rec1, bp, n_items, n_tiles, cap,
+                           sorted_vals, offsets, counts, rec, bp, n_items, n_tiles, cap,
                            overflow, pair_keys, pair_vals);
 }
 

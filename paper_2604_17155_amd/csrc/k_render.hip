@@ -86,9 +86,8 @@ void launch_view_colors(const ViewInfo* views, int n_views, uint32_t n_items, co
 template <int CC, int BIN>
 __global__ __launch_bounds__(256) void k_render(
     const ViewInfo* __restrict__ views, int n_views, uint32_t n_wt, const uint2* __restrict__ ranges,
-    const uint32_t* __restrict__ pair_vals, const float4* __restrict__ rec0,
-    const float4* __restrict__ rec1, const uint2* __restrict__ rec2,
-    const float* __restrict__ gamma, int C, int c_off, BlendParams bp, float* __restrict__ images,
+    const uint32_t* __restrict__ pair_vals, const float4* __restrict__ rec,
+    const uint32_t* __restrict__ items, const float* __restrict__ gamma, int C, int c_off, BlendParams bp, float* __restrict__ images,
     unsigned long long* __restrict__ counter, const uint32_t* __restrict__ order) {
     static_assert(CC <= 4, "one float4 of colours per entry");
     // the chunk's records and colours, read back by every lane as broadcasts
@@ -101,15 +100,13 @@ __global__ __launch_bounds__(256) void k_render(
     const uint32_t wt = queued_tile<BIN>(wi, order);  // blocks start in index order
     const TileGeom tg = tile_geom<BIN>(wt, views, n_views);
     const ViewInfo& V = views[tg.vloc];
-    const int ix = tg.x0 + (int)(lane & 15);
-    const int iy0 = tg.y0 + (int)(lane >> 4);
     float T[4];
     bool inside[4];
     float img[4][CC];
     uint32_t alive = 0;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-        inside[k] = ix < V.width && iy0 + 4 * k < V.height;
+        inside[k] = tg.x0 + block_px(lane, k) < V.width && tg.y0 + block_py(lane, k) < V.height;
         T[k] = inside[k] ? 1.0f : kOutsideT;
         alive |= (__builtin_amdgcn_ballot_w64(inside[k]) != 0 ? 1u : 0u) << k;
 #pragma unroll
@@ -126,29 +123,27 @@ __global__ __launch_bounds__(256) void k_render(
                 tmin = uniform_in_vgpr(bp.t_min);
     // the lane's pixel offsets from the tile's centre point; R0 below keeps,
     // per entry, the offset of that point from the projected centre
-    const float lx = tile_offset_col(lane);
-    float lyk[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) lyk[k] = tile_offset_row(lane, k);
+    const float lx[2] = {tile_offset_col(lane, 0), tile_offset_col(lane, 1)};
+    const float ly[2] = {tile_offset_row(lane, 0), tile_offset_row(lane, 1)};
     const float ox = tile_centre(tg.x0), oy = tile_centre(tg.y0);
     // A chunk of 64 entries is gathered at once, one entry per lane (records
     // and the item's colours), and staged in LDS, from which an entry reads
-    // them back with broadcast loads; each lane forms its entry's band mask,
-    // and only entries reaching a band with a live pixel are visited.
+    // them back with broadcast loads; each lane forms its entry's block mask,
+    // and only entries reaching a block with a live pixel are visited.
     for (uint32_t b = rg.x; b < rg.y && alive != 0u; b += 64) {
         const uint32_t nb = min(64u, rg.y - b);
-        const bool own = lane < nb;
-        const uint32_t pv = own ? pair_vals[b + lane] : 0u;
+        const uint32_t pv = lane < nb ? pair_vals[b + lane] : 0u;
+        const bool own = lane < nb && pair_reaches<BIN>(pv, tg.quad, alive);
         const uint32_t it = pv & kItemMask;
-        const float4 r = own ? rec0[it] : make_float4(0.f, 0.f, 0.f, 0.f);
+        const float4 r = own ? rec[2 * (size_t)it] : make_float4(0.f, 0.f, 0.f, 0.f);
         const float2 R0 = make_float2((ox - r.x) - r.z, (oy - r.y) - r.w);
-        const float4 R1 = own ? rec1[it] : make_float4(0.f, 0.f, 0.f, 0.f);
-        const uint2 R2 = own ? rec2[it] : make_uint2(0u, 0u);
-        const float* gl = gamma + (int64_t)R2.y * C + c_off;  // the record names the item
+        const float4 R1 = own ? rec[2 * (size_t)it + 1] : make_float4(0.f, 0.f, 0.f, 0.f);
+        const uint32_t gid = own ? items[it] : 0u;
+        const float* gl = gamma + (int64_t)gid * C + c_off;
         float RC[CC];
 #pragma unroll
         for (int c = 0; c < CC; ++c) RC[c] = (own && c_off + c < C) ? gl[c] : 0.0f;
-        const uint32_t BL = own ? (entry_bands<BIN>(pv, tg.quad, R2.x, tg.y0) & alive) : 0u;
+        const uint32_t BL = own ? (entry_blocks<BIN>(pv, R0, R1, bp) & alive) : 0u;
         uint64_t todo = __builtin_amdgcn_ballot_w64(BL != 0u);
         srec1[w][lane] = R1;
         srec0[w][lane] = R0;
@@ -159,21 +154,20 @@ __global__ __launch_bounds__(256) void k_render(
         while (todo != 0u) {
             const uint32_t j = (uint32_t)__builtin_ctzll(todo);
             todo &= todo - 1u;
-            const uint32_t bands = bcast_u(BL, j) & alive;
-            if (bands == 0u) continue;
+            const uint32_t blocks = bcast_u(BL, j) & alive;
+            if (blocks == 0u) continue;
             const float2 c0 = srec0[w][j];
             const float4 c1 = srec1[w][j];
             const float4 c4 = scol[w][j];
             const float col[4] = {c4.x, c4.y, c4.z, c4.w};
-            const float dx = c0.x + lx;
-            const float a0 = c1.x * dx * dx;
-            const float b0 = c1.y * dx;
+            const float dx[2] = {c0.x + lx[0], c0.x + lx[1]}, dy[2] = {c0.y + ly[0], c0.y + ly[1]};
+            const float a0[2] = {c1.x * dx[0] * dx[0], c1.x * dx[1] * dx[1]};
+            const float b0[2] = {c1.y * dx[0], c1.y * dx[1]};
             uint32_t nh = 0;
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                if (!((bands >> k) & 1u)) continue;
-                const float dy = c0.y + lyk[k];
-                const float q2 = fmaf(dy, fmaf(c1.z, dy, b0), a0);
+                if (!((blocks >> k) & 1u)) continue;
+                const float q2 = fmaf(dy[k >> 1], fmaf(c1.z, dy[k >> 1], b0[k & 1]), a0[k & 1]);
                 uint64_t taken, kept;
                 const float w = pixel_step(q2, c1.w, T[k], qlim, amin, amax, tmin, taken, kept);
 #pragma unroll
@@ -190,7 +184,7 @@ __global__ __launch_bounds__(256) void k_render(
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         if (!inside[k]) continue;
-        int64_t row = V.pixel_offset + (int64_t)(iy0 + 4 * k) * V.width + ix;
+        int64_t row = V.pixel_offset + (int64_t)(tg.y0 + block_py(lane, k)) * V.width + tg.x0 + block_px(lane, k);
 #pragma unroll
         for (int c = 0; c < CC; ++c)
             if (c_off + c < C) images[row * C + c_off + c] = img[k][c];
@@ -198,19 +192,17 @@ __global__ __launch_bounds__(256) void k_render(
     if (c_off == 0 && lane == 0 && cnt) atomicAdd(counter, (unsigned long long)cnt);
 }
 
-void launch_render(const ViewInfo* views, int n_views, uint32_t n_tiles, const uint2* ranges,
-                   const uint32_t* pair_vals, const float4* rec0, const float4* rec1,
-                   const uint2* rec2, int bin, const float* gamma, int C, BlendParams bp,
-                   float* images, unsigned long long* counter, hipStream_t s, const uint32_t* order) {
-    if (n_tiles == 0) return;
-    const uint32_t n_wt = wave_tiles(n_tiles, bin);
+void launch_render(const TileLists& tl, const float* gamma, int C, BlendParams bp, float* images,
+                   unsigned long long* counter, hipStream_t s) {
+    if (tl.n_bins == 0) return;
+    const uint32_t n_wt = wave_tiles(tl.n_bins, tl.bin);
     dim3 grid((n_wt + 3) / 4), block(256);
-#define GSC_RENDER(CCV, BINV)                                                                     \
-    hipLaunchKernelGGL((k_render<CCV, BINV>), grid, block, 0, s, views, n_views, n_wt, ranges,    \
-                       pair_vals, rec0, rec1, rec2, gamma, C, c_off, bp, images, counter, order)
+#define GSC_RENDER(CCV, BINV)                                                                            \
+    hipLaunchKernelGGL((k_render<CCV, BINV>), grid, block, 0, s, tl.views, tl.n_views, n_wt, tl.ranges, \
+                       tl.pair_vals, tl.rec, tl.items, gamma, C, c_off, bp, images, counter, tl.order)
     for (int c_off = 0; c_off < C; c_off += 4) {
         const bool three = C <= 3 && c_off == 0;
-        if (bin == 32) {
+        if (tl.bin == 32) {
             if (three) GSC_RENDER(3, 32); else GSC_RENDER(4, 32);
         } else {
             if (three) GSC_RENDER(3, 16); else GSC_RENDER(4, 16);
