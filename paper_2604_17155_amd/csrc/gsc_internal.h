@@ -146,6 +146,21 @@ struct TileLists {
     const uint32_t* items;
     const uint32_t* order;
 };
+// 16x16 tiles of the lists.
+inline uint32_t wave_tiles(uint32_t n_bins, int bin) { return bin == 32 ? 4u * n_bins : n_bins; }
+// Whether the tile kernels run one wave per 8x8 block instead of one per tile
+// (walk_block): launches that leave SIMDs idle and are bound by their longest
+// list.  Measured, us a call, tile form against block form.  16-pixel bins:
+// 100k blob Gaussians, degree 3, 4 / 6 / 8 views of 512x512 (4096 / 6144 /
+// 8192 tiles): 573 / 633 / 668 against 523 / 652 / 734; an optimisation step
+// on 1 / 2 / 3 views of 640x640 (1600 / 3200 / 4800): 1996 / 2139 / 2287
+// against 1205 / 1757 / 2235.  32-pixel bins (larger footprints, whose entries
+// meet all four blocks, and four times the gathers): one mask channel on
+// 480x320 / 640x480 / 2 x 640x480 (600 / 1200 / 2400 tiles): 253 / 260 / 268
+// against 239 / 279 / 355.
+inline bool few_tiles(const TileLists& tl) {
+    return wave_tiles(tl.n_bins, tl.bin) <= (tl.bin == 16 ? 4096u : 1024u);
+}
 
 // Sum of n uint32 counts into *out (u64, must be zeroed).
 void launch_sum_u64(const uint32_t* counts, uint32_t n, unsigned long long* out, hipStream_t s);

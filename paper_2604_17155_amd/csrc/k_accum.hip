@@ -332,8 +332,112 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(acc_waves_p
     if (c_off == 0 && lane == 0 && cnt) atomicAdd(counter, (unsigned long long)cnt);
 }
 
-// Waves (16x16 tiles) of a launch over n_bins bins of `bin` pixels.
-static inline uint32_t wave_tiles(uint32_t n_bins, int bin) { return bin == 32 ? 4u * n_bins : n_bins; }
+// ---- few tiles: one wave per 8x8 block ------------------------------------
+//
+// See walk_block.  Four entries' values, VPE = 1, 4, 8 or 16 per entry (the
+// weight and CC = VPE - 1 channels), are reduced over the wave 16 at a time
+// (four entries, two or one; weights only: four values at once), one atomic
+// instruction per reduction.
+template <int CC, bool BF16, int BIN>
+__global__ __launch_bounds__(256) void k_accumulate_blocks(
+    const ViewInfo* __restrict__ views, int n_views, uint32_t n_tiles, const uint2* __restrict__ ranges,
+    const uint32_t* __restrict__ pair_vals, const float4* __restrict__ rec,
+    const uint32_t* __restrict__ items, const void* __restrict__ targets, int C, int c_off, int per_view,
+    BlendParams bp, float* __restrict__ VS, unsigned long long* __restrict__ counter,
+    uint32_t* __restrict__ gcount, const uint32_t* __restrict__ order) {
+    constexpr int CCA = CC > 0 ? CC : 1;
+    constexpr int VPE = CC + 1;
+    static_assert(VPE == 1 || VPE == 4 || VPE == 8 || VPE == 16, "values per entry");
+    __shared__ WalkLds<0> lds[4];
+    const uint32_t lane = threadIdx.x & 63, kq = threadIdx.x >> 6;
+    const uint32_t wi = xcd_block(blockIdx.x, gridDim.x);
+    if (wi >= n_tiles) return;
+    const TileGeom tg = tile_geom<BIN>(queued_tile<BIN>(wi, order), views, n_views);
+    const ViewInfo& V = views[tg.vloc];
+    const int ix = tg.x0 + block_px(lane, (int)kq), iy = tg.y0 + block_py(lane, (int)kq);
+    const bool inside = (ix < V.width) & (iy < V.height);
+    if (__builtin_amdgcn_ballot_w64(inside) == 0) return;  // whole wave
+    const int64_t row = V.pixel_offset + (int64_t)iy * V.width + ix;
+    float y[CCA];
+#pragma unroll
+    for (int c = 0; c < CC; ++c) {
+        const bool use = inside && c_off + c < C;
+        const float v = load_target<BF16>(targets, use ? row * C + c_off + c : 0);
+        y[c] = use ? v : 0.0f;
+    }
+    uint2 rg = ranges[tg.bin];
+    rg.x = (uint32_t)__builtin_amdgcn_readfirstlane((int)rg.x);
+    rg.y = (uint32_t)__builtin_amdgcn_readfirstlane((int)rg.y);
+    const int64_t item_base = V.item_base, slot_base = per_view ? V.vs_base : V.g_offset, g_off = V.g_offset;
+    const int stride = C + 1;
+    const bool first_chunk = c_off == 0;
+    const float tmin = uniform_in_vgpr(bp.t_min);
+    float T = inside ? 1.0f : kOutsideT;
+    uint32_t cnt = 0;
+    walk_block<BIN, 0>(tg, kq, lane, rg, pair_vals, rec, items, bp, lds[kq], [](bool, uint32_t, float4*) {},
+                       [&](const WalkGroup<0>& g) -> bool {
+        float w[kWalkEntries];
+        uint32_t nh[kWalkEntries];
+        uint64_t kept = 0;
+#pragma unroll
+        for (int u = 0; u < kWalkEntries; ++u) {
+            w[u] = pixel_blend(g.ae[u], T, tmin, kept);
+            nh[u] = (uint32_t)__popcll(g.cand[u] & kept);
+            cnt += nh[u];
+        }
+        if (gcount != nullptr && first_chunk && lane == 0) {
+#pragma unroll
+            for (int u = 0; u < kWalkEntries; ++u)
+                if (nh[u] != 0u) atomicAdd(gcount + g_off + ((int64_t)g.item[u] - item_base), nh[u]);
+        }
+        constexpr int NV = VPE == 1 ? kWalkEntries : 16;  // values per reduction
+        constexpr int EPR = NV / VPE;                     // entries per reduction
+#pragma unroll
+        for (int e0 = 0; e0 < kWalkEntries; e0 += EPR) {
+            uint32_t any = 0;
+#pragma unroll
+            for (int e = 0; e < EPR; ++e) any |= nh[e0 + e];
+            if (any == 0u) continue;  // uniform
+            float pend[NV];
+#pragma unroll
+            for (int e = 0; e < EPR; ++e) {
+                pend[e * VPE] = w[e0 + e];
+#pragma unroll
+                for (int c = 0; c < CC; ++c) pend[e * VPE + 1 + c] = w[e0 + e] * y[c];
+            }
+            const float t = wave_sum_transposed<NV>(pend, lane);
+            const int idx = transposed_index<NV>(lane);
+            const int e = idx / VPE, v = idx % VPE;
+            uint32_t item = g.item[e0], h = nh[e0];
+#pragma unroll
+            for (int q = 1; q < EPR; ++q) {
+                item = e == q ? g.item[e0 + q] : item;
+                h = e == q ? nh[e0 + q] : h;
+            }
+            const bool use = lane < (uint32_t)NV && h != 0u && (v == 0 ? first_chunk : c_off + v - 1 < C);
+            if (use)
+                unsafeAtomicAdd(VS + (slot_base + ((int64_t)item - item_base)) * (int64_t)stride + (v == 0 ? 0 : c_off + v), t);
+        }
+        return kept != 0;
+    });
+    if (c_off == 0 && lane == 0 && cnt) atomicAdd(counter, (unsigned long long)cnt);
+}
+
+template <int CC, bool BF16>
+static void launch_acc_blocks(const TileLists& tl, const void* targets, int C, bool per_view, BlendParams bp,
+                              float* VS, unsigned long long* counter, uint32_t* gcount, hipStream_t s) {
+    const uint32_t n_wt = wave_tiles(tl.n_bins, tl.bin);
+    for (int c_off = 0; c_off < std::max(C, 1); c_off += std::max(CC, 1)) {
+        if (tl.bin == 32)
+            hipLaunchKernelGGL((k_accumulate_blocks<CC, BF16, 32>), dim3(n_wt), dim3(256), 0, s, tl.views,
+                               tl.n_views, n_wt, tl.ranges, tl.pair_vals, tl.rec, tl.items, targets, C, c_off,
+                               (int)per_view, bp, VS, counter, gcount, tl.order);
+        else
+            hipLaunchKernelGGL((k_accumulate_blocks<CC, BF16, 16>), dim3(n_wt), dim3(256), 0, s, tl.views,
+                               tl.n_views, n_wt, tl.ranges, tl.pair_vals, tl.rec, tl.items, targets, C, c_off,
+                               (int)per_view, bp, VS, counter, gcount, tl.order);
+    }
+}
 
 template <int CC, bool BF16, int BIN, bool DET = false>
 static void launch_acc_k(const TileLists& tl, const void* targets, int C, bool per_view, BlendParams bp,
@@ -804,6 +908,18 @@ void launch_accumulate(const TileLists& tl, const void* targets, int tdtype, int
     if (tl.n_bins == 0) return;
     chunk = resolve_chunk(chunk, C, tdtype);
     if (det && (chunk & kChunkMfma)) chunk = accumulate_chunk(C, GSC_F32);  // vector form only
+    if (!det && few_tiles(tl) && !(chunk & kChunkMfma)) {
+#define GSC_ACCB(CCV)                                                                                    \
+    do {                                                                                                 \
+        if (tdtype == GSC_BF16) launch_acc_blocks<CCV, true>(tl, targets, C, per_view, bp, VS, counter, gcount, s); \
+        else launch_acc_blocks<CCV, false>(tl, targets, C, per_view, bp, VS, counter, gcount, s);        \
+    } while (0)
+        if (C <= 3) GSC_ACCB(3);
+        else if (C <= 7) GSC_ACCB(7);
+        else GSC_ACCB(15);
+#undef GSC_ACCB
+        return;
+    }
     if (queues) launch_fill_u32(queues, 0u, (uint64_t)accumulate_launches(C, chunk), s);
     if (chunk & kChunkMfma) {
 #define GSC_ACCM(NB, YMV) \
@@ -835,6 +951,10 @@ void launch_accumulate(const TileLists& tl, const void* targets, int tdtype, int
 void launch_accumulate_weights(const TileLists& tl, bool per_view, BlendParams bp, float* V,
                                unsigned long long* counter, hipStream_t s) {
     if (tl.n_bins == 0) return;
+    if (few_tiles(tl)) {
+        launch_acc_blocks<0, false>(tl, nullptr, 0, per_view, bp, V, counter, nullptr, s);
+        return;
+    }
     if (tl.bin == 32)
         launch_acc_k<0, false, 32>(tl, nullptr, 0, per_view, bp, V, counter, nullptr, nullptr, s);
     else

@@ -339,10 +339,155 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(adj_waves_p
     });
 }
 
+// Few tiles: one wave per 8x8 block (walk_block) for both passes; CC = 4 EX - 1
+// channels per launch and delta as an entry's extra values.  Two passes of the
+// same arithmetic as above.
+template <int EX, bool BF16, bool GY, int BIN>
+__global__ __launch_bounds__(256) void k_blend_adjoint_blocks(
+    const ViewInfo* __restrict__ views, int n_views, uint32_t n_tiles, const uint2* __restrict__ ranges,
+    const uint32_t* __restrict__ pair_vals, const float4* __restrict__ rec,
+    const uint32_t* __restrict__ items, const void* __restrict__ ypix, int C, int c_off,
+    const float* __restrict__ beta, BlendParams bp, float* __restrict__ grad_y, float* __restrict__ grad_o,
+    const uint32_t* __restrict__ order) {
+    constexpr int CC = 4 * EX - 1;
+    __shared__ WalkLds<EX> lds[4];
+    const uint32_t lane = threadIdx.x & 63, kq = threadIdx.x >> 6;
+    const uint32_t wi = xcd_block(blockIdx.x, gridDim.x);
+    if (wi >= n_tiles) return;
+    const TileGeom tg = tile_geom<BIN>(queued_tile<BIN>(wi, order), views, n_views);
+    const ViewInfo& V = views[tg.vloc];
+    const int ix = tg.x0 + block_px(lane, (int)kq), iy = tg.y0 + block_py(lane, (int)kq);
+    const bool inside = (ix < V.width) & (iy < V.height);
+    if (__builtin_amdgcn_ballot_w64(inside) == 0) return;  // whole wave
+    const int64_t row = V.pixel_offset + (int64_t)iy * V.width + ix;
+    const int stride = C + 1;
+    const bool first_chunk = c_off == 0;
+    const int64_t g_shift = V.g_offset - (int64_t)V.item_base;
+    float yv[CC];
+#pragma unroll
+    for (int c = 0; c < CC; ++c)
+        yv[c] = (inside && grad_o && c_off + c < C) ? load_target<BF16>(ypix, row * C + c_off + c) : 0.0f;
+    uint2 rg = ranges[tg.bin];
+    rg.x = (uint32_t)__builtin_amdgcn_readfirstlane((int)rg.x);
+    rg.y = (uint32_t)__builtin_amdgcn_readfirstlane((int)rg.y);
+    const float tmin = uniform_in_vgpr(bp.t_min), amax = uniform_in_vgpr(bp.alpha_max);
+    // an entry's adjoint colours, then delta (the first channel chunk carries it)
+    auto load_ex = [&](bool own, uint32_t item, float4 (&ex)[EX]) {
+        const float* bl = beta + (int64_t)item * stride;
+        float v[4 * EX];
+#pragma unroll
+        for (int c = 0; c < CC; ++c) v[c] = (own && c_off + c < C) ? bl[c_off + c] : 0.0f;
+        v[CC] = (own && first_chunk) ? bl[C] : 0.0f;
+#pragma unroll
+        for (int x = 0; x < EX; ++x) ex[x] = make_float4(v[4 * x], v[4 * x + 1], v[4 * x + 2], v[4 * x + 3]);
+    };
+    auto values = [](const float4 (&ex)[EX], float (&v)[4 * EX]) {
+#pragma unroll
+        for (int x = 0; x < EX; ++x) {
+            v[4 * x] = ex[x].x;
+            v[4 * x + 1] = ex[x].y;
+            v[4 * x + 2] = ex[x].z;
+            v[4 * x + 3] = ex[x].w;
+        }
+    };
+    // pass 1: S = sum_k u_k w_k per pixel, and dL/dy
+    double S = 0.0;
+    float gy[GY ? CC : 1];
+#pragma unroll
+    for (int c = 0; c < (GY ? CC : 1); ++c) gy[c] = 0.0f;
+    float T = inside ? 1.0f : kOutsideT;
+    walk_block<BIN, EX>(tg, kq, lane, rg, pair_vals, rec, items, bp, lds[kq], load_ex,
+                        [&](const WalkGroup<EX>& g) -> bool {
+        uint64_t kept = 0;
+#pragma unroll
+        for (int e = 0; e < kWalkEntries; ++e) {
+            float v[4 * EX];
+            values(g.ex[e], v);
+            const float w = pixel_blend(g.ae[e], T, tmin, kept);
+            float u = -v[CC];
+#pragma unroll
+            for (int c = 0; c < CC; ++c) u = fmaf(v[c], yv[c], u);
+            S += (double)(w * u);
+            if constexpr (GY) {
+#pragma unroll
+                for (int c = 0; c < CC; ++c) gy[c] = fmaf(w, v[c], gy[c]);
+            }
+        }
+        return kept != 0;
+    });
+    if constexpr (GY) {
+        if (inside) {
+#pragma unroll
+            for (int c = 0; c < CC; ++c)
+                if (c_off + c < C) grad_y[row * C + c_off + c] = gy[c];
+        }
+    }
+    if (grad_o == nullptr) return;
+    // pass 2: dL/dalpha per entry, reduced to dL/do per Gaussian
+    double P = 0.0;
+    T = inside ? 1.0f : kOutsideT;
+    walk_block<BIN, EX>(tg, kq, lane, rg, pair_vals, rec, items, bp, lds[kq], load_ex,
+                        [&](const WalkGroup<EX>& g) -> bool {
+        uint64_t kept = 0;
+        float go[kWalkEntries];
+        uint32_t any[kWalkEntries], hit = 0;
+#pragma unroll
+        for (int e = 0; e < kWalkEntries; ++e) {
+            float v[4 * EX];
+            values(g.ex[e], v);
+            const float Tb = T;
+            const float w = pixel_blend(g.ae[e], T, tmin, kept);
+            float u = -v[CC];
+#pragma unroll
+            for (int c = 0; c < CC; ++c) u = fmaf(v[c], yv[c], u);
+            P += (double)(w * u);
+            const uint64_t taken = g.cand[e] & kept;
+            const float G = __builtin_amdgcn_exp2f(g.q2[e]);
+            const float suffix = (float)(S - P);
+            const float dal = u * Tb - suffix / (1.0f - g.ae[e]);
+            const bool use = ((taken >> lane) & 1u) != 0u && !(g.opac[e] * G >= amax);
+            go[e] = use ? dal * G : 0.0f;
+            any[e] = taken != 0 ? 1u : 0u;
+            hit |= any[e];
+        }
+        if (hit != 0u) {  // uniform
+            const float t = wave_sum_transposed<kWalkEntries>(go, lane);
+            const int e = transposed_index<kWalkEntries>(lane);
+            uint32_t item = g.item[0], h = any[0];
+#pragma unroll
+            for (int q = 1; q < kWalkEntries; ++q) {
+                item = e == q ? g.item[q] : item;
+                h = e == q ? any[q] : h;
+            }
+            if (lane < (uint32_t)kWalkEntries && h != 0u) unsafeAtomicAdd(grad_o + ((int64_t)item + g_shift), t);
+        }
+        return kept != 0;
+    });
+}
+
+template <int EX, bool GY>
+static void launch_badj_blocks(const TileLists& tl, const void* ypix, int ydtype, int C, const float* beta,
+                               BlendParams bp, float* grad_y, float* grad_o, hipStream_t s) {
+    const uint32_t n_wt = wave_tiles(tl.n_bins, tl.bin);
+    const bool bf = ydtype == GSC_BF16;
+#define GSC_BADJB(BFV, BINV)                                                                               \
+    hipLaunchKernelGGL((k_blend_adjoint_blocks<EX, BFV, GY, BINV>), dim3(n_wt), dim3(256), 0, s, tl.views, \
+                       tl.n_views, n_wt, tl.ranges, tl.pair_vals, tl.rec, tl.items, ypix, C, c_off, beta,  \
+                       bp, grad_y, grad_o, tl.order)
+    for (int c_off = 0; c_off < C; c_off += 4 * EX - 1) {
+        if (tl.bin == 32) {
+            if (bf) GSC_BADJB(true, 32); else GSC_BADJB(false, 32);
+        } else {
+            if (bf) GSC_BADJB(true, 16); else GSC_BADJB(false, 16);
+        }
+    }
+#undef GSC_BADJB
+}
+
 template <int CC, bool GY>
 static void launch_badj_cc(const TileLists& tl, const void* ypix, int ydtype, int C, const float* beta,
                            BlendParams bp, float* grad_y, float* grad_o, hipStream_t s) {
-    const uint32_t n_wt = tl.bin == 32 ? 4u * tl.n_bins : tl.n_bins;
+    const uint32_t n_wt = wave_tiles(tl.n_bins, tl.bin);
     dim3 grid((n_wt + 3) / 4), block(256);
 #define GSC_BADJ(BFV, BINV)                                                                          \
     hipLaunchKernelGGL((k_blend_adjoint<CC, BFV, GY, BINV>), grid, block, 0, s, tl.views, tl.n_views, \
@@ -362,6 +507,12 @@ static void launch_badj_cc(const TileLists& tl, const void* ypix, int ydtype, in
 template <bool GY>
 static void launch_badj(const TileLists& tl, const void* ypix, int ydtype, int C, const float* beta,
                         BlendParams bp, float* grad_y, float* grad_o, hipStream_t s) {
+    if (few_tiles(tl)) {
+        if (C <= 3) launch_badj_blocks<1, GY>(tl, ypix, ydtype, C, beta, bp, grad_y, grad_o, s);
+        else if (C <= 7) launch_badj_blocks<2, GY>(tl, ypix, ydtype, C, beta, bp, grad_y, grad_o, s);
+        else launch_badj_blocks<4, GY>(tl, ypix, ydtype, C, beta, bp, grad_y, grad_o, s);
+        return;
+    }
 #define GSC_BA(CCV) launch_badj_cc<CCV, GY>(tl, ypix, ydtype, C, beta, bp, grad_y, grad_o, s)
     switch (accumulate_chunk(C, GSC_F32)) {  // vector-lane channel chunks
         case 1: GSC_BA(1); break;

@@ -7,8 +7,6 @@
 
 namespace gsc {
 
-static inline uint32_t wave_tiles(uint32_t n_bins, int bin) { return bin == 32 ? 4u * n_bins : n_bins; }
-
 // 64 x 64 tiles through LDS: rows read and columns written as contiguous
 // runs (the padded row keeps the column reads free of bank conflicts).
 __global__ __launch_bounds__(256) void k_transpose(const float* __restrict__ in, int64_t rows, int K,
@@ -192,10 +190,85 @@ __global__ __launch_bounds__(256) void k_render(
     if (c_off == 0 && lane == 0 && cnt) atomicAdd(counter, (unsigned long long)cnt);
 }
 
+// Few tiles: one wave per 8x8 block (walk_block), CC = 4 * EX channels per launch.
+template <int EX, int BIN>
+__global__ __launch_bounds__(256) void k_render_blocks(
+    const ViewInfo* __restrict__ views, int n_views, uint32_t n_tiles, const uint2* __restrict__ ranges,
+    const uint32_t* __restrict__ pair_vals, const float4* __restrict__ rec,
+    const uint32_t* __restrict__ items, const float* __restrict__ gamma, int C, int c_off, BlendParams bp,
+    float* __restrict__ images, unsigned long long* __restrict__ counter, const uint32_t* __restrict__ order) {
+    constexpr int CC = 4 * EX;
+    __shared__ WalkLds<EX> lds[4];
+    const uint32_t lane = threadIdx.x & 63, kq = threadIdx.x >> 6;
+    const uint32_t wi = xcd_block(blockIdx.x, gridDim.x);
+    if (wi >= n_tiles) return;
+    const TileGeom tg = tile_geom<BIN>(queued_tile<BIN>(wi, order), views, n_views);
+    const ViewInfo& V = views[tg.vloc];
+    const int ix = tg.x0 + block_px(lane, (int)kq), iy = tg.y0 + block_py(lane, (int)kq);
+    const bool inside = (ix < V.width) & (iy < V.height);
+    if (__builtin_amdgcn_ballot_w64(inside) == 0) return;  // whole wave
+    uint2 rg = ranges[tg.bin];
+    rg.x = (uint32_t)__builtin_amdgcn_readfirstlane((int)rg.x);
+    rg.y = (uint32_t)__builtin_amdgcn_readfirstlane((int)rg.y);
+    const float tmin = uniform_in_vgpr(bp.t_min);
+    float T = inside ? 1.0f : kOutsideT;
+    float img[CC];
+#pragma unroll
+    for (int c = 0; c < CC; ++c) img[c] = 0.0f;
+    uint32_t cnt = 0;
+    walk_block<BIN, EX>(tg, kq, lane, rg, pair_vals, rec, items, bp, lds[kq],
+                        [&](bool own, uint32_t item, float4 (&ex)[EX]) {
+        const float* gl = gamma + (int64_t)item * C + c_off;
+        float v[CC];
+#pragma unroll
+        for (int c = 0; c < CC; ++c) v[c] = (own && c_off + c < C) ? gl[c] : 0.0f;
+#pragma unroll
+        for (int x = 0; x < EX; ++x) ex[x] = make_float4(v[4 * x], v[4 * x + 1], v[4 * x + 2], v[4 * x + 3]);
+    }, [&](const WalkGroup<EX>& g) -> bool {
+        uint64_t kept = 0;
+#pragma unroll
+        for (int u = 0; u < kWalkEntries; ++u) {
+            const float w = pixel_blend(g.ae[u], T, tmin, kept);
+            cnt += (uint32_t)__popcll(g.cand[u] & kept);
+#pragma unroll
+            for (int x = 0; x < EX; ++x) {
+                const float4 c4 = g.ex[u][x];
+                img[4 * x] = fmaf(w, c4.x, img[4 * x]);
+                img[4 * x + 1] = fmaf(w, c4.y, img[4 * x + 1]);
+                img[4 * x + 2] = fmaf(w, c4.z, img[4 * x + 2]);
+                img[4 * x + 3] = fmaf(w, c4.w, img[4 * x + 3]);
+            }
+        }
+        return kept != 0;
+    });
+    if (inside) {
+        float* out = images + (V.pixel_offset + (int64_t)iy * V.width + ix) * C + c_off;
+#pragma unroll
+        for (int c = 0; c < CC; ++c)
+            if (c_off + c < C) out[c] = img[c];
+    }
+    if (c_off == 0 && lane == 0 && cnt) atomicAdd(counter, (unsigned long long)cnt);
+}
+
 void launch_render(const TileLists& tl, const float* gamma, int C, BlendParams bp, float* images,
                    unsigned long long* counter, hipStream_t s) {
     if (tl.n_bins == 0) return;
     const uint32_t n_wt = wave_tiles(tl.n_bins, tl.bin);
+    if (few_tiles(tl)) {
+#define GSC_RENDERB(EXV, BINV)                                                                            \
+    hipLaunchKernelGGL((k_render_blocks<EXV, BINV>), dim3(n_wt), dim3(256), 0, s, tl.views, tl.n_views,   \
+                       n_wt, tl.ranges, tl.pair_vals, tl.rec, tl.items, gamma, C, c_off, bp, images,      \
+                       counter, tl.order)
+        for (int c_off = 0; c_off < C; c_off += C <= 4 ? 4 : 8) {
+            if (tl.bin == 32) {
+                if (C <= 4) GSC_RENDERB(1, 32); else GSC_RENDERB(2, 32);
+            } else {
+                if (C <= 4) GSC_RENDERB(1, 16); else GSC_RENDERB(2, 16);
+            }
+        }
+#undef GSC_RENDERB
+        return;
+    }
     dim3 grid((n_wt + 3) / 4), block(256);
 #define GSC_RENDER(CCV, BINV)                                                                            \
     hipLaunchKernelGGL((k_render<CCV, BINV>), grid, block, 0, s, tl.views, tl.n_views, n_wt, tl.ranges, \

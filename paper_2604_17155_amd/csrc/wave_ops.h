@@ -279,6 +279,139 @@ __device__ __forceinline__ float pixel_step(float q2, float opac, float& T, floa
     return keep ? wt : 0.0f;
 }
 
+// Effective alpha of a pixel (the first half of pixel_step, for walks that
+// form several entries' alphas before blending them in turn); `cand` gets the
+// lanes that pass both tests.
+__device__ __forceinline__ float pixel_alpha(float q2, float opac, float qlim, float amin, float amax,
+                                             uint64_t& cand) {
+    const float al = __builtin_amdgcn_fmed3f(opac * __builtin_amdgcn_exp2f(q2), 0.0f, amax);
+    const bool inq = q2 >= qlim, ina = al >= amin;
+    cand = __builtin_amdgcn_ballot_w64(inq) & __builtin_amdgcn_ballot_w64(ina);
+    return (inq & ina) ? al : 0.0f;
+}
+// The second half: the weight, and T after the entry.
+__device__ __forceinline__ float pixel_blend(float ae, float& T, float tmin, uint64_t& kept) {
+    const float wt = T * ae;
+    T = fmaf(-T, ae, T);
+    const bool keep = T >= tmin;
+    kept = __builtin_amdgcn_ballot_w64(keep);
+    return keep ? wt : 0.0f;
+}
+
+// ---- block walk ------------------------------------------------------------
+//
+// The form of the tile kernels for launches with few tiles: one wave owns one
+// 8x8 block (one pixel per lane) instead of a 16x16 tile, so a launch has four
+// times the waves and each walks only the entries that reach its block.  Such
+// launches are bound by the latency of their longest list (a tile's wave took
+// about 900 cycles per entry with nothing else on its SIMD to hide it), so the
+// entries are also taken four at a time without a branch: their records are
+// read from LDS together and their alphas are independent; only the products
+// with T follow one another.
+constexpr int kWalkEntries = 4;
+
+// LDS of one wave: the chunk's conic and opacity, centre offset and EX more
+// float4 per entry.
+template <int EX>
+struct WalkLds {
+    float4 rec1[64];
+    float2 rec0[64];
+    float4 ex[EX > 0 ? EX : 1][EX > 0 ? 64 : 1];
+};
+
+// Up to kWalkEntries entries, front to back.
+template <int EX>
+struct WalkGroup {
+    uint32_t item[kWalkEntries];     // their batch items (uniform)
+    float ae[kWalkEntries];          // effective alpha at the lane's pixel (0 past n)
+    float q2[kWalkEntries];
+    float opac[kWalkEntries];
+    uint64_t cand[kWalkEntries];     // lanes that pass the footprint and alpha tests
+    float4 ex[kWalkEntries][EX > 0 ? EX : 1];
+};
+
+// Walks the list rg of block kq of tile tg.  load_ex(own, item, ex) fetches an
+// entry's extra values; body(group) blends it and returns whether a pixel of
+// the block is still live.
+template <int BIN, int EX, typename LoadEx, typename Body>
+__device__ __forceinline__ void walk_block(const TileGeom& tg, uint32_t kq, uint32_t lane, uint2 rg,
+                                           const uint32_t* __restrict__ pair_vals,
+                                           const float4* __restrict__ rec, const uint32_t* __restrict__ items,
+                                           const BlendParams& bp, WalkLds<EX>& L, LoadEx&& load_ex, Body&& body) {
+    const float qlim = uniform_in_vgpr((float)(kExp2Scale * (double)bp.cut2));
+    const float amax = uniform_in_vgpr(bp.alpha_max), amin = uniform_in_vgpr(bp.alpha_min);
+    const float lx = tile_offset_col(lane, (int)(kq & 1u)), ly = tile_offset_row(lane, (int)(kq >> 1));
+    const float ox = tile_centre(tg.x0), oy = tile_centre(tg.y0);
+    struct Entry {
+        float2 r0;
+        float4 r1;
+        float4 ex[EX > 0 ? EX : 1];
+        uint32_t item;
+        bool own;
+    };
+    auto load_pv = [&](uint32_t b) -> uint32_t { return b + lane < rg.y ? pair_vals[b + lane] : 0u; };
+    auto gather = [&](uint32_t pv, uint32_t b, Entry& e) {
+        const uint32_t it = pv & kItemMask;
+        e.own = b + lane < rg.y && pair_reaches<BIN>(pv, tg.quad, 1u << kq);
+        const float4 r = e.own ? rec[2 * (size_t)it] : make_float4(0.f, 0.f, 0.f, 0.f);
+        e.r0 = make_float2((ox - r.x) - r.z, (oy - r.y) - r.w);
+        e.r1 = e.own ? rec[2 * (size_t)it + 1] : make_float4(0.f, 0.f, 0.f, 0.f);
+        e.item = e.own ? items[it] : 0u;
+        if constexpr (EX > 0) load_ex(e.own, e.item, e.ex);
+    };
+    uint32_t pv = load_pv(rg.x), pvn = load_pv(rg.x + 64);
+    Entry cur, nxt;
+    gather(pv, rg.x, cur);
+    bool live = true;
+    for (uint32_t b = rg.x; b < rg.y && live; b += 64) {
+        gather(pvn, b + 64, nxt);  // the next chunk is in flight while this one is blended
+        const uint32_t pvnn = load_pv(b + 128);
+        const uint32_t bl = cur.own ? entry_blocks<BIN>(pv, cur.r0, cur.r1, bp) : 0u;
+        uint64_t todo = __builtin_amdgcn_ballot_w64(((bl >> kq) & 1u) != 0u);
+        L.rec1[lane] = cur.r1;
+        L.rec0[lane] = cur.r0;
+        if constexpr (EX > 0) {
+#pragma unroll
+            for (int x = 0; x < EX; ++x) L.ex[x][lane] = cur.ex[x];
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        while (todo != 0u && live) {
+            WalkGroup<EX> g;
+            float2 c0[kWalkEntries];
+            float4 c1[kWalkEntries];
+            bool has[kWalkEntries];
+#pragma unroll
+            for (int u = 0; u < kWalkEntries; ++u) {
+                has[u] = todo != 0u;
+                const uint32_t j = has[u] ? (uint32_t)__builtin_ctzll(todo) : 0u;
+                todo &= todo - 1u;
+                g.item[u] = bcast_u(cur.item, j);
+                c0[u] = L.rec0[j];
+                c1[u] = L.rec1[j];
+                if constexpr (EX > 0) {
+#pragma unroll
+                    for (int x = 0; x < EX; ++x) g.ex[u][x] = L.ex[x][j];
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < kWalkEntries; ++u) {
+                const float dx = c0[u].x + lx, dy = c0[u].y + ly;
+                g.q2[u] = fmaf(dy, fmaf(c1[u].z, dy, c1[u].y * dx), c1[u].x * dx * dx);
+                g.opac[u] = c1[u].w;
+                const float ae = pixel_alpha(g.q2[u], c1[u].w, qlim, amin, amax, g.cand[u]);
+                g.ae[u] = has[u] ? ae : 0.0f;
+                g.cand[u] = has[u] ? g.cand[u] : 0ull;
+            }
+            live = body(g);
+        }
+        __builtin_amdgcn_wave_barrier();  // the next chunk's records overwrite these
+        cur = nxt;
+        pv = pvn;
+        pvn = pvnn;
+    }
+}
+
 template <bool BF16>
 __device__ __forceinline__ float load_target(const void* __restrict__ t, int64_t idx) {
     if constexpr (BF16) {
