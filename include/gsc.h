@@ -465,8 +465,9 @@ typedef struct {
     uint64_t contributions;     /* accepted contributions of the last run */
     uint64_t items;             /* (view, Gaussian) items per run */
     uint64_t pair_capacity;     /* tile pairs per run (exact for the planned geometry) */
-    uint32_t dropped_pairs;     /* items of the last run whose pairs exceeded the capacity
-                                   (non-zero only if the geometry changed after planning) */
+    uint32_t dropped_pairs;     /* items and list entries of the last run that exceeded the
+                                   capacity (non-zero only if the geometry changed after
+                                   planning) */
     uint32_t ill_conditioned;   /* Gaussians flagged GSC_G_ILL_COND by the last run */
     uint32_t batches;           /* view batches per run */
     uint32_t views;             /* views per run */

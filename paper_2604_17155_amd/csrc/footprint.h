@@ -9,9 +9,12 @@ namespace gsc {
 // Largest q at which a pixel can still pass both the footprint test
 // (q <= cut2) and the alpha floor (o exp(-q/2) >= alpha_min), with a margin
 // covering the FP32 evaluation in the blend; negative when nothing passes.
+// (No contraction here and below: binning counts, lists and masks footprints in
+// several kernels, which have to agree to the bit.)
 __device__ inline float reach_q(float o, const BlendParams& bp) {
+#pragma clang fp contract(off)
     if (!(o >= bp.alpha_min)) return -1.0f;
-    const float qa = 2.0f * __logf(o / bp.alpha_min);
+    const float qa = 2.0f * __logf(o * __builtin_amdgcn_rcpf(bp.alpha_min));
     const float q = fminf(bp.cut2, qa);
     return q * (1.0f + 1e-4f) + 1e-3f;
 }
@@ -19,107 +22,171 @@ __device__ inline float reach_q(float o, const BlendParams& bp) {
 // The ellipse {q <= qmax} of a record, q = a (dx + b dy / a)^2 + cq dy^2 with
 // (dx, dy) the offset from the projected centre.
 struct Ellipse {
-    float ia, bia, cq, qmax;
+    float bia;  // b / a
+    float qa;   // qmax / a, widened by 1e-4 in the half width it gives
+    float ca;   // cq / a, likewise
     float ry;   // row reach: |dy| <= ry
     float dyl;  // row offset of the leftmost point (the rightmost lies at -dyl)
 };
 __device__ inline bool make_ellipse(float4 r1, float qmax, Ellipse& e) {
+#pragma clang fp contract(off)
     constexpr float kInvK = (float)(1.0 / kExp2Scale);
     const float a = r1.x * kInvK, b = 0.5f * r1.y * kInvK, c = r1.z * kInvK;
     const float det = a * c - b * b;
     if (!(a > 0.0f && det > 0.0f && qmax > 0.0f)) return false;
-    e.ia = 1.0f / a;
-    e.bia = b * e.ia;
-    e.cq = det * e.ia;
-    e.qmax = qmax;
-    e.ry = __builtin_amdgcn_sqrtf(qmax / e.cq) * 1.0001f + 0.01f;
+    const float ia = __builtin_amdgcn_rcpf(a), cq = det * ia;
+    e.bia = b * ia;
+    e.qa = qmax * ia * 1.0002f;
+    e.ca = cq * ia * 1.0002f;
+    e.ry = __builtin_amdgcn_sqrtf(qmax * __builtin_amdgcn_rcpf(cq)) * 1.0001f + 0.01f;
     // dy = -sqrt(qmax / Sxx) Sxy with Sxx = c / det, Sxy = -b / det
-    const float idet = 1.0f / det, sxx = c * idet;
-    e.dyl = __builtin_amdgcn_sqrtf(qmax / sxx) * b * idet;
+    // (= sqrt(qmax / (c det)) b)
+    e.dyl = __builtin_amdgcn_sqrtf(qmax * __builtin_amdgcn_rcpf(c * det)) * b;
     return true;
 }
-// Offsets of the left and right edge over the rows [sa, sb] (row offsets from
-// the centre): the left edge is convex and the right edge concave in dy, so
-// each extreme lies at the row of the ellipse's leftmost / rightmost point,
-// clamped to the span.  Widened by 0.01 pixel and 1e-4 relative, so that a
-// walk over these extents is conservative with respect to the blend's FP32
-// test (and covers the ~1 ulp of the hardware square root).
-__device__ inline void ellipse_span(const Ellipse& e, float sa, float sb, float& l, float& r) {
+// Left and right edge over the rows [sa, sb] (row offsets from the centre) of
+// an ellipse centred at column c: the left edge is convex and the right edge
+// concave in dy, so each extreme lies at the row of the ellipse's leftmost /
+// rightmost point, clamped to the span.  Widened by 0.01 pixel and 1e-4
+// relative, so that a walk over these extents is conservative with respect to
+// the blend's FP32 test (and covers the ~1 ulp of the hardware square root,
+// reciprocal and logarithm used here).
+__device__ inline void ellipse_span(const Ellipse& e, float c, float sa, float sb, float& l, float& r) {
+#pragma clang fp contract(off)
     const float dl = __builtin_amdgcn_fmed3f(e.dyl, sa, sb), dr = __builtin_amdgcn_fmed3f(-e.dyl, sa, sb);
-    const float hl = __builtin_amdgcn_sqrtf(fmaxf(e.qmax - e.cq * dl * dl, 0.0f) * e.ia) * 1.0001f + 0.01f;
-    const float hr = __builtin_amdgcn_sqrtf(fmaxf(e.qmax - e.cq * dr * dr, 0.0f) * e.ia) * 1.0001f + 0.01f;
-    l = -e.bia * dl - hl;
-    r = -e.bia * dr + hr;
+    const float hl = __builtin_amdgcn_sqrtf(fmaxf(fmaf(-e.ca * dl, dl, e.qa), 0.0f));
+    const float hr = __builtin_amdgcn_sqrtf(fmaxf(fmaf(-e.ca * dr, dr, e.qa), 0.0f));
+    l = fmaf(-e.bia, dl, c - 0.01f) - hl;
+    r = fmaf(-e.bia, dr, c + 0.01f) + hr;
 }
 
-// Walks a record's footprint in rows of SUB x SUB pixel blocks and calls
-// visit(block_row, lo, hi) for every block row with a block whose pixel
-// centres come within the footprint: blocks lo..hi of that row.  Used
-// identically for counting and emitting.
-template <int SUB, typename Visit>
-__device__ inline void footprint_rows(float4 r0, float4 r1, float qmax, int W, int H, Visit&& visit) {
-    constexpr int kShift = SUB == 8 ? 3 : 4;
-    static_assert(SUB == 8 || SUB == 16, "blocks of 8 or 16 pixels");
+// Pixel rows [y0, y1] and the ellipse of a record's footprint in an image of
+// height H; false when no row is reached.
+struct Footprint {
     Ellipse e;
-    if (!make_ellipse(r1, qmax, e)) return;
+    float u, ulo, v, vlo;  // the projected centre as hi / lo pairs
+    int y0, y1;
+};
+__device__ inline bool make_footprint(float4 r0, float4 r1, float qmax, int H, Footprint& f) {
+#pragma clang fp contract(off)
+    if (!make_ellipse(r1, qmax, f.e)) return false;
     const float vc = r0.y - 0.5f + r0.w;  // row index whose centre is the mean
-    const float fy0 = fmaxf(ceilf(vc - e.ry), 0.0f);
-    const float fy1 = fminf(floorf(vc + e.ry), (float)(H - 1));
-    if (!(fy0 <= fy1)) return;
-    const int y0 = (int)fy0, y1 = (int)fy1;
-    const float cx = r0.x - 0.5f + r0.z;  // column index whose centre is the mean
-    for (int ya = y0; ya <= y1; ya = (ya | (SUB - 1)) + 1) {
-        const int yb = min(ya | (SUB - 1), y1);
-        float l, r;
-        ellipse_span(e, ((float)ya + 0.5f - r0.y) - r0.w, ((float)yb + 0.5f - r0.y) - r0.w, l, r);
-        const float xf = fmaxf(ceilf(cx + l), 0.0f);
-        const float xl = fminf(floorf(cx + r), (float)(W - 1));
-        if (xf <= xl) visit(ya >> kShift, (int)xf >> kShift, (int)xl >> kShift);
+    const float fy0 = fmaxf(ceilf(vc - f.e.ry), 0.0f);
+    const float fy1 = fminf(floorf(vc + f.e.ry), (float)(H - 1));
+    if (!(fy0 <= fy1)) return false;
+    f.u = r0.x;
+    f.ulo = r0.z;
+    f.v = r0.y;
+    f.vlo = r0.w;
+    f.y0 = (int)fy0;
+    f.y1 = (int)fy1;
+    return true;
+}
+// Pixel columns [xa, xb] of an image of width W whose centres the footprint
+// reaches over the rows ya..yb; false when there are none.
+__device__ inline bool footprint_cols(const Footprint& f, int ya, int yb, int W, int& xa, int& xb) {
+#pragma clang fp contract(off)
+    float l, r;
+    const float cx = f.u - 0.5f + f.ulo;  // column index whose centre is the mean
+    ellipse_span(f.e, cx, ((float)ya + 0.5f - f.v) - f.vlo, ((float)yb + 0.5f - f.v) - f.vlo, l, r);
+    const float xf = fmaxf(ceilf(l), 0.0f), xl = fminf(floorf(r), (float)(W - 1));
+    if (!(xf <= xl)) return false;
+    xa = (int)xf;
+    xb = (int)xl;
+    return true;
+}
+
+// A group is 4 x 4 bins, 8 x 8 blocks of BIN / 2 pixels.
+template <int BIN>
+constexpr int group_shift() { return BIN == 16 ? 6 : 7; }
+
+// Calls visit(group_row, gx0, gx1) for every group row with a group that the
+// footprint reaches.
+template <int BIN, typename Visit>
+__device__ inline void footprint_groups(const Footprint& f, int W, Visit&& visit) {
+    constexpr int kS = group_shift<BIN>();
+    for (int gy = f.y0 >> kS; gy <= f.y1 >> kS; ++gy) {
+        const int ya = max(f.y0, gy << kS), yb = min(f.y1, (gy << kS) + (1 << kS) - 1);
+        int xa, xb;
+        if (footprint_cols(f, ya, yb, W, xa, xb)) visit(gy, xa >> kS, xb >> kS);
     }
 }
 
-// Footprint per bin row; a bin is 2 x 2 blocks of BIN / 2 pixels and the
-// 4-bit mask's bit 2h + c marks the block in row half h and column half c.
-// visit(bin_row, t0, t1, mask_of, n, h) is called per bin row with the bin
-// columns [t0, t1], a function giving a bin column's mask (0: not reached),
-// n, the number of columns in [t0, t1] whose mask is not 0, and h = the first
-// and last block column reached in each row half (lo0, hi0, lo1, hi1; lo > hi:
-// none).
-template <int BIN, typename Visit>
-__device__ inline void footprint_bins(float4 r0, float4 r1, float qmax, int W, int H, Visit&& visit) {
-    static_assert(BIN == 16 || BIN == 32, "bins are 16 or 32 pixels");
-    int cur = -1, lo[2] = {1 << 30, 1 << 30}, hi[2] = {-1, -1};
-    auto flush = [&]() {
-        if (cur < 0) return;
-        // a bin column t has a block of row half h reached exactly when
-        // lo[h] >> 1 <= t <= hi[h] >> 1 (block columns are >= 0; an unreached
-        // half has lo > hi and gives an empty range), so the reached columns
-        // are the union of two ranges
-        const int a0 = lo[0] >> 1, a1 = hi[0] >> 1, c0 = lo[1] >> 1, c1 = hi[1] >> 1;
-        const int na = max(a1 - a0 + 1, 0), nc = max(c1 - c0 + 1, 0);
-        const int nboth = max(min(a1, c1) - max(a0, c0) + 1, 0);
-        visit(cur, min(lo[0], lo[1]) >> 1, max(hi[0], hi[1]) >> 1, [&](int t) {
-            uint32_t m = 0;
-            for (int h = 0; h < 2; ++h)
-                for (int c = 0; c < 2; ++c)
-                    m |= (lo[h] <= 2 * t + c && 2 * t + c <= hi[h]) ? (1u << (2 * h + c)) : 0u;
-            return m;
-        }, na + nc - nboth, make_int4(lo[0], hi[0], lo[1], hi[1]));
-    };
-    footprint_rows<BIN / 2>(r0, r1, qmax, W, H, [&](int br, int l, int h) {
-        if ((br >> 1) != cur) {
-            flush();
-            cur = br >> 1;
-            lo[0] = lo[1] = 1 << 30;
-            hi[0] = hi[1] = -1;
-        }
-        // (selects, so that the ranges stay in registers)
-        lo[0] = (br & 1) ? lo[0] : l;
-        hi[0] = (br & 1) ? hi[0] : h;
-        lo[1] = (br & 1) ? l : lo[1];
-        hi[1] = (br & 1) ? h : hi[1];
-    });
-    flush();
+// The groups an item is listed in: their number, and in `rect` how to list
+// them.  Footprints whose bounding box meets few groups or a single row or
+// column of them (nearly all) are listed by the box, column | row << 9 |
+// width << 18; others by the walk above, rect = kRectWalk.
+constexpr uint32_t kRectWalk = 1u << 31;
+template <int BIN>
+__device__ inline uint32_t count_groups(const Footprint& f, int W, uint32_t& rect) {
+    constexpr int kS = group_shift<BIN>();
+    rect = 0u;
+    int xa, xb;
+    if (!footprint_cols(f, f.y0, f.y1, W, xa, xb)) return 0u;
+    const uint32_t gx = (uint32_t)(xa >> kS), gy = (uint32_t)(f.y0 >> kS);
+    const uint32_t w = (uint32_t)(xb >> kS) - gx + 1u, h = (uint32_t)(f.y1 >> kS) - gy + 1u;
+    if (w * h <= 4u || w == 1u || h == 1u) {
+        rect = gx | (gy << 9) | (w << 18);
+        return w * h;
+    }
+    rect = kRectWalk;
+    uint32_t n = 0;
+    footprint_groups<BIN>(f, W, [&](int, int a, int b) { n += (uint32_t)(b - a + 1); });
+    return n;
+}
+
+// The blocks of the group at pixel (X0, Y0) that the footprint reaches, as
+// 4-bit masks of its bins: bin f = 4 * bin_row + bin_col has bits 4 (f & 7) ..
+// + 3 of x (f < 8) or y.  `on`: this lane has a record.  The active lanes step
+// through block rows together, each through its own footprint's, so a wave
+// takes as many steps as its tallest footprint.
+template <int BIN>
+__device__ inline uint2 group_masks(bool on, const Footprint& f, int X0, int Y0, int W) {
+#pragma clang fp contract(off)
+    constexpr int kSub = BIN / 2, kS = BIN == 16 ? 3 : 4;
+    const int ya0 = max(f.y0 - Y0, 0), yb0 = min(f.y1 - Y0, 8 * kSub - 1);  // rows within the group
+    int s = ya0 >> kS;
+    const int s1 = on ? yb0 >> kS : -1;
+    // offsets of the first and last row, and of row 0 of the current block row
+    const float dy0 = ((float)Y0 + 0.5f - f.v) - f.vlo;
+    const float da = dy0 + (float)ya0, db = dy0 + (float)yb0;
+    float d = dy0 + (float)(s << kS);
+    const float cx = (f.u - (float)X0) - 0.5f + f.ulo;  // columns within the group
+    const float xmax = (float)min(8 * kSub - 1, W - 1 - X0);
+    uint32_t sh = 8u * (uint32_t)s;
+    uint64_t m = 0;  // bit 8 * block_row + block_col
+    while (__builtin_amdgcn_ballot_w64(s <= s1) != 0) {  // uniform
+        float l, r;
+        ellipse_span(f.e, cx, fmaxf(d, da), fminf(d + (float)(kSub - 1), db), l, r);
+        const int lo = (int)fmaxf(ceilf(l), 0.0f) >> kS, hi = (int)fminf(floorf(r), xmax) >> kS;
+        // block columns lo..hi (hi < lo: none)
+        const uint32_t n = s <= s1 ? (uint32_t)max(hi - lo + 1, 0) : 0u;
+        const uint32_t byte = ((1u << (n & 31u)) - 1u) << (lo & 31);
+        m |= (uint64_t)byte << (sh & 63u);
+        ++s;
+        sh += 8u;
+        d += (float)kSub;
+    }
+    // two bits per bin to the low (even rows) or high half of its nibble
+    uint32_t o[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const uint32_t x = h ? (uint32_t)(m >> 32) : (uint32_t)m;
+        uint32_t even = x & 0x00FF00FFu, odd = (x >> 8) & 0x00FF00FFu;
+        even = (even | (even << 4)) & 0x0F0F0F0Fu;
+        odd = (odd | (odd << 4)) & 0x0F0F0F0Fu;
+        even = (even | (even << 2)) & 0x33333333u;
+        odd = (odd | (odd << 2)) & 0x33333333u;
+        o[h] = even | (odd << 2);
+    }
+    return make_uint2(o[0], o[1]);
+}
+// Bit 4 (f & 7) of x or y: bin f is reached.
+__device__ __forceinline__ uint2 reached_bins(uint2 m) {
+    uint32_t x = m.x | (m.x >> 1), y = m.y | (m.y >> 1);
+    x = (x | (x >> 2)) & 0x11111111u;
+    y = (y | (y >> 2)) & 0x11111111u;
+    return make_uint2(x, y);
 }
 
 // The 8x8 pixel blocks (bit 2 * row half + column half) of a 16x16 tile that
@@ -134,14 +201,11 @@ __device__ inline uint32_t footprint_blocks(float2 off, float4 r1, float qmax) {
     for (int h = 0; h < 2; ++h) {
         const float sa = off.y + (h ? 0.5f : -7.5f), sb = sa + 7.0f;
         const float ca = fmaxf(sa, -e.ry), cb = fminf(sb, e.ry);
-        float l, r;
-        ellipse_span(e, ca, cb, l, r);
+        float l, r;  // about the tile centre
+        ellipse_span(e, -off.x, ca, cb, l, r);
         const bool in = ca <= cb;
-#pragma unroll
-        for (int c = 0; c < 2; ++c) {
-            const float xa = off.x + (c ? 0.5f : -7.5f);
-            m |= (in && l <= xa + 7.0f && r >= xa) ? (1u << (2 * h + c)) : 0u;
-        }
+        m |= (in && l <= -0.5f && r >= -7.5f) ? (1u << (2 * h)) : 0u;
+        m |= (in && l <= 7.5f && r >= 0.5f) ? (2u << (2 * h)) : 0u;
     }
     return m;
 }

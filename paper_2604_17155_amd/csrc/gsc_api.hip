@@ -62,7 +62,9 @@ struct DevBuf {
     hipError_t ensure(size_t bytes) {
         if (bytes <= cap && p) return hipSuccess;
         if (arena) {
-            const size_t off = (arena->used + 255) & ~(size_t)255;
+            // the buffer carved last grows in place (its contents stay)
+            const bool last = p && static_cast<char*>(p) + cap == arena->base + arena->used;
+            const size_t off = last ? (size_t)(static_cast<char*>(p) - arena->base) : (arena->used + 255) & ~(size_t)255;
             if (off + bytes > arena->cap) {
                 if (arena->need == 0) arena->need = off + bytes;
                 return hipErrorOutOfMemory;
@@ -145,12 +147,14 @@ struct gsc_ctx {
     bool cache_valid = false;
     BinKey cache_key;
     int cache_bin = 16;
-    uint32_t cache_tiles = 0, cache_pairs = 0;
+    uint32_t cache_tiles = 0;
     uint64_t cache_items = 0;
     // device scratch
-    DevBuf views, views_all, cov, keys, vals, keys_alt, vals_alt, counts, offsets, rec,
-        sort_scratch, pkeys, pvals, pkeys_alt, pvals_alt, ranges, vs, gamma, bbar, misc, order, queues,
+    DevBuf views, views_all, cov, keys, vals, keys_alt, vals_alt, rec,
+        sort_scratch, pkeys, pvals, pkeys_alt, pvals_alt, granges, gfirst, gcounts, lists, ranges, vs, gamma, bbar, misc, order, queues,
         coef_t, factor, img, stat, wbuf, post, vsdet, chk, obs;
+    uint64_t pairs_counted = 0;  // bin pairs of the call's batches that were read back
+    hipEvent_t ev_read = nullptr;  // after a count's copy to the host
     bool order_valid = false;  // `order` holds the tile order of the current binning
     // host staging
     ViewInfo* h_views = nullptr;  // staging of one batch's table
@@ -171,9 +175,9 @@ struct gsc_ctx {
     size_t ev_used = 0;
     struct Mark { int stage; hipEvent_t a, b; uint32_t launches; };
     std::vector<Mark> marks;
-    std::array<DevBuf*, 31> bufs() {
-        return {&views, &views_all, &cov, &keys, &vals, &keys_alt, &vals_alt, &counts,
-                &offsets, &rec, &sort_scratch, &pkeys, &pvals, &pkeys_alt,
+    std::array<DevBuf*, 33> bufs() {
+        return {&views, &views_all, &cov, &keys, &vals, &keys_alt, &vals_alt,
+                &granges, &gfirst, &gcounts, &lists, &rec, &sort_scratch, &pkeys, &pvals, &pkeys_alt,
                 &pvals_alt, &ranges, &vs, &gamma, &bbar, &misc, &order, &queues, &coef_t,
                 &factor, &img, &stat, &wbuf, &post, &vsdet, &chk, &obs};
     }
@@ -184,6 +188,7 @@ struct gsc_ctx {
             if (h_all) (void)hipHostFree(h_all);
             if (h_total) (void)hipHostFree(h_total);
         }
+        if (ev_read) (void)hipEventDestroy(ev_read);
         for (hipEvent_t e : ev_pool) (void)hipEventDestroy(e);
     }
 };
@@ -251,10 +256,11 @@ struct StageTimer {
 };
 }  // namespace
 
-// misc buffer layout (device): [0] u64 contributions, [8] u32 pair total, [12] u32 ill count,
-// [16] u64 pair total (overflow check)
+// misc buffer layout (device): [0] u64 contributions, [8] u32 group pair total, [12] u32 ill count,
+// [16] u64 group pair total (where it may exceed 32 bits), [64] u32 bin pairs of the current batch,
+// [72] u64 bin pairs of the call
 namespace {
-constexpr size_t kMiscBytes = 64;  // [32..63]: geometry statistics (4 doubles)
+constexpr size_t kMiscBytes = 80;  // [32..63]: geometry statistics (4 doubles)
 // bin_views result asking the caller to retry with fewer views per batch
 constexpr gsc_status kSplit = (gsc_status)1;
 
@@ -389,6 +395,7 @@ ViewInfo make_view(const gsc_camera& c, int j, int64_t N, int bin) {
     v.height = c.height;
     v.tiles_x = (c.width + bin - 1) / bin;
     v.tiles_y = (c.height + bin - 1) / bin;
+    v.groups_x = (v.tiles_x + 3) / 4;
     v.pixel_offset = c.pixel_offset;
     v.g_offset = 0;
     v.vs_base = (int64_t)j * N;
@@ -406,30 +413,39 @@ int bits_for(uint64_t n) {
 // Result of binning one view batch.
 struct Binned {
     uint32_t n_tiles = 0;
-    uint32_t n_pairs = 0;
     uint64_t n_items = 0;
 };
 
 // The tile order of the current binning for launches that take it, or
 // nullptr (tile index order) under GSC_SCHEDULE_GRID.
-const uint32_t* tile_order(const gsc_ctx* ctx, uint32_t n_tiles) {
+const uint32_t* tile_order(const gsc_ctx* ctx) {
     if (ctx->opt.schedule == GSC_SCHEDULE_GRID || !ctx->order_valid) return nullptr;
-    return ctx->order.as<uint32_t>() + n_tiles;
+    return ctx->order.as<uint32_t>();
 }
 
 // The tile lists left by the current binning of nv views.
 TileLists tile_lists(const gsc_ctx* ctx, int nv, const Binned& bn) {
     return TileLists{ctx->views.as<ViewInfo>(), nv,  bn.n_tiles, ctx->bin, ctx->ranges.as<uint2>(),
-                     ctx->pvals.as<uint32_t>(), ctx->rec.as<float4>(), ctx->vals.as<uint32_t>(),
-                     tile_order(ctx, bn.n_tiles)};
+                     (ctx->no_alloc ? ctx->pkeys : ctx->lists).as<uint32_t>(), ctx->rec.as<float4>(),
+                     ctx->vals.as<uint32_t>(), tile_order(ctx)};
 }
 
-// Project, depth-sort, emit and tile-sort the views [v0, v0+nv) of `all`.
-// The batch's ViewInfo table is uploaded to ctx->views (tile_base local to
-// the batch).  Synchronises `s` once to read the pair count.
+// Groups of a view (its bins in 4x4s).
+inline uint64_t view_groups(const ViewInfo& v) { return (uint64_t)v.groups_x * (uint64_t)((v.tiles_y + 3) / 4); }
+
+// Bin pairs above which a batch's list buffer is sized by their count, a second
+// read-back (10-20 us): below, 16 bins for each group pair are allocated (at
+// most 512 MB; about a third of it is used).
+constexpr uint64_t kListsUncounted = 1ull << 27;
+
+// Project, depth-sort and list the views [v0, v0+nv) of `all`.  The batch's
+// ViewInfo table is uploaded to ctx->views (tile_base local to the batch).
+// Synchronises `s` once to read the group pair count, and again for the bin
+// pair count where that sizes the lists.  `count`: add the bin pairs to the
+// call's statistics.
 gsc_status bin_views(gsc_ctx* ctx, const ViewInfo* all, int v0, int nv,
                      const float* means, const float* opac, int64_t N, const BlendParams& bp,
-                     hipStream_t s, Binned* out) {
+                     hipStream_t s, Binned* out, bool count) {
     ctx->order_valid = false;  // until this binning's order is built
     // tile numbering local to the batch
     if ((size_t)nv > ctx->h_views_cap) {
@@ -438,13 +454,15 @@ gsc_status bin_views(gsc_ctx* ctx, const ViewInfo* all, int v0, int nv,
         GSC_HIP(hipHostMalloc((void**)&ctx->h_views, sizeof(ViewInfo) * (size_t)nv));
         ctx->h_views_cap = (size_t)nv;
     }
-    uint64_t tiles = 0, items = 0;
+    uint64_t tiles = 0, items = 0, groups = 0;
     bool uniform = true;
     for (int k = 0; k < nv; ++k) {
         ViewInfo v = all[v0 + k];
         v.tile_base = (uint32_t)tiles;
         v.item_base = (uint32_t)items;
+        v.group_base = (uint32_t)groups;
         tiles += (uint64_t)v.tiles_x * v.tiles_y;
+        groups += view_groups(v);
         items += v.n_gauss;
         uniform = uniform && v.n_gauss == all[v0].n_gauss;
         ctx->h_views[k] = v;
@@ -457,15 +475,15 @@ gsc_status bin_views(gsc_ctx* ctx, const ViewInfo* all, int v0, int nv,
                            hipMemcpyHostToDevice, s));
     out->n_items = items;
     out->n_tiles = (uint32_t)tiles;
-    const uint32_t ni = (uint32_t)items;
+    const uint32_t ni = (uint32_t)items, ng = (uint32_t)groups;
     GSC_HIP(ctx->keys.ensure(4 * items + 4));
     GSC_HIP(ctx->vals.ensure(4 * items + 4));
     GSC_HIP(ctx->keys_alt.ensure(4 * items + 4));
     GSC_HIP(ctx->vals_alt.ensure(4 * items + 4));
-    GSC_HIP(ctx->counts.ensure(4 * items + 4));
-    GSC_HIP(ctx->offsets.ensure(4 * items + 4));
     GSC_HIP(ctx->rec.ensure(32 * items + 32));
     GSC_HIP(ctx->ranges.ensure(sizeof(uint2) * (tiles + 1)));
+    GSC_HIP(ctx->granges.ensure(12 * (groups + 1)));  // the groups' ranges, then their totals
+    GSC_HIP(ctx->gfirst.ensure(4 * groups + 4));
     const ViewInfo* dviews = ctx->views.as<ViewInfo>();
     {
         StageTimer t(ctx, s, GSC_STAGE_PROJECT);
@@ -473,7 +491,7 @@ gsc_status bin_views(gsc_ctx* ctx, const ViewInfo* all, int v0, int nv,
                           ctx->vals.as<uint32_t>(), s);
         GSC_LAUNCHED("depth keys");
     }
-    size_t scr = std::max(radix_scratch_words(ni), scan_scratch_words(ni));
+    size_t scr = std::max({radix_scratch_words(ni), scan_scratch_words(ni), scan_scratch_words(ng)});
     GSC_HIP(ctx->sort_scratch.ensure(4 * scr + 256));
     {
         StageTimer t(ctx, s, GSC_STAGE_DEPTH_SORT);
@@ -481,70 +499,119 @@ gsc_status bin_views(gsc_ctx* ctx, const ViewInfo* all, int v0, int nv,
                    ctx->vals_alt.as<uint32_t>(), ni, 32, ctx->sort_scratch.as<uint32_t>(), s);
         GSC_LAUNCHED("depth sort");
     }
+    // (the sort is done with its keys and alternates: the counts, rectangles
+    // and offsets of the items take their place)
+    uint32_t* counts = ctx->keys.as<uint32_t>();
+    uint32_t* rects = ctx->keys_alt.as<uint32_t>();
+    uint32_t* offsets = ctx->vals_alt.as<uint32_t>();
     {
         // projection in depth order: records and counts land at the depth rank
         StageTimer t(ctx, s, GSC_STAGE_PROJECT);
-        launch_project(dviews, nv, ni, ctx->vals.as<uint32_t>(), ctx->cov.as<float>(), bp,
-                       ctx->counts.as<uint32_t>(), ctx->rec.as<float4>(), ctx->bin, s);
+        launch_project(dviews, nv, ni, ctx->vals.as<uint32_t>(), ctx->cov.as<float>(), bp, counts, rects,
+                       ctx->rec.as<float4>(), ctx->bin, s);
         GSC_LAUNCHED("project");
     }
-    StageTimer* scan_t = new StageTimer(ctx, s, GSC_STAGE_SCAN);
     uint32_t* d_total = reinterpret_cast<uint32_t*>(ctx->misc.as<char>() + 8);
     unsigned long long* d_total64 = reinterpret_cast<unsigned long long*>(ctx->misc.as<char>() + 16);
-    launch_fill_u32(reinterpret_cast<uint32_t*>(d_total64), 0u, 2, s);
-    launch_sum_u64(ctx->counts.as<uint32_t>(), ni, d_total64, s);
-    launch_scan(ctx->counts.as<uint32_t>(), ctx->offsets.as<uint32_t>(), ni, d_total,
-                ctx->sort_scratch.as<uint32_t>(), s);
-    delete scan_t;
+    uint32_t* d_bins = reinterpret_cast<uint32_t*>(ctx->misc.as<char>() + 64);
+    unsigned long long* d_pairs = reinterpret_cast<unsigned long long*>(ctx->misc.as<char>() + 72);
+    // 32 bits hold the group pairs unless every item could lie in most groups
+    uint64_t most = 0;
+    for (int k = 0; k < nv; ++k) most += (uint64_t)all[v0 + k].n_gauss * view_groups(all[v0 + k]);
+    const bool wide = most > 0xFFFFFFFFull;
+    {
+        StageTimer t(ctx, s, GSC_STAGE_SCAN);
+        if (wide) {
+            launch_fill_u32(reinterpret_cast<uint32_t*>(d_total64), 0u, 2, s);
+            launch_sum_u64(counts, ni, d_total64, s);
+        }
+        launch_scan(counts, offsets, ni, d_total, ctx->sort_scratch.as<uint32_t>(), s);
+    }
     GSC_LAUNCHED("count scan");
     GSC_HIP(hipMemcpyAsync(ctx->h_total, ctx->misc.as<char>() + 8, 16, hipMemcpyDeviceToHost, s));
     GSC_HIP(hipStreamSynchronize(s));
-    uint64_t pairs64 = 0;
-    memcpy(&pairs64, reinterpret_cast<const char*>(ctx->h_total) + 8, 8);
-    if (pairs64 > batch_pair_limit(ctx->opt) && nv > 1) return kSplit;
-    if (pairs64 >= kMaxPairsPerBatch) {
+    uint64_t pairs = *ctx->h_total;
+    if (wide) memcpy(&pairs, reinterpret_cast<const char*>(ctx->h_total) + 8, 8);
+    // a group pair holds at least about one bin pair
+    if (pairs >= kMaxPairsPerBatch) {
+        if (nv > 1) return kSplit;
         return fail(GSC_ERR_CAPACITY, "one view produces %llu tile pairs (limit %llu)",
-                    (unsigned long long)pairs64, (unsigned long long)kMaxPairsPerBatch);
+                    (unsigned long long)pairs, (unsigned long long)kMaxPairsPerBatch);
     }
-    const uint64_t pairs = pairs64;
-    if (pairs != *ctx->h_total) return fail(GSC_ERR_HIP, "pair count mismatch");
-    out->n_pairs = (uint32_t)pairs;
-    GSC_HIP(ctx->pkeys.ensure(4 * pairs + 4));
-    GSC_HIP(ctx->pvals.ensure(4 * pairs + 4));
-    GSC_HIP(ctx->pkeys_alt.ensure(4 * pairs + 4));
-    GSC_HIP(ctx->pvals_alt.ensure(4 * pairs + 4));
-    {
-        StageTimer t(ctx, s, GSC_STAGE_EMIT);
-        launch_emit(dviews, nv, ctx->vals.as<uint32_t>(), ctx->offsets.as<uint32_t>(),
-                    ctx->counts.as<uint32_t>(), ctx->rec.as<float4>(), bp, ni, (uint32_t)tiles, ctx->pkeys.as<uint32_t>(),
-                    ctx->pvals.as<uint32_t>(), ctx->bin, s);
-        GSC_LAUNCHED("emit");
-    }
+    const int gbits = bits_for(groups + 1);
+    // per (window, group) row sixteen counts, then the windows' first groups
+    const uint64_t count_words = group_count_words(pairs, groups);
+    GSC_HIP(ctx->gcounts.ensure(4 * (count_words + group_windows(pairs)) + 64));
     size_t pscr = radix_scratch_words((uint32_t)pairs);
     GSC_HIP(ctx->sort_scratch.ensure(4 * std::max(pscr, scr) + 256));
+    if (ctx->opt.schedule != GSC_SCHEDULE_GRID) GSC_HIP(ctx->order.ensure(4 * tile_order_words((uint32_t)tiles)));
+    // the buffer in which the sorted keys end comes last (its place takes the
+    // bin lists of the allocation-free call)
+    const bool odd = ((gbits + 7) / 8) % 2 != 0;
+    GSC_HIP(ctx->pvals.ensure(4 * pairs + 4));
+    GSC_HIP(ctx->pvals_alt.ensure(4 * pairs + 4));
+    GSC_HIP((odd ? ctx->pkeys : ctx->pkeys_alt).ensure(4 * pairs + 4));
+    GSC_HIP((odd ? ctx->pkeys_alt : ctx->pkeys).ensure(4 * pairs + 4));
     {
-        StageTimer t(ctx, s, GSC_STAGE_TILE_SORT);
-        bool in_alt = false;
-        radix_sort(ctx->pkeys.as<uint32_t>(), ctx->pvals.as<uint32_t>(), ctx->pkeys_alt.as<uint32_t>(),
-                   ctx->pvals_alt.as<uint32_t>(), (uint32_t)pairs, bits_for(tiles + 1),
-                   ctx->sort_scratch.as<uint32_t>(), s, nullptr, &in_alt);
-        GSC_LAUNCHED("tile sort");
-        if (in_alt) {  // the sorted pairs are in the alternate buffers: swap roles, no copy
-            std::swap(ctx->pkeys, ctx->pkeys_alt);
-            std::swap(ctx->pvals, ctx->pvals_alt);
-        }
-        launch_fill_u32(ctx->ranges.as<uint32_t>(), 0u, (uint64_t)2 * tiles, s);
-        launch_tile_ranges(ctx->pkeys.as<uint32_t>(), (uint32_t)pairs, (uint32_t)tiles,
-                           ctx->ranges.as<uint2>(), s);
-        GSC_LAUNCHED("tile ranges");
-        ctx->order_valid = false;
-        if (ctx->opt.schedule != GSC_SCHEDULE_GRID) {
-            GSC_HIP(ctx->order.ensure(4 * tile_order_words((uint32_t)tiles)));
-            launch_tile_order(ctx->ranges.as<uint2>(), (uint32_t)tiles, ctx->order.as<uint32_t>(), s);
-            GSC_LAUNCHED("tile order");
-            ctx->order_valid = true;
-        }
+        StageTimer t(ctx, s, GSC_STAGE_EMIT);
+        launch_emit(dviews, nv, ctx->vals.as<uint32_t>(), offsets, counts, rects, ctx->rec.as<float4>(), bp, ni,
+                    ng, ctx->pkeys.as<uint32_t>(), ctx->pvals.as<uint32_t>(), ctx->bin, s);
+        GSC_LAUNCHED("emit");
     }
+    StageTimer t(ctx, s, GSC_STAGE_TILE_SORT);
+    bool in_alt = false;
+    radix_sort(ctx->pkeys.as<uint32_t>(), ctx->pvals.as<uint32_t>(), ctx->pkeys_alt.as<uint32_t>(),
+               ctx->pvals_alt.as<uint32_t>(), (uint32_t)pairs, gbits,
+               ctx->sort_scratch.as<uint32_t>(), s, nullptr, &in_alt);
+    GSC_LAUNCHED("group sort");
+    if (in_alt) {  // the sorted pairs are in the alternate buffers: swap roles, no copy
+        std::swap(ctx->pkeys, ctx->pkeys_alt);
+        std::swap(ctx->pvals, ctx->pvals_alt);
+    }
+    launch_fill_u32(ctx->granges.as<uint32_t>(), 0u, (uint64_t)3 * groups, s);
+    launch_tile_ranges(ctx->pkeys.as<uint32_t>(), (uint32_t)pairs, ng, ctx->granges.as<uint2>(), s);
+    const GroupLists gl{dviews, nv, ng, ctx->bin, (uint32_t)pairs, nullptr, ctx->granges.as<uint2>(),
+                        ctx->pkeys.as<uint32_t>(), ctx->pvals.as<uint32_t>(), ctx->rec.as<float4>(),
+                        ctx->pkeys_alt.as<uint32_t>(), ctx->pvals_alt.as<uint32_t>(), ctx->gcounts.as<uint32_t>(),
+                        ctx->gcounts.as<uint32_t>() + count_words, ctx->granges.as<uint32_t>() + 2 * groups};
+    launch_group_masks(gl, bp, s);
+    launch_scan(gl.totals, ctx->gfirst.as<uint32_t>(), ng, d_bins, ctx->sort_scratch.as<uint32_t>(), s);
+    const bool counted = ctx->no_alloc || 16 * pairs > std::min(kListsUncounted, batch_pair_limit(ctx->opt));
+    if (counted) GSC_HIP(hipMemcpyAsync(ctx->h_total, d_bins, 4, hipMemcpyDeviceToHost, s));
+    if (counted && 16 * pairs > 0xFFFFFFFFull) {  // the scan's total may have wrapped
+        launch_fill_u32(reinterpret_cast<uint32_t*>(d_total64), 0u, 2, s);
+        launch_sum_u64(gl.totals, ng, d_total64, s);
+        GSC_HIP(hipMemcpyAsync(ctx->h_total + 2, d_total64, 8, hipMemcpyDeviceToHost, s));
+    }
+    if (counted && !ctx->no_alloc) {
+        if (!ctx->ev_read) GSC_HIP(hipEventCreateWithFlags(&ctx->ev_read, hipEventDisableTiming));
+        GSC_HIP(hipEventRecord(ctx->ev_read, s));
+    }
+    // (the ranges and the tile order keep the device busy during the read-back;
+    // a batch that is split after it leaves its pairs out of the count)
+    launch_bin_ranges(gl, ctx->gfirst.as<uint32_t>(), ctx->ranges.as<uint2>(), 0xFFFFFFFFu, d_bins,
+                      count && !counted ? d_pairs : nullptr, s);
+    GSC_LAUNCHED("bin ranges");
+    if (ctx->opt.schedule != GSC_SCHEDULE_GRID) {
+        launch_tile_order(ctx->ranges.as<uint2>(), (uint32_t)tiles, ctx->order.as<uint32_t>(), s);
+        GSC_LAUNCHED("tile order");
+        ctx->order_valid = true;
+    }
+    uint64_t bins = 16 * pairs;
+    if (counted) {
+        GSC_HIP(ctx->no_alloc ? hipStreamSynchronize(s) : hipEventSynchronize(ctx->ev_read));
+        bins = *ctx->h_total;
+        if (16 * pairs > 0xFFFFFFFFull) memcpy(&bins, ctx->h_total + 2, 8);
+        if (bins > batch_pair_limit(ctx->opt) && nv > 1) return kSplit;
+        if (bins >= kMaxPairsPerBatch)
+            return fail(GSC_ERR_CAPACITY, "one view produces %llu tile pairs (limit %llu)",
+                        (unsigned long long)bins, (unsigned long long)kMaxPairsPerBatch);
+    }
+    if (counted && count) ctx->pairs_counted += bins;
+    DevBuf& lists = ctx->no_alloc ? ctx->pkeys : ctx->lists;
+    GSC_HIP(lists.ensure(4 * bins + 4));
+    launch_bin_lists(gl, lists.as<uint32_t>(), 0xFFFFFFFFu, nullptr, s);
+    GSC_LAUNCHED("bin lists");
     return GSC_OK;
 }
 
@@ -554,15 +621,14 @@ gsc_status bin_views(gsc_ctx* ctx, const ViewInfo* all, int v0, int nv,
 template <typename Body>
 gsc_status for_view_batches(gsc_ctx* ctx, const ViewInfo* all, int n_cams,
                             const float* means, const float* opac, int64_t N, const BlendParams& bp,
-                            hipStream_t s, Body body, const BinKey* key = nullptr, bool reuse = false) {
+                            hipStream_t s, Body body, const BinKey* key = nullptr, bool reuse = false,
+                            bool count = true) {
     if (reuse) {  // the only batch of the previous call is still in place
         Binned bn;
         bn.n_tiles = ctx->cache_tiles;
-        bn.n_pairs = ctx->cache_pairs;
         bn.n_items = ctx->cache_items;
         gsc_status st = body(0, n_cams, bn);
         if (st != GSC_OK) return st;
-        ctx->stats.pairs += bn.n_pairs;
         ctx->stats.items += bn.n_items;
         ctx->stats.view_batches += 1;
         return GSC_OK;
@@ -574,14 +640,13 @@ gsc_status for_view_batches(gsc_ctx* ctx, const ViewInfo* all, int n_cams,
     while (v < n_cams) {
         int nv = std::min(per, n_cams - v);
         Binned bn;
-        gsc_status st = bin_views(ctx, all, v, nv, means, opac, N, bp, s, &bn);
+        gsc_status st = bin_views(ctx, all, v, nv, means, opac, N, bp, s, &bn, count);
         if (st == kSplit) {
             per = std::max(1, nv / 2);
             continue;
         }
         if (st != GSC_OK) return st;
         if ((st = body(v, nv, bn)) != GSC_OK) return st;
-        ctx->stats.pairs += bn.n_pairs;
         ctx->stats.items += bn.n_items;
         ctx->stats.view_batches += 1;
         v += nv;
@@ -593,7 +658,6 @@ gsc_status for_view_batches(gsc_ctx* ctx, const ViewInfo* all, int n_cams,
         ctx->cache_key = *key;
         ctx->cache_bin = ctx->bin;
         ctx->cache_tiles = last.n_tiles;
-        ctx->cache_pairs = last.n_pairs;
         ctx->cache_items = last.n_items;
     }
     return GSC_OK;
@@ -631,7 +695,8 @@ gsc_status ensure_common(gsc_ctx* ctx, const float* means, const float* scales,
     if (!ctx->h_total) GSC_HIP(hipHostMalloc((void**)&ctx->h_total, 64));
     if (reuse) {  // bin size and packed geometry of the cached binning
         ctx->bin = ctx->cache_bin;
-        launch_fill_u32(ctx->misc.as<uint32_t>(), 0u, kMiscBytes / 4, s);
+        // (the bin pair count of the cached binning stays)
+        launch_fill_u32(ctx->misc.as<uint32_t>(), 0u, 16, s);
         return GSC_OK;
     }
     ctx->bin = ctx->opt.bin_size;
@@ -667,6 +732,7 @@ gsc_status ensure_common(gsc_ctx* ctx, const float* means, const float* scales,
     }
     GSC_HIP(ctx->cov.ensure(sizeof(float) * kGeoStride * (size_t)std::max<int64_t>(N, 1)));
     launch_fill_u32(ctx->misc.as<uint32_t>(), 0u, kMiscBytes / 4, s);
+    ctx->pairs_counted = 0;
     launch_cov3d(means, opac, scales, quats, ctx->cov.as<float>(), N, s);
     GSC_LAUNCHED("cov3d");
     return GSC_OK;
@@ -705,8 +771,9 @@ struct gsc_plan {
     bool per_view = false;
     struct Batch {
         int v0, nv;
-        uint32_t n_items, n_tiles, pair_cap;
-        int tile_bits;
+        uint32_t n_items, n_tiles, n_groups;
+        uint32_t group_cap, pair_cap;  // group pairs and bin pairs
+        int group_bits;
     };
     std::vector<Batch> batches;
     std::vector<ViewInfo> views;      // all views, tile_base/item_base local to their batch
@@ -714,7 +781,7 @@ struct gsc_plan {
     std::vector<int> scene_nviews;    // views of each scene in `views`
     std::vector<int64_t> scene_vs0;   // first per-view slot of each scene
     uint64_t vs_slots = 0;
-    uint32_t max_items = 0, max_pairs = 0, max_tiles = 0;
+    uint32_t max_items = 0, max_group_pairs = 0, max_pairs = 0, max_tiles = 0, max_groups = 0;
     uint64_t items_total = 0, pairs_total = 0;
     int bin = 16;                     // bin size in pixels
     int acc_chunk = 0;                // accumulate variant (0: default for the targets' type)
@@ -722,12 +789,12 @@ struct gsc_plan {
     bool acc_persistent = false;      // persistent work-queue accumulate
     float tune_ms[8] = {};
     int tune_variant[8] = {};
-    DevBuf d_views, cov, keys, vals, keys_alt, vals_alt, counts, offsets, rec,
-        sort_scratch, pkeys, pvals, pkeys_alt, pvals_alt, ranges, vs, misc, queues, order, obs;
+    DevBuf d_views, cov, keys, vals, keys_alt, vals_alt, rec, sort_scratch, pkeys, pvals, pkeys_alt,
+        pvals_alt, granges, gfirst, gcounts, lists, ranges, vs, misc, queues, order, obs;
     ~gsc_plan() {
-        DevBuf* all[] = {&d_views, &cov, &keys, &vals, &keys_alt, &vals_alt, &counts,
-                         &offsets, &rec, &sort_scratch, &pkeys, &pvals, &pkeys_alt,
-                         &pvals_alt, &ranges, &vs, &misc, &queues, &order, &obs};
+        DevBuf* all[] = {&d_views, &cov, &keys, &vals, &keys_alt, &vals_alt, &rec, &sort_scratch,
+                         &pkeys, &pvals, &pkeys_alt, &pvals_alt, &granges, &gfirst, &gcounts,
+                         &lists, &ranges, &vs, &misc, &queues, &order, &obs};
         for (DevBuf* b : all) b->release();
     }
 };
@@ -735,7 +802,7 @@ struct gsc_plan {
 namespace {
 // plan misc layout (device): [0] u64 contributions, [8] u32 live pair count of
 // the current batch, [12] u32 dropped-pair events, [16] u32 ill-conditioned
-// count, [24] u64 pair total (plan creation), [32..63] geometry statistics
+// count, [32..63] geometry statistics or pair totals (plan creation)
 constexpr size_t kPlanMiscBytes = 64;
 
 gsc_status validate_cameras(const gsc_camera* cams, int32_t n_cams) {
@@ -743,40 +810,47 @@ gsc_status validate_cameras(const gsc_camera* cams, int32_t n_cams) {
     return validate_geometry(nullptr, nullptr, nullptr, nullptr, 0, cams, n_cams, &rows);
 }
 
-// Project one batch of the plan and count its tile pairs (synchronises).
-gsc_status plan_count_pairs(gsc_plan* P, const gsc_plan::Batch& b, hipStream_t s, uint64_t* pairs) {
+// Project one batch of the plan and count its group and bin pairs (synchronises).
+gsc_status plan_count_pairs(gsc_plan* P, const gsc_plan::Batch& b, hipStream_t s, uint64_t* group_pairs,
+                            uint64_t* bin_pairs) {
     const ViewInfo* dv = P->d_views.as<ViewInfo>() + b.v0;
-    launch_project(dv, b.nv, b.n_items, nullptr, P->cov.as<float>(), P->bp,
-                   P->counts.as<uint32_t>(), P->rec.as<float4>(), P->bin, s);
+    uint32_t* counts = P->keys.as<uint32_t>();
+    launch_project(dv, b.nv, b.n_items, nullptr, P->cov.as<float>(), P->bp, counts, P->keys_alt.as<uint32_t>(),
+                   P->rec.as<float4>(), P->bin, s);
     GSC_LAUNCHED("project");
-    unsigned long long* d64 = reinterpret_cast<unsigned long long*>(P->misc.as<char>() + 24);
-    launch_fill_u32(reinterpret_cast<uint32_t*>(d64), 0u, 2, s);
-    launch_sum_u64(P->counts.as<uint32_t>(), b.n_items, d64, s);
+    unsigned long long* d64 = reinterpret_cast<unsigned long long*>(P->misc.as<char>() + 32);
+    launch_fill_u32(reinterpret_cast<uint32_t*>(d64), 0u, 4, s);
+    launch_sum_u64(counts, b.n_items, d64, s);
+    launch_count_bins(dv, b.nv, b.n_items, counts, P->keys_alt.as<uint32_t>(), P->rec.as<float4>(), P->bp, P->bin, d64 + 1, s);
     GSC_LAUNCHED("count");
-    uint64_t h = 0;
-    GSC_HIP(hipMemcpyAsync(&h, d64, 8, hipMemcpyDeviceToHost, s));
+    uint64_t h[2] = {0, 0};
+    GSC_HIP(hipMemcpyAsync(h, d64, 16, hipMemcpyDeviceToHost, s));
     GSC_HIP(hipStreamSynchronize(s));
-    *pairs = h;
+    *group_pairs = h[0];
+    *bin_pairs = h[1];
     return GSC_OK;
 }
 
 // Assign batch-local tile and item numbering to the views of every batch.
 void plan_number_views(gsc_plan* P) {
     for (auto& b : P->batches) {
-        uint64_t tiles = 0, items = 0;
+        uint64_t tiles = 0, items = 0, groups = 0;
         bool uniform = true;
         for (int k = 0; k < b.nv; ++k) {
             ViewInfo& v = P->views[b.v0 + k];
             v.tile_base = (uint32_t)tiles;
             v.item_base = (uint32_t)items;
+            v.group_base = (uint32_t)groups;
             tiles += (uint64_t)v.tiles_x * v.tiles_y;
+            groups += view_groups(v);
             items += v.n_gauss;
             uniform = uniform && v.n_gauss == P->views[b.v0].n_gauss;
         }
         for (int k = 0; k < b.nv; ++k) P->views[b.v0 + k].uniform_n = uniform ? P->views[b.v0].n_gauss : 0u;
         b.n_tiles = (uint32_t)tiles;
+        b.n_groups = (uint32_t)groups;
         b.n_items = (uint32_t)items;
-        b.tile_bits = bits_for(tiles + 1);
+        b.group_bits = bits_for(groups + 1);
     }
 }
 
@@ -784,8 +858,8 @@ gsc_status plan_accumulate(gsc_plan* P, const gsc_plan::Batch& b, const void* ta
                            int chunk, bool persistent, hipStream_t s) {
     unsigned long long* d_counter = reinterpret_cast<unsigned long long*>(P->misc.p);
     const TileLists tl{P->d_views.as<ViewInfo>() + b.v0, b.nv, b.n_tiles, P->bin, P->ranges.as<uint2>(),
-                       P->pvals.as<uint32_t>(), P->rec.as<float4>(), P->vals.as<uint32_t>(),
-                       P->order.as<uint32_t>() + b.n_tiles};
+                       P->lists.as<uint32_t>(), P->rec.as<float4>(), P->vals.as<uint32_t>(),
+                       P->order.as<uint32_t>()};
     launch_accumulate(tl, targets, tdtype, P->C, P->per_view, P->bp, P->vs.as<float>(), d_counter, nullptr,
                       chunk, s, persistent ? P->queues.as<uint32_t>() : nullptr);
     GSC_LAUNCHED("accumulate");
@@ -810,41 +884,52 @@ gsc_status plan_bin_batch(gsc_plan* P, const gsc_plan::Batch& b, hipStream_t s) 
                    P->vals_alt.as<uint32_t>(), b.n_items, 32, P->sort_scratch.as<uint32_t>(), s);
         GSC_LAUNCHED("depth sort");
     }
+    // (in the sort's spent buffers, as in bin_views)
+    uint32_t* counts = P->keys.as<uint32_t>();
+    uint32_t* rects = P->keys_alt.as<uint32_t>();
+    uint32_t* offsets = P->vals_alt.as<uint32_t>();
     {
         StageTimer t(ctx, s, GSC_STAGE_PROJECT);
-        launch_project(dv, b.nv, b.n_items, P->vals.as<uint32_t>(), P->cov.as<float>(),
-                       P->bp, P->counts.as<uint32_t>(), P->rec.as<float4>(), P->bin, s);
+        launch_project(dv, b.nv, b.n_items, P->vals.as<uint32_t>(), P->cov.as<float>(), P->bp, counts, rects,
+                       P->rec.as<float4>(), P->bin, s);
         GSC_LAUNCHED("project");
     }
     {
         StageTimer t(ctx, s, GSC_STAGE_SCAN);
-        launch_scan(P->counts.as<uint32_t>(), P->offsets.as<uint32_t>(), b.n_items, d_live,
-                    P->sort_scratch.as<uint32_t>(), s);
+        launch_scan(counts, offsets, b.n_items, d_live, P->sort_scratch.as<uint32_t>(), s);
         GSC_LAUNCHED("count scan");
     }
     {
         StageTimer t(ctx, s, GSC_STAGE_EMIT);
-        launch_emit(dv, b.nv, P->vals.as<uint32_t>(), P->offsets.as<uint32_t>(),
-                    P->counts.as<uint32_t>(), P->rec.as<float4>(), P->bp,
-                    b.n_items, b.n_tiles, P->pkeys.as<uint32_t>(), P->pvals.as<uint32_t>(), P->bin, s,
-                    b.pair_cap, d_drop);
+        launch_emit(dv, b.nv, P->vals.as<uint32_t>(), offsets, counts, rects, P->rec.as<float4>(), P->bp,
+                    b.n_items, b.n_groups, P->pkeys.as<uint32_t>(), P->pvals.as<uint32_t>(), P->bin, s,
+                    b.group_cap, d_drop);
         GSC_LAUNCHED("emit");
     }
     {
         StageTimer t(ctx, s, GSC_STAGE_TILE_SORT);
         bool in_alt = false;
         radix_sort(P->pkeys.as<uint32_t>(), P->pvals.as<uint32_t>(), P->pkeys_alt.as<uint32_t>(),
-                   P->pvals_alt.as<uint32_t>(), b.pair_cap, b.tile_bits,
+                   P->pvals_alt.as<uint32_t>(), b.group_cap, b.group_bits,
                    P->sort_scratch.as<uint32_t>(), s, d_live, &in_alt);
         if (in_alt) {  // swap roles instead of copying; every run swaps alike
             std::swap(P->pkeys, P->pkeys_alt);
             std::swap(P->pvals, P->pvals_alt);
         }
-        launch_fill_u32(P->ranges.as<uint32_t>(), 0u, (uint64_t)2 * b.n_tiles, s);
-        launch_tile_ranges(P->pkeys.as<uint32_t>(), b.pair_cap, b.n_tiles, P->ranges.as<uint2>(), s,
+        launch_fill_u32(P->granges.as<uint32_t>(), 0u, (uint64_t)3 * b.n_groups, s);
+        launch_tile_ranges(P->pkeys.as<uint32_t>(), b.group_cap, b.n_groups, P->granges.as<uint2>(), s,
                            d_live);
+        const GroupLists gl{dv, b.nv, b.n_groups, P->bin, b.group_cap, d_live, P->granges.as<uint2>(),
+                            P->pkeys.as<uint32_t>(), P->pvals.as<uint32_t>(), P->rec.as<float4>(),
+                            P->pkeys_alt.as<uint32_t>(), P->pvals_alt.as<uint32_t>(), P->gcounts.as<uint32_t>(),
+                            P->gcounts.as<uint32_t>() + group_count_words(b.group_cap, b.n_groups),
+                            P->granges.as<uint32_t>() + 2 * (size_t)b.n_groups};
+        launch_group_masks(gl, P->bp, s);
+        launch_scan(gl.totals, P->gfirst.as<uint32_t>(), b.n_groups, nullptr, P->sort_scratch.as<uint32_t>(), s);
+        launch_bin_ranges(gl, P->gfirst.as<uint32_t>(), P->ranges.as<uint2>(), b.pair_cap, nullptr, nullptr, s);
+        launch_bin_lists(gl, P->lists.as<uint32_t>(), b.pair_cap, d_drop, s);
         launch_tile_order(P->ranges.as<uint2>(), b.n_tiles, P->order.as<uint32_t>(), s);
-        GSC_LAUNCHED("tile sort");
+        GSC_LAUNCHED("bin lists");
     }
     return GSC_OK;
 }
@@ -1177,6 +1262,7 @@ gsc_status gsc_colorize_ex(gsc_ctx* ctx, const float* means, const float* scales
     hipStream_t s = (hipStream_t)stream;
     if ((st = refuse_capture(s, "gsc_colorize")) != GSC_OK) return st;
     memset(&ctx->stats, 0, sizeof(ctx->stats));
+    ctx->stats_pending = false;
     if (N == 0) return GSC_OK;
     const BinKey key = make_key(ctx, means, scales, quats, opacities, N, cams, n_cams, blend_params(ctx->opt));
     const bool reuse = can_reuse(ctx, key);
@@ -1216,6 +1302,7 @@ gsc_status gsc_colorize_noalloc(gsc_ctx* ctx, const float* means, const float* s
     if ((st = refuse_capture(s, "gsc_colorize_noalloc")) != GSC_OK) return st;
     memset(&ctx->stats, 0, sizeof(ctx->stats));
     ctx->stats_pending = false;
+    ctx->stats_pending = false;
     if (N == 0) return GSC_OK;
     std::lock_guard<std::mutex> lock(g_noalloc_mu);
     void* base = nullptr;
@@ -1246,6 +1333,7 @@ gsc_status gsc_colorize_noalloc(gsc_ctx* ctx, const float* means, const float* s
         return st;
     }
     ctx->stats = w.stats;
+    ctx->pairs_counted = w.pairs_counted;
     ctx->bin = w.bin;
     ctx->stats_pending = true;
     ctx->stats_dev = w.misc.p;  // inside the scratch: valid until the next call on this GPU
@@ -1277,6 +1365,7 @@ gsc_status gsc_colorize_refine(gsc_ctx* ctx, const float* means, const float* sc
     hipStream_t s = (hipStream_t)stream;
     if ((st = refuse_capture(s, "gsc_colorize_refine")) != GSC_OK) return st;
     memset(&ctx->stats, 0, sizeof(ctx->stats));
+    ctx->stats_pending = false;
     if (N == 0) return GSC_OK;
     const BinKey key = make_key(ctx, means, scales, quats, opacities, N, cams, n_cams, blend_params(ctx->opt));
     const bool reuse = can_reuse(ctx, key);
@@ -1341,7 +1430,7 @@ gsc_status gsc_colorize_refine(gsc_ctx* ctx, const float* means, const float* sc
             GSC_LAUNCHED("refinement pass");
             (void)v0;
             return GSC_OK;
-        }, &key, single);
+        }, &key, single, false);
         if (st != GSC_OK) return st;
         StageTimer t(ctx, s, GSC_STAGE_SOLVE);
         launch_refine_update(ctx->views_all.as<ViewInfo>(), n_cams, means, ctx->vs.as<float>(), N, C,
@@ -1372,6 +1461,7 @@ gsc_status gsc_render(gsc_ctx* ctx, const float* means, const float* scales, con
     hipStream_t s = (hipStream_t)stream;
     if ((st = refuse_capture(s, "gsc_render")) != GSC_OK) return st;
     memset(&ctx->stats, 0, sizeof(ctx->stats));
+    ctx->stats_pending = false;
     if (n_cams == 0) return GSC_OK;
     BlendParams bp = blend_params(ctx->opt);
     const BinKey key = make_key(ctx, means, scales, quats, opacities, N, cams, n_cams, bp);
@@ -1423,6 +1513,7 @@ gsc_status gsc_colorize_backward(gsc_ctx* ctx, const float* means, const float* 
     hipStream_t s = (hipStream_t)stream;
     if ((st = refuse_capture(s, "gsc_colorize_backward")) != GSC_OK) return st;
     memset(&ctx->stats, 0, sizeof(ctx->stats));
+    ctx->stats_pending = false;
     if (grad_targets && rows > 0) launch_fill_u32((uint32_t*)grad_targets, 0u, (uint64_t)rows * C, s);
     if (grad_opacities && N > 0) launch_fill_u32((uint32_t*)grad_opacities, 0u, (uint64_t)N, s);
     if (N == 0 || n_cams == 0 || (!grad_targets && !grad_opacities)) return GSC_OK;
@@ -1487,10 +1578,9 @@ gsc_status gsc_colorize_backward(gsc_ctx* ctx, const float* means, const float* 
     if (pass1.view_batches == 1) {
         st = body(0, n_cams, last);  // the binning of the only batch is still in place
     } else {
-        st = for_view_batches(ctx, all.data(), n_cams, means, opacities, N, bp, s, body, &key, false);
+        st = for_view_batches(ctx, all.data(), n_cams, means, opacities, N, bp, s, body, &key, false, false);
     }
     if (st != GSC_OK) return st;
-    ctx->stats.pairs = pass1.pairs;
     ctx->stats.items = pass1.items;
     ctx->stats.view_batches = pass1.view_batches;
     ctx->stats_pending = true;
@@ -1514,6 +1604,7 @@ gsc_status gsc_render_backward(gsc_ctx* ctx, const float* means, const float* sc
     hipStream_t s = (hipStream_t)stream;
     if ((st = refuse_capture(s, "gsc_render_backward")) != GSC_OK) return st;
     memset(&ctx->stats, 0, sizeof(ctx->stats));
+    ctx->stats_pending = false;
     const int nb = (sh_deg + 1) * (sh_deg + 1);
     if (grad_coeffs && N > 0) launch_fill_u32((uint32_t*)grad_coeffs, 0u, (uint64_t)N * nb * C, s);
     if (grad_opacities && N > 0) launch_fill_u32((uint32_t*)grad_opacities, 0u, (uint64_t)N, s);
@@ -1653,14 +1744,14 @@ gsc_status gsc_plan_create(gsc_ctx* ctx, const gsc_scene* scenes, int32_t n_scen
         for (int v = 0; v < (int)P->views.size(); ++v) {
             const uint64_t ni = P->views[v].n_gauss, nt = (uint64_t)P->views[v].tiles_x * P->views[v].tiles_y;
             if (v > v0 && (items + ni > plan_item_limit(ctx->opt) || tiles + nt >= (1ull << 31))) {
-                P->batches.push_back({v0, v - v0, 0, 0, 0, 0});
+                P->batches.push_back({v0, v - v0, 0, 0, 0, 0, 0, 0});
                 v0 = v;
                 items = tiles = 0;
             }
             items += ni;
             tiles += nt;
         }
-        if (v0 < (int)P->views.size()) P->batches.push_back({v0, (int)P->views.size() - v0, 0, 0, 0, 0});
+        if (v0 < (int)P->views.size()) P->batches.push_back({v0, (int)P->views.size() - v0, 0, 0, 0, 0, 0, 0});
     }
     plan_number_views(P);
     for (const auto& b : P->batches) P->max_items = std::max(P->max_items, b.n_items);
@@ -1671,8 +1762,6 @@ gsc_status gsc_plan_create(gsc_ctx* ctx, const gsc_scene* scenes, int32_t n_scen
     GSC_HIP(P->vals.ensure(4 * mi + 4));
     GSC_HIP(P->keys_alt.ensure(4 * mi + 4));
     GSC_HIP(P->vals_alt.ensure(4 * mi + 4));
-    GSC_HIP(P->counts.ensure(4 * mi + 4));
-    GSC_HIP(P->offsets.ensure(4 * mi + 4));
     GSC_HIP(P->rec.ensure(32 * mi + 32));
     GSC_HIP(P->d_views.ensure(sizeof(ViewInfo) * std::max<size_t>(P->views.size(), 1)));
     if (!P->views.empty())
@@ -1682,38 +1771,47 @@ gsc_status gsc_plan_create(gsc_ctx* ctx, const gsc_scene* scenes, int32_t n_scen
     GSC_LAUNCHED("cov3d");
     // exact pair counts per batch (the geometry is fixed); split oversized batches
     for (size_t k = 0; k < P->batches.size();) {
-        uint64_t pairs = 0;
-        if ((st = plan_count_pairs(P, P->batches[k], s, &pairs)) != GSC_OK) return st;
-        if (pairs >= kMaxPairsPerBatch || (pairs > batch_pair_limit(ctx->opt) && P->batches[k].nv > 1)) {
+        uint64_t group_pairs = 0, pairs = 0;
+        if ((st = plan_count_pairs(P, P->batches[k], s, &group_pairs, &pairs)) != GSC_OK) return st;
+        if (pairs >= kMaxPairsPerBatch || group_pairs >= kMaxPairsPerBatch || (pairs > batch_pair_limit(ctx->opt) && P->batches[k].nv > 1)) {
             gsc_plan::Batch b = P->batches[k];
             if (b.nv == 1) return fail(GSC_ERR_CAPACITY, "one view produces %llu tile pairs", (unsigned long long)pairs);
             const int h = b.nv / 2;
             P->batches[k].nv = h;
-            P->batches.insert(P->batches.begin() + k + 1, gsc_plan::Batch{b.v0 + h, b.nv - h, 0, 0, 0, 0});
+            P->batches.insert(P->batches.begin() + k + 1, gsc_plan::Batch{b.v0 + h, b.nv - h, 0, 0, 0, 0, 0, 0});
             plan_number_views(P);
             GSC_HIP(hipMemcpyAsync(P->d_views.p, P->views.data(), sizeof(ViewInfo) * P->views.size(),
                                    hipMemcpyHostToDevice, s));
             continue;
         }
+        P->batches[k].group_cap = (uint32_t)group_pairs;
         P->batches[k].pair_cap = (uint32_t)pairs;
         ++k;
     }
     GSC_HIP(hipStreamSynchronize(s));
+    size_t part_words = 0;
     for (const auto& b : P->batches) {
+        P->max_group_pairs = std::max(P->max_group_pairs, b.group_cap);
         P->max_pairs = std::max(P->max_pairs, b.pair_cap);
+        P->max_groups = std::max(P->max_groups, b.n_groups);
+        part_words = std::max(part_words, (size_t)(group_count_words(b.group_cap, b.n_groups) + group_windows(b.group_cap)));
         P->max_tiles = std::max(P->max_tiles, b.n_tiles);
         P->items_total += b.n_items;
         P->pairs_total += b.pair_cap;
     }
-    const size_t mp = (size_t)P->max_pairs;
+    const size_t mp = (size_t)P->max_group_pairs, mg = (size_t)P->max_groups;
     GSC_HIP(P->pkeys.ensure(4 * mp + 4));
     GSC_HIP(P->pvals.ensure(4 * mp + 4));
     GSC_HIP(P->pkeys_alt.ensure(4 * mp + 4));
     GSC_HIP(P->pvals_alt.ensure(4 * mp + 4));
+    GSC_HIP(P->granges.ensure(12 * (mg + 1)));  // the groups' ranges, then their totals
+    GSC_HIP(P->gfirst.ensure(4 * mg + 4));
+    GSC_HIP(P->gcounts.ensure(4 * part_words + 64));
+    GSC_HIP(P->lists.ensure(4 * (size_t)P->max_pairs + 4));
     GSC_HIP(P->ranges.ensure(sizeof(uint2) * ((size_t)P->max_tiles + 1)));
     GSC_HIP(P->order.ensure(4 * tile_order_words(P->max_tiles)));
     const size_t scr = std::max({radix_scratch_words(P->max_items), scan_scratch_words(P->max_items),
-                                 radix_scratch_words(P->max_pairs)});
+                                 radix_scratch_words(P->max_group_pairs), scan_scratch_words(P->max_groups)});
     GSC_HIP(P->sort_scratch.ensure(4 * scr + 256));
     GSC_HIP(P->vs.ensure(4 * P->vs_slots * (size_t)(C + 1)));
     GSC_HIP(P->queues.ensure(4 * (size_t)kMaxC));
@@ -1929,6 +2027,7 @@ gsc_status gsc_select_views(gsc_ctx* ctx, const float* means, const float* scale
     hipStream_t s = (hipStream_t)stream;
     if ((st = refuse_capture(s, "gsc_select_views")) != GSC_OK) return st;
     memset(&ctx->stats, 0, sizeof(ctx->stats));
+    ctx->stats_pending = false;
     if (objective) *objective = 0;
     if (k == 0) return GSC_OK;
     const int64_t words = (N + 63) / 64;
@@ -2001,10 +2100,11 @@ gsc_status gsc_select_views(gsc_ctx* ctx, const float* means, const float* scale
 gsc_status gsc_get_stats(gsc_ctx* ctx, gsc_stats* out) {
     if (!ctx || !out) return fail(GSC_ERR_INVALID_ARG, "null ctx or output");
     if (ctx->stats_pending && (ctx->stats_dev || ctx->misc.p)) {
-        uint64_t buf[2] = {0, 0};
+        uint64_t buf[kMiscBytes / 8] = {};
         GSC_HIP(hipDeviceSynchronize());
-        GSC_HIP(hipMemcpy(buf, ctx->stats_dev ? ctx->stats_dev : ctx->misc.p, 16, hipMemcpyDeviceToHost));
+        GSC_HIP(hipMemcpy(buf, ctx->stats_dev ? ctx->stats_dev : ctx->misc.p, kMiscBytes, hipMemcpyDeviceToHost));
         ctx->stats.contributions = buf[0];
+        ctx->stats.pairs = buf[9] + ctx->pairs_counted;
         ctx->stats.ill_conditioned = (uint32_t)(buf[1] >> 32);
         ctx->stats_pending = false;
     }

@@ -29,6 +29,8 @@ struct ViewInfo {
     int32_t tiles_x, tiles_y;  // bins per row and column
     uint32_t tile_base;    // first global bin id of this view within its batch
     uint32_t item_base;    // first item of this view within its batch
+    uint32_t group_base;   // first group (4x4 bins) of this view within its batch
+    int32_t groups_x;      // groups per row
     int64_t pixel_offset;  // first target row
     int64_t g_offset;      // first Gaussian of the view's scene
     int64_t vs_base;       // first per-view sum slot of this view (per-view layouts)
@@ -117,18 +119,63 @@ void launch_depth_keys(const ViewInfo* views, int n_views, uint32_t n_items, con
                        hipStream_t s);
 
 // Projection in depth order: position k handles item i = order[k] (k if order
-// is null) and writes counts[k] and, when counts[k] > 0, the record rec[2k],
-// rec[2k + 1] (records are only ever read through tile pairs).
+// is null) and writes counts[k], the groups of 4x4 bins its footprint is
+// listed in, rects[k], how to list them (count_groups), and, when counts[k] > 0,
+// the record rec[2k], rec[2k + 1] (records are only ever read through lists).
 void launch_project(const ViewInfo* views, int n_views, uint32_t n_items, const uint32_t* order,
-                    const float* geo, BlendParams bp, uint32_t* counts, float4* rec, int bin,
-                    hipStream_t s);
+                    const float* geo, BlendParams bp, uint32_t* counts, uint32_t* rects, float4* rec,
+                    int bin, hipStream_t s);
 
-// Pairs of the depth-ordered records: pair values carry the depth rank k.
-// Pairs at offsets >= cap are dropped and counted in *overflow (if given).
-void launch_emit(const ViewInfo* views, int n_views, const uint32_t* sorted_vals,
-                 const uint32_t* offsets, const uint32_t* counts, const float4* rec, BlendParams bp,
-                 uint32_t n_items, uint32_t n_tiles, uint32_t* pair_keys, uint32_t* pair_vals,
-                 int bin, hipStream_t s, uint32_t cap = 0xFFFFFFFFu, uint32_t* overflow = nullptr);
+// (group, depth rank) pairs of the depth-ordered records.  Pairs at offsets >=
+// cap are dropped and their items counted in *overflow (if given).
+void launch_emit(const ViewInfo* views, int n_views, const uint32_t* items, const uint32_t* offsets,
+                 const uint32_t* counts, const uint32_t* rects, const float4* rec, BlendParams bp,
+                 uint32_t n_items, uint32_t n_groups, uint32_t* pair_keys, uint32_t* pair_vals, int bin,
+                 hipStream_t s, uint32_t cap = 0xFFFFFFFFu, uint32_t* overflow = nullptr);
+
+// Pairs of (bin, item) over all items in any order (plan creation): adds to *out.
+void launch_count_bins(const ViewInfo* views, int n_views, uint32_t n_items, const uint32_t* counts,
+                       const uint32_t* rects, const float4* rec, BlendParams bp, int bin, unsigned long long* out, hipStream_t s);
+
+// The lists of the groups of a view batch (sorted (group, rank) pairs), turned
+// into bin lists in three steps.  The pairs are taken in windows of kWindow,
+// one per wave, whatever groups they hold, so that lists of any length spread
+// evenly.  Window u's pairs of group g have row u + g of `counts` (unique, as
+// both grow along the pairs).
+//   launch_group_masks: every pair's blocks (mask_lo, mask_hi), each row's
+//     entries per bin, and the windows' first groups; adds each group's bin
+//     entries to totals[group] (zero before).
+//   launch_bin_ranges: with first[group] the exclusive scan of totals, the
+//     bins' ranges, and counts turned into each row's first list positions;
+//     adds *total to *sum (if given).
+//   launch_bin_lists: the bins' entries, depth rank | mask << kItemBits.
+// Positions past cap are cut off; the entries that lose one are counted in
+// *overflow (if given).  n_dev (optional): the live pair count, clamped to
+// n_pairs.
+constexpr uint32_t kWindow = 256;
+struct GroupLists {
+    const ViewInfo* views;
+    int n_views;
+    uint32_t n_groups;
+    int bin;
+    uint32_t n_pairs;
+    const uint32_t* n_dev;
+    const uint2* ranges;
+    const uint32_t* keys;
+    const uint32_t* vals;
+    const float4* rec;
+    uint32_t* mask_lo;
+    uint32_t* mask_hi;
+    uint32_t* counts;       // 16 words per row
+    uint32_t* first_group;  // per window
+    uint32_t* totals;
+};
+inline uint64_t group_windows(uint64_t pairs) { return (pairs + kWindow - 1) / kWindow; }
+inline uint64_t group_count_words(uint64_t pairs, uint64_t groups) { return 16 * (group_windows(pairs) + groups); }
+void launch_group_masks(const GroupLists& g, BlendParams bp, hipStream_t s);
+void launch_bin_ranges(const GroupLists& g, const uint32_t* first, uint2* ranges, uint32_t cap,
+                       const uint32_t* total, unsigned long long* sum, hipStream_t s);
+void launch_bin_lists(const GroupLists& g, uint32_t* lists, uint32_t cap, uint32_t* overflow, hipStream_t s);
 
 // The tile lists of a view batch, as the tile kernels read them: bin b's
 // entries are pair_vals[ranges[b].x .. ranges[b].y), front to back; an entry
@@ -162,11 +209,11 @@ inline bool few_tiles(const TileLists& tl) {
     return wave_tiles(tl.n_bins, tl.bin) <= (tl.bin == 16 ? 4096u : 1024u);
 }
 
-// Sum of n uint32 counts into *out (u64, must be zeroed).
+// Adds the sum of n uint32 counts to *out.
 void launch_sum_u64(const uint32_t* counts, uint32_t n, unsigned long long* out, hipStream_t s);
 
-// Pairs whose key is >= n_tiles are ignored.  n_dev (optional, device): live
-// pair count, clamped to n_pairs.
+// Ranges of equal keys.  Keys >= n_tiles are ignored.  n_dev (optional,
+// device): live pair count, clamped to n_pairs.
 void launch_tile_ranges(const uint32_t* sorted_keys, uint32_t n_pairs, uint32_t n_tiles,
                         uint2* ranges, hipStream_t s, const uint32_t* n_dev = nullptr);
 
@@ -184,10 +231,10 @@ void launch_scan(const uint32_t* in, uint32_t* out, uint32_t n, uint32_t* total,
 // launches are sized for); no host synchronisation is needed.
 size_t radix_scratch_words(uint32_t n);
 // Bins by decreasing octave of their list length (floor log2 of
-// ranges[b].y - ranges[b].x + 1; bin order within an octave) at
-// work + n_bins.  work holds tile_order_words(n_bins) words.
+// ranges[b].y - ranges[b].x + 1; bin order within an octave) to order[0 ..
+// n_bins), which holds tile_order_words(n_bins) words.
 size_t tile_order_words(uint32_t n_bins);
-const uint32_t* launch_tile_order(const uint2* ranges, uint32_t n_bins, uint32_t* work, hipStream_t s);
+void launch_tile_order(const uint2* ranges, uint32_t n_bins, uint32_t* order, hipStream_t s);
 // Stable LSD radix sort of (key, value) by the low `bits` key bits, 8 per
 // pass.  The result lands in keys/vals, except with result_in_alt: then an odd
 // pass count leaves it in keys_alt/vals_alt (*result_in_alt = true) instead of

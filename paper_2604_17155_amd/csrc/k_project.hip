@@ -119,14 +119,12 @@ void launch_depth_keys(const ViewInfo* views, int n_views, uint32_t n_items, con
 // form pixel offsets d = (p - u_hi) - u_lo exactly to one FP32 ulp of d; a
 // single FP32 coordinate of a 512-pixel image is only good to ~3e-5 pixel,
 // enough to move alpha by ~1e-4 relative at the footprint edge.
-// A tile is binned only if its pixel centres come within the footprint
-// reach (3-sigma ellipse, shrunk by the alpha floor for faint splats).
 template <int BIN>
 __global__ __launch_bounds__(256) void k_project(const ViewInfo* __restrict__ views, int n_views,
                                                  uint32_t n_items, const uint32_t* __restrict__ order,
                                                  const float* __restrict__ geo,
                                                  BlendParams bp, uint32_t* __restrict__ counts,
-                                                 float4* __restrict__ rec) {
+                                                 uint32_t* __restrict__ rects, float4* __restrict__ rec) {
     __shared__ uint32_t sbase[kViewLds];
     const bool vlds = stage_view_bases(views, n_views, sbase);
     const uint32_t k = blockIdx.x * blockDim.x + threadIdx.x;
@@ -141,7 +139,7 @@ __global__ __launch_bounds__(256) void k_project(const ViewInfo* __restrict__ vi
     const double2 s01 = gd[0], s23 = gd[1], s45 = gd[2];  // xx xy | xz yy | yz zz
     float mx = ga.x, my = ga.y, mz = ga.z;
     float key = __fmaf_rn(V.R[6], mx, __fmaf_rn(V.R[7], my, __fmaf_rn(V.R[8], mz, V.t[2])));
-    uint32_t cnt = 0;
+    uint32_t cnt = 0, rect = 0;
     float4 r0 = make_float4(0.f, 0.f, 0.f, 0.f), r1 = r0;
     const float og = ga.w;
     const float qmax = reach_q(og, bp);
@@ -179,93 +177,114 @@ __global__ __launch_bounds__(256) void k_project(const ViewInfo* __restrict__ vi
             r0 = make_float4(uh, vh, (float)(u - (double)uh), (float)(vv - (double)vh));
             r1 = make_float4((float)(kExp2Scale * syy * inv), (float)(-2.0 * kExp2Scale * sxy * inv),
                              (float)(kExp2Scale * sxx * inv), og);
-            footprint_bins<BIN>(r0, r1, qmax, V.width, V.height, [&](int, int, int, auto&&, int n, int4) {
-                cnt += (uint32_t)n;
-            });
+            Footprint f;
+            if (make_footprint(r0, r1, qmax, V.height, f)) cnt = count_groups<BIN>(f, V.width, rect);
         }
     }
     counts[k] = cnt;
     // records are read only through tile pairs: an item with none keeps its
     // slot unwritten
     if (cnt != 0) {
+        rects[k] = rect;
         rec[2 * (size_t)k] = r0;
         rec[2 * (size_t)k + 1] = r1;
     }
 }
 
 void launch_project(const ViewInfo* views, int n_views, uint32_t n_items, const uint32_t* order,
-                    const float* geo, BlendParams bp, uint32_t* counts, float4* rec, int bin,
-                    hipStream_t s) {
+                    const float* geo, BlendParams bp, uint32_t* counts, uint32_t* rects, float4* rec,
+                    int bin, hipStream_t s) {
     if (n_items == 0 || n_views <= 0) return;
     if (bin == 32)
         hipLaunchKernelGGL(k_project<32>, dim3((n_items + 255) / 256), dim3(256), 0, s, views, n_views,
-                           n_items, order, geo, bp, counts, rec);
+                           n_items, order, geo, bp, counts, rects, rec);
     else
         hipLaunchKernelGGL(k_project<16>, dim3((n_items + 255) / 256), dim3(256), 0, s, views, n_views,
-                           n_items, order, geo, bp, counts, rec);
+                           n_items, order, geo, bp, counts, rects, rec);
 }
 
-// a3: emit (global bin id, k | mask) pairs in depth order, k being the depth
-// rank of the item (records, counts and offsets are in that order); a stable
-// sort by bin id then yields every bin's list in front-to-back order.
+// a3: lists.  Items are first listed by group (4x4 bins; one to four groups
+// for nearly every item), in depth order; a stable sort by group id keeps that
+// order, and each group's list is then spread over its 16 bins.  Against one
+// (bin, rank) pair per bin reached, sorted: 21.6 M pairs become 7.6 M on the
+// relighting workload (100k Gaussians, 50 views of 512x512), a bin's entries
+// are written once (4 bytes) instead of emitted (8) and moved (16) per radix
+// pass, and the footprint's blocks are found by waves whose lanes all have an
+// entry of the same group instead of lanes that walk footprints of different
+// sizes.  us a call, before -> after: that workload 1886 -> 1813, three scenes
+// of 16 label channels in a plan 5247 -> 4766, 500k Gaussians x 100 views of
+// 64 feature channels 24717 -> 23371.
 constexpr uint32_t kEmitStage = 2048;  // pairs a block stages in LDS (16 KB: eight resident blocks per CU)
 
+// (group, k) pairs in depth order, k being the depth rank.  The block's items
+// are consecutive ranks, so their pairs form one contiguous range [base,
+// end_all): when it fits, it is assembled in LDS and stored with full-width
+// coalesced writes.
 template <int BIN>
 __global__ __launch_bounds__(256) void k_emit(const ViewInfo* __restrict__ views, int n_views,
-                                              const uint32_t* __restrict__ sorted_vals,
+                                              const uint32_t* __restrict__ items,
                                               const uint32_t* __restrict__ offsets,
                                               const uint32_t* __restrict__ counts,
+                                              const uint32_t* __restrict__ rects,
                                               const float4* __restrict__ rec, BlendParams bp,
                                               uint32_t n_items, uint32_t sentinel, uint32_t cap,
                                               uint32_t* __restrict__ overflow,
                                               uint32_t* __restrict__ pair_keys,
                                               uint32_t* __restrict__ pair_vals) {
-    // The block's items are consecutive depth ranks, so their pairs form one
-    // contiguous range [base, end_all): when it fits, the pairs are assembled
-    // in LDS and stored with full-width coalesced writes.
     __shared__ uint32_t skey[kEmitStage];
     __shared__ uint32_t sval[kEmitStage];
+    __shared__ uint32_t sbase[kViewLds];
+    const bool vlds = stage_view_bases(views, n_views, sbase);
     const uint32_t k0 = blockIdx.x * blockDim.x;
     const uint32_t klast = min(k0 + blockDim.x, n_items) - 1;
     const uint32_t base = offsets[k0];
     const uint32_t end_all = offsets[klast] + counts[klast];
     const bool staged = end_all - base <= kEmitStage;
     const uint32_t k = k0 + threadIdx.x;
-    if (k < n_items) {
-        const uint32_t cnt = counts[k];
-        if (cnt != 0) {
-            const ViewInfo& V = views[find_view_item(views, n_views, sorted_vals[k])];
-            const float4 r0 = rec[2 * (size_t)k], r1 = rec[2 * (size_t)k + 1];
-            uint32_t off = offsets[k];
-            uint32_t end = off + cnt;
-            if (end > cap || end < off) {  // capacity exceeded: keep what fits, report the rest
-                if (overflow) atomicAdd(overflow, 1u);
-                end = off < cap ? cap : off;
+    const uint32_t cnt = k < n_items ? counts[k] : 0u;
+    if (cnt != 0) {
+        const ViewInfo& V = views[view_of(views, n_views, sbase, vlds, items[k])];
+        const uint32_t gbase = V.group_base, gx = (uint32_t)V.groups_x;
+        const uint32_t rect = rects[k];
+        uint32_t off = offsets[k];
+        uint32_t end = off + cnt;
+        if (end > cap || end < off) {  // capacity exceeded: keep what fits, report the rest
+            if (overflow) atomicAdd(overflow, 1u);
+            end = off < cap ? cap : off;
+        }
+        auto put = [&](uint32_t key) {
+            if (off >= end) return;
+            if (staged) {
+                skey[off - base] = key;
+                sval[off - base] = k;
+            } else {
+                pair_keys[off] = key;
+                pair_vals[off] = k;
             }
-            auto put = [&](uint32_t o, uint32_t key, uint32_t val) {
-                if (staged) {
-                    skey[o - base] = key;
-                    sval[o - base] = val;
-                } else {
-                    pair_keys[o] = key;
-                    pair_vals[o] = val;
+            ++off;
+        };
+        if (!(rect & kRectWalk)) {
+            const uint32_t w = (rect >> 18) & 0x3FFu;
+            uint32_t key = gbase + ((rect >> 9) & 0x1FFu) * gx + (rect & 0x1FFu);
+            uint32_t c = 0;
+            for (uint32_t i = 0; i < cnt; ++i) {
+                put(key + c);
+                if (++c == w) {
+                    c = 0;
+                    key += gx;
                 }
-            };
-            footprint_bins<BIN>(r0, r1, reach_q(r1.w, bp), V.width, V.height,
-                                [&](int ty, int t0, int t1, auto&& mask_of, int, int4) {
-                for (int t = t0; t <= t1; ++t) {
-                    const uint32_t m = mask_of(t);
-                    if (m == 0u || off >= end) continue;
-                    put(off, V.tile_base + (uint32_t)ty * (uint32_t)V.tiles_x + (uint32_t)t,
-                        k | (m << kItemBits));
-                    ++off;
-                }
-            });
+            }
+        } else {
+            const float4 r0 = rec[2 * (size_t)k], r1 = rec[2 * (size_t)k + 1];
+            Footprint f;
+            if (make_footprint(r0, r1, reach_q(r1.w, bp), V.height, f))
+                footprint_groups<BIN>(f, V.width, [&](int gy, int a, int b) {
+                    for (int g = a; g <= b; ++g) put(gbase + (uint32_t)gy * gx + (uint32_t)g);
+                });
             // The walk above and the one that counted are the same code on the
-            // same record; should they ever disagree, unused slots get a tile
-            // id past the last tile, which sorts last and is ignored by the
-            // range kernel.
-            for (; off < end; ++off) put(off, sentinel, 0u);
+            // same record; should they ever disagree, unused slots get a group
+            // id past the last one, which sorts last and is ignored.
+            while (off < end) put(sentinel);
         }
     }
     if (!staged) return;  // uniform over the block
@@ -277,193 +296,325 @@ __global__ __launch_bounds__(256) void k_emit(const ViewInfo* __restrict__ views
     }
 }
 
-// 32-pixel bins, emitted by the block together.  Each lane walks its item's
-// footprint as above, but records every bin row it reaches as one segment
-// in LDS (the row's first output slot, the lane, and the two tile-row
-// halves' column ranges, whose union is the row's reached bin columns);
-// the first slot of each segment is marked.  A max-scan over the block's
-// output slots then names each slot's segment, and every thread writes one
-// pair per step: the pair's bin column is found by rank within its segment,
-// so an item's pair count no longer holds the other 63 lanes of its wave,
-// and the stores are coalesced.  Pairs come out in the order the per-lane
-// walk writes them.  Blocks whose range exceeds kEmitStage slots, or whose
-// rows exceed kEmitSegs segments, fall back to that walk.
-constexpr uint32_t kEmitSegs = 1024;  // bin-row segments a block collects (16 KB)
-
-// A tile-column range packed as lo | hi << 16; no columns: (0x7FFF, 0).
-__device__ inline uint32_t pack_cols(int lo, int hi) {
-    return lo <= hi ? ((uint32_t)lo | ((uint32_t)hi << 16)) : 0x7FFFu;
-}
-
-__global__ __launch_bounds__(256) void k_emit32(const ViewInfo* __restrict__ views, int n_views,
-                                                const uint32_t* __restrict__ sorted_vals,
-                                                const uint32_t* __restrict__ offsets,
-                                                const uint32_t* __restrict__ counts,
-                                                const float4* __restrict__ rec, BlendParams bp,
-                                                uint32_t n_items, uint32_t sentinel, uint32_t cap,
-                                                uint32_t* __restrict__ overflow,
-                                                uint32_t* __restrict__ pair_keys,
-                                                uint32_t* __restrict__ pair_vals) {
-    __shared__ uint4 sseg[kEmitSegs];        // (first slot | lane << 16 | sentinel << 31, bin row, half 0, half 1)
-    __shared__ uint16_t sslot[kEmitStage];   // segment marks, then each slot's segment
-    __shared__ uint32_t sitem[256], stbase[256], stx[256];
-    __shared__ uint32_t wtop[4];
-    __shared__ uint32_t nseg;
-    __shared__ uint32_t sbase[kViewLds];
-    static_assert(kEmitStage == 8 * 256, "eight slots per thread");
-    const bool vlds = stage_view_bases(views, n_views, sbase);
-    const uint32_t tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const uint32_t k0 = blockIdx.x * blockDim.x;
-    const uint32_t klast = min(k0 + blockDim.x, n_items) - 1;
-    const uint32_t base = offsets[k0];
-    const uint32_t end_all = offsets[klast] + counts[klast];
-    const bool staged = end_all - base <= kEmitStage;  // uniform over the block
-    const uint32_t k = k0 + tid;
-    uint32_t cnt = 0, off = 0, end = 0;
-    const ViewInfo* V = nullptr;
-    float4 r0 = make_float4(0.f, 0.f, 0.f, 0.f), r1 = r0;
-    if (k < n_items) {
-        cnt = counts[k];
-        if (cnt != 0) {
-            V = &views[view_of(views, n_views, sbase, vlds, sorted_vals[k])];
-            r0 = rec[2 * (size_t)k];
-            r1 = rec[2 * (size_t)k + 1];
-            off = offsets[k];
-            end = off + cnt;
-            if (end > cap || end < off) {  // capacity exceeded: keep what fits, report the rest
-                if (overflow) atomicAdd(overflow, 1u);
-                end = off < cap ? cap : off;
-            }
-        }
-    }
-    if (staged) {
-        reinterpret_cast<uint4*>(sslot)[tid] = make_uint4(0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu);
-        if (tid == 0) nseg = 0u;
-        __syncthreads();
-        if (cnt != 0) {
-            sitem[tid] = k;
-            stbase[tid] = V->tile_base;
-            stx[tid] = V->tiles_x;
-            uint32_t o = off;
-            auto add_seg = [&](uint32_t x, uint32_t y, uint32_t z, uint32_t ww) {
-                const uint32_t si = atomicAdd(&nseg, 1u);
-                if (si < kEmitSegs) {
-                    sseg[si] = make_uint4(x, y, z, ww);
-                    sslot[o - base] = (uint16_t)si;
-                }
-            };
-            footprint_bins<32>(r0, r1, reach_q(r1.w, bp), V->width, V->height,
-                               [&](int ty, int, int, auto&&, int n, int4 h) {
-                if (n <= 0) return;
-                if (o < end)
-                    add_seg((o - base) | (tid << 16), (uint32_t)ty, pack_cols(h.x, h.y), pack_cols(h.z, h.w));
-                o += (uint32_t)n;
-            });
-            // The walk above and the one that counted are the same code on the
-            // same record; should they ever disagree, unused slots get a tile
-            // id past the last tile, which sorts last and is ignored by the
-            // range kernel.
-            if (o < end) add_seg((o - base) | (tid << 16) | 0x80000000u, 0u, 0x7FFFu, 0x7FFFu);
-        }
-        __syncthreads();
-        if (nseg <= kEmitSegs) {  // uniform over the block
-            // each slot's segment: the last mark at or before it, by a max-scan
-            // of (slot + 1) << 16 | segment over the marked slots
-            const uint4 raw = reinterpret_cast<const uint4*>(sslot)[tid];
-            const uint32_t words[4] = {raw.x, raw.y, raw.z, raw.w};
-            uint32_t inc[8], run = 0u;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const uint32_t mk = (words[j >> 1] >> (16 * (j & 1))) & 0xFFFFu;
-                if (mk != 0xFFFFu) run = ((8u * tid + (uint32_t)j + 1u) << 16) | mk;
-                inc[j] = run;
-            }
-            uint32_t sc = run;  // wave inclusive max-scan of the threads' last marks
-#pragma unroll
-            for (int d = 1; d < 64; d <<= 1) {
-                const uint32_t o2 = __shfl_up(sc, d, 64);
-                if ((int)lane >= d) sc = max(sc, o2);
-            }
-            if (lane == 63) wtop[w] = sc;
-            uint32_t carry = __shfl_up(sc, 1, 64);
-            if (lane == 0) carry = 0u;
-            __syncthreads();
-            for (uint32_t q = 0; q < w; ++q) carry = max(carry, wtop[q]);
-            uint32_t outw[4];
-#pragma unroll
-            for (int j = 0; j < 8; j += 2)
-                outw[j >> 1] = (max(carry, inc[j]) & 0xFFFFu) | ((max(carry, inc[j + 1]) & 0xFFFFu) << 16);
-            reinterpret_cast<uint4*>(sslot)[tid] = make_uint4(outw[0], outw[1], outw[2], outw[3]);
-            __syncthreads();
-            const uint32_t lim = min(end_all, max(cap, base));
-            for (uint32_t i = tid; base + i < lim; i += blockDim.x) {
-                const uint4 sg = sseg[sslot[i]];
-                uint32_t key = sentinel, val = 0u;
-                if (!(sg.x & 0x80000000u)) {
-                    const uint32_t l = (sg.x >> 16) & 0xFFu;
-                    const int r = (int)(i - (sg.x & 0xFFFFu));
-                    const int lo0 = (int)(sg.z & 0xFFFFu), hi0 = (int)(sg.z >> 16);
-                    const int lo1 = (int)(sg.w & 0xFFFFu), hi1 = (int)(sg.w >> 16);
-                    // the row's reached bin columns, [a0, a1] u [c0, c1], in
-                    // increasing order
-                    const int a0 = lo0 >> 1, a1 = hi0 >> 1, c0 = lo1 >> 1, c1 = hi1 >> 1;
-                    int t;
-                    if (a1 < a0) {
-                        t = c0 + r;
-                    } else if (c1 < c0) {
-                        t = a0 + r;
-                    } else {
-                        const bool af = a0 <= c0;
-                        const int f0 = af ? a0 : c0, f1 = af ? a1 : c1, s0 = af ? c0 : a0;
-                        const int nf = f1 - f0 + 1;
-                        t = (s0 <= f1 + 1 || r < nf) ? f0 + r : s0 + (r - nf);
-                    }
-                    uint32_t m = 0u;
-#pragma unroll
-                    for (int c = 0; c < 2; ++c) {
-                        m |= (lo0 <= 2 * t + c && 2 * t + c <= hi0) ? (1u << c) : 0u;
-                        m |= (lo1 <= 2 * t + c && 2 * t + c <= hi1) ? (1u << (2 + c)) : 0u;
-                    }
-                    key = stbase[l] + sg.y * stx[l] + (uint32_t)t;
-                    val = sitem[l] | (m << kItemBits);
-                }
-                pair_keys[base + i] = key;
-                pair_vals[base + i] = val;
-            }
-            return;
-        }
-    }
-    // each lane writes its own pairs
-    if (cnt == 0) return;
-    footprint_bins<32>(r0, r1, reach_q(r1.w, bp), V->width, V->height,
-                       [&](int ty, int t0, int t1, auto&& mask_of, int, int4) {
-        for (int t = t0; t <= t1; ++t) {
-            const uint32_t m = mask_of(t);
-            if (m == 0u || off >= end) continue;
-            pair_keys[off] = V->tile_base + (uint32_t)ty * (uint32_t)V->tiles_x + (uint32_t)t;
-            pair_vals[off] = k | (m << kItemBits);
-            ++off;
-        }
-    });
-    for (; off < end; ++off) {
-        pair_keys[off] = sentinel;
-        pair_vals[off] = 0u;
-    }
-}
-
-void launch_emit(const ViewInfo* views, int n_views, const uint32_t* sorted_vals,
-                 const uint32_t* offsets, const uint32_t* counts, const float4* rec, BlendParams bp,
-                 uint32_t n_items, uint32_t n_tiles, uint32_t* pair_keys, uint32_t* pair_vals,
-                 int bin, hipStream_t s, uint32_t cap, uint32_t* overflow) {
+void launch_emit(const ViewInfo* views, int n_views, const uint32_t* items, const uint32_t* offsets,
+                 const uint32_t* counts, const uint32_t* rects, const float4* rec, BlendParams bp,
+                 uint32_t n_items, uint32_t n_groups, uint32_t* pair_keys, uint32_t* pair_vals, int bin,
+                 hipStream_t s, uint32_t cap, uint32_t* overflow) {
     if (n_items == 0) return;
     if (bin == 32)
-        hipLaunchKernelGGL(k_emit32, dim3((n_items + 255) / 256), dim3(256), 0, s, views, n_views,
-                           sorted_vals, offsets, counts, rec, bp, n_items, n_tiles, cap,
-                           overflow, pair_keys, pair_vals);
+        hipLaunchKernelGGL(k_emit<32>, dim3((n_items + 255) / 256), dim3(256), 0, s, views, n_views, items,
+                           offsets, counts, rects, rec, bp, n_items, n_groups, cap, overflow, pair_keys,
+                           pair_vals);
     else
-        hipLaunchKernelGGL(k_emit<16>, dim3((n_items + 255) / 256), dim3(256), 0, s, views, n_views,
-                           sorted_vals, offsets, counts, rec, bp, n_items, n_tiles, cap,
-                           overflow, pair_keys, pair_vals);
+        hipLaunchKernelGGL(k_emit<16>, dim3((n_items + 255) / 256), dim3(256), 0, s, views, n_views, items,
+                           offsets, counts, rects, rec, bp, n_items, n_groups, cap, overflow, pair_keys,
+                           pair_vals);
+}
+
+namespace {
+
+// The view of a group and the group's origin.
+struct GroupGeom {
+    int view;
+    int X0, Y0;        // first pixel
+    uint32_t bx, by;   // first bin column and row
+};
+template <int BIN>
+__device__ inline GroupGeom group_geom(uint32_t g, const ViewInfo* __restrict__ views, int n_views) {
+    int lo = 0, hi = n_views - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (views[mid].group_base <= g) lo = mid;
+        else hi = mid - 1;
+    }
+    const uint32_t local = g - views[lo].group_base, gx = (uint32_t)views[lo].groups_x;
+    const uint32_t cx = local % gx, cy = local / gx;
+    return GroupGeom{lo, (int)(cx << group_shift<BIN>()), (int)(cy << group_shift<BIN>()), 4 * cx, 4 * cy};
+}
+
+__device__ inline uint32_t live_pairs(const GroupLists& G) { return G.n_dev ? min(G.n_pairs, *G.n_dev) : G.n_pairs; }
+
+}  // namespace
+
+// Bound by instruction issue and by the random 32-byte record reads: 64 pairs
+// take about 500 vector instructions, most of them in the block rows (45 each,
+// as many as the wave's tallest footprint has).  7.6 M pairs of the relighting
+// workload: 177 us (250 us with a division per ellipse term, separate edges
+// per row and one part of a group's list per wave).
+template <int BIN>
+__global__ __launch_bounds__(256) void k_group_masks(GroupLists G, BlendParams bp) {
+    const uint32_t lane = threadIdx.x & 63;
+    const uint32_t u = (uint32_t)__builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
+    const uint32_t n = live_pairs(G), begin = u * kWindow;
+    if (begin >= n) return;  // whole wave
+    const uint32_t end = min(begin + kWindow, n);
+    // the next 64 pairs' records are in flight while 64 are masked
+    auto pair = [&](uint32_t b, uint32_t& key, uint32_t& k) {
+        const bool in = b + lane < end;
+        const uint32_t at = in ? b + lane : begin;
+        key = G.keys[at];
+        k = G.vals[at];
+        key = in ? key : 0xFFFFFFFFu;
+    };
+    auto load = [&](uint32_t key, uint32_t k, float4& r0, float4& r1) {
+        const size_t at = 2 * (size_t)(key < G.n_groups ? k : 0u);
+        r0 = G.rec[at];
+        r1 = G.rec[at + 1];
+    };
+    uint32_t key, k, keyn, kn;
+    pair(begin, key, k);
+    pair(begin + 64, keyn, kn);
+    float4 r0, r1, q0, q1;
+    load(key, k, r0, r1);
+    uint32_t g = (uint32_t)__builtin_amdgcn_readfirstlane((int)key);  // the current group
+    if (lane == 0) G.first_group[u] = g;
+    uint32_t c[16];  // its entries per bin (uniform)
+#pragma unroll
+    for (int q = 0; q < 16; ++q) c[q] = 0u;
+    GroupGeom gg{};
+    int W = 1, H = 1;
+    auto enter = [&]() {
+        if (g >= G.n_groups) return;
+        gg = group_geom<BIN>(g, G.views, G.n_views);
+        W = G.views[gg.view].width;
+        H = G.views[gg.view].height;
+    };
+    auto leave = [&]() {  // writes the group's row
+        if (g >= G.n_groups) return;
+        uint32_t cnt = c[0];
+#pragma unroll
+        for (int q = 1; q < 16; ++q) cnt = (lane & 15u) == (uint32_t)q ? c[q] : cnt;
+        if (lane < 16) G.counts[((size_t)u + g) * 16 + lane] = cnt;
+        uint32_t t = 0;
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+            t += c[q];
+            c[q] = 0u;
+        }
+        if (lane == 0 && t != 0u) atomicAdd(G.totals + g, t);
+    };
+    enter();
+    for (uint32_t b = begin; b < end; b += 64) {
+        load(keyn, kn, q0, q1);
+        uint32_t keynn, knn;
+        pair(b + 128, keynn, knn);
+        for (;;) {
+            const bool mine = key == g;
+            Footprint f{};
+            const bool on = mine && g < G.n_groups && make_footprint(r0, r1, reach_q(r1.w, bp), H, f);
+            const uint2 m = group_masks<BIN>(on, f, gg.X0, gg.Y0, W);
+            if (mine) {
+                G.mask_lo[b + lane] = m.x;
+                G.mask_hi[b + lane] = m.y;
+            }
+            const uint2 t = reached_bins(m);
+#pragma unroll
+            for (int q = 0; q < 16; ++q)
+                c[q] += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64((((q < 8 ? t.x : t.y) >> (4 * (q & 7))) & 1u) != 0u));
+            // the next group among these 64 pairs, if any
+            const uint64_t later = __builtin_amdgcn_ballot_w64(key > g && key != 0xFFFFFFFFu);
+            if (later == 0) break;  // uniform
+            leave();
+            g = (uint32_t)__builtin_amdgcn_readlane((int)key, __builtin_ctzll(later));
+            enter();
+        }
+        key = keyn;
+        k = kn;
+        keyn = keynn;
+        kn = knn;
+        r0 = q0;
+        r1 = q1;
+    }
+    leave();
+}
+
+void launch_group_masks(const GroupLists& g, BlendParams bp, hipStream_t s) {
+    if (g.n_groups == 0 || g.n_pairs == 0) return;
+    const dim3 grid((unsigned)((group_windows(g.n_pairs) + 3) / 4)), block(256);
+    if (g.bin == 32) hipLaunchKernelGGL(k_group_masks<32>, grid, block, 0, s, g, bp);
+    else hipLaunchKernelGGL(k_group_masks<16>, grid, block, 0, s, g, bp);
+}
+
+// One block per group; thread 16 j + f takes bin f of rows j, j + 16, ...
+template <int BIN>
+__global__ __launch_bounds__(256) void k_bin_ranges(GroupLists G, const uint32_t* __restrict__ first,
+                                                    uint2* __restrict__ ranges, uint32_t cap,
+                                                    const uint32_t* __restrict__ total,
+                                                    unsigned long long* __restrict__ sum) {
+    __shared__ uint32_t part[16][17];
+    const uint32_t g = blockIdx.x, f = threadIdx.x & 15u, j = threadIdx.x >> 4;
+    if (g == 0 && threadIdx.x == 0 && sum) atomicAdd(sum, (unsigned long long)*total);
+    const uint2 rg = G.ranges[g];
+    const uint32_t u0 = rg.x / kWindow, rows = rg.x < rg.y ? (rg.y - 1) / kWindow - u0 + 1 : 0u;
+    uint32_t* cnt = G.counts + ((size_t)u0 + g) * 16 + f;
+    // thread j takes `per` consecutive rows
+    const uint32_t per = (rows + 15u) / 16u, p0 = min(j * per, rows), p1 = min(p0 + per, rows);
+    uint32_t mine = 0;
+#pragma unroll 8
+    for (uint32_t p = p0; p < p1; ++p) mine += cnt[(size_t)p * 16];
+    part[j][f] = mine;
+    __syncthreads();
+    uint32_t tot = 0, before = 0;
+#pragma unroll
+    for (uint32_t q = 0; q < 16; ++q) {
+        const uint32_t c = part[q][f];
+        before += q < j ? c : 0u;
+        tot += c;
+    }
+    uint32_t inc = tot;  // inclusive scan over the sixteen bins
+#pragma unroll
+    for (int d = 1; d < 16; d <<= 1) {
+        const uint32_t o = (uint32_t)__shfl_up((int)inc, d, 16);
+        if ((int)f >= d) inc += o;
+    }
+    const uint32_t start = first[g] + inc - tot;
+    uint32_t run = start + before;
+#pragma unroll 8
+    for (uint32_t p = p0; p < p1; ++p) {
+        const uint32_t c = cnt[(size_t)p * 16];
+        cnt[(size_t)p * 16] = run;
+        run += c;
+    }
+    if (j != 0) return;
+    const GroupGeom gg = group_geom<BIN>(g, G.views, G.n_views);
+    const ViewInfo& V = G.views[gg.view];
+    const uint32_t bx = gg.bx + (f & 3u), by = gg.by + (f >> 2);
+    if (bx < (uint32_t)V.tiles_x && by < (uint32_t)V.tiles_y)
+        ranges[V.tile_base + by * (uint32_t)V.tiles_x + bx] = make_uint2(min(start, cap), min(start + tot, cap));
+}
+
+void launch_bin_ranges(const GroupLists& g, const uint32_t* first, uint2* ranges, uint32_t cap,
+                       const uint32_t* total, unsigned long long* sum, hipStream_t s) {
+    if (g.n_groups == 0) return;
+    const dim3 grid(g.n_groups), block(256);
+    if (g.bin == 32) hipLaunchKernelGGL(k_bin_ranges<32>, grid, block, 0, s, g, first, ranges, cap, total, sum);
+    else hipLaunchKernelGGL(k_bin_ranges<16>, grid, block, 0, s, g, first, ranges, cap, total, sum);
+}
+
+// One wave per window: each bin's entries of 64 pairs at once, by ballot, so
+// the bin lists keep the group list's (depth) order.  The 64 pairs' entries
+// (180 of 1024 on the relighting workload) are packed in LDS with their places
+// and stored 64 at a time; stored bin by bin, with 16 partly filled store
+// instructions per 64 pairs, the kernel was bound by store issue (124 -> 87 us
+// there).
+template <bool CAP>
+__global__ __launch_bounds__(256) void k_bin_lists(GroupLists G, uint32_t* __restrict__ lists, uint32_t cap,
+                                                   uint32_t* __restrict__ overflow) {
+    __shared__ uint2 stage[4][1024];
+    const uint32_t lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const uint32_t u = (uint32_t)__builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + w));
+    const uint32_t n = live_pairs(G), begin = u * kWindow;
+    if (begin >= n) return;  // whole wave (no block barrier below)
+    const uint32_t end = min(begin + kWindow, n);
+    uint32_t g = (uint32_t)__builtin_amdgcn_readfirstlane((int)G.first_group[u]);
+    uint32_t at = begin;
+    // the group lists the window meets, one after the other
+    while (at < end && g < G.n_groups) {
+        const uint2 rg = G.ranges[g];
+        const uint32_t stop = min(end, (uint32_t)__builtin_amdgcn_readfirstlane((int)rg.y));
+        if (__builtin_amdgcn_readfirstlane((int)rg.x) == __builtin_amdgcn_readfirstlane((int)rg.y) || stop <= at) {
+            ++g;  // a group without pairs
+            continue;
+        }
+        uint32_t pos[16];
+#pragma unroll
+        for (int f = 0; f < 16; ++f) pos[f] = G.counts[((size_t)u + g) * 16 + f];
+        for (uint32_t b = at; b < stop; b += 64) {
+            const bool in = b + lane < stop;
+            const uint32_t idx = in ? b + lane : at;
+            const uint32_t k = G.vals[idx];
+            uint2 m = make_uint2(G.mask_lo[idx], G.mask_hi[idx]);
+            m = in ? m : make_uint2(0u, 0u);
+            uint32_t fill = 0;  // entries staged (uniform)
+#pragma unroll
+            for (int f = 0; f < 16; ++f) {
+                const uint32_t bm = ((f < 8 ? m.x : m.y) >> (4 * (f & 7))) & 15u;
+                const uint64_t bal = __builtin_amdgcn_ballot_w64(bm != 0u);
+                const uint32_t pre = __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32),
+                                                               __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
+                if (bm != 0u) stage[w][fill + pre] = make_uint2(k | (bm << kItemBits), pos[f] + pre);
+                const uint32_t c = (uint32_t)__popcll(bal);
+                fill += c;
+                pos[f] += c;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            uint32_t lost = 0;
+            for (uint32_t i = lane; i < fill; i += 64) {
+                const uint2 e = stage[w][i];
+                if (!CAP || e.y < cap) lists[e.y] = e.x;
+                else ++lost;
+            }
+            if constexpr (CAP) {
+                if (lost != 0u && overflow) atomicAdd(overflow, lost);
+            }
+            __builtin_amdgcn_wave_barrier();  // the next 64 pairs overwrite the stage
+        }
+        at = stop;
+        ++g;
+    }
+}
+
+void launch_bin_lists(const GroupLists& g, uint32_t* lists, uint32_t cap, uint32_t* overflow, hipStream_t s) {
+    if (g.n_groups == 0 || g.n_pairs == 0) return;
+    const dim3 grid((unsigned)((group_windows(g.n_pairs) + 3) / 4)), block(256);
+    if (cap != 0xFFFFFFFFu) hipLaunchKernelGGL(k_bin_lists<true>, grid, block, 0, s, g, lists, cap, overflow);
+    else hipLaunchKernelGGL(k_bin_lists<false>, grid, block, 0, s, g, lists, cap, overflow);
+}
+
+// Bins listed for every item (the sizes a plan fixes): the same groups and the
+// same masks as above.
+template <int BIN>
+__global__ __launch_bounds__(256) void k_count_bins(const ViewInfo* __restrict__ views, int n_views,
+                                                    uint32_t n_items, const uint32_t* __restrict__ counts,
+                                                    const uint32_t* __restrict__ rects,
+                                                    const float4* __restrict__ rec, BlendParams bp,
+                                                    unsigned long long* __restrict__ out) {
+    __shared__ unsigned long long part[4];
+    unsigned long long acc = 0;
+    constexpr int kS = group_shift<BIN>();
+    for (uint32_t k0 = blockIdx.x * blockDim.x; k0 < n_items; k0 += gridDim.x * blockDim.x) {
+        const uint32_t k = k0 + threadIdx.x;
+        const uint32_t n = k < n_items ? counts[k] : 0u;
+        if (n == 0u) continue;
+        const ViewInfo& V = views[find_view_item(views, n_views, k)];
+        const float4 r0 = rec[2 * (size_t)k], r1 = rec[2 * (size_t)k + 1];
+        Footprint f{};
+        const bool on = make_footprint(r0, r1, reach_q(r1.w, bp), V.height, f);
+        auto add = [&](int gx, int gy) {
+            const uint2 t = reached_bins(group_masks<BIN>(on, f, gx << kS, gy << kS, V.width));
+            acc += (uint32_t)(__popc(t.x) + __popc(t.y));
+        };
+        const uint32_t rect = rects[k];
+        if (!(rect & kRectWalk)) {
+            const int w = (int)((rect >> 18) & 0x3FFu), gx = (int)(rect & 0x1FFu), gy = (int)((rect >> 9) & 0x1FFu);
+            int c = 0, row = 0;
+            for (uint32_t i = 0; i < n; ++i) {
+                add(gx + c, gy + row);
+                if (++c == w) {
+                    c = 0;
+                    ++row;
+                }
+            }
+        } else {
+            footprint_groups<BIN>(f, V.width, [&](int gy, int ga, int gb) {
+                for (int gx = ga; gx <= gb; ++gx) add(gx, gy);
+            });
+        }
+    }
+    for (int d = 32; d >= 1; d >>= 1) acc += __shfl_xor(acc, d, 64);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = acc;
+    __syncthreads();
+    if (threadIdx.x == 0) atomicAdd(out, part[0] + part[1] + part[2] + part[3]);
+}
+
+void launch_count_bins(const ViewInfo* views, int n_views, uint32_t n_items, const uint32_t* counts,
+                       const uint32_t* rects, const float4* rec, BlendParams bp, int bin,
+                       unsigned long long* out, hipStream_t s) {
+    if (n_items == 0) return;
+    const dim3 grid(std::min<uint32_t>((n_items + 255) / 256, 4096u)), block(256);
+    if (bin == 32) hipLaunchKernelGGL(k_count_bins<32>, grid, block, 0, s, views, n_views, n_items, counts, rects, rec, bp, out);
+    else hipLaunchKernelGGL(k_count_bins<16>, grid, block, 0, s, views, n_views, n_items, counts, rects, rec, bp, out);
 }
 
 // A modest grid (one 64-bit atomic per block on the same word) reading 16

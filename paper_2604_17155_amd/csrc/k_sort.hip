@@ -489,28 +489,90 @@ void radix_sort(uint32_t* keys, uint32_t* vals, uint32_t* keys_alt, uint32_t* va
     }
 }
 
-__global__ void k_tile_work_keys(const uint2* __restrict__ ranges, uint32_t n_bins,
-                                 uint32_t* __restrict__ keys, uint32_t* __restrict__ vals) {
-    const uint32_t b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= n_bins) return;
-    const uint2 r = ranges[b];
-    // the octave of the list length, longest first; index order within one
-    // octave keeps neighbouring tiles of a view together (shared records in L2)
-    keys[b] = 31u - (31u - __clz(r.y - r.x + 1u));
-    vals[b] = b;
+// ---- tile order ------------------------------------------------------------
+//
+// Bins by the octave of their list length, longest first, index order within
+// an octave (neighbouring tiles of a view stay together and share records in
+// L2): a stable counting sort over 33 classes, 4096 bins per block, the class
+// taken from the ranges in both kernels (no keys or values are stored).  A
+// launch of up to 4096 bins is one block, which counts and places in one
+// kernel.
+namespace {
+constexpr uint32_t kToBins = 4096, kToClasses = 64, kToThreads = 1024, kToWaves = kToThreads / 64;
+__device__ __forceinline__ uint32_t tile_class(uint2 r) { return (uint32_t)__clz((int)(r.y - r.x + 1u)); }
+}  // namespace
+
+template <bool PLACE>
+__global__ __launch_bounds__(kToThreads) void k_tile_order(const uint2* __restrict__ ranges, uint32_t n_bins,
+                                                           uint32_t* __restrict__ hist, uint32_t n_blocks,
+                                                           uint32_t* __restrict__ out) {
+    __shared__ uint32_t cnt[kToWaves][kToClasses];
+    const uint32_t tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    for (uint32_t i = tid; i < kToWaves * kToClasses; i += kToThreads) (&cnt[0][0])[i] = 0u;
+    __syncthreads();
+    // wave w takes 256 consecutive bins, 64 at a time
+    const uint64_t b0 = (uint64_t)blockIdx.x * kToBins + w * (kToBins / kToWaves);
+    uint32_t cls[4], rank[4];
+#pragma unroll
+    for (int it = 0; it < 4; ++it) {
+        const uint64_t b = b0 + it * 64 + lane;
+        cls[it] = b < n_bins ? tile_class(ranges[b]) : 63u;
+    }
+#pragma unroll
+    for (int it = 0; it < 4; ++it) {
+        uint64_t m = ~0ull;  // lanes of the same class
+#pragma unroll
+        for (int k = 0; k < 6; ++k) {
+            const uint64_t bb = __ballot((cls[it] >> k) & 1u);
+            m &= ((cls[it] >> k) & 1u) ? bb : ~bb;
+        }
+        const uint32_t pre = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+        const uint32_t c = cnt[w][cls[it]];
+        __builtin_amdgcn_wave_barrier();
+        if (pre == 0) cnt[w][cls[it]] = c + (uint32_t)__popcll(m);
+        __builtin_amdgcn_wave_barrier();
+        rank[it] = c + pre;
+    }
+    __syncthreads();
+    if (tid < kToClasses) {  // wave 0: prefix over the waves, then over the classes
+        uint32_t run = 0;
+        for (uint32_t k = 0; k < kToWaves; ++k) {
+            const uint32_t c = cnt[k][tid];
+            cnt[k][tid] = run;
+            run += c;
+        }
+        if constexpr (!PLACE) {
+            hist[(uint64_t)tid * n_blocks + blockIdx.x] = tid < 63u ? run : 0u;
+        } else {
+            const uint32_t base = n_blocks > 1 ? hist[(uint64_t)tid * n_blocks + blockIdx.x]
+                                               : wave_inclusive_scan(run) - run;
+            for (uint32_t k = 0; k < kToWaves; ++k) cnt[k][tid] += base;
+        }
+    }
+    if constexpr (PLACE) {
+        __syncthreads();
+#pragma unroll
+        for (int it = 0; it < 4; ++it) {
+            const uint64_t b = b0 + it * 64 + lane;
+            if (b < n_bins) out[cnt[w][cls[it]] + rank[it]] = (uint32_t)b;
+        }
+    }
 }
 
 size_t tile_order_words(uint32_t n_bins) {
-    return 4 * (size_t)n_bins + radix_scratch_words(n_bins);
+    const size_t nb = ((size_t)n_bins + kToBins - 1) / kToBins;
+    return (size_t)n_bins + 64 + (nb > 1 ? kToClasses * nb + scan_scratch_words(kToClasses * nb) : 0);
 }
 
-const uint32_t* launch_tile_order(const uint2* ranges, uint32_t n_bins, uint32_t* work, hipStream_t s) {
-    uint32_t *keys = work, *vals = work + n_bins, *keys_alt = work + 2 * (size_t)n_bins,
-             *vals_alt = work + 3 * (size_t)n_bins;
-    if (n_bins == 0) return vals;
-    hipLaunchKernelGGL(k_tile_work_keys, dim3((n_bins + 255) / 256), dim3(256), 0, s, ranges, n_bins, keys, vals);
-    radix_sort(keys, vals, keys_alt, vals_alt, n_bins, 5, work + 4 * (size_t)n_bins, s);
-    return vals;
+void launch_tile_order(const uint2* ranges, uint32_t n_bins, uint32_t* order, hipStream_t s) {
+    if (n_bins == 0) return;
+    const uint32_t nb = (uint32_t)(((uint64_t)n_bins + kToBins - 1) / kToBins);
+    uint32_t* hist = order + (((size_t)n_bins + 63) / 64) * 64;
+    if (nb > 1) {
+        hipLaunchKernelGGL(k_tile_order<false>, dim3(nb), dim3(kToThreads), 0, s, ranges, n_bins, hist, nb, order);
+        launch_scan(hist, hist, kToClasses * nb, nullptr, hist + kToClasses * nb, s);
+    }
+    hipLaunchKernelGGL(k_tile_order<true>, dim3(nb), dim3(kToThreads), 0, s, ranges, n_bins, hist, nb, order);
 }
 
 }  // namespace gsc
