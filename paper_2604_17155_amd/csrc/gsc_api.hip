@@ -454,10 +454,17 @@ gsc_status bin_views(gsc_ctx* ctx, const ViewInfo* all, int v0, int nv,
         GSC_HIP(hipHostMalloc((void**)&ctx->h_views, sizeof(ViewInfo) * (size_t)nv));
         ctx->h_views_cap = (size_t)nv;
     }
-    uint64_t tiles = 0, items = 0, groups = 0;
+    uint64_t tiles = 0, items = 0, groups = 0, sort_tiles = 0;
     bool uniform = true;
+    uint32_t max_n = 0;
+    for (int k = 0; k < nv; ++k) max_n = std::max(max_n, all[v0 + k].n_gauss);
+    uint64_t total_n = 0;
+    for (int k = 0; k < nv; ++k) total_n += all[v0 + k].n_gauss;
+    const DepthSortShape dsort = depth_sort_shape(max_n, total_n);
     for (int k = 0; k < nv; ++k) {
         ViewInfo v = all[v0 + k];
+        v.sort_base = (uint32_t)sort_tiles;
+        if (dsort.tile) sort_tiles += (v.n_gauss + dsort.tile - 1) / dsort.tile;
         v.tile_base = (uint32_t)tiles;
         v.item_base = (uint32_t)items;
         v.group_base = (uint32_t)groups;
@@ -485,18 +492,13 @@ gsc_status bin_views(gsc_ctx* ctx, const ViewInfo* all, int v0, int nv,
     GSC_HIP(ctx->granges.ensure(12 * (groups + 1)));  // the groups' ranges, then their totals
     GSC_HIP(ctx->gfirst.ensure(4 * groups + 4));
     const ViewInfo* dviews = ctx->views.as<ViewInfo>();
-    {
-        StageTimer t(ctx, s, GSC_STAGE_PROJECT);
-        launch_depth_keys(dviews, nv, ni, means, opac, bp, ctx->keys.as<uint32_t>(),
-                          ctx->vals.as<uint32_t>(), s);
-        GSC_LAUNCHED("depth keys");
-    }
-    size_t scr = std::max({radix_scratch_words(ni), scan_scratch_words(ni), scan_scratch_words(ng)});
+    size_t scr = std::max({depth_sort_scratch_words(dsort, sort_tiles), scan_scratch_words(ni), scan_scratch_words(ng)});
     GSC_HIP(ctx->sort_scratch.ensure(4 * scr + 256));
     {
         StageTimer t(ctx, s, GSC_STAGE_DEPTH_SORT);
-        radix_sort(ctx->keys.as<uint32_t>(), ctx->vals.as<uint32_t>(), ctx->keys_alt.as<uint32_t>(),
-                   ctx->vals_alt.as<uint32_t>(), ni, 32, ctx->sort_scratch.as<uint32_t>(), s);
+        launch_depth_sort(dviews, nv, ni, dsort, max_n, uniform ? max_n : 0u, (uint32_t)sort_tiles, means, opac, bp,
+                          ctx->keys.as<uint32_t>(), ctx->vals.as<uint32_t>(), ctx->keys_alt.as<uint32_t>(),
+                          ctx->vals_alt.as<uint32_t>(), ctx->sort_scratch.as<uint32_t>(), s);
         GSC_LAUNCHED("depth sort");
     }
     // (the sort is done with its keys and alternates: the counts, rectangles
@@ -554,8 +556,8 @@ gsc_status bin_views(gsc_ctx* ctx, const ViewInfo* all, int v0, int nv,
     GSC_HIP((odd ? ctx->pkeys_alt : ctx->pkeys).ensure(4 * pairs + 4));
     {
         StageTimer t(ctx, s, GSC_STAGE_EMIT);
-        launch_emit(dviews, nv, ctx->vals.as<uint32_t>(), offsets, counts, rects, ctx->rec.as<float4>(), bp, ni,
-                    ng, ctx->pkeys.as<uint32_t>(), ctx->pvals.as<uint32_t>(), ctx->bin, s);
+        launch_emit(dviews, nv, offsets, counts, rects, ctx->rec.as<float4>(), bp, ni, ng,
+                    ctx->pkeys.as<uint32_t>(), ctx->pvals.as<uint32_t>(), ctx->bin, s);
         GSC_LAUNCHED("emit");
     }
     StageTimer t(ctx, s, GSC_STAGE_TILE_SORT);
@@ -774,6 +776,8 @@ struct gsc_plan {
         uint32_t n_items, n_tiles, n_groups;
         uint32_t group_cap, pair_cap;  // group pairs and bin pairs
         int group_bits;
+        uint32_t max_n, uniform_n, sort_tiles;
+        DepthSortShape dsort;
     };
     std::vector<Batch> batches;
     std::vector<ViewInfo> views;      // all views, tile_base/item_base local to their batch
@@ -834,10 +838,18 @@ gsc_status plan_count_pairs(gsc_plan* P, const gsc_plan::Batch& b, hipStream_t s
 // Assign batch-local tile and item numbering to the views of every batch.
 void plan_number_views(gsc_plan* P) {
     for (auto& b : P->batches) {
-        uint64_t tiles = 0, items = 0, groups = 0;
+        uint64_t tiles = 0, items = 0, groups = 0, sort_tiles = 0;
         bool uniform = true;
+        b.max_n = 0;
+        for (int k = 0; k < b.nv; ++k) b.max_n = std::max(b.max_n, P->views[b.v0 + k].n_gauss);
+        uint64_t total_n = 0;
+        for (int k = 0; k < b.nv; ++k) total_n += P->views[b.v0 + k].n_gauss;
+        b.dsort = depth_sort_shape(b.max_n, total_n);
+        const DepthSortShape& dsort = b.dsort;
         for (int k = 0; k < b.nv; ++k) {
             ViewInfo& v = P->views[b.v0 + k];
+            v.sort_base = (uint32_t)sort_tiles;
+            if (dsort.tile) sort_tiles += (v.n_gauss + dsort.tile - 1) / dsort.tile;
             v.tile_base = (uint32_t)tiles;
             v.item_base = (uint32_t)items;
             v.group_base = (uint32_t)groups;
@@ -847,6 +859,8 @@ void plan_number_views(gsc_plan* P) {
             uniform = uniform && v.n_gauss == P->views[b.v0].n_gauss;
         }
         for (int k = 0; k < b.nv; ++k) P->views[b.v0 + k].uniform_n = uniform ? P->views[b.v0].n_gauss : 0u;
+        b.uniform_n = uniform ? b.max_n : 0u;
+        b.sort_tiles = (uint32_t)sort_tiles;
         b.n_tiles = (uint32_t)tiles;
         b.n_groups = (uint32_t)groups;
         b.n_items = (uint32_t)items;
@@ -873,15 +887,10 @@ gsc_status plan_bin_batch(gsc_plan* P, const gsc_plan::Batch& b, hipStream_t s) 
     uint32_t* d_live = reinterpret_cast<uint32_t*>(P->misc.as<char>() + 8);
     uint32_t* d_drop = reinterpret_cast<uint32_t*>(P->misc.as<char>() + 12);
     {
-        StageTimer t(ctx, s, GSC_STAGE_PROJECT);
-        launch_depth_keys(dv, b.nv, b.n_items, P->means, P->opac, P->bp, P->keys.as<uint32_t>(),
-                          P->vals.as<uint32_t>(), s);
-        GSC_LAUNCHED("depth keys");
-    }
-    {
         StageTimer t(ctx, s, GSC_STAGE_DEPTH_SORT);
-        radix_sort(P->keys.as<uint32_t>(), P->vals.as<uint32_t>(), P->keys_alt.as<uint32_t>(),
-                   P->vals_alt.as<uint32_t>(), b.n_items, 32, P->sort_scratch.as<uint32_t>(), s);
+        launch_depth_sort(dv, b.nv, b.n_items, b.dsort, b.max_n, b.uniform_n, b.sort_tiles,
+                          P->means, P->opac, P->bp, P->keys.as<uint32_t>(), P->vals.as<uint32_t>(),
+                          P->keys_alt.as<uint32_t>(), P->vals_alt.as<uint32_t>(), P->sort_scratch.as<uint32_t>(), s);
         GSC_LAUNCHED("depth sort");
     }
     // (in the sort's spent buffers, as in bin_views)
@@ -901,8 +910,8 @@ gsc_status plan_bin_batch(gsc_plan* P, const gsc_plan::Batch& b, hipStream_t s) 
     }
     {
         StageTimer t(ctx, s, GSC_STAGE_EMIT);
-        launch_emit(dv, b.nv, P->vals.as<uint32_t>(), offsets, counts, rects, P->rec.as<float4>(), P->bp,
-                    b.n_items, b.n_groups, P->pkeys.as<uint32_t>(), P->pvals.as<uint32_t>(), P->bin, s,
+        launch_emit(dv, b.nv, offsets, counts, rects, P->rec.as<float4>(), P->bp, b.n_items,
+                    b.n_groups, P->pkeys.as<uint32_t>(), P->pvals.as<uint32_t>(), P->bin, s,
                     b.group_cap, d_drop);
         GSC_LAUNCHED("emit");
     }
@@ -1744,14 +1753,14 @@ gsc_status gsc_plan_create(gsc_ctx* ctx, const gsc_scene* scenes, int32_t n_scen
         for (int v = 0; v < (int)P->views.size(); ++v) {
             const uint64_t ni = P->views[v].n_gauss, nt = (uint64_t)P->views[v].tiles_x * P->views[v].tiles_y;
             if (v > v0 && (items + ni > plan_item_limit(ctx->opt) || tiles + nt >= (1ull << 31))) {
-                P->batches.push_back({v0, v - v0, 0, 0, 0, 0, 0, 0});
+                P->batches.push_back(gsc_plan::Batch{v0, v - v0});
                 v0 = v;
                 items = tiles = 0;
             }
             items += ni;
             tiles += nt;
         }
-        if (v0 < (int)P->views.size()) P->batches.push_back({v0, (int)P->views.size() - v0, 0, 0, 0, 0, 0, 0});
+        if (v0 < (int)P->views.size()) P->batches.push_back(gsc_plan::Batch{v0, (int)P->views.size() - v0});
     }
     plan_number_views(P);
     for (const auto& b : P->batches) P->max_items = std::max(P->max_items, b.n_items);
@@ -1778,7 +1787,7 @@ gsc_status gsc_plan_create(gsc_ctx* ctx, const gsc_scene* scenes, int32_t n_scen
             if (b.nv == 1) return fail(GSC_ERR_CAPACITY, "one view produces %llu tile pairs", (unsigned long long)pairs);
             const int h = b.nv / 2;
             P->batches[k].nv = h;
-            P->batches.insert(P->batches.begin() + k + 1, gsc_plan::Batch{b.v0 + h, b.nv - h, 0, 0, 0, 0, 0, 0});
+            P->batches.insert(P->batches.begin() + k + 1, gsc_plan::Batch{b.v0 + h, b.nv - h});
             plan_number_views(P);
             GSC_HIP(hipMemcpyAsync(P->d_views.p, P->views.data(), sizeof(ViewInfo) * P->views.size(),
                                    hipMemcpyHostToDevice, s));
@@ -1810,8 +1819,12 @@ gsc_status gsc_plan_create(gsc_ctx* ctx, const gsc_scene* scenes, int32_t n_scen
     GSC_HIP(P->lists.ensure(4 * (size_t)P->max_pairs + 4));
     GSC_HIP(P->ranges.ensure(sizeof(uint2) * ((size_t)P->max_tiles + 1)));
     GSC_HIP(P->order.ensure(4 * tile_order_words(P->max_tiles)));
-    const size_t scr = std::max({radix_scratch_words(P->max_items), scan_scratch_words(P->max_items),
+    size_t scr = std::max({scan_scratch_words(P->max_items),
                                  radix_scratch_words(P->max_group_pairs), scan_scratch_words(P->max_groups)});
+    for (const auto& b : P->batches) {
+        scr = std::max(scr, depth_sort_scratch_words(b.dsort, b.sort_tiles));
+        scr = std::max(scr, radix_scratch_words(b.group_cap));
+    }
     GSC_HIP(P->sort_scratch.ensure(4 * scr + 256));
     GSC_HIP(P->vs.ensure(4 * P->vs_slots * (size_t)(C + 1)));
     GSC_HIP(P->queues.ensure(4 * (size_t)kMaxC));

@@ -31,6 +31,7 @@ struct ViewInfo {
     uint32_t item_base;    // first item of this view within its batch
     uint32_t group_base;   // first group (4x4 bins) of this view within its batch
     int32_t groups_x;      // groups per row
+    uint32_t sort_base;    // first depth-sort tile of this view within its batch
     int64_t pixel_offset;  // first target row
     int64_t g_offset;      // first Gaussian of the view's scene
     int64_t vs_base;       // first per-view sum slot of this view (per-view layouts)
@@ -112,11 +113,23 @@ void launch_cov3d(const float* means, const float* opac, const float* scales, co
 void launch_geometry_stats(const float* means, const float* scales, int64_t N, double* out,
                            hipStream_t s);
 
-// Depth keys of the batch items (n_items = sum of n_gauss over the batch's
-// views): keys[i] = binary32 depth bits or 0xFFFFFFFF (culled), vals[i] = i.
-void launch_depth_keys(const ViewInfo* views, int n_views, uint32_t n_items, const float* means,
-                       const float* opac, BlendParams bp, uint32_t* keys, uint32_t* vals,
-                       hipStream_t s);
+// Depth sort of the batch's items, view by view: vals becomes the items of
+// each view in depth order (ties by Gaussian index) at the view's own places
+// [item_base, item_base + n_gauss).  keys and the alternates are scratch.
+// Its shape follows from the largest view and the item count; tiles: the views' ceil(n_gauss /
+// tile) summed (0 when the views are sorted in LDS), numbered by sort_base;
+// uniform_n: n_gauss when all views have the same, else 0.
+struct DepthSortShape {
+    bool in_lds;
+    int items;
+    uint32_t tile;
+};
+DepthSortShape depth_sort_shape(uint32_t max_n, uint64_t n_items);
+size_t depth_sort_scratch_words(const DepthSortShape& d, uint64_t tiles);
+void launch_depth_sort(const ViewInfo* views, int n_views, uint32_t n_items, const DepthSortShape& d,
+                       uint32_t max_n, uint32_t uniform_n, uint32_t tiles, const float* means, const float* opac,
+                       BlendParams bp, uint32_t* keys, uint32_t* vals, uint32_t* keys_alt, uint32_t* vals_alt,
+                       uint32_t* scratch, hipStream_t s);
 
 // Projection in depth order: position k handles item i = order[k] (k if order
 // is null) and writes counts[k], the groups of 4x4 bins its footprint is
@@ -128,8 +141,8 @@ void launch_project(const ViewInfo* views, int n_views, uint32_t n_items, const 
 
 // (group, depth rank) pairs of the depth-ordered records.  Pairs at offsets >=
 // cap are dropped and their items counted in *overflow (if given).
-void launch_emit(const ViewInfo* views, int n_views, const uint32_t* items, const uint32_t* offsets,
-                 const uint32_t* counts, const uint32_t* rects, const float4* rec, BlendParams bp,
+void launch_emit(const ViewInfo* views, int n_views, const uint32_t* offsets, const uint32_t* counts,
+                 const uint32_t* rects, const float4* rec, BlendParams bp,
                  uint32_t n_items, uint32_t n_groups, uint32_t* pair_keys, uint32_t* pair_vals, int bin,
                  hipStream_t s, uint32_t cap = 0xFFFFFFFFu, uint32_t* overflow = nullptr);
 
@@ -225,23 +238,19 @@ size_t scan_scratch_words(uint64_t n);
 void launch_scan(const uint32_t* in, uint32_t* out, uint32_t n, uint32_t* total, uint32_t* scratch,
                  hipStream_t s);
 
-// Stable LSD radix sort of (key, val) on the low `bits` bits of key. The
-// result ends in (keys, vals); alt buffers are scratch of the same size.
-// n_dev (optional, device): the live count, clamped to n (the capacity the
-// launches are sized for); no host synchronisation is needed.
 size_t radix_scratch_words(uint32_t n);
 // Bins by decreasing octave of their list length (floor log2 of
 // ranges[b].y - ranges[b].x + 1; bin order within an octave) to order[0 ..
 // n_bins), which holds tile_order_words(n_bins) words.
 size_t tile_order_words(uint32_t n_bins);
 void launch_tile_order(const uint2* ranges, uint32_t n_bins, uint32_t* order, hipStream_t s);
-// Stable LSD radix sort of (key, value) by the low `bits` key bits, 8 per
-// pass.  The result lands in keys/vals, except with result_in_alt: then an odd
-// pass count leaves it in keys_alt/vals_alt (*result_in_alt = true) instead of
-// copying it back.
+// Stable LSD radix sort of (key, value) by the low `bits` key bits, up to 8 per
+// pass.  An odd pass count leaves the result in keys_alt/vals_alt
+// (*result_in_alt = true).  n_dev (optional, device): the live count, clamped to
+// n (the capacity the launches are sized for).
 void radix_sort(uint32_t* keys, uint32_t* vals, uint32_t* keys_alt, uint32_t* vals_alt,
-                uint32_t n, int bits, uint32_t* scratch, hipStream_t s,
-                const uint32_t* n_dev = nullptr, bool* result_in_alt = nullptr);
+                uint32_t n, int bits, uint32_t* scratch, hipStream_t s, const uint32_t* n_dev,
+                bool* result_in_alt);
 
 // Accumulate variants ("chunks"): the channels per launch (launches =
 // ceil(C / channels)), plus kChunkMfma for the matrix-core forms: BF16

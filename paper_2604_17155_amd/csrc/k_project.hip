@@ -81,35 +81,6 @@ void launch_geometry_stats(const float* means, const float* scales, int64_t N, d
     hipLaunchKernelGGL(k_geometry_stats, dim3((unsigned)blocks), dim3(256), 0, s, means, scales, N, out);
 }
 
-// a2, first step: the depth key of every (view, Gaussian) item of the batch,
-// keys[i] = bits of the camera-space depth of the mean computed in binary32
-// (positive floats order like their bit patterns), 0xFFFFFFFF for items culled
-// by the near plane or too faint to pass the alpha floor anywhere; vals[i] = i.
-__global__ __launch_bounds__(256) void k_depth_keys(const ViewInfo* __restrict__ views, int n_views,
-                                                    uint32_t n_items, const float* __restrict__ means,
-                                                    const float* __restrict__ opac, BlendParams bp,
-                                                    uint32_t* __restrict__ keys,
-                                                    uint32_t* __restrict__ vals) {
-    __shared__ uint32_t sbase[kViewLds];
-    const bool vlds = stage_view_bases(views, n_views, sbase);
-    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n_items) return;
-    const ViewInfo& V = views[view_of(views, n_views, sbase, vlds, i)];
-    const int64_t g = V.g_offset + (int64_t)(i - V.item_base);
-    const float key = __fmaf_rn(V.R[6], means[3 * g],
-                                __fmaf_rn(V.R[7], means[3 * g + 1], __fmaf_rn(V.R[8], means[3 * g + 2], V.t[2])));
-    keys[i] = (key > bp.znear && reach_q(opac[g], bp) > 0.0f) ? __float_as_uint(key) : 0xFFFFFFFFu;
-    vals[i] = i;
-}
-
-void launch_depth_keys(const ViewInfo* views, int n_views, uint32_t n_items, const float* means,
-                       const float* opac, BlendParams bp, uint32_t* keys, uint32_t* vals,
-                       hipStream_t s) {
-    if (n_items == 0 || n_views <= 0) return;
-    hipLaunchKernelGGL(k_depth_keys, dim3((n_items + 255) / 256), dim3(256), 0, s, views, n_views,
-                       n_items, means, opac, bp, keys, vals);
-}
-
 // a2: projection of the items in depth order: thread k handles item
 // order[k] (k itself when order is null) and writes its record and tile-pair
 // count at position k, so that binning reads them contiguously; the random
@@ -129,8 +100,9 @@ __global__ __launch_bounds__(256) void k_project(const ViewInfo* __restrict__ vi
     const bool vlds = stage_view_bases(views, n_views, sbase);
     const uint32_t k = blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= n_items) return;
+    // (the order is view by view: place k belongs to the view of item k)
     const uint32_t i = order ? order[k] : k;
-    const ViewInfo& V = views[view_of(views, n_views, sbase, vlds, i)];
+    const ViewInfo& V = views[view_of(views, n_views, sbase, vlds, k)];
     const int64_t g = V.g_offset + (int64_t)(i - V.item_base);
     // one 64-byte record per Gaussian: a single cache line per random gather
     const float4* gr = reinterpret_cast<const float4*>(geo + kGeoStride * g);
@@ -222,7 +194,6 @@ constexpr uint32_t kEmitStage = 2048;  // pairs a block stages in LDS (16 KB: ei
 // coalesced writes.
 template <int BIN>
 __global__ __launch_bounds__(256) void k_emit(const ViewInfo* __restrict__ views, int n_views,
-                                              const uint32_t* __restrict__ items,
                                               const uint32_t* __restrict__ offsets,
                                               const uint32_t* __restrict__ counts,
                                               const uint32_t* __restrict__ rects,
@@ -243,7 +214,7 @@ __global__ __launch_bounds__(256) void k_emit(const ViewInfo* __restrict__ views
     const uint32_t k = k0 + threadIdx.x;
     const uint32_t cnt = k < n_items ? counts[k] : 0u;
     if (cnt != 0) {
-        const ViewInfo& V = views[view_of(views, n_views, sbase, vlds, items[k])];
+        const ViewInfo& V = views[view_of(views, n_views, sbase, vlds, k)];
         const uint32_t gbase = V.group_base, gx = (uint32_t)V.groups_x;
         const uint32_t rect = rects[k];
         uint32_t off = offsets[k];
@@ -296,17 +267,17 @@ __global__ __launch_bounds__(256) void k_emit(const ViewInfo* __restrict__ views
     }
 }
 
-void launch_emit(const ViewInfo* views, int n_views, const uint32_t* items, const uint32_t* offsets,
-                 const uint32_t* counts, const uint32_t* rects, const float4* rec, BlendParams bp,
+void launch_emit(const ViewInfo* views, int n_views, const uint32_t* offsets, const uint32_t* counts,
+                 const uint32_t* rects, const float4* rec, BlendParams bp,
                  uint32_t n_items, uint32_t n_groups, uint32_t* pair_keys, uint32_t* pair_vals, int bin,
                  hipStream_t s, uint32_t cap, uint32_t* overflow) {
     if (n_items == 0) return;
     if (bin == 32)
-        hipLaunchKernelGGL(k_emit<32>, dim3((n_items + 255) / 256), dim3(256), 0, s, views, n_views, items,
+        hipLaunchKernelGGL(k_emit<32>, dim3((n_items + 255) / 256), dim3(256), 0, s, views, n_views,
                            offsets, counts, rects, rec, bp, n_items, n_groups, cap, overflow, pair_keys,
                            pair_vals);
     else
-        hipLaunchKernelGGL(k_emit<16>, dim3((n_items + 255) / 256), dim3(256), 0, s, views, n_views, items,
+        hipLaunchKernelGGL(k_emit<16>, dim3((n_items + 255) / 256), dim3(256), 0, s, views, n_views,
                            offsets, counts, rects, rec, bp, n_items, n_groups, cap, overflow, pair_keys,
                            pair_vals);
 }

@@ -168,12 +168,107 @@ void launch_fill_u32(uint32_t* p, uint32_t v, uint64_t n, hipStream_t s) {
 }
 
 // ---- radix sort ----------------------------------------------------------
+//
+// Sorts run over segments: the whole array, or each view's items of a batch
+// (the depth sort).  A segment is cut into tiles of 512 * ITEMS keys, one block
+// each; tile counters are laid out segment by segment, digit-major within one,
+// so that a scan over all of them gives output positions.
 
-// Digit histogram of one 8192-key tile, written digit-major: hist[d * nblocks + b]
-// for the digits d <= mask of the pass ((key >> shift) & mask).
-// n_dev (optional): the live key count, read on the device and clamped to n;
-// the grid is sized for n.
-__global__ __launch_bounds__(kRsThreads) void k_rs_hist(const uint32_t* __restrict__ keys, uint32_t n,
+// Where a sort's keys come from and how its segments lie.
+struct SortSource {
+    const uint32_t* keys;    // null: depth keys of the views' items (first pass)
+    const uint32_t* vals;
+    const ViewInfo* views;   // null: one segment
+    int n_views;
+    uint32_t view_tiles;     // tiles of every view when they are alike, else 0 (views[].sort_base)
+    const float* means;
+    const float* opac;
+    float znear, alpha_min;
+};
+namespace {
+// The tile a block works on.
+struct SortTile {
+    uint64_t begin, end;  // keys of the tile
+    uint64_t seg;         // first key of the segment
+    uint32_t j, nb;       // tile within the segment, tiles of the segment
+    uint32_t first;       // tiles before the segment
+    int view;
+};
+template <int ITEMS>
+__device__ inline SortTile sort_tile(const SortSource& S, uint32_t t, uint32_t n, uint32_t nblocks) {
+    constexpr uint32_t kTileKeys = kRsThreads * ITEMS;
+    SortTile T;
+    if (S.views == nullptr) {
+        T.view = 0;
+        T.seg = 0;
+        T.j = t;
+        T.nb = nblocks;
+        T.first = 0;
+        T.begin = (uint64_t)t * kTileKeys;
+        T.end = min(T.begin + kTileKeys, (uint64_t)n);
+        return T;
+    }
+    int v;
+    if (S.view_tiles != 0u) {
+        v = (int)(t / S.view_tiles);
+        T.first = (uint32_t)v * S.view_tiles;
+    } else {
+        int lo = 0, hi = S.n_views - 1;
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (S.views[mid].sort_base <= t) lo = mid;
+            else hi = mid - 1;
+        }
+        v = lo;
+        T.first = S.views[v].sort_base;
+    }
+    const ViewInfo& V = S.views[v];
+    T.view = v;
+    T.seg = V.item_base;
+    T.j = t - T.first;
+    T.nb = (V.n_gauss + kTileKeys - 1) / kTileKeys;
+    T.begin = T.seg + (uint64_t)T.j * kTileKeys;
+    T.end = min(T.begin + kTileKeys, T.seg + V.n_gauss);
+    return T;
+}
+// Depth key of Gaussian g (index within the batch's arrays) in view V: the bits
+// of the camera-space depth of the mean computed in binary32 (positive floats
+// order like their bit patterns), 0xFFFFFFFF for items culled by the near plane
+// or too faint to pass the alpha floor anywhere.
+__device__ __forceinline__ uint32_t depth_key(const SortSource& S, const ViewInfo& V, uint64_t g) {
+    const float key = __fmaf_rn(V.R[6], S.means[3 * g],
+                                __fmaf_rn(V.R[7], S.means[3 * g + 1], __fmaf_rn(V.R[8], S.means[3 * g + 2], V.t[2])));
+    return (key > S.znear && S.opac[g] >= S.alpha_min) ? __float_as_uint(key) : 0xFFFFFFFFu;
+}
+// Keys and values of a thread's places begin + it * step (the last key's past the end).
+template <int ITEMS>
+__device__ __forceinline__ void sort_load(const SortSource& S, const SortTile& T, uint64_t base, uint32_t step,
+                                          uint32_t (&kk)[ITEMS], uint32_t* vv) {
+    if (S.keys != nullptr) {
+#pragma unroll
+        for (int it = 0; it < ITEMS; ++it) {
+            const uint64_t i = min(base + (uint64_t)it * step, T.end - 1);
+            kk[it] = S.keys[i];
+            if (vv) vv[it] = S.vals[i];
+        }
+    } else {
+        const ViewInfo& V = S.views[T.view];
+#pragma unroll
+        for (int it = 0; it < ITEMS; ++it) {
+            const uint64_t i = min(base + (uint64_t)it * step, T.end - 1);
+            kk[it] = depth_key(S, V, (uint64_t)V.g_offset + (i - T.seg));
+            if (vv) vv[it] = (uint32_t)i;
+        }
+    }
+}
+}  // namespace
+
+// Digit histogram of one tile, digit-major within its segment: counter
+// first * digits + d * nb + j for the digits d <= mask of the pass
+// ((key >> shift) & mask).  n_dev (optional, one segment): the live key count,
+// read on the device and clamped to n; the grid is sized for n.
+template <int ITEMS>
+__global__ __launch_bounds__(kRsThreads) void k_rs_hist(SortSource S, uint32_t n,
                                                         const uint32_t* __restrict__ n_dev,
                                                         int shift, uint32_t mask, uint32_t* __restrict__ hist,
                                                         uint32_t nblocks) {
@@ -185,22 +280,19 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_hist(const uint32_t* __restri
     constexpr int kSets = 4, kRow = 264;
     __shared__ uint32_t h[kRsWaves * kSets][kRow];
     const int w = (int)(threadIdx.x >> 6) * kSets + (int)(threadIdx.x & (kSets - 1));
-    const uint64_t base = (uint64_t)blockIdx.x * kRsTile;
-    // All sixteen loads of a thread are issued before the counters are
-    // cleared (sixteen coalesced loads in flight per wave, not one); an index
-    // past the end reads the last key and is not counted.
-    uint32_t kk[kRsItems];
-    if (base < n) {
-#pragma unroll
-        for (int it = 0; it < kRsItems; ++it)
-            kk[it] = keys[min(base + (uint64_t)it * kRsThreads + threadIdx.x, (uint64_t)n - 1)];
-    }
+    const SortTile T = sort_tile<ITEMS>(S, blockIdx.x, n, nblocks);
+    // All loads of a thread are issued before the counters are cleared (ITEMS
+    // coalesced loads in flight per wave, not one); an index past the end
+    // reads the last key and is not counted.
+    uint32_t kk[ITEMS];
+    const bool live = T.begin < T.end;
+    if (live) sort_load<ITEMS>(S, T, T.begin + threadIdx.x, kRsThreads, kk, nullptr);
     for (int k = threadIdx.x; k < kRsWaves * kSets * kRow; k += kRsThreads) (&h[0][0])[k] = 0;
     __syncthreads();
-    if (base < n) {
+    if (live) {
 #pragma unroll
-        for (int it = 0; it < kRsItems; ++it)
-            if (base + (uint64_t)it * kRsThreads + threadIdx.x < n)
+        for (int it = 0; it < ITEMS; ++it)
+            if (T.begin + (uint64_t)it * kRsThreads + threadIdx.x < T.end)
                 atomicAdd(&h[w][(kk[it] >> shift) & mask], 1u);
     }
     __syncthreads();
@@ -209,78 +301,89 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_hist(const uint32_t* __restri
     uint32_t sum = 0;
 #pragma unroll
     for (int k = 0; k < kRsWaves * kSets; ++k) sum += h[k][d];
-    hist[(uint64_t)d * nblocks + blockIdx.x] = sum;
+    hist[(uint64_t)T.first * (mask + 1u) + (uint64_t)d * T.nb + T.j] = sum;
 }
 
-// Stable scatter of one 8192-key tile (512 threads, 74 KB of LDS: two blocks
-// and sixteen waves per CU).  Each wave ranks its 1024 keys (16 rounds of 64)
-// against per-wave digit counters in LDS, with no block barrier; the eight
-// waves' counts then give every key its position in the tile sorted by digit
-// (threads 0..255 own one digit each).  The tile is reordered through LDS and written out in
-// digit order, so each digit's run of keys is stored contiguously at the
-// tile's offset for that digit.
+// Stable scatter of one tile (512 threads; 16 keys per thread, 74 KB of LDS:
+// two blocks and sixteen waves per CU).  Each wave ranks its keys (ITEMS
+// rounds of 64) against per-wave digit counters in LDS, with no block barrier;
+// the eight waves' counts then give every key its position in the tile sorted
+// by digit (threads 0..255 own one digit each).  The tile is reordered through
+// LDS and written out in digit order, so each digit's run of keys is stored
+// contiguously at the tile's offset for that digit.
 //
-// ONE_SWEEP = false: the offsets come from the scanned digit-major histogram
-// `offs` of a separate histogram pass.  ONE_SWEEP = true: a single kernel per
-// pass (decoupled look-back).  Each block takes the next tile number from a
-// ticket counter, so every lower tile belongs to a block that is already
-// running.  Once ranked, it publishes its per-digit counts in `status`, then
-// adds up its predecessors' (a tile that has published its inclusive prefix
-// ends the walk) and publishes its own inclusive prefix; the digit's start
-// comes from the global digit counts `gcount`.  A status word holds the
-// value in bits 0..29, kStAgg once the tile's own count is there and kStInc
-// once its inclusive prefix is.  Every wait is bounded: after kLookbackSpins
-// polls a block gives up, sets *fault (a word of the sort's scratch, not
-// reported further) and goes on, so no kernel can hang; its output is then
-// wrong, but only a predecessor that never publishes could cause that, and
-// the ticket order guarantees every predecessor is running.
+// MODE kScanned: the offsets are the scanned tile counters `offs`.  MODE kRaw:
+// `offs` holds the counters themselves; the block adds up its segment's (at
+// most kRawTiles tiles, a few KB from L2) instead of two launches that scan
+// them.  MODE kOneSweep: a single kernel per pass (decoupled look-back).  Each
+// block takes the next tile number from a ticket counter, so every lower tile
+// belongs to a block that is already running.  Once ranked, it publishes its
+// per-digit counts in `status`, then adds up its predecessors' (a tile that
+// has published its inclusive prefix ends the walk) and publishes its own
+// inclusive prefix; the digit's start comes from the global digit counts
+// `gcount`.  A status word holds the value in bits 0..29, kStAgg once the
+// tile's own count is there and kStInc once its inclusive prefix is.  Every
+// wait is bounded: after kLookbackSpins polls a block gives up, sets *fault (a
+// word of the sort's scratch, not reported further) and goes on, so no kernel
+// can hang; its output is then wrong, but only a predecessor that never
+// publishes could cause that, and the ticket order guarantees every
+// predecessor is running.
 constexpr uint32_t kStAgg = 1u << 30, kStInc = 1u << 31, kStVal = kStAgg - 1u;
 constexpr uint32_t kLookbackSpins = 1u << 22;
+constexpr int kScanned = 0, kRaw = 1, kOneSweep = 2;
+constexpr uint32_t kRawTiles = 64;
 
-template <bool ONE_SWEEP>
-__global__ __launch_bounds__(kRsThreads) void k_rs_scatter(const uint32_t* __restrict__ keys_in,
-                                                           const uint32_t* __restrict__ vals_in,
-                                                           uint32_t* __restrict__ keys_out,
+template <int MODE, int ITEMS>
+__global__ __launch_bounds__(kRsThreads) void k_rs_scatter(SortSource S, uint32_t* __restrict__ keys_out,
                                                            uint32_t* __restrict__ vals_out,
                                                            uint32_t n, const uint32_t* __restrict__ n_dev, int shift, uint32_t mask,
                                                            const uint32_t* __restrict__ offs,
                                                            uint32_t nblocks, uint32_t* status,
                                                            const uint32_t* __restrict__ gcount,
                                                            uint32_t* ticket, uint32_t* fault) {
+    constexpr uint32_t kTileKeys = kRsThreads * ITEMS;
     if (n_dev) n = min(n, *n_dev);
     __shared__ uint32_t wcnt[kRsWaves][256];
     __shared__ uint32_t dstart[256];
     __shared__ uint32_t gbase[256];
     __shared__ uint32_t wsum[kRsThreads / 64];
-    __shared__ uint32_t skey[kRsTile];
-    __shared__ uint32_t sval[kRsTile];
+    __shared__ uint32_t skey[kTileKeys];
+    __shared__ uint32_t sval[kTileKeys];
     __shared__ uint32_t stile;
     uint32_t tile = blockIdx.x;
-    if constexpr (ONE_SWEEP) {
+    if constexpr (MODE == kOneSweep) {
         if (threadIdx.x == 0) stile = atomicAdd(ticket, 1u);
         __syncthreads();
         tile = stile;
     }
-    if ((uint64_t)tile * kRsTile >= n) return;  // whole block: no live keys (no live tile follows)
+    const SortTile T = sort_tile<ITEMS>(S, tile, n, nblocks);
+    if (T.begin >= T.end) return;  // whole block: no live keys (no live tile of the segment follows)
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
     for (int k = lane; k < 256; k += 64) wcnt[w][k] = 0u;
-    if (!ONE_SWEEP && threadIdx.x <= mask) gbase[threadIdx.x] = offs[(uint64_t)threadIdx.x * nblocks + tile];
-    const uint64_t tile0 = (uint64_t)tile * kRsTile;
-    const uint64_t base = tile0 + (uint64_t)w * (kRsTile / kRsWaves);
-    uint32_t kk[kRsItems], vv[kRsItems], rk[kRsItems];
-    // The wave's 32 loads are all issued before the ranking, whose wave
+    const uint64_t row = (uint64_t)T.first * (mask + 1u) + (uint64_t)threadIdx.x * T.nb;
+    uint32_t before = 0u, dtot = 0u;  // kRaw: the digit's keys in earlier tiles, and in all
+    if constexpr (MODE == kScanned) {
+        if (threadIdx.x <= mask) gbase[threadIdx.x] = offs[row + T.j];
+    } else if constexpr (MODE == kRaw) {
+        if (threadIdx.x <= mask) {
+#pragma unroll 8
+            for (uint32_t b = 0; b < T.nb; ++b) {
+                const uint32_t c = offs[row + b];
+                before += b < T.j ? c : 0u;
+                dtot += c;
+            }
+        }
+    }
+    const uint64_t base = T.begin + (uint64_t)w * (kTileKeys / kRsWaves);
+    uint32_t kk[ITEMS], vv[ITEMS], rk[ITEMS];
+    // The wave's loads are all issued before the ranking, whose wave
     // barriers would otherwise hold each round's loads until the round
     // before has been ranked; an index past the end reads the last pair.
+    sort_load<ITEMS>(S, T, base + lane, 64, kk, vv);
 #pragma unroll
-    for (int it = 0; it < kRsItems; ++it) {
-        const uint64_t idx = min(base + (uint64_t)it * 64 + lane, (uint64_t)n - 1);
-        kk[it] = keys_in[idx];
-        vv[it] = vals_in[idx];
-    }
-#pragma unroll
-    for (int it = 0; it < kRsItems; ++it) {
+    for (int it = 0; it < ITEMS; ++it) {
         const uint64_t idx = base + (uint64_t)it * 64 + lane;
-        const bool valid = idx < n;
+        const bool valid = idx < T.end;
         const uint32_t key = kk[it];
         const uint32_t d = (key >> shift) & mask;
         uint64_t m = __ballot(valid);
@@ -313,7 +416,11 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(const uint32_t* __res
         uint32_t tot;
         const uint32_t ds = block_exclusive_scan<kRsThreads>(run, wsum, &tot);
         if (t < 256) dstart[t] = ds;
-        if constexpr (ONE_SWEEP) {
+        if constexpr (MODE == kRaw) {
+            const uint32_t gs = block_exclusive_scan<kRsThreads>(dtot, wsum, &tot);
+            if (t <= mask) gbase[t] = (uint32_t)T.seg + gs + before;
+        }
+        if constexpr (MODE == kOneSweep) {
             // the digit's first output position, over all tiles
             const uint32_t gc = t <= mask ? gcount[t] : 0u;
             const uint32_t gstart = block_exclusive_scan<kRsThreads>(gc, wsum, &tot);
@@ -352,7 +459,7 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(const uint32_t* __res
     }
     __syncthreads();
 #pragma unroll
-    for (int it = 0; it < kRsItems; ++it) {
+    for (int it = 0; it < ITEMS; ++it) {
         if (rk[it] != 0xFFFFFFFFu) {
             const uint32_t d = (kk[it] >> shift) & mask;
             const uint32_t lp = dstart[d] + wcnt[w][d] + rk[it];
@@ -361,7 +468,7 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(const uint32_t* __res
         }
     }
     __syncthreads();
-    const uint32_t cnt = (uint32_t)min((uint64_t)kRsTile, (uint64_t)n - tile0);
+    const uint32_t cnt = (uint32_t)(T.end - T.begin);
     for (uint32_t i = threadIdx.x; i < cnt; i += kRsThreads) {
         const uint32_t key = skey[i];
         const uint32_t d = (key >> shift) & mask;
@@ -410,31 +517,55 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_counts(const uint32_t* __rest
     }
 }
 
-size_t radix_scratch_words(uint32_t n) {
-    uint64_t nb = (n + kRsTile - 1) / kRsTile;
-    uint64_t h = 256 * (nb > 0 ? nb : 1);
-    const size_t classic = (size_t)(((h + 63) / 64) * 64 + scan_scratch_words(h));
-    const size_t one_sweep = kOneSweepHead + 4 * (size_t)h;  // up to four passes of status rows
-    return std::max(classic, one_sweep);
+namespace {
+// Tiles of 2048 keys (a short chain of ranking rounds, four times the blocks)
+// for up to 2^19 keys, as long as a segment's tiles stay within the counters a
+// block adds up itself; else of 8192 (runs of about 32 keys per digit in the
+// scattered output).
+inline int sort_items(uint64_t segment, uint64_t total) {
+    return segment <= (uint64_t)kRawTiles * kRsThreads * 4 && total <= (1u << 19) ? 4 : kRsItems;
 }
 
-__global__ void k_copy_pairs(const uint32_t* __restrict__ ka, const uint32_t* __restrict__ va,
-                             uint32_t* __restrict__ kb, uint32_t* __restrict__ vb, uint32_t n,
-                             const uint32_t* __restrict__ n_dev) {
-    if (n_dev) n = min(n, *n_dev);
-    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-        kb[i] = ka[i];
-        vb[i] = va[i];
+// One histogram and scatter pass; `tiles` over all segments, `seg_tiles` of the longest.
+void radix_pass(const SortSource& src, uint32_t* dk, uint32_t* dv, uint32_t n, const uint32_t* n_dev, int shift,
+                uint32_t mask, uint32_t tiles, uint32_t seg_tiles, int items, uint32_t* scratch, hipStream_t s) {
+    uint32_t* hist = scratch;
+    uint32_t* sscr = scratch + (((uint64_t)(mask + 1u) * tiles + 63) / 64) * 64;
+    const dim3 grid(tiles), block(kRsThreads);
+    uint32_t* nu = nullptr;
+    const uint32_t* nc = nullptr;
+    if (items == 4) hipLaunchKernelGGL(k_rs_hist<4>, grid, block, 0, s, src, n, n_dev, shift, mask, hist, tiles);
+    else hipLaunchKernelGGL(k_rs_hist<kRsItems>, grid, block, 0, s, src, n, n_dev, shift, mask, hist, tiles);
+    if (seg_tiles <= kRawTiles) {
+        if (items == 4)
+            hipLaunchKernelGGL((k_rs_scatter<kRaw, 4>), grid, block, 0, s, src, dk, dv, n, n_dev, shift, mask,
+                               hist, tiles, nu, nc, nu, nu);
+        else
+            hipLaunchKernelGGL((k_rs_scatter<kRaw, kRsItems>), grid, block, 0, s, src, dk, dv, n, n_dev, shift,
+                               mask, hist, tiles, nu, nc, nu, nu);
+        return;
     }
+    launch_scan(hist, hist, (mask + 1u) * tiles, nullptr, sscr, s);
+    hipLaunchKernelGGL((k_rs_scatter<kScanned, kRsItems>), grid, block, 0, s, src, dk, dv, n, n_dev, shift, mask,
+                       hist, tiles, nu, nc, nu, nu);
+}
+inline size_t pass_scratch_words(uint64_t tiles) {
+    const uint64_t h = 256 * (tiles > 0 ? tiles : 1);
+    return (size_t)(((h + 63) / 64) * 64 + scan_scratch_words(h));
+}
+}  // namespace
+
+size_t radix_scratch_words(uint32_t n) {
+    const uint64_t nb = ((uint64_t)n + kRsTile - 1) / kRsTile;
+    const uint64_t small = std::min<uint64_t>(((uint64_t)n + kRsThreads * 4 - 1) / (kRsThreads * 4), kRawTiles);
+    const size_t one_sweep = kOneSweepHead + 4 * (size_t)(256 * (nb > 0 ? nb : 1));  // up to four passes of status rows
+    return std::max({pass_scratch_words(nb), pass_scratch_words(small), one_sweep});
 }
 
 void radix_sort(uint32_t* keys, uint32_t* vals, uint32_t* keys_alt, uint32_t* vals_alt, uint32_t n,
                 int bits, uint32_t* scratch, hipStream_t s, const uint32_t* n_dev, bool* result_in_alt) {
-    if (result_in_alt) *result_in_alt = false;
+    *result_in_alt = false;
     if (n <= 1 || bits <= 0) return;
-    uint32_t nb = (n + kRsTile - 1) / kRsTile;
-    uint32_t* hist = scratch;
-    uint32_t* sscr = scratch + ((256ull * nb + 63) / 64) * 64;
     // as many passes as 8-bit digits need, with the bits spread evenly over
     // them (19 bits: 7 + 6 + 6): narrower digits leave longer runs of equal
     // digits in each tile, so the scattered writes come in fuller lines
@@ -449,9 +580,11 @@ void radix_sort(uint32_t* keys, uint32_t* vals, uint32_t* keys_alt, uint32_t* va
     // One sweep per pass for large sorts (where the status words can hold
     // every count); the scratch then holds [global digit counts | tickets,
     // fault | status rows].  Below 2^25 keys the look-back's waits cost more
-    // than the histogram pass and scan they save (a 2^24-key depth sort: 0.45
-    // against 0.37 ms; a 10^8-key pair sort of two passes: 1.09 against 1.26).
+    // than the histogram pass and scan they save (a 2^24-key sort of four
+    // passes: 0.45 against 0.37 ms; 10^8 keys in two: 1.09 against 1.26).
     const bool one_sweep = n >= (1u << 25) && n < kStAgg;
+    const int items = one_sweep ? kRsItems : sort_items(n, n);
+    const uint32_t nb = (uint32_t)(((uint64_t)n + kRsThreads * items - 1) / (kRsThreads * items));
     uint32_t* gcount = scratch;
     uint32_t* tickets = scratch + 1024;
     uint32_t* fault = scratch + 1024 + 4;
@@ -463,29 +596,202 @@ void radix_sort(uint32_t* keys, uint32_t* vals, uint32_t* keys_alt, uint32_t* va
     }
     uint32_t *sk = keys, *sv = vals, *dk = keys_alt, *dv = vals_alt;
     for (int p = 0; p < passes; ++p) {
-        const int shift = dg.shift[p];
-        const uint32_t mask = dg.mask[p];
-        if (one_sweep) {
-            hipLaunchKernelGGL(k_rs_scatter<true>, dim3(nb), dim3(kRsThreads), 0, s, sk, sv, dk, dv, n, n_dev,
-                               shift, mask, (const uint32_t*)nullptr, nb, status + (uint64_t)p * 256u * nb,
-                               gcount + 256 * p, tickets + p, fault);
-        } else {
-            hipLaunchKernelGGL(k_rs_hist, dim3(nb), dim3(kRsThreads), 0, s, sk, n, n_dev, shift, mask, hist, nb);
-            launch_scan(hist, hist, (mask + 1u) * nb, nullptr, sscr, s);
-            hipLaunchKernelGGL(k_rs_scatter<false>, dim3(nb), dim3(kRsThreads), 0, s, sk, sv, dk, dv, n, n_dev,
-                               shift, mask, hist, nb, (uint32_t*)nullptr, (const uint32_t*)nullptr,
-                               (uint32_t*)nullptr, (uint32_t*)nullptr);
-        }
-        uint32_t* t;
-        t = sk; sk = dk; dk = t;
-        t = sv; sv = dv; dv = t;
+        SortSource src{};
+        src.keys = sk;
+        src.vals = sv;
+        if (one_sweep)
+            hipLaunchKernelGGL((k_rs_scatter<kOneSweep, kRsItems>), dim3(nb), dim3(kRsThreads), 0, s, src, dk, dv,
+                               n, n_dev, dg.shift[p], dg.mask[p], (const uint32_t*)nullptr, nb,
+                               status + (uint64_t)p * 256u * nb, gcount + 256 * p, tickets + p, fault);
+        else
+            radix_pass(src, dk, dv, n, n_dev, dg.shift[p], dg.mask[p], nb, nb, items, scratch, s);
+        std::swap(sk, dk);
+        std::swap(sv, dv);
     }
-    if (sk != keys && result_in_alt) {
-        *result_in_alt = true;  // the caller takes the result from the alternate buffers
-    } else if (sk != keys) {
-        // odd pass count: copy back with a kernel (plain kernel nodes under graph capture)
-        const uint32_t blocks = std::min<uint32_t>((n + 255) / 256, 8192u);
-        hipLaunchKernelGGL(k_copy_pairs, dim3(blocks), dim3(256), 0, s, sk, sv, keys, vals, n, n_dev);
+    *result_in_alt = sk != keys;  // an odd pass count leaves the result there
+}
+
+// ---- depth sort ------------------------------------------------------------
+//
+// Each view's items by depth, ties by Gaussian index; the order is view by
+// view, so that a view's records lie together (3.2 MB for 100k Gaussians, less
+// than an XCD's L2) for the random reads of the masks and the tile kernels.
+// Views of up to kViewSort items are sorted by one block each, in LDS and one
+// launch; larger ones in four passes over segments, the first of which forms
+// the keys itself.  us a call, one sort of the whole batch -> by view: 2k
+// Gaussians x 8 views 220 -> 149 (13 launches of the call become one); 500k x
+// 100 views 23371 -> 22795 (k_group_masks 1784 -> 1453 us, k_project 1508 ->
+// 1165: their reads hit L2), 100k x 50 views 1813 -> 1816.
+constexpr uint32_t kViewThreads = 1024, kViewWaves = kViewThreads / 64;
+constexpr uint32_t kViewSort = 24576;
+
+// IPT: items per thread at most.  The item's index within the view is 16 bits.
+// Only the bits in which the view's depths differ are sorted.
+template <int IPT>
+__global__ __launch_bounds__(kViewThreads) void k_sort_view(SortSource S, uint32_t* __restrict__ vals) {
+    constexpr uint32_t kCap = IPT * kViewThreads;
+    __shared__ uint32_t skey[kCap];
+    __shared__ uint16_t sidx[kCap];
+    __shared__ uint16_t cnt[kViewWaves][256];
+    __shared__ uint32_t wsum[kViewWaves];
+    __shared__ uint32_t range[2];
+    const ViewInfo& V = S.views[blockIdx.x];
+    const uint32_t n = V.n_gauss;
+    if (n == 0u) return;
+    const uint32_t tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const uint32_t rounds = (n + kViewThreads - 1) / kViewThreads;  // uniform, <= IPT
+    const uint32_t base = w * rounds * 64;                          // the wave's places
+    if (tid == 0) {
+        range[0] = 0xFFFFFFFFu;
+        range[1] = 0u;
+    }
+    uint32_t kk[IPT], id[IPT], rk[IPT];
+    uint32_t lo = 0xFFFFFFFFu, hi = 0u;
+#pragma unroll
+    for (uint32_t it = 0; it < (uint32_t)IPT; ++it) {
+        if (it >= rounds) break;
+        const uint32_t i = base + it * 64 + lane;
+        id[it] = i;
+        kk[it] = i < n ? depth_key(S, V, (uint64_t)V.g_offset + i) : 0xFFFFFFFFu;
+        if (kk[it] != 0xFFFFFFFFu) {
+            lo = min(lo, kk[it]);
+            hi = max(hi, kk[it]);
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        lo = min(lo, (uint32_t)__shfl_xor((int)lo, d, 64));
+        hi = max(hi, (uint32_t)__shfl_xor((int)hi, d, 64));
+    }
+    if (lane == 0 && lo <= hi) {
+        atomicMin(&range[0], lo);
+        atomicMax(&range[1], hi);
+    }
+    __syncthreads();
+    lo = range[0];
+    hi = range[1];
+    // keys relative to the nearest; culled items one past the farthest
+    const uint32_t top = lo <= hi ? hi - lo + 1u : 0u;
+    const int bits = top ? 32 - __clz((int)top) : 0;
+#pragma unroll
+    for (uint32_t it = 0; it < (uint32_t)IPT; ++it) {
+        if (it >= rounds) break;
+        kk[it] = kk[it] == 0xFFFFFFFFu ? top : kk[it] - lo;
+    }
+    const int passes = (bits + 7) / 8;
+    for (int p = 0, shift = 0; p < passes; ++p) {
+        const int width = bits / passes + (p < bits % passes ? 1 : 0);
+        const uint32_t mask = (1u << width) - 1u;
+        for (uint32_t k = lane; k < 256; k += 64) cnt[w][k] = 0u;
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (uint32_t it = 0; it < (uint32_t)IPT; ++it) {
+            if (it >= rounds) break;
+            const bool valid = base + it * 64 + lane < n;
+            const uint32_t d = (kk[it] >> shift) & mask;
+            uint64_t m = __ballot(valid);
+#pragma unroll
+            for (int b = 0; b < 8; ++b) {
+                const uint64_t bb = __ballot((d >> b) & 1u);
+                m &= ((d >> b) & 1u) ? bb : ~bb;
+            }
+            const uint32_t pre = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                                           __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+            const uint32_t c = cnt[w][d];
+            __builtin_amdgcn_wave_barrier();
+            if (valid && pre == 0) cnt[w][d] = (uint16_t)(c + (uint32_t)__popcll(m));
+            __builtin_amdgcn_wave_barrier();
+            rk[it] = c + pre;
+        }
+        __syncthreads();
+        {
+            // thread t owns digit t: prefix over the waves, then over the digits
+            uint32_t run = 0;
+            uint32_t c[kViewWaves];
+            if (tid < 256) {
+#pragma unroll
+                for (uint32_t k = 0; k < kViewWaves; ++k) {
+                    c[k] = run;
+                    run += cnt[k][tid];
+                }
+            }
+            uint32_t tot;
+            const uint32_t ds = block_exclusive_scan<kViewThreads>(tid < 256 ? run : 0u, wsum, &tot);
+            if (tid < 256) {
+#pragma unroll
+                for (uint32_t k = 0; k < kViewWaves; ++k) cnt[k][tid] = (uint16_t)(c[k] + ds);
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (uint32_t it = 0; it < (uint32_t)IPT; ++it) {
+            if (it >= rounds) break;
+            if (base + it * 64 + lane < n) {
+                const uint32_t at = cnt[w][(kk[it] >> shift) & mask] + rk[it];
+                skey[at] = kk[it];
+                sidx[at] = (uint16_t)id[it];
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (uint32_t it = 0; it < (uint32_t)IPT; ++it) {
+            if (it >= rounds) break;
+            const uint32_t i = base + it * 64 + lane;
+            if (i < n) {
+                kk[it] = skey[i];
+                id[it] = sidx[i];
+            }
+        }
+        shift += width;
+    }
+#pragma unroll
+    for (uint32_t it = 0; it < (uint32_t)IPT; ++it) {
+        if (it >= rounds) break;
+        const uint32_t i = base + it * 64 + lane;
+        if (i < n) vals[V.item_base + i] = V.item_base + id[it];
+    }
+}
+
+DepthSortShape depth_sort_shape(uint32_t max_n, uint64_t n_items) {
+    DepthSortShape d;
+    d.in_lds = max_n <= kViewSort;
+    d.items = d.in_lds ? 0 : sort_items(max_n, n_items);
+    d.tile = d.in_lds ? 0u : (uint32_t)(kRsThreads * d.items);
+    return d;
+}
+
+size_t depth_sort_scratch_words(const DepthSortShape& d, uint64_t tiles) {
+    return d.in_lds ? 0 : pass_scratch_words(tiles);
+}
+
+void launch_depth_sort(const ViewInfo* views, int n_views, uint32_t n_items, const DepthSortShape& d,
+                       uint32_t max_n, uint32_t uniform_n, uint32_t tiles, const float* means, const float* opac,
+                       BlendParams bp, uint32_t* keys, uint32_t* vals, uint32_t* keys_alt, uint32_t* vals_alt,
+                       uint32_t* scratch, hipStream_t s) {
+    if (n_items == 0 || n_views <= 0) return;
+    SortSource src{};
+    src.views = views;
+    src.n_views = n_views;
+    src.means = means;
+    src.opac = opac;
+    src.znear = bp.znear;
+    src.alpha_min = bp.alpha_min;
+    if (d.in_lds) {
+        const dim3 grid((unsigned)n_views), block(kViewThreads);
+        if (max_n <= 4 * kViewThreads) hipLaunchKernelGGL(k_sort_view<4>, grid, block, 0, s, src, vals);
+        else hipLaunchKernelGGL(k_sort_view<(int)(kViewSort / kViewThreads)>, grid, block, 0, s, src, vals);
+        return;
+    }
+    const uint32_t seg_tiles = (max_n + d.tile - 1) / d.tile;
+    src.view_tiles = uniform_n ? seg_tiles : 0u;
+    uint32_t *dk = keys_alt, *dv = vals_alt, *ok = keys, *ov = vals;
+    for (int p = 0; p < 4; ++p) {
+        radix_pass(src, dk, dv, n_items, nullptr, 8 * p, 255u, tiles, seg_tiles, d.items, scratch, s);
+        src.keys = dk;
+        src.vals = dv;
+        std::swap(dk, ok);
+        std::swap(dv, ov);
     }
 }
 
