@@ -1197,7 +1197,7 @@ gsc_status colorize_core(gsc_ctx* ctx, const float* means, const float* scales,
     unsigned int* d_ill = reinterpret_cast<unsigned int*>(ctx->misc.as<char>() + 12);
     uint32_t* obs = nullptr;
     if (sh_deg > 0) {
-        GSC_HIP(ctx->obs.ensure(4 * (size_t)fold_obs_words(N)));
+        GSC_HIP(ctx->obs.ensure(4 * (size_t)fold_obs_words(N, n_cams)));
         obs = ctx->obs.as<uint32_t>();
     }
     StageTimer t_solve(ctx, s, GSC_STAGE_SOLVE);
@@ -1299,7 +1299,7 @@ gsc_status gsc_colorize_noalloc(gsc_ctx* ctx, const float* means, const float* s
     const uint64_t items = (uint64_t)N * (uint64_t)n_cams;
     const uint64_t vs_words = (uint64_t)(sh_deg > 0 ? std::max(n_cams, 1) : 1) * (uint64_t)N * (uint64_t)(C + 1);
     const uint64_t known = 2 * sizeof(ViewInfo) * (uint64_t)n_cams + 4ull * kGeoStride * (uint64_t)N +
-                           64ull * items + 4 * vs_words + (sh_deg > 0 ? 4ull * fold_obs_words(N) : 0);
+                           64ull * items + 4 * vs_words + (sh_deg > 0 ? 4ull * fold_obs_words(N, 0) : 0);
     if (known > kNoallocScratchBytes)
         return fail(GSC_ERR_CAPACITY,
                     "gsc_colorize_noalloc: %llu Gaussians x %d views x %d channels need at least %llu "
@@ -1555,13 +1555,15 @@ gsc_status gsc_colorize_backward(gsc_ctx* ctx, const float* means, const float* 
     if (per_view && (st = upload_all_views(ctx, all.data(), n_cams, s)) != GSC_OK) return st;
     const size_t nbc = (size_t)N * nb * C;
     GSC_HIP(ctx->bbar.ensure(4 * (nbc + (size_t)N) + 4 * (size_t)N));
+    if (per_view) GSC_HIP(ctx->obs.ensure(4 * (size_t)fold_obs_words(N, n_cams)));
     float* d_bbar = ctx->bbar.as<float>();
     float* d_rho = d_bbar + nbc;
     float* d_wsum = d_rho + N;
     {
         StageTimer t(ctx, s, GSC_STAGE_SOLVE);
         launch_adjoint_solve(ctx->views_all.as<ViewInfo>(), n_cams, means, ctx->vs.as<float>(), per_view,
-                             N, C, sh_deg, lam, grad_coeffs, coeffs, d_bbar, d_rho, d_wsum, s);
+                             N, C, sh_deg, lam, grad_coeffs, coeffs, d_bbar, d_rho, d_wsum,
+                             ctx->obs.as<uint32_t>(), s);
         GSC_LAUNCHED("adjoint solve");
     }
     // coefficients and Bbar transposed for the adjoint colours
@@ -1829,9 +1831,9 @@ gsc_status gsc_plan_create(gsc_ctx* ctx, const gsc_scene* scenes, int32_t n_scen
     GSC_HIP(P->vs.ensure(4 * P->vs_slots * (size_t)(C + 1)));
     GSC_HIP(P->queues.ensure(4 * (size_t)kMaxC));
     if (sh_deg > 0) {  // observed lists of the fold, one scene at a time
-        int64_t nmax = 1;
-        for (const gsc_scene& sc : P->scenes) nmax = std::max<int64_t>(nmax, sc.n_gaussians);
-        GSC_HIP(P->obs.ensure(4 * (size_t)fold_obs_words(nmax)));
+        int64_t words = 1;
+        for (const gsc_scene& sc : P->scenes) words = std::max(words, fold_obs_words(sc.n_gaussians, sc.n_cameras));
+        GSC_HIP(P->obs.ensure(4 * (size_t)words));
     }
     *out = guard.release();
     return GSC_OK;

@@ -310,17 +310,15 @@ void launch_render(const TileLists& tl, const float* gamma, int C, BlendParams b
 // factor (optional, sh_deg >= 1): per Gaussian the Cholesky factor of
 // A_g + w_g Lambda, packed by rows (row i at i (i + 1) / 2, 1/L_ii on the
 // diagonal), then w_g: refine_factor_words(sh_deg) doubles.
-// obs_scratch (optional, sh_deg >= 1): fold_obs_words(N) words; then the
-// unobserved Gaussians (no view saw them) are written directly and the fold
-// runs over an ordered list of the observed ones only.
+// obs_scratch (sh_deg >= 1): fold_obs_words(N, n_views) words, 8-byte aligned;
+// the unobserved Gaussians (no view saw them) are written directly and the fold
+// runs over a list of the observed ones only.
 void launch_fold_solve(const ViewInfo* views, int n_views, const float* means, const float* VS,
                        bool per_view, int64_t N, int C, int sh_deg, const double* lam_nb /*host, nb*/,
                        float kappa_max, float* coeffs, uint8_t* status, float* wout,
                        float* dc_scratch, unsigned int* ill_count, hipStream_t s,
                        double* factor = nullptr, uint32_t* obs_scratch = nullptr);
-inline int64_t fold_obs_words(int64_t N) {  // list, block counts, int64 total, flag bytes
-    return N + (N + 1023) / 1024 + 4 + (N + 3) / 4;
-}
+int64_t fold_obs_words(int64_t N, int n_views);
 inline int refine_factor_words(int sh_deg) {
     const int nb = (sh_deg + 1) * (sh_deg + 1);
     return nb * (nb + 1) / 2 + 1;
@@ -349,11 +347,11 @@ void launch_accumulate_weights(const TileLists& tl, bool per_view, BlendParams b
 // Adjoint solve: bbar = (A_g + w_g Lambda)^{-1} grad_coeffs and
 // rho_g = sum lambda_m bbar[m][c] coeffs[m][c].  V holds per-view
 // visibilities [n_views][N] (per_view) or their sums [N].  w_scratch: N floats
-// (sh_deg == 0 with per_view).
+// (sh_deg == 0 with per_view); obs_scratch as for launch_fold_solve.
 void launch_adjoint_solve(const ViewInfo* views, int n_views, const float* means, const float* V,
                           bool per_view, int64_t N, int C, int sh_deg, const double* lam_nb,
                           const float* grad_coeffs, const float* coeffs, float* bbar, float* rho,
-                          float* w_scratch, hipStream_t s);
+                          float* w_scratch, uint32_t* obs_scratch, hipStream_t s);
 
 // Adjoint colours of batch item i: beta [i][C+1] = (beta_gj, delta_gj).
 // render: beta = c^T phi, delta = 0.  Otherwise beta = bbar^T phi and
