@@ -152,7 +152,7 @@ struct gsc_ctx {
     // device scratch
     DevBuf views, views_all, cov, keys, vals, keys_alt, vals_alt, rec,
         sort_scratch, pkeys, pvals, pkeys_alt, pvals_alt, granges, gfirst, gcounts, lists, ranges, vs, gamma, bbar, misc, order, queues,
-        coef_t, factor, img, stat, wbuf, post, vsdet, chk, obs;
+        factor, img, stat, wbuf, post, vsdet, chk, obs;
     uint64_t pairs_counted = 0;  // bin pairs of the call's batches that were read back
     hipEvent_t ev_read = nullptr;  // after a count's copy to the host
     bool order_valid = false;  // `order` holds the tile order of the current binning
@@ -175,10 +175,10 @@ struct gsc_ctx {
     size_t ev_used = 0;
     struct Mark { int stage; hipEvent_t a, b; uint32_t launches; };
     std::vector<Mark> marks;
-    std::array<DevBuf*, 33> bufs() {
+    std::array<DevBuf*, 32> bufs() {
         return {&views, &views_all, &cov, &keys, &vals, &keys_alt, &vals_alt,
                 &granges, &gfirst, &gcounts, &lists, &rec, &sort_scratch, &pkeys, &pvals, &pkeys_alt,
-                &pvals_alt, &ranges, &vs, &gamma, &bbar, &misc, &order, &queues, &coef_t,
+                &pvals_alt, &ranges, &vs, &gamma, &bbar, &misc, &order, &queues,
                 &factor, &img, &stat, &wbuf, &post, &vsdet, &chk, &obs};
     }
     ~gsc_ctx() {
@@ -1402,11 +1402,9 @@ gsc_status gsc_colorize_refine(gsc_ctx* ctx, const float* means, const float* sc
     // pass bins every batch again (once for its render and accumulate).
     const bool single = ctx->cache_valid && ctx->cache_key.same(key);
     const int nb = (sh_deg + 1) * (sh_deg + 1);
-    const int kc = nb * C;
     const bool per_view = sh_deg > 0;
     int64_t rows = 0;
     for (int j = 0; j < n_cams; ++j) rows = std::max<int64_t>(rows, cams[j].pixel_offset + (int64_t)cams[j].width * cams[j].height);
-    GSC_HIP(ctx->coef_t.ensure(4 * (size_t)N * (size_t)kc));
     GSC_HIP(ctx->img.ensure(4 * (size_t)rows * (size_t)C));
     const uint64_t vs_words = (uint64_t)(per_view ? n_cams : 1) * (uint64_t)N * (uint64_t)(C + 1);
     BlendParams bp = blend_params(ctx->opt);
@@ -1415,7 +1413,6 @@ gsc_status gsc_colorize_refine(gsc_ctx* ctx, const float* means, const float* sc
     const int chunk = resolve_chunk(ctx->opt.accumulate_variant, C, GSC_F32);
     const gsc_stats first = ctx->stats;
     for (int step = 0; step < n_refine; ++step) {
-        launch_transpose(coeffs, N, kc, ctx->coef_t.as<float>(), s);
         launch_fill_u32(ctx->vs.as<uint32_t>(), 0u, vs_words, s);
         GSC_LAUNCHED("refinement setup");
         st = for_view_batches(ctx, all.data(), n_cams, means, opacities, N, bp, s,
@@ -1425,8 +1422,8 @@ gsc_status gsc_colorize_refine(gsc_ctx* ctx, const float* means, const float* sc
             for (int k = 0; k < nv; ++k) max_px = std::max(max_px, all[v0 + k].width * all[v0 + k].height);
             const TileLists tl = tile_lists(ctx, nv, bn);
             StageTimer t(ctx, s, GSC_STAGE_BLEND);
-            launch_view_colors(ctx->views.as<ViewInfo>(), nv, (uint32_t)bn.n_items, means,
-                               ctx->coef_t.as<float>(), N, C, sh_deg, ctx->gamma.as<float>(), s);
+            launch_view_colors(ctx->views.as<ViewInfo>(), nv, N, means, coeffs, C, sh_deg,
+                               ctx->gamma.as<float>(), s);
             launch_render(tl, ctx->gamma.as<float>(), C, bp, ctx->img.as<float>(), d_pass_counter, s);
             launch_residual(ctx->views.as<ViewInfo>(), nv, max_px, targets, tdtype, C, ctx->img.as<float>(), s);
             uint32_t* queues = nullptr;
@@ -1479,17 +1476,13 @@ gsc_status gsc_render(gsc_ctx* ctx, const float* means, const float* scales, con
     std::vector<ViewInfo> all(n_cams);
     for (int j = 0; j < n_cams; ++j) all[j] = make_view(cams[j], j, N, ctx->bin);
     unsigned long long* d_counter = reinterpret_cast<unsigned long long*>(ctx->misc.p);
-    const int kc = (sh_deg + 1) * (sh_deg + 1) * C;
-    GSC_HIP(ctx->coef_t.ensure(4 * (size_t)std::max<int64_t>(N, 1) * (size_t)kc));
-    launch_transpose(coeffs, N, kc, ctx->coef_t.as<float>(), s);
-    GSC_LAUNCHED("transpose");
     st = for_view_batches_k(ctx, all.data(), n_cams, means, opacities, N, bp, s, &key, reuse,
                           [&](int v0, int nv, const Binned& bn) -> gsc_status {
         (void)v0;
         StageTimer t(ctx, s, GSC_STAGE_BLEND, 1 + (uint32_t)((C + 3) / 4));
         GSC_HIP(ctx->gamma.ensure(4 * (size_t)nv * (size_t)std::max<int64_t>(N, 1) * (size_t)C));
-        launch_view_colors(ctx->views.as<ViewInfo>(), nv, (uint32_t)bn.n_items, means,
-                           ctx->coef_t.as<float>(), N, C, sh_deg, ctx->gamma.as<float>(), s);
+        launch_view_colors(ctx->views.as<ViewInfo>(), nv, N, means, coeffs, C, sh_deg,
+                           ctx->gamma.as<float>(), s);
         GSC_LAUNCHED("view colors");
         launch_render(tile_lists(ctx, nv, bn), ctx->gamma.as<float>(), C, bp, images, d_counter, s);
         GSC_LAUNCHED("render");
@@ -1566,20 +1559,13 @@ gsc_status gsc_colorize_backward(gsc_ctx* ctx, const float* means, const float* 
                              ctx->obs.as<uint32_t>(), s);
         GSC_LAUNCHED("adjoint solve");
     }
-    // coefficients and Bbar transposed for the adjoint colours
-    GSC_HIP(ctx->coef_t.ensure(4 * 2 * nbc));
-    float* d_coef_t = ctx->coef_t.as<float>();
-    float* d_bbar_t = d_coef_t + nbc;
-    launch_transpose(coeffs, N, nb * C, d_coef_t, s);
-    launch_transpose(d_bbar, N, nb * C, d_bbar_t, s);
-    GSC_LAUNCHED("transpose");
     // 3. per view batch: adjoint colours, then the two-pass blend adjoint
     auto body = [&](int v0, int nv, const Binned& bn) -> gsc_status {
         (void)v0;
         GSC_HIP(ctx->gamma.ensure(4 * (size_t)nv * (size_t)N * (size_t)(C + 1)));
         StageTimer t(ctx, s, GSC_STAGE_BLEND_ADJOINT);
-        launch_view_adjoint(ctx->views.as<ViewInfo>(), nv, (uint32_t)bn.n_items, means, d_coef_t,
-                            d_bbar_t, N, d_rho, C, sh_deg, false, ctx->gamma.as<float>(), s);
+        launch_view_adjoint(ctx->views.as<ViewInfo>(), nv, N, means, coeffs, d_bbar, d_rho, C, sh_deg,
+                            ctx->gamma.as<float>(), s);
         GSC_LAUNCHED("view adjoint");
         launch_blend_adjoint(tile_lists(ctx, nv, bn), targets, tdtype, C, ctx->gamma.as<float>(), bp,
                              grad_targets, grad_opacities, s);
@@ -1633,11 +1619,6 @@ gsc_status gsc_render_backward(gsc_ctx* ctx, const float* means, const float* sc
         launch_fill_u32(ctx->vs.as<uint32_t>(), 0u, vs_words, s);
     }
     unsigned long long* d_counter = reinterpret_cast<unsigned long long*>(ctx->misc.p);
-    if (grad_opacities) {
-        GSC_HIP(ctx->coef_t.ensure(4 * (size_t)N * (size_t)(nb * C)));
-        launch_transpose(coeffs, N, nb * C, ctx->coef_t.as<float>(), s);
-        GSC_LAUNCHED("transpose");
-    }
     st = for_view_batches_k(ctx, all.data(), n_cams, means, opacities, N, bp, s, &key, reuse,
                           [&](int v0, int nv, const Binned& bn) -> gsc_status {
         if (grad_coeffs) {
@@ -1652,8 +1633,7 @@ gsc_status gsc_render_backward(gsc_ctx* ctx, const float* means, const float* sc
         if (grad_opacities) {
             GSC_HIP(ctx->gamma.ensure(4 * (size_t)nv * (size_t)N * (size_t)(C + 1)));
             StageTimer t(ctx, s, GSC_STAGE_BLEND_ADJOINT);
-            launch_view_adjoint(ctx->views.as<ViewInfo>(), nv, (uint32_t)bn.n_items, means,
-                                ctx->coef_t.as<float>(), nullptr, N, nullptr, C, sh_deg, true,
+            launch_view_adjoint(ctx->views.as<ViewInfo>(), nv, N, means, coeffs, nullptr, nullptr, C, sh_deg,
                                 ctx->gamma.as<float>(), s);
             GSC_LAUNCHED("view colours");
             launch_blend_adjoint(tile_lists(ctx, nv, bn), grad_images, GSC_F32, C, ctx->gamma.as<float>(), bp,

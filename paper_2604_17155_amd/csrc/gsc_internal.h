@@ -289,16 +289,10 @@ void launch_accumulate(const TileLists& tl, const void* targets, int tdtype, int
                        int chunk, hipStream_t s, uint32_t* queues = nullptr,
                        const float2* det = nullptr);
 
-// out[k][r] = in[r][k] (rows x K row-major in, K x rows row-major out).
-void launch_transpose(const float* in, int64_t rows, int K, float* out, hipStream_t s);
-
-// Colour of batch item i (view v, Gaussian g):
-// gamma[i][c] = sum_m coeffs[g][m][c] phi_m(dir_gv), from the coefficients
-// transposed: coeffs_t[m * C + c][g], rows of ldn floats (consecutive items
-// read consecutive floats).
-void launch_view_colors(const ViewInfo* views, int n_views, uint32_t n_items, const float* means,
-                        const float* coeffs_t, int64_t ldn, int C, int sh_deg, float* gamma,
-                        hipStream_t s);
+// Colour of batch item i (view v, Gaussian g of the N): gamma[i][c] =
+// sum_m coeffs[g][m][c] phi_m(dir_gv).
+void launch_view_colors(const ViewInfo* views, int n_views, int64_t N, const float* means,
+                        const float* coeffs, int C, int sh_deg, float* gamma, hipStream_t s);
 
 void launch_render(const TileLists& tl, const float* gamma, int C, BlendParams bp, float* images,
                    unsigned long long* counter, hipStream_t s);
@@ -353,13 +347,12 @@ void launch_adjoint_solve(const ViewInfo* views, int n_views, const float* means
                           const float* grad_coeffs, const float* coeffs, float* bbar, float* rho,
                           float* w_scratch, uint32_t* obs_scratch, hipStream_t s);
 
-// Adjoint colours of batch item i: beta [i][C+1] = (beta_gj, delta_gj).
-// render: beta = c^T phi, delta = 0.  Otherwise beta = bbar^T phi and
-// delta = beta^T (c^T phi) + rho_g.  coeffs_t and bbar_t are transposed as
-// for launch_view_colors (rows of ldn floats).
-void launch_view_adjoint(const ViewInfo* views, int n_views, uint32_t n_items, const float* means,
-                         const float* coeffs_t, const float* bbar_t, int64_t ldn, const float* rho,
-                         int C, int sh_deg, bool render, float* beta, hipStream_t s);
+// Adjoint colours of batch item i: beta [i][C+1] = (beta_gj, delta_gj), with
+// beta = bbar^T phi and delta = beta^T (c^T phi) + rho_g; for a render (bbar
+// null) beta = c^T phi, delta = 0.
+void launch_view_adjoint(const ViewInfo* views, int n_views, int64_t N, const float* means,
+                         const float* coeffs, const float* bbar, const float* rho, int C, int sh_deg,
+                         float* beta, hipStream_t s);
 
 // Blend adjoint over the binned tiles: grad_y[row][c] = sum_g w beta (every
 // pixel of every view written, if grad_y) and grad_o[g] += dL/do (atomics, if grad_o).

@@ -30,77 +30,6 @@
 
 namespace gsc {
 
-// beta[i*(C+1) + c] = beta_gj[c] and [.. + C] = delta_gj for batch item i
-// (view v, Gaussian g), items in their own order; the coefficient arrays are
-// transposed ([m * C + c][g], rows of ldn floats) so that consecutive threads
-// read consecutive floats.
-template <int L, bool RENDER>
-__global__ void k_view_adjoint(const ViewInfo* __restrict__ views, int n_views, uint32_t n_items,
-                               const float* __restrict__ means, const float* __restrict__ coeffs_t,
-                               const float* __restrict__ bbar_t, int64_t ldn,
-                               const float* __restrict__ rho, int C, float* __restrict__ beta) {
-    constexpr int NB = (L + 1) * (L + 1);
-    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n_items) return;
-    const ViewInfo& V = views[find_view_item(views, n_views, i)];
-    const int64_t g = V.g_offset + (int64_t)(i - V.item_base);
-    const double dx = (double)means[3 * g] - V.centre[0];
-    const double dy = (double)means[3 * g + 1] - V.centre[1];
-    const double dz = (double)means[3 * g + 2] - V.centre[2];
-    const double inv = 1.0 / sqrt(dx * dx + dy * dy + dz * dz);
-    float phi[NB];
-    sh_eval<float, L>((float)(dx * inv), (float)(dy * inv), (float)(dz * inv), phi);
-    const float* cg = coeffs_t + g;
-    float* out = beta + (int64_t)i * (C + 1);
-    if constexpr (RENDER) {
-        for (int c = 0; c < C; ++c) {
-            float a = 0.0f;
-#pragma unroll
-            for (int m = 0; m < NB; ++m) a = fmaf(cg[(int64_t)(m * C + c) * ldn], phi[m], a);
-            out[c] = a;
-        }
-        out[C] = 0.0f;
-    } else {
-        const float* bg = bbar_t + g;
-        double delta = (double)rho[g];
-        for (int c = 0; c < C; ++c) {
-            float a = 0.0f, b = 0.0f;
-#pragma unroll
-            for (int m = 0; m < NB; ++m) {
-                const int64_t k = (int64_t)(m * C + c) * ldn;
-                a = fmaf(cg[k], phi[m], a);
-                b = fmaf(bg[k], phi[m], b);
-            }
-            out[c] = b;
-            delta += (double)a * (double)b;
-        }
-        out[C] = (float)delta;
-    }
-}
-
-void launch_view_adjoint(const ViewInfo* views, int n_views, uint32_t n_items, const float* means,
-                         const float* coeffs_t, const float* bbar_t, int64_t ldn, const float* rho,
-                         int C, int sh_deg, bool render, float* beta, hipStream_t s) {
-    if (n_items == 0 || n_views <= 0) return;
-    dim3 grid((n_items + 255) / 256), block(256);
-#define GSC_VA(LL)                                                                                   \
-    do {                                                                                             \
-        if (render)                                                                                  \
-            hipLaunchKernelGGL((k_view_adjoint<LL, true>), grid, block, 0, s, views, n_views,        \
-                               n_items, means, coeffs_t, bbar_t, ldn, rho, C, beta);                 \
-        else                                                                                         \
-            hipLaunchKernelGGL((k_view_adjoint<LL, false>), grid, block, 0, s, views, n_views,       \
-                               n_items, means, coeffs_t, bbar_t, ldn, rho, C, beta);                 \
-    } while (0)
-    switch (sh_deg) {
-        case 0: GSC_VA(0); break;
-        case 1: GSC_VA(1); break;
-        case 2: GSC_VA(2); break;
-        default: GSC_VA(3); break;
-    }
-#undef GSC_VA
-}
-
 namespace {
 
 // One front-to-back step of one pixel (the decisions of the forward blend).

@@ -1,82 +1,190 @@
 // Render: per-item view colours from SH coefficients, then the same
 // front-to-back tile blend as the accumulate pass, writing each pixel's
 // blended colour (eq. 2 with the colours of eq. 3).
+#include <algorithm>
+
 #include "gsc_internal.h"
 #include "sh.h"
 #include "wave_ops.h"
 
 namespace gsc {
 
-// 64 x 64 tiles through LDS: rows read and columns written as contiguous
-// runs (the padded row keeps the column reads free of bank conflicts).
-__global__ __launch_bounds__(256) void k_transpose(const float* __restrict__ in, int64_t rows, int K,
-                                                   float* __restrict__ out) {
-    __shared__ float t[64][65];
-    const int64_t r0 = (int64_t)blockIdx.x * 64;
-    const int k0 = (int)blockIdx.y * 64;
-    const int tx = (int)(threadIdx.x & 63), ty = (int)(threadIdx.x >> 6);
-    for (int j = ty; j < 64; j += 4) {
-        const int64_t r = r0 + j;
-        const int k = k0 + tx;
-        t[j][tx] = (r < rows && k < K) ? in[r * K + k] : 0.0f;
-    }
-    __syncthreads();
-    for (int j = ty; j < 64; j += 4) {
-        const int k = k0 + j;
-        const int64_t r = r0 + tx;
-        if (k < K && r < rows) out[(int64_t)k * rows + r] = t[tx][j];
-    }
-}
+// Per-item terms of the blends, from the SH coefficients (batch item i is view
+// v's Gaussian g, items in their own order, phi = phi(dir_gv)):
+//   kColours        out[i*C + c]       = sum_m c_g[m][c] phi_m
+//   kRenderAdjoint  out[i*(C+1) + c]   the same, and 0 at C (delta of a render)
+//   kAdjoint        out[i*(C+1) + c]   = beta_c = sum_m Bbar_g[m][c] phi_m, and
+//                   out[i*(C+1) + C]   = delta = rho_g + sum_c beta_c (c_g^T phi)_c
+//
+// Bound by the writes (12-16 bytes an item at C = 3) and the FP64 direction;
+// the coefficients (108 bytes a Gaussian at L = 2, C = 3, twice that for
+// kAdjoint) are an order more than the result if every item reads its own.  So
+// a thread owns a Gaussian and takes its views kTermViews at a time: the
+// block's coefficients go to LDS once, by coalesced loads of the caller's own
+// layout, and one LDS read serves kTermViews items.  Where the channels do not
+// fit, they are staged a few at a time for each set of views.
+// 300k Gaussians, 40 views, L = 3, C = 3: kColours 373 -> 117 us, kRenderAdjoint
+// 384 -> 111, kAdjoint 749 -> 211, and two or four transposes of the
+// coefficients (27-157 us) gone (before, a thread an item reading transposed
+// coefficients).
+enum TermMode { kColours, kRenderAdjoint, kAdjoint };
+constexpr int kTermBlock = 128, kTermViews = 4;
+constexpr int kTermLoads = 8;  // loads in flight a thread while staging
+// coefficients of one Gaussian in LDS at a time: 96 x 129 floats, three blocks a CU
+constexpr int kTermStage = 96;
 
-void launch_transpose(const float* in, int64_t rows, int K, float* out, hipStream_t s) {
-    if (rows <= 0 || K <= 0) return;
-    dim3 grid((unsigned)((rows + 63) / 64), (unsigned)((K + 63) / 64)), block(256);
-    hipLaunchKernelGGL(k_transpose, grid, block, 0, s, in, rows, K, out);
-}
-
-// gamma[i*C + c] = sum_m coeffs[g][m][c] * phi_m(dir_gv) for batch item i
-// (view v, Gaussian g): items in their own order, reading the transposed
-// coefficients, so that consecutive threads read consecutive floats.
-template <int L>
-__global__ void k_view_colors(const ViewInfo* __restrict__ views, int n_views, uint32_t n_items,
-                              const float* __restrict__ means, const float* __restrict__ coeffs_t,
-                              int64_t ldn, int C, float* __restrict__ gamma) {
-    constexpr int NB = (L + 1) * (L + 1);
-    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n_items) return;
-    const ViewInfo& V = views[find_view_item(views, n_views, i)];
-    const int64_t g = V.g_offset + (int64_t)(i - V.item_base);
-    double dx = (double)means[3 * g] - V.centre[0];
-    double dy = (double)means[3 * g + 1] - V.centre[1];
-    double dz = (double)means[3 * g + 2] - V.centre[2];
-    double inv = 1.0 / sqrt(dx * dx + dy * dy + dz * dz);
-    float phi[NB];
-    sh_eval<float, L>((float)(dx * inv), (float)(dy * inv), (float)(dz * inv), phi);
-    const float* cg = coeffs_t + g;
-    float* out = gamma + (int64_t)i * C;
-    for (int c = 0; c < C; ++c) {
-        float a = 0.0f;
+// Channels c0 .. c0+cw of the block's Gaussians: dst[(m * cw + c) * (kTermBlock + 1) + t].
+template <int NB>
+__device__ __forceinline__ void stage_terms(const float* __restrict__ src, int64_t g0, int n, int C, int c0,
+                                            int cw, float* dst) {
+    const int per = NB * cw;
+    const int dq = kTermBlock / per, dr = kTermBlock - dq * per;
+    int t = (int)threadIdx.x / per, k = (int)threadIdx.x - t * per;
+    if (cw == C) {  // contiguous
+        const float* from = src + g0 * per;
+        const int total = n * per;
+        for (int i0 = (int)threadIdx.x; i0 < total; i0 += kTermBlock * kTermLoads) {
+            float x[kTermLoads];
 #pragma unroll
-        for (int m = 0; m < NB; ++m) a += cg[(int64_t)(m * C + c) * ldn] * phi[m];
-        out[c] = a;
+            for (int u = 0; u < kTermLoads; ++u) x[u] = from[min(i0 + u * kTermBlock, total - 1)];
+#pragma unroll
+            for (int u = 0; u < kTermLoads; ++u) {
+                if (i0 + u * kTermBlock < total) dst[k * (kTermBlock + 1) + t] = x[u];
+                t += dq;
+                k += dr;
+                if (k >= per) k -= per, ++t;
+            }
+        }
+    } else {
+        while (t < n) {
+            const int m = k / cw, c = k - m * cw;
+            dst[k * (kTermBlock + 1) + t] = src[(g0 + t) * (int64_t)(NB * C) + m * C + c0 + c];
+            t += dq;
+            k += dr;
+            if (k >= per) k -= per, ++t;
+        }
     }
 }
 
-void launch_view_colors(const ViewInfo* views, int n_views, uint32_t n_items, const float* means,
-                        const float* coeffs_t, int64_t ldn, int C, int sh_deg, float* gamma,
-                        hipStream_t s) {
-    if (n_items == 0 || n_views <= 0) return;
-    dim3 grid((n_items + 255) / 256), block(256);
-#define GSC_VC(LL)                                                                                   \
-    hipLaunchKernelGGL(k_view_colors<LL>, grid, block, 0, s, views, n_views, n_items, means, coeffs_t, \
-                       ldn, C, gamma)
-    switch (sh_deg) {
-        case 0: GSC_VC(0); break;
-        case 1: GSC_VC(1); break;
-        case 2: GSC_VC(2); break;
-        default: GSC_VC(3); break;
+template <int L, int MODE>
+__global__ __launch_bounds__(kTermBlock) void k_view_terms(
+    const ViewInfo* __restrict__ views, int n_views, int views_per_row, int64_t N,
+    const float* __restrict__ means, const float* __restrict__ coeffs, const float* __restrict__ bbar,
+    const float* __restrict__ rho, int C, int cw, float* __restrict__ out) {
+    constexpr int NB = (L + 1) * (L + 1);
+    constexpr int LD = kTermBlock + 1;
+    extern __shared__ float stage[];
+    float* sc = stage;                  // c_g
+    float* sb = stage + NB * cw * LD;   // Bbar_g
+    const int64_t g0 = (int64_t)blockIdx.x * kTermBlock;
+    const int n = (int)min((int64_t)kTermBlock, N - g0);
+    const int t = (int)threadIdx.x;
+    const int64_t g = g0 + t;
+    const bool own = t < n;
+    const double px = own ? (double)means[3 * g] : 0.0, py = own ? (double)means[3 * g + 1] : 0.0,
+                 pz = own ? (double)means[3 * g + 2] : 0.0;
+    const double rg = (MODE == kAdjoint && own) ? (double)rho[g] : 0.0;
+    const int v_first = (int)blockIdx.y * views_per_row, v_end = min(n_views, v_first + views_per_row);
+    const int stride = MODE == kColours ? C : C + 1;
+    for (int vb = v_first; vb < v_end; vb += kTermViews) {
+        float phi[kTermViews][NB];
+        float* dst[kTermViews];
+        double delta[kTermViews];
+#pragma unroll
+        for (int j = 0; j < kTermViews; ++j) {
+            const ViewInfo& V = views[min(vb + j, v_end - 1)];
+            const int64_t k = g - V.g_offset;
+            const bool in = own && vb + j < v_end && k >= 0 && k < (int64_t)V.n_gauss;
+            dst[j] = in ? out + ((int64_t)V.item_base + k) * stride : nullptr;
+            const double dx = px - V.centre[0], dy = py - V.centre[1], dz = pz - V.centre[2];
+            const double inv = 1.0 / sqrt(dx * dx + dy * dy + dz * dz);
+            sh_eval<float, L>((float)(dx * inv), (float)(dy * inv), (float)(dz * inv), phi[j]);
+            delta[j] = rg;
+        }
+        for (int c0 = 0; c0 < C; c0 += cw) {
+            const int w = min(cw, C - c0);
+            if (vb == v_first || cw < C) {  // uniform over the block
+                __syncthreads();
+                stage_terms<NB>(coeffs, g0, n, C, c0, w, sc);
+                if constexpr (MODE == kAdjoint) stage_terms<NB>(bbar, g0, n, C, c0, w, sb);
+                __syncthreads();
+            }
+            for (int c = 0; c < w; ++c) {
+                float a[kTermViews] = {}, b[kTermViews] = {};
+#pragma unroll
+                for (int m = 0; m < NB; ++m) {
+                    const float x = sc[(m * w + c) * LD + t];
+#pragma unroll
+                    for (int j = 0; j < kTermViews; ++j) a[j] = fmaf(x, phi[j][m], a[j]);
+                    if constexpr (MODE == kAdjoint) {
+                        const float y = sb[(m * w + c) * LD + t];
+#pragma unroll
+                        for (int j = 0; j < kTermViews; ++j) b[j] = fmaf(y, phi[j][m], b[j]);
+                    }
+                }
+#pragma unroll
+                for (int j = 0; j < kTermViews; ++j) {
+                    if constexpr (MODE == kAdjoint) delta[j] += (double)a[j] * (double)b[j];
+                    if (dst[j]) dst[j][c0 + c] = MODE == kAdjoint ? b[j] : a[j];
+                }
+            }
+        }
+        if constexpr (MODE != kColours) {
+#pragma unroll
+            for (int j = 0; j < kTermViews; ++j)
+                if (dst[j]) dst[j][C] = MODE == kAdjoint ? (float)delta[j] : 0.0f;
+        }
     }
-#undef GSC_VC
+}
+
+namespace {
+
+template <int L, int MODE>
+void launch_terms(const ViewInfo* views, int n_views, int64_t N, const float* means, const float* coeffs,
+                  const float* bbar, const float* rho, int C, float* out, hipStream_t s) {
+    constexpr int NB = (L + 1) * (L + 1);
+    const int sets = MODE == kAdjoint ? 2 : 1;
+    const int cw = std::min(C, kTermStage / (NB * sets));
+    const int64_t gx = (N + kTermBlock - 1) / kTermBlock;
+    // views split over grid rows where the Gaussians alone give under 4096
+    // blocks (two waves each: eight a SIMD).  Each row stages the coefficients
+    // again: 2344 blocks by 40 views take 117 us in one row, 127 in five
+    const int sets_of_views = (n_views + kTermViews - 1) / kTermViews;
+    const int64_t rows = std::min<int64_t>(std::max<int64_t>(4096 / gx, 1), sets_of_views);
+    const int per_row = (int)((sets_of_views + rows - 1) / rows) * kTermViews;
+    dim3 grid((unsigned)gx, (unsigned)((n_views + per_row - 1) / per_row)), block(kTermBlock);
+    const size_t lds = sizeof(float) * (size_t)(sets * NB * cw) * (kTermBlock + 1);
+    hipLaunchKernelGGL((k_view_terms<L, MODE>), grid, block, lds, s, views, n_views, per_row, N, means, coeffs,
+                       bbar, rho, C, cw, out);
+}
+
+template <int MODE>
+void launch_terms_deg(int sh_deg, const ViewInfo* views, int n_views, int64_t N, const float* means,
+                      const float* coeffs, const float* bbar, const float* rho, int C, float* out,
+                      hipStream_t s) {
+    if (N <= 0 || n_views <= 0) return;
+    switch (sh_deg) {
+        case 0: launch_terms<0, MODE>(views, n_views, N, means, coeffs, bbar, rho, C, out, s); break;
+        case 1: launch_terms<1, MODE>(views, n_views, N, means, coeffs, bbar, rho, C, out, s); break;
+        case 2: launch_terms<2, MODE>(views, n_views, N, means, coeffs, bbar, rho, C, out, s); break;
+        default: launch_terms<3, MODE>(views, n_views, N, means, coeffs, bbar, rho, C, out, s); break;
+    }
+}
+
+}  // namespace
+
+void launch_view_colors(const ViewInfo* views, int n_views, int64_t N, const float* means,
+                        const float* coeffs, int C, int sh_deg, float* gamma, hipStream_t s) {
+    launch_terms_deg<kColours>(sh_deg, views, n_views, N, means, coeffs, nullptr, nullptr, C, gamma, s);
+}
+
+void launch_view_adjoint(const ViewInfo* views, int n_views, int64_t N, const float* means,
+                         const float* coeffs, const float* bbar, const float* rho, int C, int sh_deg,
+                         float* beta, hipStream_t s) {
+    if (bbar == nullptr)
+        launch_terms_deg<kRenderAdjoint>(sh_deg, views, n_views, N, means, coeffs, nullptr, nullptr, C, beta, s);
+    else
+        launch_terms_deg<kAdjoint>(sh_deg, views, n_views, N, means, coeffs, bbar, rho, C, beta, s);
 }
 
 // images[row][c] = sum_g w_gp * gamma_gv[c]; every pixel of every tile is
