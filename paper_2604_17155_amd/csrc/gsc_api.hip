@@ -875,7 +875,8 @@ gsc_status plan_accumulate(gsc_plan* P, const gsc_plan::Batch& b, const void* ta
                        P->lists.as<uint32_t>(), P->rec.as<float4>(), P->vals.as<uint32_t>(),
                        P->order.as<uint32_t>()};
     launch_accumulate(tl, targets, tdtype, P->C, P->per_view, P->bp, P->vs.as<float>(), d_counter, nullptr,
-                      chunk, s, persistent ? P->queues.as<uint32_t>() : nullptr);
+                      chunk, s, persistent ? P->queues.as<uint32_t>() : nullptr, nullptr,
+                      split_sums(P->per_view, tdtype, P->C, resolve_chunk(chunk, P->C, tdtype)) ? P->n_total : 0);
     GSC_LAUNCHED("accumulate");
     return GSC_OK;
 }
@@ -943,14 +944,14 @@ gsc_status plan_bin_batch(gsc_plan* P, const gsc_plan::Batch& b, hipStream_t s) 
     return GSC_OK;
 }
 
-gsc_status plan_solve(gsc_plan* P, const double* lam, float* coeffs, uint8_t* status, hipStream_t s) {
+gsc_status plan_solve(gsc_plan* P, bool split, const double* lam, float* coeffs, uint8_t* status, hipStream_t s) {
     gsc_ctx* ctx = P->ctx;
     StageTimer t(ctx, s, GSC_STAGE_SOLVE);
     unsigned int* d_ill = reinterpret_cast<unsigned int*>(P->misc.as<char>() + 16);
     const int nb = (P->sh_deg + 1) * (P->sh_deg + 1);
     if (!P->per_view) {
         launch_fold_solve(nullptr, 0, P->means, P->vs.as<float>(), false, P->n_total, P->C, 0, lam,
-                          ctx->opt.kappa_max, coeffs, status, nullptr, nullptr, d_ill, s);
+                          ctx->opt.kappa_max, coeffs, status, nullptr, nullptr, d_ill, s, nullptr, nullptr, split);
         GSC_LAUNCHED("solve");
         return GSC_OK;
     }
@@ -976,15 +977,16 @@ gsc_status plan_run(gsc_plan* P, const void* targets, int tdtype, const double* 
     launch_fill_u32(P->vs.as<uint32_t>(), 0u, P->vs_slots * (uint64_t)(P->C + 1), s);
     launch_cov3d(P->means, P->opac, P->scales, P->quats, P->cov.as<float>(), P->n_total, s);
     GSC_LAUNCHED("cov3d");
+    const int chunk = P->acc_chunk ? P->acc_chunk : P->ctx->opt.accumulate_variant;
     for (const auto& b : P->batches) {
         gsc_status st = plan_bin_batch(P, b, s);
         if (st != GSC_OK) return st;
         StageTimer t(P->ctx, s, GSC_STAGE_BLEND);
-        const int chunk = P->acc_chunk ? P->acc_chunk : P->ctx->opt.accumulate_variant;
         if ((st = plan_accumulate(P, b, targets, tdtype, chunk, P->acc_persistent, s)) != GSC_OK)
             return st;
     }
-    return plan_solve(P, lam, coeffs, status, s);
+    return plan_solve(P, split_sums(P->per_view, tdtype, P->C, resolve_chunk(chunk, P->C, tdtype)), lam, coeffs,
+                      status, s);
 }
 
 }  // namespace
@@ -1159,9 +1161,10 @@ gsc_status colorize_core(gsc_ctx* ctx, const float* means, const float* scales,
     }
     if (x_cnt) launch_fill_u32(x_cnt, 0u, (uint64_t)N, s);
     unsigned long long* d_counter = reinterpret_cast<unsigned long long*>(ctx->misc.p);
+    const int chunk = resolve_chunk(ctx->opt.accumulate_variant, C, tdtype);
+    const bool split = split_sums(per_view, tdtype, C, chunk);
     st = for_view_batches_k(ctx, all, n_cams, means, opacities, N, bp, s, key, reuse,
                           [&](int v0, int nv, const Binned& bn) -> gsc_status {
-        const int chunk = resolve_chunk(ctx->opt.accumulate_variant, C, tdtype);
         StageTimer t(ctx, s, GSC_STAGE_BLEND, (uint32_t)accumulate_launches(C, chunk));
         (void)v0;
         // Tiles in the longest-first order: the vector form as a grid whose
@@ -1175,7 +1178,7 @@ gsc_status colorize_core(gsc_ctx* ctx, const float* means, const float* scales,
             queues = ctx->queues.as<uint32_t>();
         }
         launch_accumulate(tl, targets, tdtype, C, per_view, bp, acc_vs, d_counter, x_cnt, chunk, s, queues,
-                          det ? &dsc : nullptr);
+                          det ? &dsc : nullptr, split ? N : 0);
         GSC_LAUNCHED("accumulate");
         return GSC_OK;
     });
@@ -1203,7 +1206,7 @@ gsc_status colorize_core(gsc_ctx* ctx, const float* means, const float* scales,
     StageTimer t_solve(ctx, s, GSC_STAGE_SOLVE);
     launch_fold_solve(ctx->views_all.as<ViewInfo>(), per_view ? n_cams : 0, means, ctx->vs.as<float>(),
                       per_view, N, C, sh_deg, lam, ctx->opt.kappa_max, coeffs, status, x_vis,
-                      dc_scratch, d_ill, s, factor, obs);
+                      dc_scratch, d_ill, s, factor, obs, split);
     GSC_LAUNCHED("fold/solve");
     ctx->stats_pending = true;
     ctx->stats_dev = nullptr;

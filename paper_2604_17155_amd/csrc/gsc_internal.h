@@ -271,6 +271,29 @@ int accumulate_chunk(int C, int tdtype);
 // tdtype, else the default.
 int resolve_chunk(int requested, int C, int tdtype);
 
+// The sums of one slot: *(v + slot * v_stride) and the C floats at s + slot *
+// s_stride.  Interleaved slots of C + 1 floats, or (split_n slots) the S rows
+// first and the V after them: rows of whole 64-byte units where C is a multiple
+// of 16 (from an aligned base), so that 16 channels are one atomic request and
+// not two.  Atomics leave the XCDs' caches (every request reaches the fabric)
+// at about 14-16 G requests/s, which bounds the wide matrix-core accumulate: 8.1
+// requests a row of 64 channels interleaved, 5 split (in launches of 32
+// channels, where it mattered less, 15.56 -> 14.49 ms).
+struct SumRows {
+    float* v;
+    float* s;
+    int v_stride, s_stride;
+};
+inline SumRows sum_rows(float* VS, int C, int64_t split_n) {
+    if (split_n > 0) return SumRows{VS + split_n * C, VS, 1, C};
+    return SumRows{VS, VS + 1, C + 1, C + 1};
+}
+// Whether sums over views (one slot a Gaussian, read by the L = 0 solve alone)
+// are kept split: for the matrix-core forms and whole blocks of 16 channels.
+inline bool split_sums(bool per_view, int tdtype, int C, int chunk) {
+    return !per_view && tdtype == GSC_BF16 && C % 16 == 0 && (chunk & kChunkMfma) && chunk != kChunkPacked;
+}
+
 // Accumulate V_gj and S_gj into slot (view.vs_base + g) when per_view, else
 // into slot (view.g_offset + g), summed over views; slots hold C+1 floats.
 // chunk: the accumulate variant (1, 2, 3, 4, 8 or 16 channels per launch, or
@@ -287,7 +310,7 @@ bool accumulate_chunk_valid(int chunk, int tdtype);
 void launch_accumulate(const TileLists& tl, const void* targets, int tdtype, int C, bool per_view,
                        BlendParams bp, float* VS, unsigned long long* counter, uint32_t* gcount,
                        int chunk, hipStream_t s, uint32_t* queues = nullptr,
-                       const float2* det = nullptr);
+                       const float2* det = nullptr, int64_t split_n = 0);
 
 // Colour of batch item i (view v, Gaussian g of the N): gamma[i][c] =
 // sum_m coeffs[g][m][c] phi_m(dir_gv).
@@ -311,7 +334,7 @@ void launch_fold_solve(const ViewInfo* views, int n_views, const float* means, c
                        bool per_view, int64_t N, int C, int sh_deg, const double* lam_nb /*host, nb*/,
                        float kappa_max, float* coeffs, uint8_t* status, float* wout,
                        float* dc_scratch, unsigned int* ill_count, hipStream_t s,
-                       double* factor = nullptr, uint32_t* obs_scratch = nullptr);
+                       double* factor = nullptr, uint32_t* obs_scratch = nullptr, bool split = false);
 int64_t fold_obs_words(int64_t N, int n_views);
 inline int refine_factor_words(int sh_deg) {
     const int nb = (sh_deg + 1) * (sh_deg + 1);

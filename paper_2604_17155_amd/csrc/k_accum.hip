@@ -484,7 +484,7 @@ static void launch_acc_cc(const TileLists& tl, const void* targets, int tdtype, 
 // W (Gaussians x pixels) . Y (pixels x channels).  Here the blend runs as in
 // accumulate_tile, but each entry's weights go to LDS as a row of W, split
 // into a BF16 high part (w's upper half) and a BF16 remainder (the exact
-// w - hi rounded; w = hi + lo to 2^-16 relative).  Every 8 or 16 entries,
+// w - hi rounded; w = hi + lo to 2^-16 relative).  Every 8 entries,
 // v_mfma_f32_16x16x32_bf16 forms (W_hi + W_lo) . [Y | 1] over the tile's 256
 // pixels (eight K-steps of 32 pixels): the targets, held as B operands in
 // registers for the whole tile, give S, and a block of ones gives
@@ -500,27 +500,23 @@ typedef float floatx4_t __attribute__((ext_vector_type(4)));
 constexpr int kWRow = 264;       // LDS row of W in BF16 elements (256 + padding against bank conflicts)
 constexpr int kMfmaWaves = 2;    // waves per block
 
-// W rows of one wave: ROWS list entries per matrix product (8 or 16; with 8,
-// the A operand holds the high parts in rows 0..7 and the remainders in rows
-// 8..15, and less LDS per wave leaves room for more waves).
-template <int ROWS>
+// W rows of one wave: kMfmaRows list entries per matrix product (the A operand
+// holds the high parts in rows 0..7 and the remainders in rows 8..15).
+constexpr int kMfmaRows = 8;
 struct alignas(16) MfmaLds {
-    __bf16 whi[ROWS * kWRow];
-    __bf16 wlo[ROWS * kWRow];
-    uint32_t gslot[ROWS];  // local Gaussian of each group row (0xFFFFFFFF: no contribution)
+    __bf16 whi[kMfmaRows * kWRow];
+    __bf16 wlo[kMfmaRows * kWRow];
+    uint32_t gslot[kMfmaRows];  // local Gaussian of each group row (0xFFFFFFFF: no contribution)
     float4 crec1[64];      // the chunk's records, read back by every lane as one broadcast:
     float2 crec0[64];      // conic and opacity; the centre offset (one channel block only)
 };
 
-template <int NBLK>
-constexpr int mfma_rows() { return NBLK <= 2 ? 8 : 16; }
 // Waves per SIMD the register allocation is held to (the weight rows in LDS
 // allow them): the 32-channel form ran at two waves per SIMD with 208
 // registers and runs at three with 168; the 16-channel and packed forms at
-// four (128 registers, up from three).  The 64-channel form keeps its 128
-// target registers unconstrained.
+// four (128 registers, up from three).
 template <int NBLK>
-constexpr int mfma_waves_per_simd() { return NBLK == 2 ? 3 : (NBLK == 1 ? 4 : 1); }
+constexpr int mfma_waves_per_simd() { return NBLK == 2 ? 3 : 4; }
 
 // YM: target layout in the B operand.  0: BF16, NBLK blocks of 16 channels,
 // V from a separate product against ones.  1: BF16, C <= 15 channels packed
@@ -529,20 +525,22 @@ constexpr int mfma_waves_per_simd() { return NBLK == 2 ? 3 : (NBLK == 1 ? 4 : 1)
 // C..2C-1), ones in column 2C.  Packed forms run in one launch (c_off = 0).
 template <int NBLK, int BIN, int YM>
 __device__ __forceinline__ uint32_t accumulate_tile_mfma(
-    uint32_t tile, uint32_t lane, MfmaLds<mfma_rows<NBLK>()>& L, const ViewInfo* __restrict__ views, int n_views,
+    uint32_t tile, uint32_t lane, MfmaLds& L, const ViewInfo* __restrict__ views, int n_views,
     const uint2* __restrict__ ranges, const uint32_t* __restrict__ pair_vals,
     const float4* __restrict__ rec, const uint32_t* __restrict__ items,
     const void* __restrict__ targets, int C, int c_off, int per_view, const BlendParams& bp,
-    float* __restrict__ VS, uint32_t* __restrict__ gcount) {
+    const SumRows& out, uint32_t* __restrict__ gcount) {
     const TileGeom tg = tile_geom<BIN>(tile, views, n_views);
     const ViewInfo& V = views[tg.vloc];
     // view fields read once (plain values: the conditions below need no branch)
     const int vw = V.width, vh = V.height;
     const int64_t poff = V.pixel_offset;
-    const int stride = C + 1;
     const uint32_t n16 = lane & 15, q4 = lane >> 4;
-    constexpr int ROWS = mfma_rows<NBLK>();
 
+    uint2 rg = ranges[tg.bin];
+    rg.x = (uint32_t)__builtin_amdgcn_readfirstlane((int)rg.x);
+    rg.y = (uint32_t)__builtin_amdgcn_readfirstlane((int)rg.y);
+    if (rg.x >= rg.y) return 0;
     // targets of the tile as B operands: Y[s][b] holds the eight pixels of
     // row 4 (s & 1) + q4 of block s / 2, channel c_off + 16 b + n16
     bf16x8_t Y[8][NBLK];
@@ -550,77 +548,32 @@ __device__ __forceinline__ uint32_t accumulate_tile_mfma(
     const int pc = YM == 2 ? ((int)n16 < C ? (int)n16 : (int)n16 - C) : (int)n16;
     const bool pcol = YM == 2 ? (int)n16 < 2 * C : (int)n16 < C;   // a target column
     const bool pone = YM == 2 ? (int)n16 == 2 * C : (int)n16 == C;  // the ones column
-    if constexpr (NBLK == 1) {
-        // One 64-bit offset per row of eight pixels, then a uniform step of C
-        // elements per pixel; element 0 of the view stands in outside (no branch).
-        // All loads are issued before any is used (one channel block: 5.37 ->
-        // 5.31-5.34 ms per launch on the 32-scene plan; with two blocks the
-        // loaded values spill, 8.0 -> 8.2 ms, and the form below is kept).
-        using TY = std::conditional_t<YM == 2, float, uint16_t>;
-        const TY* vt = (const TY*)targets + poff * C;
-        TY xv[8][NBLK][8];
+    // Rows, columns and channels past the end read the nearest pixel of the
+    // tile and the last channel instead: those pixels have weight 0
+    // and those columns are not stored, so no value needs a mask (the masks of
+    // 64-128 loads were spilled scalar registers).  Offsets from the tile's
+    // first row fit 32 bits (16 image rows hold at most 2^25 values).
+    using TY = std::conditional_t<YM == 2, float, uint16_t>;
+    const int yb = min(tg.y0, vh - 1);
+    const TY* trow = (const TY*)targets + (poff + (int64_t)yb * vw) * C;
 #pragma unroll
-        for (int s = 0; s < 8; ++s) {
-            const int gy = tg.y0 + 8 * (s >> 2) + 4 * (s & 1) + (int)q4;
-            const int gx0 = tg.x0 + 8 * ((s >> 1) & 1);
+    for (int s = 0; s < 8; ++s) {
+        const int gy = min(tg.y0 + 8 * (s >> 2) + 4 * (s & 1) + (int)q4, vh - 1);
+        const int gx0 = tg.x0 + 8 * ((s >> 1) & 1);
+        const uint32_t ro = (uint32_t)(gy - yb) * (uint32_t)vw * (uint32_t)C;
 #pragma unroll
-            for (int b = 0; b < NBLK; ++b) {
-                const int c = YM == 0 ? c_off + 16 * b + (int)n16 : pc;
-                const bool rowin = (gy < vh) & (YM == 0 ? c < C : pcol);
-                const TY* rp = vt + (rowin ? ((int64_t)gy * vw + gx0) * C + c : (int64_t)0);
+        for (int b = 0; b < NBLK; ++b) {
+            const uint32_t vo = ro + (uint32_t)(YM == 0 ? min(c_off + 16 * b + (int)n16, C - 1) : (pcol ? pc : 0));
 #pragma unroll
-                for (int i = 0; i < 8; ++i) xv[s][b][i] = *((rowin & (gx0 + i < vw)) ? rp + i * C : vt);
-            }
-        }
-#pragma unroll
-        for (int s = 0; s < 8; ++s) {
-            const int gy = tg.y0 + 8 * (s >> 2) + 4 * (s & 1) + (int)q4;
-            const int gx0 = tg.x0 + 8 * ((s >> 1) & 1);
-#pragma unroll
-            for (int b = 0; b < NBLK; ++b) {
-                const int c = YM == 0 ? c_off + 16 * b + (int)n16 : pc;
-                const bool rowin = (gy < vh) & (YM == 0 ? c < C : pcol);
-#pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    const bool in = rowin & (gx0 + i < vw);
-                    const TY x = xv[s][b][i];
-                    if constexpr (YM == 2) {
-                        const __bf16 hi = (__bf16)x;
-                        const __bf16 v = (int)n16 < C ? hi : (__bf16)(x - (float)hi);
-                        Y[s][b][i] = in ? v : (pone ? (__bf16)1.0f : (__bf16)0.0f);
-                    } else {
-                        const __bf16 v = __builtin_bit_cast(__bf16, x);
-                        Y[s][b][i] = in ? v : ((YM == 1 && pone) ? (__bf16)1.0f : (__bf16)0.0f);
-                    }
-                }
-            }
-        }
-    } else {
-        // a 64-bit element index per load
-#pragma unroll
-        for (int s = 0; s < 8; ++s) {
-            const int gy = tg.y0 + 8 * (s >> 2) + 4 * (s & 1) + (int)q4;
-            const int gx0 = tg.x0 + 8 * ((s >> 1) & 1);
-#pragma unroll
-            for (int b = 0; b < NBLK; ++b) {
-                const int c = YM == 0 ? c_off + 16 * b + (int)n16 : pc;
-#pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    const int gx = gx0 + i;
-                    const bool in = (gx < vw) & (gy < vh) & (YM == 0 ? c < C : pcol);
-                    const int64_t row = poff + (int64_t)gy * vw + gx;
-                    // unconditional load (element 0 stands in outside): no branch
-                    const int64_t e = in ? row * C + c : 0;
-                    if constexpr (YM == 2) {
-                        const float f = ((const float*)targets)[e];
-                        const __bf16 hi = (__bf16)f;
-                        const __bf16 v = (int)n16 < C ? hi : (__bf16)(f - (float)hi);
-                        Y[s][b][i] = in ? v : (pone ? (__bf16)1.0f : (__bf16)0.0f);
-                    } else {
-                        const uint16_t u = ((const uint16_t*)targets)[e];
-                        const __bf16 v = __builtin_bit_cast(__bf16, u);
-                        Y[s][b][i] = in ? v : ((YM == 1 && pone) ? (__bf16)1.0f : (__bf16)0.0f);
-                    }
+            for (int i = 0; i < 8; ++i) {
+                const TY x = (trow + (int64_t)min(gx0 + i, vw - 1) * C)[vo];
+                if constexpr (YM == 2) {
+                    const __bf16 hi = (__bf16)x;
+                    const __bf16 v = (int)n16 < C ? hi : (__bf16)(x - (float)hi);
+                    Y[s][b][i] = pone ? (__bf16)1.0f : v;
+                } else {
+                    const __bf16 v = __builtin_bit_cast(__bf16, x);
+                    Y[s][b][i] = (YM == 1 && pone) ? (__bf16)1.0f : v;
                 }
             }
         }
@@ -650,9 +603,6 @@ __device__ __forceinline__ uint32_t accumulate_tile_mfma(
         alive |= (__builtin_amdgcn_ballot_w64(inside) != 0 ? 1u : 0u) << k;
     }
     alive = (uint32_t)__builtin_amdgcn_readfirstlane((int)alive);
-    uint2 rg = ranges[tg.bin];
-    rg.x = (uint32_t)__builtin_amdgcn_readfirstlane((int)rg.x);
-    rg.y = (uint32_t)__builtin_amdgcn_readfirstlane((int)rg.y);
     uint32_t cnt = 0;
     const int64_t item_base = V.item_base;
     const int64_t slot_base = per_view ? V.vs_base : V.g_offset;
@@ -674,12 +624,9 @@ __device__ __forceinline__ uint32_t accumulate_tile_mfma(
     // the operand in the flush, for one and for two channel blocks).
 
     // one matrix product over the group's `rows` entries, then the atomics.
-    // With 8 rows per group the A operand's rows 0..7 take the weights' high
-    // parts and rows 8..15 their remainders, so one product per K-step forms
-    // both halves; each output row then adds its two halves (lanes l and
-    // l + 32).  With 16 rows the high parts and the remainders take a
-    // product each.
-    constexpr bool kSplitRows = ROWS == 8;
+    // The A operand's rows 0..7 take the weights' high parts and rows 8..15
+    // their remainders, so one product per K-step forms both halves; each
+    // output row then adds its two halves (lanes l and l + 32).
     auto flush = [&](uint32_t rows) {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -687,30 +634,19 @@ __device__ __forceinline__ uint32_t accumulate_tile_mfma(
 #pragma unroll
         for (int b = 0; b < NBLK; ++b) D[b] = floatx4_t{0.f, 0.f, 0.f, 0.f};
         DV = floatx4_t{0.f, 0.f, 0.f, 0.f};
-        const uint32_t arow = kSplitRows ? (n16 & 7u) : n16;
-        const __bf16* ah_p = &((kSplitRows && n16 >= 8u) ? L.wlo : L.whi)[arow * kWRow + 8 * q4];
-        const __bf16* al_p = &L.wlo[arow * kWRow + 8 * q4];
+        const __bf16* ah_p = &(n16 >= 8u ? L.wlo : L.whi)[(n16 & 7u) * kWRow + 8 * q4];
 #pragma unroll
         for (int s = 0; s < 8; ++s) {
             const bf16x8_t ah = *reinterpret_cast<const bf16x8_t*>(ah_p + 32 * s);
             if (YM == 0 && first_chunk) DV = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, ones, DV, 0, 0, 0);
 #pragma unroll
             for (int b = 0; b < NBLK; ++b) D[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, Y[s][b], D[b], 0, 0, 0);
-            if constexpr (!kSplitRows) {
-                const bf16x8_t al = *reinterpret_cast<const bf16x8_t*>(al_p + 32 * s);
-                if (YM == 0 && first_chunk) DV = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, ones, DV, 0, 0, 0);
-#pragma unroll
-                for (int b = 0; b < NBLK; ++b)
-                    D[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, Y[s][b], D[b], 0, 0, 0);
-            }
         }
-        if constexpr (kSplitRows) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                if (YM == 0 && first_chunk) DV[i] += __shfl_xor(DV[i], 32, 64);
+        for (int i = 0; i < 4; ++i) {
+            if (YM == 0 && first_chunk) DV[i] += __shfl_xor(DV[i], 32, 64);
 #pragma unroll
-                for (int b = 0; b < NBLK; ++b) D[b][i] += __shfl_xor(D[b][i], 32, 64);
-            }
+            for (int b = 0; b < NBLK; ++b) D[b][i] += __shfl_xor(D[b][i], 32, 64);
         }
         // lane holds rows 4 q4 + i, column n16
 #pragma unroll
@@ -721,17 +657,18 @@ __device__ __forceinline__ uint32_t accumulate_tile_mfma(
             if (m >= rows) continue;
             const uint32_t gl = L.gslot[m];
             if (gl == 0xFFFFFFFFu) continue;
-            float* slot = VS + (slot_base + (int64_t)gl) * (int64_t)stride;
+            float* srow = out.s + (slot_base + (int64_t)gl) * (int64_t)out.s_stride;
+            float* vsum = out.v + (slot_base + (int64_t)gl) * (int64_t)out.v_stride;
             if constexpr (YM == 0) {
-                if (first_chunk && n16 == 0) unsafeAtomicAdd(slot, DV[i]);
+                if (first_chunk && n16 == 0) unsafeAtomicAdd(vsum, DV[i]);
 #pragma unroll
                 for (int b = 0; b < NBLK; ++b) {
                     const int c = c_off + 16 * b + (int)n16;
-                    if (c < C) unsafeAtomicAdd(slot + 1 + c, D[b][i]);
+                    if (c < C) unsafeAtomicAdd(srow + c, D[b][i]);
                 }
             } else {
-                if (pone) unsafeAtomicAdd(slot, D[0][i]);
-                else if ((int)n16 < C) unsafeAtomicAdd(slot + 1 + n16, D[0][i] + lo);
+                if (pone) unsafeAtomicAdd(vsum, D[0][i]);
+                else if ((int)n16 < C) unsafeAtomicAdd(srow + n16, D[0][i] + lo);
             }
         }
         // the next group overwrites these rows
@@ -806,7 +743,7 @@ __device__ __forceinline__ uint32_t accumulate_tile_mfma(
             const uint32_t gl = (uint32_t)((int64_t)bcast_u(gid, j) - item_base);
             if (lane == 0) L.gslot[rows] = nh != 0u ? gl : 0xFFFFFFFFu;
             if (nh != 0u && gcount != nullptr && first_chunk && lane == 0) atomicAdd(gcount + g_off + gl, nh);
-            if (++rows == (uint32_t)ROWS) {
+            if (++rows == (uint32_t)kMfmaRows) {
                 flush(rows);
                 rows = 0;
             }
@@ -825,9 +762,9 @@ __attribute__((amdgpu_waves_per_eu(mfma_waves_per_simd<NBLK>()))) void k_accumul
     const uint32_t* __restrict__ pair_vals, const float4* __restrict__ rec,
     const uint32_t* __restrict__ items,
     const void* __restrict__ targets, int C, int c_off, int per_view, BlendParams bp,
-    float* __restrict__ VS, unsigned long long* __restrict__ counter, uint32_t* __restrict__ gcount,
+    SumRows out, unsigned long long* __restrict__ counter, uint32_t* __restrict__ gcount,
     uint32_t* __restrict__ queue, const uint32_t* __restrict__ order) {
-    __shared__ MfmaLds<mfma_rows<NBLK>()> lds[kMfmaWaves];
+    __shared__ MfmaLds lds[kMfmaWaves];
     const uint32_t lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     uint32_t cnt = 0;
     if (queue == nullptr) {
@@ -835,7 +772,7 @@ __attribute__((amdgpu_waves_per_eu(mfma_waves_per_simd<NBLK>()))) void k_accumul
         if (wi >= n_tiles) return;  // whole wave
         const uint32_t tile = queued_tile<BIN>(wi, order);  // blocks start in index order
         cnt = accumulate_tile_mfma<NBLK, BIN, YM>(tile, lane, lds[w], views, n_views, ranges, pair_vals,
-                                              rec, items, targets, C, c_off, per_view, bp, VS,
+                                              rec, items, targets, C, c_off, per_view, bp, out,
                                               gcount);
     } else {
         for (;;) {
@@ -846,7 +783,7 @@ __attribute__((amdgpu_waves_per_eu(mfma_waves_per_simd<NBLK>()))) void k_accumul
             const uint32_t tile = queued_tile<BIN>(tq, order);
             cnt += accumulate_tile_mfma<NBLK, BIN, YM>(tile, lane, lds[w], views, n_views, ranges,
                                                    pair_vals, rec, items, targets, C, c_off,
-                                                   per_view, bp, VS, gcount);
+                                                   per_view, bp, out, gcount);
         }
     }
     if (c_off == 0 && lane == 0 && cnt) atomicAdd(counter, (unsigned long long)cnt);
@@ -854,7 +791,7 @@ __attribute__((amdgpu_waves_per_eu(mfma_waves_per_simd<NBLK>()))) void k_accumul
 
 template <int NBLK, int BIN, int YM>
 static void launch_acc_mfma(const TileLists& tl, const void* targets, int C, bool per_view, BlendParams bp,
-                            float* VS, unsigned long long* counter, uint32_t* gcount, uint32_t* queues,
+                            const SumRows& out, unsigned long long* counter, uint32_t* gcount, uint32_t* queues,
                             hipStream_t s) {
     const uint32_t n_wt = wave_tiles(tl.n_bins, BIN);
     const uint32_t full = (n_wt + kMfmaWaves - 1) / kMfmaWaves;
@@ -865,24 +802,255 @@ static void launch_acc_mfma(const TileLists& tl, const void* targets, int C, boo
         uint32_t* q = queues ? queues + pass : nullptr;
         hipLaunchKernelGGL((k_accumulate_mfma<NBLK, BIN, YM>), grid, block, 0, s, tl.views, tl.n_views,
                            n_wt, tl.ranges, tl.pair_vals, tl.rec, tl.items, targets, C, c_off,
-                           (int)per_view, bp, VS, counter, gcount, q, tl.order);
+                           (int)per_view, bp, out, counter, gcount, q, tl.order);
     }
 }
 
 template <int NBLK, int YM>
 static void launch_acc_mfma_bin(const TileLists& tl, const void* targets, int C, bool per_view,
-                                BlendParams bp, float* VS, unsigned long long* counter, uint32_t* gcount,
-                                uint32_t* queues, hipStream_t s) {
+                                BlendParams bp, const SumRows& out, unsigned long long* counter,
+                                uint32_t* gcount, uint32_t* queues, hipStream_t s) {
     if (tl.bin == 32)
-        launch_acc_mfma<NBLK, 32, YM>(tl, targets, C, per_view, bp, VS, counter, gcount, queues, s);
+        launch_acc_mfma<NBLK, 32, YM>(tl, targets, C, per_view, bp, out, counter, gcount, queues, s);
     else
-        launch_acc_mfma<NBLK, 16, YM>(tl, targets, C, per_view, bp, VS, counter, gcount, queues, s);
+        launch_acc_mfma<NBLK, 16, YM>(tl, targets, C, per_view, bp, out, counter, gcount, queues, s);
+}
+
+// ---- 33 to 64 channels: one block per tile --------------------------------
+//
+// The block's four waves share a group's weight rows.  Each blends one 8x8 block
+// of the tile (every pixel's weights once, where two launches of the form above
+// form them twice) and multiplies the rows of all 256 pixels by 16 channels of
+// its own, held as B operands in 32 registers (one wave with all 64 channels
+// needs 128 and runs alone on its SIMD).  The list is gathered 256 entries at a
+// time, one a thread, and those that reach a live block are put together in
+// LDS in list order; groups of 16 of them share a barrier between the blend and
+// the product.  A Gaussian's sums leave the tile once: splitting the tile's
+// pixels over independent waves (16x8 or 8x8 pixels by 64 channels each) was
+// bound by the atomics instead (25 and 44 ms; see SumRows).
+// 500k Gaussians, 100 views of 960x540, 64 channels: 15.9 ms in two launches of
+// 32 channels -> 8.85 ms, near the rate of the atomics (142 M requests).  Held to
+// 80 registers, six blocks a CU: 8.85 ms, 96: 8.97, 125: 9.66.
+constexpr int kWideRows = 16;
+struct alignas(16) WideLds {
+    __bf16 whi[kWideRows * kWRow];
+    __bf16 wlo[kWideRows * kWRow];
+    float4 rec1[256];      // the chunk's entries: conic and opacity,
+    float2 rec0[256];      // offset of the tile's centre point from the centre,
+    uint32_t gid[256];     // local Gaussian,
+    uint32_t blocks[256];  // blocks reached
+    uint32_t count[4];     // entries each wave put in
+    uint32_t hit[4];       // rows of the group that got weight in each block
+    uint32_t live[4];      // block has live pixels
+    uint32_t next;         // tile taken from the queue
+};
+
+template <int BIN>
+__device__ __forceinline__ uint32_t accumulate_tile_wide(
+    uint32_t tile, uint32_t lane, uint32_t wave, WideLds& L, const ViewInfo* __restrict__ views, int n_views,
+    const uint2* __restrict__ ranges, const uint32_t* __restrict__ pair_vals, const float4* __restrict__ rec,
+    const uint32_t* __restrict__ items, const uint16_t* __restrict__ targets, int C, int per_view,
+    const BlendParams& bp, const SumRows& out, uint32_t* __restrict__ gcount) {
+    const TileGeom tg = tile_geom<BIN>(tile, views, n_views);
+    const ViewInfo& V = views[tg.vloc];
+    uint2 rg = ranges[tg.bin];
+    rg.x = (uint32_t)__builtin_amdgcn_readfirstlane((int)rg.x);
+    rg.y = (uint32_t)__builtin_amdgcn_readfirstlane((int)rg.y);
+    if (rg.x >= rg.y) return 0;  // the same for every wave
+    const int vw = V.width, vh = V.height;
+    const int64_t item_base = V.item_base, g_off = V.g_offset;
+    const int64_t slot_base = per_view ? V.vs_base : V.g_offset;
+    const uint32_t n16 = lane & 15, q4 = lane >> 4;
+    const int c = 16 * (int)wave + (int)n16;
+    const bool channels = 16 * (int)wave < C;  // uniform
+
+    // targets: as in the form above (nearest pixel, last channel past the ends)
+    bf16x8_t Y[8];
+    {
+        const int yb = min(tg.y0, vh - 1);
+        const uint16_t* trow = targets + (V.pixel_offset + (int64_t)yb * vw) * C;
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+            const int gy = min(tg.y0 + 8 * (s >> 2) + 4 * (s & 1) + (int)q4, vh - 1);
+            const int gx0 = tg.x0 + 8 * ((s >> 1) & 1);
+            const uint32_t vo = (uint32_t)(gy - yb) * (uint32_t)vw * (uint32_t)C + (uint32_t)min(c, C - 1);
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                Y[s][i] = __builtin_bit_cast(__bf16, (trow + (int64_t)min(gx0 + i, vw - 1) * C)[vo]);
+        }
+    }
+    bf16x8_t ones;
+    {
+        uint32_t o4[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) o4[i] = (uint32_t)__builtin_amdgcn_mov_dpp(0x3F803F80, 0xE4, 0xF, 0xF, true);
+        ones = __builtin_bit_cast(bf16x8_t, o4);
+    }
+    const float ox = tile_centre(tg.x0), oy = tile_centre(tg.y0);
+    const float lx = tile_offset_col(lane, (int)(wave & 1u)), ly = tile_offset_row(lane, (int)(wave >> 1));
+    const float qlim = uniform_in_vgpr((float)(kExp2Scale * (double)bp.cut2));
+    const float amax = uniform_in_vgpr(bp.alpha_max), amin = uniform_in_vgpr(bp.alpha_min),
+                tmin = uniform_in_vgpr(bp.t_min);
+    uint32_t alive = 0;  // blocks of the tile with pixels inside the image
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        alive |= (tg.x0 + 8 * (k & 1) < vw && tg.y0 + 8 * (k >> 1) < vh ? 1u : 0u) << k;
+    float T = (tg.x0 + block_px(lane, (int)wave) < vw) & (tg.y0 + block_py(lane, (int)wave) < vh) ? 1.0f : kOutsideT;
+    bool live = ((alive >> wave) & 1u) != 0u;
+    uint32_t cnt = 0, turn = 0;
+    uint32_t dirty = 0xFFFFu;  // rows whose weights of this block may be other than zero
+    __bf16* wh = &L.whi[64 * wave + lane];
+    __bf16* wl = &L.wlo[64 * wave + lane];
+
+    for (uint32_t b = rg.x; b < rg.y && alive != 0u; b += 256) {
+        const uint32_t e = b + 64 * wave + lane;
+        const bool in_list = e < rg.y;
+        const uint32_t pv = in_list ? pair_vals[e] : 0u;
+        const uint32_t it = pv & kItemMask;
+        const bool own = in_list && pair_reaches<BIN>(pv, tg.quad, alive);
+        const float4 r = own ? rec[2 * (size_t)it] : make_float4(0.f, 0.f, 0.f, 0.f);
+        const float2 R0 = make_float2((ox - r.x) - r.z, (oy - r.y) - r.w);
+        const float4 R1 = own ? rec[2 * (size_t)it + 1] : make_float4(0.f, 0.f, 0.f, 0.f);
+        const uint32_t gid = own ? items[it] : 0u;
+        const uint32_t BL = own ? (entry_blocks<BIN>(pv, R0, R1, bp) & alive) : 0u;
+        const uint64_t put = __builtin_amdgcn_ballot_w64(BL != 0u);
+        if (lane == 0) {
+            L.count[wave] = (uint32_t)__popcll(put);
+            L.live[wave] = live ? 1u : 0u;
+        }
+        __syncthreads();  // the counts; the last chunk's entries are done with
+        uint32_t n = 0, at = 0;
+#pragma unroll
+        for (uint32_t k = 0; k < 4; ++k) {
+            const uint32_t x = L.count[k];
+            at += k < wave ? x : 0u;
+            n += x;
+        }
+        n = (uint32_t)__builtin_amdgcn_readfirstlane((int)n);
+        if (BL != 0u) {
+            at += __builtin_amdgcn_mbcnt_hi((uint32_t)(put >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)put, 0u));
+            L.rec1[at] = R1;
+            L.rec0[at] = R0;
+            L.gid[at] = (uint32_t)((int64_t)gid - item_base);
+            L.blocks[at] = BL;
+        }
+        __syncthreads();  // the entries
+        for (uint32_t g = 0; g < n; g += kWideRows) {
+            const uint32_t rows = min((uint32_t)kWideRows, n - g);
+            const uint32_t bl = lane < rows ? L.blocks[g + lane] : 0u;
+            uint32_t todo = live ? (uint32_t)__builtin_amdgcn_ballot_w64(((bl >> wave) & 1u) != 0u) : 0u;
+            uint32_t hit = 0, zero = dirty & ~todo;
+            dirty = todo;
+            while (zero != 0u) {
+                const uint32_t m = (uint32_t)__builtin_ctz(zero);
+                zero &= zero - 1u;
+                wh[m * kWRow] = (__bf16)0.0f;
+                wl[m * kWRow] = (__bf16)0.0f;
+            }
+            while (todo != 0u) {
+                const uint32_t m = (uint32_t)__builtin_ctz(todo);
+                todo &= todo - 1u;
+                const float2 c0 = L.rec0[g + m];
+                const float4 c1 = L.rec1[g + m];
+                const float dx = c0.x + lx, dy = c0.y + ly;
+                const float q2 = fmaf(dy, fmaf(c1.z, dy, c1.y * dx), c1.x * dx * dx);
+                uint64_t taken, kept;
+                const float w = pixel_step(q2, c1.w, T, qlim, amin, amax, tmin, taken, kept);
+                const uint32_t wb = __float_as_uint(w);
+                wh[m * kWRow] = __builtin_bit_cast(__bf16, (uint16_t)(wb >> 16));
+                wl[m * kWRow] = (__bf16)(w - __uint_as_float(wb & 0xffff0000u));
+                const uint32_t nh = (uint32_t)__popcll(taken);
+                cnt += nh;
+                hit |= (nh != 0u ? 1u : 0u) << m;
+                if (nh != 0u && gcount != nullptr && lane == 0) atomicAdd(gcount + g_off + L.gid[g + m], nh);
+                live = kept != 0;
+            }
+            // (a block that has stopped gives zero weights from then on)
+            if (lane == 0) {
+                L.hit[wave] = hit;
+                L.live[wave] = live ? 1u : 0u;
+            }
+            __syncthreads();  // the rows
+            const uint32_t hits = (uint32_t)__builtin_amdgcn_readfirstlane((int)(L.hit[0] | L.hit[1] | L.hit[2] | L.hit[3]));
+            if (hits != 0u) {
+                const bool vturn = turn == wave;  // the waves form V in turn
+                turn = (turn + 1u) & 3u;
+                floatx4_t D = {0.f, 0.f, 0.f, 0.f}, E = D, DV = D;
+                const __bf16* ah_p = &L.whi[n16 * kWRow + 8 * q4];
+                const __bf16* al_p = &L.wlo[n16 * kWRow + 8 * q4];
+#pragma unroll
+                for (int s = 0; s < 8; ++s) {
+                    const bf16x8_t ah = *reinterpret_cast<const bf16x8_t*>(ah_p + 32 * s);
+                    const bf16x8_t al = *reinterpret_cast<const bf16x8_t*>(al_p + 32 * s);
+                    D = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, Y[s], D, 0, 0, 0);
+                    E = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, Y[s], E, 0, 0, 0);
+                    if (vturn) {
+                        DV = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, ones, DV, 0, 0, 0);
+                        DV = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, ones, DV, 0, 0, 0);
+                    }
+                }
+                // lane holds rows 4 q4 + i, column n16
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const uint32_t m = 4 * q4 + (uint32_t)i;
+                    if (!((hits >> m) & 1u)) continue;
+                    const int64_t slot = slot_base + (int64_t)L.gid[g + m];
+                    if (c < C) unsafeAtomicAdd(out.s + slot * out.s_stride + c, D[i] + E[i]);
+                    if (vturn && n16 == 0) unsafeAtomicAdd(out.v + slot * out.v_stride, DV[i]);
+                }
+            }
+            __syncthreads();  // the rows and the flags are done with
+        }
+        alive = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) alive |= L.live[k] << k;
+        alive = (uint32_t)__builtin_amdgcn_readfirstlane((int)alive);
+    }
+    return cnt;
+}
+
+template <int BIN>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void k_accumulate_wide(
+    const ViewInfo* __restrict__ views, int n_views, uint32_t n_tiles, const uint2* __restrict__ ranges,
+    const uint32_t* __restrict__ pair_vals, const float4* __restrict__ rec, const uint32_t* __restrict__ items,
+    const uint16_t* __restrict__ targets, int C, int per_view, BlendParams bp, SumRows out,
+    unsigned long long* __restrict__ counter, uint32_t* __restrict__ gcount, uint32_t* __restrict__ queue,
+    const uint32_t* __restrict__ order) {
+    __shared__ WideLds L;
+    const uint32_t lane = threadIdx.x & 63;
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    uint32_t cnt = 0;
+    if (queue == nullptr) {
+        const uint32_t tile = queued_tile<BIN>(xcd_block(blockIdx.x, gridDim.x), order);
+        cnt = accumulate_tile_wide<BIN>(tile, lane, wave, L, views, n_views, ranges, pair_vals, rec, items, targets,
+                                        C, per_view, bp, out, gcount);
+    } else {
+        for (;;) {
+            if (threadIdx.x == 0) L.next = atomicAdd(queue, 1u);
+            __syncthreads();
+            const uint32_t tq = (uint32_t)__builtin_amdgcn_readfirstlane((int)L.next);
+            if (tq >= n_tiles) break;  // the same for every wave
+            cnt += accumulate_tile_wide<BIN>(queued_tile<BIN>(tq, order), lane, wave, L, views, n_views, ranges,
+                                             pair_vals, rec, items, targets, C, per_view, bp, out, gcount);
+            __syncthreads();  // the number is read, the tile's entries are done with
+        }
+    }
+    if (lane == 0 && cnt) atomicAdd(counter, (unsigned long long)cnt);
+}
+
+template <int BIN>
+static void launch_acc_wide(const TileLists& tl, const void* targets, int C, bool per_view, BlendParams bp,
+                            const SumRows& out, unsigned long long* counter, uint32_t* gcount, uint32_t* queues,
+                            hipStream_t s) {
+    const uint32_t n_wt = wave_tiles(tl.n_bins, BIN);
+    dim3 grid(queues ? std::min(n_wt, kPersistentBlocks) : n_wt), block(256);
+    hipLaunchKernelGGL(k_accumulate_wide<BIN>, grid, block, 0, s, tl.views, tl.n_views, n_wt, tl.ranges,
+                       tl.pair_vals, tl.rec, tl.items, (const uint16_t*)targets, C, (int)per_view, bp, out, counter,
+                       gcount, queues, tl.order);
 }
 
 int accumulate_chunk(int C, int tdtype) {
-    // (one 64-channel launch holds its targets in 128 registers and runs one
-    // wave per SIMD; two 32-channel launches measure as fast or faster)
-    if (tdtype == GSC_BF16 && C >= 16) return kChunkMfma | (C <= 16 ? 16 : 32);
+    if (tdtype == GSC_BF16 && C >= 16) return kChunkMfma | (C <= 16 ? 16 : C <= 32 ? 32 : 64);
     return C <= 3 ? C : (C <= 4 ? 4 : (C <= 8 ? 8 : 16));
 }
 
@@ -904,7 +1072,7 @@ bool accumulate_chunk_valid(int chunk, int tdtype) {
 
 void launch_accumulate(const TileLists& tl, const void* targets, int tdtype, int C, bool per_view,
                        BlendParams bp, float* VS, unsigned long long* counter, uint32_t* gcount,
-                       int chunk, hipStream_t s, uint32_t* queues, const float2* det) {
+                       int chunk, hipStream_t s, uint32_t* queues, const float2* det, int64_t split_n) {
     if (tl.n_bins == 0) return;
     chunk = resolve_chunk(chunk, C, tdtype);
     if (det && (chunk & kChunkMfma)) chunk = accumulate_chunk(C, GSC_F32);  // vector form only
@@ -922,15 +1090,19 @@ void launch_accumulate(const TileLists& tl, const void* targets, int tdtype, int
     }
     if (queues) launch_fill_u32(queues, 0u, (uint64_t)accumulate_launches(C, chunk), s);
     if (chunk & kChunkMfma) {
+        const SumRows rows = sum_rows(VS, C, split_n);
 #define GSC_ACCM(NB, YMV) \
-    launch_acc_mfma_bin<NB, YMV>(tl, targets, C, per_view, bp, VS, counter, gcount, queues, s)
+    launch_acc_mfma_bin<NB, YMV>(tl, targets, C, per_view, bp, rows, counter, gcount, queues, s)
         switch (chunk_channels(chunk)) {
             case 1:
                 if (tdtype == GSC_BF16) GSC_ACCM(1, 1); else GSC_ACCM(1, 2);
                 break;
             case 16: GSC_ACCM(1, 0); break;
             case 32: GSC_ACCM(2, 0); break;
-            default: GSC_ACCM(4, 0); break;
+            default:
+                if (tl.bin == 32) launch_acc_wide<32>(tl, targets, C, per_view, bp, rows, counter, gcount, queues, s);
+                else launch_acc_wide<16>(tl, targets, C, per_view, bp, rows, counter, gcount, queues, s);
+                break;
         }
 #undef GSC_ACCM
         return;

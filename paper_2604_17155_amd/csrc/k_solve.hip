@@ -33,13 +33,13 @@ struct ObsList {
 
 constexpr double kY0 = 0.28209479177387814;
 
-__global__ void k_solve_dc(const float* __restrict__ VS, int64_t N, int C, double lam0,
+__global__ void k_solve_dc(const SumRows sums, int64_t N, int C, double lam0,
                            float* __restrict__ coeffs, uint8_t* __restrict__ status,
                            float* __restrict__ wout) {
     int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (g >= N) return;
-    const float* s = VS + g * (int64_t)(C + 1);
-    double w = s[0];
+    const float* s = sums.s + g * (int64_t)sums.s_stride;
+    double w = sums.v[g * sums.v_stride];
     if (wout) wout[g] = (float)w;
     float* out = coeffs + g * C;
     if (w == 0.0) {
@@ -48,7 +48,7 @@ __global__ void k_solve_dc(const float* __restrict__ VS, int64_t N, int C, doubl
         return;
     }
     double den = w * (kY0 * kY0 + lam0);
-    for (int c = 0; c < C; ++c) out[c] = (float)(kY0 * (double)s[1 + c] / den);
+    for (int c = 0; c < C; ++c) out[c] = (float)(kY0 * (double)s[c] / den);
     if (status) status[g] = 0;
 }
 
@@ -718,7 +718,7 @@ void launch_fold_solve(const ViewInfo* views, int n_views, const float* means, c
                        bool per_view, int64_t N, int C, int sh_deg, const double* lam_nb,
                        float kappa_max, float* coeffs, uint8_t* status, float* wout,
                        float* dc_scratch, unsigned int* ill_count, hipStream_t s, double* factor,
-                       uint32_t* obs_scratch) {
+                       uint32_t* obs_scratch, bool split) {
     if (N <= 0) return;
     if (sh_deg == 0) {
         const float* src = VS;
@@ -728,7 +728,8 @@ void launch_fold_solve(const ViewInfo* views, int n_views, const float* means, c
                                n_views, N, C + 1, dc_scratch);
             src = dc_scratch;
         }
-        hipLaunchKernelGGL(k_solve_dc, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, s, src, N, C,
+        hipLaunchKernelGGL(k_solve_dc, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, s,
+                           sum_rows(const_cast<float*>(src), C, split ? N : 0), N, C,
                            lam_nb[0], coeffs, status, wout);
         return;
     }
