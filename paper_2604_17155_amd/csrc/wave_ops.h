@@ -30,6 +30,12 @@ __device__ __forceinline__ float sum_xor32(float x) {
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
+// Lanes 0..31: a of the lane plus a of the lane 32 on; lanes 32..63: the same of b.
+__device__ __forceinline__ float fold_halves(float a, float b) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
 // Sum over the 64 lanes; the result is uniform.  All lanes must be active.
 __device__ __forceinline__ float wave_sum(float v) {
     v += dpp_mov<kQuadXor1>(v);
