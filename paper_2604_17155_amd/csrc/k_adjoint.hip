@@ -32,29 +32,14 @@ namespace gsc {
 
 namespace {
 
-// One front-to-back step of one pixel (the decisions of the forward blend).
-struct Step {
-    float w;      // accepted weight alpha*T (0 if not accepted)
-    float alpha;  // alpha of the entry
-    float G;      // exp(-q/2)
-    float Tb;     // transmittance before the entry
-    bool take;
-};
-
-__device__ __forceinline__ Step blend_step(float& T, bool& live, float q2, float opac,
-                                           float qlim, const BlendParams& bp) {
-    Step st;
-    st.G = __builtin_amdgcn_exp2f(q2);
-    st.alpha = fminf(bp.alpha_max, opac * st.G);
-    const float test = fmaf(-T, st.alpha, T);
-    const bool cand = live && q2 >= qlim && st.alpha >= bp.alpha_min;
-    const bool stop = cand && test < bp.t_min;
-    st.take = cand && !stop;
-    live = live && !stop;
-    st.Tb = T;
-    st.w = st.take ? st.alpha * T : 0.0f;
-    T = st.take ? test : T;
-    return st;
+// a / d for d in (0, 1]: the hardware reciprocal (1 ulp) and one correction by
+// the residual, which leaves the quotient within an ulp of the rounded one.  The
+// compiler's division takes twice the instructions and switches the denormal
+// mode around them.
+__device__ __forceinline__ float quotient(float a, float d) {
+    const float r = __builtin_amdgcn_rcpf(d);
+    const float q = a * r;
+    return fmaf(fmaf(-d, q, a), r, q);
 }
 
 }  // namespace
@@ -63,7 +48,12 @@ __device__ __forceinline__ Step blend_step(float& T, bool& live, float q2, float
 // linear in the channels, so chunk launches add their shares of dL/do; the
 // first chunk also carries -delta.
 // The forms of up to three channels are held to seven waves per SIMD (72
-// registers), as the forward accumulate.
+// registers), as the forward accumulate (both adjoints 4.53 ms; six 4.58).
+//
+// Bound by vector issue, as the forward walks: 300k Gaussians, 40 views of
+// 800x800, degree 3, 3 channels: colorize 3.78 -> 2.32 ms, render 3.73 -> 2.20
+// (before: a live flag per pixel carried through every step, the compiler's
+// division, one wave reduction and one atomic per entry).
 template <int CC>
 constexpr int adj_waves_per_simd() { return CC >= 1 && CC <= 3 ? 7 : 1; }
 
@@ -77,6 +67,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(adj_waves_p
     // the chunk's records and, for up to three channels, the entry's adjoint
     // colours and offset, read back by every lane as broadcasts
     constexpr bool kLdsB = CC <= 3;
+    constexpr int kGroup = 4;
     __shared__ float4 srec1[4][64];
     __shared__ float4 sbet[4][kLdsB ? 64 : 1];
     __shared__ float2 srec0[4][64];
@@ -93,10 +84,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(adj_waves_p
     const int64_t g_shift = V.g_offset - (int64_t)V.item_base;
     // loop constants in vector registers (see uniform_in_vgpr)
     const float qlim = uniform_in_vgpr((float)(kExp2Scale * (double)bp.cut2));
-    BlendParams bpv = bp;
-    bpv.alpha_max = uniform_in_vgpr(bp.alpha_max);
-    bpv.alpha_min = uniform_in_vgpr(bp.alpha_min);
-    bpv.t_min = uniform_in_vgpr(bp.t_min);
+    const float amax = uniform_in_vgpr(bp.alpha_max), amin = uniform_in_vgpr(bp.alpha_min),
+                tmin = uniform_in_vgpr(bp.t_min);
 
     bool inside[4];
     float yv[4][CC];  // pixel values (read only when dL/do is wanted)
@@ -123,21 +112,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(adj_waves_p
     // lane (records and the entry's adjoint colours), and staged in LDS, from
     // which an entry reads them back with broadcast loads (adjoint colours of
     // wider chunks by readlane); each lane forms its entry's block mask, and
-    // only entries reaching a block with a live pixel are visited.  A
-    // pixel that stopped adds nothing in either pass, so the skipped entries
-    // and blocks change no sum.
+    // only entries reaching a block with a live pixel are visited, four at a
+    // time: `body` gets each with its place in the group, `group` ends it.
+    // Liveness is refreshed once a group: a pixel that stopped (T < t_min) adds
+    // nothing in either pass, so the skipped entries and blocks change no sum.
     uint32_t alive0 = 0;  // blocks holding a pixel of the image
 #pragma unroll
     for (int k = 0; k < 4; ++k) alive0 |= (__builtin_amdgcn_ballot_w64(inside[k]) != 0 ? 1u : 0u) << k;
     alive0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)alive0);
     float T[4];
-    bool live[4];
-    auto walk = [&](auto&& body) {
+    auto walk = [&](auto&& body, auto&& group) {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            T[k] = 1.0f;
-            live[k] = inside[k];
-        }
+        for (int k = 0; k < 4; ++k) T[k] = inside[k] ? 1.0f : kOutsideT;
         uint32_t alive = alive0;
         for (uint32_t b = rg.x; b < rg.y && alive != 0u; b += 64) {
             const uint32_t nb = min(64u, rg.y - b);
@@ -152,7 +138,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(adj_waves_p
             float RB[CC];
 #pragma unroll
             for (int c = 0; c < CC; ++c) RB[c] = (own && c_off + c < C) ? bl[c_off + c] : 0.0f;
-            const float RD = (own && first_chunk) ? bl[C] : 0.0f;
+            const float RD = (own && first_chunk) ? -bl[C] : 0.0f;
             const uint32_t BL = own ? (entry_blocks<BIN>(pv, R0, R1, bp) & alive) : 0u;
             uint64_t todo = __builtin_amdgcn_ballot_w64(BL != 0u);
             srec1[w][lane] = R1;
@@ -162,33 +148,52 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(adj_waves_p
                                             CC > 2 ? RB[CC > 2 ? 2 : 0] : 0.0f, RD);
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
-            while (todo != 0u) {
-                const uint32_t j = (uint32_t)__builtin_ctzll(todo);
-                todo &= todo - 1u;
-                const uint32_t blocks = bcast_u(BL, j) & alive;
-                if (blocks == 0u) continue;
-                const uint32_t item = bcast_u(gid, j);
-                const float2 c0 = srec0[w][j];
-                const float4 c1 = srec1[w][j];
-                float bet[CC];
-                float del;
-                if constexpr (kLdsB) {
-                    const float4 b4 = sbet[w][kLdsB ? j : 0];
-                    const float bb[3] = {b4.x, b4.y, b4.z};
+            while (todo != 0u && alive != 0u) {
 #pragma unroll
-                    for (int c = 0; c < CC; ++c) bet[c] = bb[c < 3 ? c : 0];
-                    del = b4.w;
-                } else {
+                for (int e = 0; e < kGroup; ++e) {
+                    const bool any = todo != 0u;
+                    const uint32_t j = any ? (uint32_t)__builtin_ctzll(todo) : 0u;
+                    todo &= todo - 1u;
+                    const uint32_t item = bcast_u(gid, j);
+                    const uint32_t blocks = any ? bcast_u(BL, j) & alive : 0u;
+                    float bet[CC];
+                    float del;  // - delta
+                    if constexpr (!kLdsB) {
 #pragma unroll
-                    for (int c = 0; c < CC; ++c) bet[c] = bcast(RB[c], j);
-                    del = bcast(RD, j);
+                        for (int c = 0; c < CC; ++c) bet[c] = bcast(RB[c], j);
+                        del = bcast(RD, j);
+                    }
+                    auto visit = [&](auto&& step) {
+                        if (blocks == 0u) return;  // uniform
+                        const float2 c0 = srec0[w][j];
+                        const float4 c1 = srec1[w][j];
+                        if constexpr (kLdsB) {
+                            const float4 b4 = sbet[w][kLdsB ? j : 0];
+                            const float bb[3] = {b4.x, b4.y, b4.z};
+#pragma unroll
+                            for (int c = 0; c < CC; ++c) bet[c] = bb[c < 3 ? c : 0];
+                            del = b4.w;
+                        }
+                        const float dx[2] = {c0.x + lx[0], c0.x + lx[1]}, dy[2] = {c0.y + ly[0], c0.y + ly[1]};
+                        const float a0[2] = {c1.x * dx[0] * dx[0], c1.x * dx[1] * dx[1]};
+                        const float b0[2] = {c1.y * dx[0], c1.y * dx[1]};
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) {
+                            if (!((blocks >> k) & 1u)) continue;  // uniform
+                            const float q2 = fmaf(dy[k >> 1], fmaf(c1.z, dy[k >> 1], b0[k & 1]), a0[k & 1]);
+                            float u = del;
+#pragma unroll
+                            for (int c = 0; c < CC; ++c) u = fmaf(bet[c], yv[k][c], u);
+                            step(k, q2, c1.w, u, bet);
+                        }
+                    };
+                    body(e, item, visit);
                 }
-                body(blocks, c0, c1, item, bet, del);
+                group();
 #pragma unroll
                 for (int k = 0; k < 4; ++k)
-                    if (((blocks >> k) & 1u) && __builtin_amdgcn_ballot_w64(live[k]) == 0) alive &= ~(1u << k);
+                    if (((alive >> k) & 1u) && __builtin_amdgcn_ballot_w64(T[k] >= tmin) == 0) alive &= ~(1u << k);
                 alive = (uint32_t)__builtin_amdgcn_readfirstlane((int)alive);
-                if (alive == 0u) break;
             }
             __builtin_amdgcn_wave_barrier();  // the next chunk overwrites the records
         }
@@ -203,26 +208,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(adj_waves_p
 #pragma unroll
         for (int c = 0; c < (GY ? CC : 1); ++c) gy[k][c] = 0.0f;
     }
-    walk([&](uint32_t blocks, const float2& c0, const float4& c1, uint32_t item, const float (&bet)[CC],
-             float del) {
-        const float dx[2] = {c0.x + lx[0], c0.x + lx[1]}, dy[2] = {c0.y + ly[0], c0.y + ly[1]};
-        const float a0[2] = {c1.x * dx[0] * dx[0], c1.x * dx[1] * dx[1]};
-        const float b0[2] = {c1.y * dx[0], c1.y * dx[1]};
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            if (!((blocks >> k) & 1u)) continue;  // uniform
-            const float q2 = fmaf(dy[k >> 1], fmaf(c1.z, dy[k >> 1], b0[k & 1]), a0[k & 1]);
-            const Step st = blend_step(T[k], live[k], q2, c1.w, qlim, bpv);
-            float u = -del;
-#pragma unroll
-            for (int c = 0; c < CC; ++c) u = fmaf(bet[c], yv[k][c], u);
-            S[k] += (double)(st.w * u);
+    walk([&](int e, uint32_t item, auto&& visit) {
+        visit([&](int k, float q2, float opac, float u, const float (&bet)[CC]) {
+            uint64_t taken, kept;
+            const float wt = pixel_step(q2, opac, T[k], qlim, amin, amax, tmin, taken, kept);
+            S[k] += (double)(wt * u);
             if constexpr (GY) {
 #pragma unroll
-                for (int c = 0; c < CC; ++c) gy[k][c] = fmaf(st.w, bet[c], gy[k][c]);
+                for (int c = 0; c < CC; ++c) gy[k][c] = fmaf(wt, bet[c], gy[k][c]);
             }
-        }
-    });
+        });
+    }, [] {});
     if constexpr (GY) {
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
@@ -236,34 +232,46 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(adj_waves_p
     if (grad_o == nullptr) return;
 
     // ---- pass 2: dL/dalpha per entry, reduced to dL/do per Gaussian -------
+    // The step is pixel_step's, with the transmittance before the entry kept; a
+    // group's four sums share one reduction and one atomic.
     double P[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) P[k] = 0.0;
-    walk([&](uint32_t blocks, const float2& c0, const float4& c1, uint32_t item, const float (&bet)[CC],
-             float del) {
-        const float dx[2] = {c0.x + lx[0], c0.x + lx[1]}, dy[2] = {c0.y + ly[0], c0.y + ly[1]};
-        const float a0[2] = {c1.x * dx[0] * dx[0], c1.x * dx[1] * dx[1]};
-        const float b0[2] = {c1.y * dx[0], c1.y * dx[1]};
-        float go = 0.0f;
-        uint32_t any = 0;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            if (!((blocks >> k) & 1u)) continue;  // uniform
-            const float q2 = fmaf(dy[k >> 1], fmaf(c1.z, dy[k >> 1], b0[k & 1]), a0[k & 1]);
-            const Step st = blend_step(T[k], live[k], q2, c1.w, qlim, bpv);
-            float u = -del;
-#pragma unroll
-            for (int c = 0; c < CC; ++c) u = fmaf(bet[c], yv[k][c], u);
-            P[k] += (double)(st.w * u);
+    float go[kGroup];
+    uint32_t who[kGroup], hit[kGroup];
+    walk([&](int e, uint32_t item, auto&& visit) {
+        float sum = 0.0f;
+        uint64_t hits = 0;
+        visit([&](int k, float q2, float opac, float u, const float (&bet)[CC]) {
+            const float G = __builtin_amdgcn_exp2f(q2);
+            const float al = __builtin_amdgcn_fmed3f(opac * G, 0.0f, amax);
+            const bool inq = q2 >= qlim, ina = al >= amin;
+            const float ae = (inq & ina) ? al : 0.0f;
+            const float Tb = T[k], wt = Tb * ae;
+            T[k] = fmaf(-Tb, ae, Tb);
+            const bool keep = T[k] >= tmin;
+            P[k] += (double)((keep ? wt : 0.0f) * u);
             const float suffix = (float)(S[k] - P[k]);
-            const float dal = u * st.Tb - suffix / (1.0f - st.alpha);
-            const bool clamped = c1.w * st.G >= bp.alpha_max;
-            go += (st.take && !clamped) ? dal * st.G : 0.0f;
-            any |= st.take ? 1u : 0u;
-        }
-        if (__ballot(any != 0) != 0) {
-            const float t = wave_sum(go);
-            if (lane == 0) unsafeAtomicAdd(grad_o + ((int64_t)item + g_shift), t);
+            const float dal = fmaf(u, Tb, -quotient(suffix, 1.0f - ae));
+            const bool take = inq & ina & keep;
+            hits |= __builtin_amdgcn_ballot_w64(inq) & __builtin_amdgcn_ballot_w64(ina) & __builtin_amdgcn_ballot_w64(keep);
+            // (al is amax where the alpha is clamped: no derivative)
+            sum += (take & !(al >= amax)) ? dal * G : 0.0f;
+        });
+        go[e] = sum;
+        who[e] = item;
+        hit[e] = hits != 0 ? 1u : 0u;
+    }, [&] {
+        if ((hit[0] | hit[1] | hit[2] | hit[3]) != 0u) {  // uniform
+            const float t = wave_sum_transposed<kGroup>(go, lane);
+            const int e = transposed_index<kGroup>(lane);
+            uint32_t item = who[0], h = hit[0];
+#pragma unroll
+            for (int q = 1; q < kGroup; ++q) {
+                item = e == q ? who[q] : item;
+                h = e == q ? hit[q] : h;
+            }
+            if (lane < (uint32_t)kGroup && h != 0u) unsafeAtomicAdd(grad_o + ((int64_t)item + g_shift), t);
         }
     });
 }
@@ -373,7 +381,7 @@ __global__ __launch_bounds__(256) void k_blend_adjoint_blocks(
             const uint64_t taken = g.cand[e] & kept;
             const float G = __builtin_amdgcn_exp2f(g.q2[e]);
             const float suffix = (float)(S - P);
-            const float dal = u * Tb - suffix / (1.0f - g.ae[e]);
+            const float dal = fmaf(u, Tb, -quotient(suffix, 1.0f - g.ae[e]));
             const bool use = ((taken >> lane) & 1u) != 0u && !(g.opac[e] * G >= amax);
             go[e] = use ? dal * G : 0.0f;
             any[e] = taken != 0 ? 1u : 0u;
