@@ -80,7 +80,7 @@ __device__ __forceinline__ uint32_t accumulate_tile(
     uint2 rg = ranges[tg.bin];
     rg.x = (uint32_t)__builtin_amdgcn_readfirstlane((int)rg.x);
     rg.y = (uint32_t)__builtin_amdgcn_readfirstlane((int)rg.y);
-    uint32_t cnt = 0;
+    uint32_t cnt = 0;  // contributions of the lane's pixels
     // item = V.item_base + g (g local to the view's scene)
     const int64_t item_base = V.item_base;
     const int64_t slot_base = per_view ? V.vs_base : V.g_offset;
@@ -141,25 +141,32 @@ __device__ __forceinline__ uint32_t accumulate_tile(
         lrec0[lane] = R0;
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
-        if constexpr (CC >= 1 && CC <= 3) {
-            // Entries in groups of four: each entry's tile sums (V, S) stay in
-            // a fixed register slot, and one wave reduction of the group's 16
-            // values (lane e*4+v, bit-reversed) feeds one atomic per value.
+        if constexpr (CC <= 3) {
+            // Weights alone, 300k Gaussians, 40 views of 800x800: 1.36 -> 1.24 ms
+            // (before, a reduction and an atomic per entry; contributions counted
+            // by scalar instructions); one channel, 120k, 20 views: 601 -> 587 us.
+            // Entries in groups: each entry's tile sums (V, S) stay in a fixed
+            // register slot, and one wave reduction of the group's kGroup x
+            // kVals values (lane e*kVals+v, bit-reversed) feeds one atomic per value.
             // Tile liveness is refreshed once per group: entries after the
             // last live pixel stopped meet T < t_min everywhere and add nothing.
+            constexpr int kVals = CC == 0 ? 1 : (CC == 1 ? 2 : 4), kGroup = CC <= 1 ? 8 : 4;
+            constexpr int kPend = kVals * kGroup;
             while (todo != 0u && alive != 0u) {
-                float pend[16];
-                int64_t gslot[4];
-                bool has[4];
+                float pend[kPend];
+                uint32_t who[kGroup];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
+                for (int u = 0; u < kGroup; ++u) {
                     const bool any = todo != 0u;
                     const uint32_t j = any ? (uint32_t)__builtin_ctzll(todo) : 0u;
                     todo &= todo - 1u;
-                    const uint32_t gid = bcast_u(gi, j);  // the entry's item
+                    who[u] = bcast_u(gi, j);  // the entry's item
                     const uint32_t blocks = any ? bcast_u(BL, j) & alive : 0u;
-                    float sv = 0.0f, s0 = 0.0f, s1 = 0.0f, s2 = 0.0f;
-                    uint32_t nh = 0;
+                    float sv = 0.0f;
+                    float ss[CCA];
+#pragma unroll
+                    for (int c = 0; c < CCA; ++c) ss[c] = 0.0f;
+                    const uint32_t before = cnt;
                     if (blocks != 0u) {
                         const float2 c0 = lrec0[j];
                         const float4 c1 = lrec1[j];
@@ -170,38 +177,38 @@ __device__ __forceinline__ uint32_t accumulate_tile(
                         for (int k = 0; k < 4; ++k) {
                             if (!((blocks >> k) & 1u)) continue;  // uniform
                             const float q2 = fmaf(dy[k >> 1], fmaf(c1.z, dy[k >> 1], b0[k & 1]), a0[k & 1]);
-                            uint64_t taken, kept;
-                            const float w = pixel_step(q2, c1.w, T[k], qlim, amin, amax, tmin, taken, kept);
+                            const float w = lane_step(q2, c1.w, T[k], qlim, amin, amax, tmin, cnt);
                             sv += w;
-                            s0 = fmaf(w, y[k][0], s0);
-                            if constexpr (CC > 1) s1 = fmaf(w, y[k][CC > 1 ? 1 : 0], s1);
-                            if constexpr (CC > 2) s2 = fmaf(w, y[k][CC > 2 ? 2 : 0], s2);
-                            nh += (uint32_t)__popcll(taken);
+#pragma unroll
+                            for (int c = 0; c < CC; ++c) ss[c] = fmaf(w, y[k][c], ss[c]);
                         }
                     }
-                    nh = (uint32_t)__builtin_amdgcn_readfirstlane((int)nh);
-                    cnt += nh;
-                    const int64_t g = (int64_t)gid - item_base;
-                    if (nh != 0u && gcount != nullptr && first_chunk && lane == 0)
-                        atomicAdd(gcount + V.g_offset + g, nh);
-                    has[u] = nh != 0u;
-                    gslot[u] = slot_base + g;
-                    pend[4 * u] = sv;
-                    pend[4 * u + 1] = s0;
-                    pend[4 * u + 2] = s1;
-                    pend[4 * u + 3] = s2;
+                    if (gcount != nullptr && first_chunk) {  // uniform
+                        const uint32_t nh = wave_sum_u32(cnt - before);
+                        if (nh != 0u && lane == 0)
+                            atomicAdd(gcount + V.g_offset + ((int64_t)who[u] - item_base), nh);
+                    }
+                    pend[kVals * u] = sv;
+#pragma unroll
+                    for (int v = 1; v < kVals; ++v) pend[kVals * u + v] = v <= CC ? ss[v <= CC && CC > 0 ? v - 1 : 0] : 0.0f;
                 }
 #pragma unroll
-                for (int k = 0; k < 4; ++k)
-                    if (((alive >> k) & 1u) && __builtin_amdgcn_ballot_w64(T[k] >= tmin) == 0) alive &= ~(1u << k);
+                for (int k = 0; k < 4; ++k) alive &= __builtin_amdgcn_ballot_w64(T[k] >= tmin) != 0 ? 15u : ~(1u << k);
                 alive = (uint32_t)__builtin_amdgcn_readfirstlane((int)alive);
-                if (has[0] || has[1] || has[2] || has[3]) {
-                    const float t = wave_sum_transposed<16>(pend, lane);
-                    const int idx = transposed_index<16>(lane);
-                    const int e = idx >> 2, v = idx & 3;
-                    const bool he = e == 0 ? has[0] : (e == 1 ? has[1] : (e == 2 ? has[2] : has[3]));
-                    const int64_t sl = e == 0 ? gslot[0] : (e == 1 ? gslot[1] : (e == 2 ? gslot[2] : gslot[3]));
-                    const bool use = lane < 16u && he && (v == 0 ? first_chunk : (v <= CC && c_off + v - 1 < C));
+                {
+                    const float t = wave_sum_transposed<kPend>(pend, lane);
+                    const int idx = transposed_index<kPend>(lane);
+                    const int e = idx / kVals, v = idx % kVals;
+                    // lane L & (kGroup - 1) holds the V of L's entry: entries
+                    // without weight in the tile add nothing
+                    const uint32_t hits = (uint32_t)__builtin_amdgcn_ballot_w64(t > 0.0f);
+                    const uint32_t he = (hits >> (lane & (uint32_t)(kGroup - 1))) & 1u;
+                    uint32_t item = who[0];
+#pragma unroll
+                    for (int q = 1; q < kGroup; ++q) item = e == q ? who[q] : item;
+                    const int64_t sl = slot_base + ((int64_t)item - item_base);
+                    const bool use = lane < (uint32_t)kPend && he != 0u &&
+                                     (v == 0 ? first_chunk : (v <= CC && c_off + v - 1 < C));
                     if (use) vs_add<DET>(VS, VS + sl * (int64_t)stride + (v == 0 ? 0 : c_off + v), t,
                                          v == 0 ? dsc.x : dsc.y);
                 }
@@ -222,51 +229,32 @@ __device__ __forceinline__ uint32_t accumulate_tile(
                 float ss[CCA];
 #pragma unroll
                 for (int c = 0; c < CCA; ++c) ss[c] = 0.0f;
-                uint32_t nh = 0;    // contributions of this entry (wave total)
+                const uint32_t before = cnt;
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
                     if (!((blocks >> k) & 1u)) continue;  // uniform
                     const float q2 = fmaf(dy[k >> 1], fmaf(c1.z, dy[k >> 1], b0[k & 1]), a0[k & 1]);
-                    uint64_t taken, kept;
-                    const float w = pixel_step(q2, c1.w, T[k], qlim, amin, amax, tmin, taken, kept);
+                    const float w = lane_step(q2, c1.w, T[k], qlim, amin, amax, tmin, cnt);
                     sv += w;
 #pragma unroll
                     for (int c = 0; c < CC; ++c) ss[c] = fmaf(w, y[k][c], ss[c]);
-                    nh += (uint32_t)__popcll(taken);
-                    if (kept == 0) alive &= ~(1u << k);
+                    if (__builtin_amdgcn_ballot_w64(T[k] >= tmin) == 0) alive &= ~(1u << k);
                 }
-                // keep the block mask and the count in scalar registers
-                alive = (uint32_t)__builtin_amdgcn_readfirstlane((int)alive);
-                nh = (uint32_t)__builtin_amdgcn_readfirstlane((int)nh);
-                cnt += nh;
-                if (nh != 0u) {
+                alive = (uint32_t)__builtin_amdgcn_readfirstlane((int)alive);  // keep it in a scalar register
+                if (__builtin_amdgcn_ballot_w64(cnt != before) != 0) {
                     // the pair carries the depth rank; the record names the item
                     const int64_t g = (int64_t)gid - item_base;
-                    if (gcount != nullptr && first_chunk && lane == 0) atomicAdd(gcount + V.g_offset + g, nh);
+                    if (gcount != nullptr && first_chunk) {
+                        const uint32_t nh = wave_sum_u32(cnt - before);
+                        if (lane == 0) atomicAdd(gcount + V.g_offset + g, nh);
+                    }
                     float* slot = VS + (slot_base + g) * (int64_t)stride;
-                    if constexpr (CC == 0) {
-                        const float tv = wave_sum(sv);
-                        if (lane == 0) vs_add<DET>(VS, slot, tv, dsc.x);
-                    } else if constexpr (CC <= 3) {
-                        const float v1 = CC > 1 ? ss[CC > 1 ? 1 : 0] : 0.0f;
-                        const float v2 = CC > 2 ? ss[CC > 2 ? 2 : 0] : 0.0f;
-                        const float t = wave_sum4_transposed(sv, ss[0], v1, v2, lane);
-                        if (lane < 4u) {
-                            const int idx = transposed_index<4>(lane);
-                            if (idx == 0) {
-                                if (first_chunk) vs_add<DET>(VS, slot, t, dsc.x);
-                            } else if (idx <= CC && c_off + idx - 1 < C) {
-                                vs_add<DET>(VS, slot + c_off + idx, t, dsc.y);
-                            }
-                        }
-                    } else {
-                        const float tv = wave_sum(sv);
-                        const float t = wave_sum_transposed<CC>(ss, lane);
-                        if (lane == 0 && first_chunk) vs_add<DET>(VS, slot, tv, dsc.x);
-                        if (lane < (uint32_t)CC) {
-                            const int c = c_off + transposed_index<CC>(lane);
-                            if (c < C) vs_add<DET>(VS, slot + 1 + c, t, dsc.y);
-                        }
+                    const float tv = wave_sum(sv);
+                    const float t = wave_sum_transposed<CC>(ss, lane);
+                    if (lane == 0 && first_chunk) vs_add<DET>(VS, slot, tv, dsc.x);
+                    if (lane < (uint32_t)CC) {
+                        const int c = c_off + transposed_index<CC>(lane);
+                        if (c < C) vs_add<DET>(VS, slot + 1 + c, t, dsc.y);
                     }
                 }
                 if (alive == 0u) break;
@@ -287,18 +275,19 @@ __device__ __forceinline__ uint32_t accumulate_tile(
 }
 
 // CC: channels handled by this launch (chunk [c_off, c_off + CC) of C).
-// queue == nullptr: one tile per wave (4 per block) over a grid covering all
+// queue == nullptr: one tile per wave (kTileWaves a block) over a grid covering all
 // tiles.  Otherwise persistent: a fixed grid whose waves take tiles from the
 // counter *queue (zero before the launch) until none are left.  Either way
 // tiles come in the order `order` gives (nullptr: tile index order).
-// Waves per SIMD the register allocation is held to: the forms of up to
-// three channels fit seven (72 registers) and run faster there; wider ones
-// spill when held below their natural count and are left alone.
+// Waves per SIMD the register allocation is held to: the weights alone and one
+// channel fit seven (72 registers), two and three channels six (80; held to
+// seven they spill 18 values, 1.43 -> 1.54 ms on 300k Gaussians, 40 views);
+// wider ones are left alone.
 template <int CC>
-constexpr int acc_waves_per_simd() { return CC >= 1 && CC <= 3 ? 7 : 1; }
+constexpr int acc_waves_per_simd() { return CC <= 1 ? 7 : (CC <= 3 ? 6 : 1); }
 
 template <int CC, bool BF16, int BIN, bool DET>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(acc_waves_per_simd<CC>()))) void k_accumulate(
+__global__ __launch_bounds__(64 * kTileWaves) __attribute__((amdgpu_waves_per_eu(acc_waves_per_simd<CC>()))) void k_accumulate(
     const ViewInfo* __restrict__ views, int n_views, uint32_t n_tiles, const uint2* __restrict__ ranges,
     const uint32_t* __restrict__ pair_vals,
     const float4* __restrict__ rec, const uint32_t* __restrict__ items,
@@ -306,12 +295,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(acc_waves_p
     int per_view, BlendParams bp, float* __restrict__ VS, float2 dsc,
     unsigned long long* __restrict__ counter, uint32_t* __restrict__ gcount,
     uint32_t* __restrict__ queue, const uint32_t* __restrict__ order) {
-    __shared__ float4 srec1[4][64];
-    __shared__ float2 srec0[4][64];
+    __shared__ float4 srec1[kTileWaves][64];
+    __shared__ float2 srec0[kTileWaves][64];
     const uint32_t lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     uint32_t cnt = 0;
     if (queue == nullptr) {
-        const uint32_t wi = xcd_block(blockIdx.x, gridDim.x) * 4 + w;
+        const uint32_t wi = xcd_block<128 / kTileWaves>(blockIdx.x, gridDim.x) * kTileWaves + w;
         if (wi >= n_tiles) return;  // whole wave
         const uint32_t tile = queued_tile<BIN>(wi, order);  // blocks start in index order
         cnt = accumulate_tile<CC, BF16, BIN, DET>(tile, lane, views, n_views, ranges, pair_vals,
@@ -329,7 +318,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(acc_waves_p
                                                        per_view, bp, VS, dsc, gcount, srec1[w], srec0[w]);
         }
     }
-    if (c_off == 0 && lane == 0 && cnt) atomicAdd(counter, (unsigned long long)cnt);
+    if (c_off == 0) {
+        cnt = wave_sum_u32(cnt);
+        if (lane == 0 && cnt) atomicAdd(counter, (unsigned long long)cnt);
+    }
 }
 
 // ---- few tiles: one wave per 8x8 block ------------------------------------
@@ -444,8 +436,8 @@ static void launch_acc_k(const TileLists& tl, const void* targets, int C, bool p
                          float* VS, unsigned long long* counter, uint32_t* gcount, uint32_t* queues,
                          hipStream_t s, float2 dsc = make_float2(0.f, 0.f)) {
     const uint32_t n_wt = wave_tiles(tl.n_bins, BIN);
-    const uint32_t full = (n_wt + 3) / 4;
-    dim3 grid(queues ? std::min(full, kPersistentBlocks) : full), block(256);
+    const uint32_t full = (n_wt + kTileWaves - 1) / kTileWaves;
+    dim3 grid(queues ? std::min(full, kPersistentBlocks * 4 / kTileWaves) : full), block(64 * kTileWaves);
     int pass = 0;
     const int step = CC > 0 ? CC : C + 1;
     for (int c_off = 0; c_off < std::max(C, 1); c_off += step, ++pass) {

@@ -58,7 +58,7 @@ template <int CC>
 constexpr int adj_waves_per_simd() { return CC >= 1 && CC <= 3 ? 7 : 1; }
 
 template <int CC, bool BF16, bool GY, int BIN>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(adj_waves_per_simd<CC>()))) void k_blend_adjoint(
+__global__ __launch_bounds__(64 * kTileWaves) __attribute__((amdgpu_waves_per_eu(adj_waves_per_simd<CC>()))) void k_blend_adjoint(
     const ViewInfo* __restrict__ views, int n_views, uint32_t n_wt, const uint2* __restrict__ ranges,
     const uint32_t* __restrict__ pair_vals,
     const float4* __restrict__ rec, const uint32_t* __restrict__ items, const void* __restrict__ ypix, int C, int c_off,
@@ -68,11 +68,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(adj_waves_p
     // colours and offset, read back by every lane as broadcasts
     constexpr bool kLdsB = CC <= 3;
     constexpr int kGroup = 4;
-    __shared__ float4 srec1[4][64];
-    __shared__ float4 sbet[4][kLdsB ? 64 : 1];
-    __shared__ float2 srec0[4][64];
+    __shared__ float4 srec1[kTileWaves][64];
+    __shared__ float4 sbet[kTileWaves][kLdsB ? 64 : 1];
+    __shared__ float2 srec0[kTileWaves][64];
     const uint32_t lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const uint32_t wi = xcd_block(blockIdx.x, gridDim.x) * 4 + w;
+    const uint32_t wi = xcd_block<128 / kTileWaves>(blockIdx.x, gridDim.x) * kTileWaves + w;
     if (wi >= n_wt) return;  // whole wave
     const uint32_t wt = queued_tile<BIN>(wi, order);  // blocks start in index order
     const TileGeom tg = tile_geom<BIN>(wt, views, n_views);
@@ -425,7 +425,7 @@ template <int CC, bool GY>
 static void launch_badj_cc(const TileLists& tl, const void* ypix, int ydtype, int C, const float* beta,
                            BlendParams bp, float* grad_y, float* grad_o, hipStream_t s) {
     const uint32_t n_wt = wave_tiles(tl.n_bins, tl.bin);
-    dim3 grid((n_wt + 3) / 4), block(256);
+    dim3 grid((n_wt + kTileWaves - 1) / kTileWaves), block(64 * kTileWaves);
 #define GSC_BADJ(BFV, BINV)                                                                          \
     hipLaunchKernelGGL((k_blend_adjoint<CC, BFV, GY, BINV>), grid, block, 0, s, tl.views, tl.n_views, \
                        n_wt, tl.ranges, tl.pair_vals, tl.rec, tl.items, ypix, C, c_off, beta, bp,     \

@@ -190,18 +190,18 @@ void launch_view_adjoint(const ViewInfo* views, int n_views, int64_t N, const fl
 // images[row][c] = sum_g w_gp * gamma_gv[c]; every pixel of every tile is
 // written.  Same tile walk and blend decisions as accumulate_tile.
 template <int CC, int BIN>
-__global__ __launch_bounds__(256) void k_render(
+__global__ __launch_bounds__(64 * kTileWaves) void k_render(
     const ViewInfo* __restrict__ views, int n_views, uint32_t n_wt, const uint2* __restrict__ ranges,
     const uint32_t* __restrict__ pair_vals, const float4* __restrict__ rec,
     const uint32_t* __restrict__ items, const float* __restrict__ gamma, int C, int c_off, BlendParams bp, float* __restrict__ images,
     unsigned long long* __restrict__ counter, const uint32_t* __restrict__ order) {
     static_assert(CC <= 4, "one float4 of colours per entry");
     // the chunk's records and colours, read back by every lane as broadcasts
-    __shared__ float4 srec1[4][64];
-    __shared__ float4 scol[4][64];
-    __shared__ float2 srec0[4][64];
+    __shared__ float4 srec1[kTileWaves][64];
+    __shared__ float4 scol[kTileWaves][64];
+    __shared__ float2 srec0[kTileWaves][64];
     const uint32_t lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const uint32_t wi = xcd_block(blockIdx.x, gridDim.x) * 4 + w;
+    const uint32_t wi = xcd_block<128 / kTileWaves>(blockIdx.x, gridDim.x) * kTileWaves + w;
     if (wi >= n_wt) return;
     const uint32_t wt = queued_tile<BIN>(wi, order);  // blocks start in index order
     const TileGeom tg = tile_geom<BIN>(wt, views, n_views);
@@ -257,33 +257,34 @@ __global__ __launch_bounds__(256) void k_render(
                                     CC > 3 ? RC[CC > 3 ? 3 : 0] : 0.0f);
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
-        while (todo != 0u) {
-            const uint32_t j = (uint32_t)__builtin_ctzll(todo);
-            todo &= todo - 1u;
-            const uint32_t blocks = bcast_u(BL, j) & alive;
-            if (blocks == 0u) continue;
-            const float2 c0 = srec0[w][j];
-            const float4 c1 = srec1[w][j];
-            const float4 c4 = scol[w][j];
-            const float col[4] = {c4.x, c4.y, c4.z, c4.w};
-            const float dx[2] = {c0.x + lx[0], c0.x + lx[1]}, dy[2] = {c0.y + ly[0], c0.y + ly[1]};
-            const float a0[2] = {c1.x * dx[0] * dx[0], c1.x * dx[1] * dx[1]};
-            const float b0[2] = {c1.y * dx[0], c1.y * dx[1]};
-            uint32_t nh = 0;
+        // (liveness is refreshed every four entries: an entry after the last live
+        // pixel stopped meets T < t_min everywhere and adds nothing)
+        while (todo != 0u && alive != 0u) {
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                if (!((blocks >> k) & 1u)) continue;
-                const float q2 = fmaf(dy[k >> 1], fmaf(c1.z, dy[k >> 1], b0[k & 1]), a0[k & 1]);
-                uint64_t taken, kept;
-                const float w = pixel_step(q2, c1.w, T[k], qlim, amin, amax, tmin, taken, kept);
+            for (int u = 0; u < 4; ++u) {
+                const uint32_t j = todo != 0u ? (uint32_t)__builtin_ctzll(todo) : 0u;
+                const uint32_t blocks = todo != 0u ? bcast_u(BL, j) & alive : 0u;
+                todo &= todo - 1u;
+                if (blocks == 0u) continue;
+                const float2 c0 = srec0[w][j];
+                const float4 c1 = srec1[w][j];
+                const float4 c4 = scol[w][j];
+                const float col[4] = {c4.x, c4.y, c4.z, c4.w};
+                const float dx[2] = {c0.x + lx[0], c0.x + lx[1]}, dy[2] = {c0.y + ly[0], c0.y + ly[1]};
+                const float a0[2] = {c1.x * dx[0] * dx[0], c1.x * dx[1] * dx[1]};
+                const float b0[2] = {c1.y * dx[0], c1.y * dx[1]};
 #pragma unroll
-                for (int c = 0; c < CC; ++c) img[k][c] = fmaf(w, col[c], img[k][c]);
-                nh += (uint32_t)__popcll(taken);
-                if (kept == 0) alive &= ~(1u << k);
+                for (int k = 0; k < 4; ++k) {
+                    if (!((blocks >> k) & 1u)) continue;
+                    const float q2 = fmaf(dy[k >> 1], fmaf(c1.z, dy[k >> 1], b0[k & 1]), a0[k & 1]);
+                    const float w = lane_step(q2, c1.w, T[k], qlim, amin, amax, tmin, cnt);
+#pragma unroll
+                    for (int c = 0; c < CC; ++c) img[k][c] = fmaf(w, col[c], img[k][c]);
+                }
             }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) alive &= __builtin_amdgcn_ballot_w64(T[k] >= tmin) != 0 ? 15u : ~(1u << k);
             alive = (uint32_t)__builtin_amdgcn_readfirstlane((int)alive);
-            cnt += (uint32_t)__builtin_amdgcn_readfirstlane((int)nh);
-            if (alive == 0u) break;
         }
         __builtin_amdgcn_wave_barrier();  // the next chunk overwrites the records
     }
@@ -295,7 +296,10 @@ __global__ __launch_bounds__(256) void k_render(
         for (int c = 0; c < CC; ++c)
             if (c_off + c < C) images[row * C + c_off + c] = img[k][c];
     }
-    if (c_off == 0 && lane == 0 && cnt) atomicAdd(counter, (unsigned long long)cnt);
+    if (c_off == 0) {
+        cnt = wave_sum_u32(cnt);
+        if (lane == 0 && cnt) atomicAdd(counter, (unsigned long long)cnt);
+    }
 }
 
 // Few tiles: one wave per 8x8 block (walk_block), CC = 4 * EX channels per launch.
@@ -377,7 +381,7 @@ void launch_render(const TileLists& tl, const float* gamma, int C, BlendParams b
 #undef GSC_RENDERB
         return;
     }
-    dim3 grid((n_wt + 3) / 4), block(256);
+    dim3 grid((n_wt + kTileWaves - 1) / kTileWaves), block(64 * kTileWaves);
 #define GSC_RENDER(CCV, BINV)                                                                            \
     hipLaunchKernelGGL((k_render<CCV, BINV>), grid, block, 0, s, tl.views, tl.n_views, n_wt, tl.ranges, \
                        tl.pair_vals, tl.rec, tl.items, gamma, C, c_off, bp, images, counter, tl.order)

@@ -116,14 +116,6 @@ __device__ __forceinline__ int transposed_index(uint32_t lane) {
     }
     return idx;
 }
-
-// Four values at once (NV = 4); lane L < 4 holds value 2*(L&1) + ((L>>1)&1).
-__device__ __forceinline__ float wave_sum4_transposed(float v0, float v1, float v2, float v3,
-                                                      uint32_t lane) {
-    const float v[4] = {v0, v1, v2, v3};
-    return wave_sum_transposed<4>(v, lane);
-}
-
 __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v) {
     v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, false);
     v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, false);
@@ -184,7 +176,12 @@ __device__ __forceinline__ TileGeom tile_geom(uint32_t vt, const ViewInfo* __res
 // which read the same Gaussian records, and the quadrant waves of one
 // 32-pixel bin) share an L2, while the groups still start in order.  Blocks
 // of a last, incomplete group keep their index.  A bijection on [0, G).
-constexpr uint32_t kXcds = 8, kXcdRun = 32;
+constexpr uint32_t kXcds = 8;
+// Tiles (waves) per block of the tile kernels: a block holds its place on the CU
+// until its longest list ends (four a block: both adjoints 4.53 -> 4.48 ms, the
+// forwards within 1%; one: the same as two).
+constexpr uint32_t kTileWaves = 2;
+template <uint32_t kXcdRun = 32>
 __device__ __forceinline__ uint32_t xcd_block(uint32_t b, uint32_t G) {
     constexpr uint32_t group = kXcds * kXcdRun;
     if (b >= G - G % group) return b;
@@ -282,6 +279,22 @@ __device__ __forceinline__ float pixel_step(float q2, float opac, float& T, floa
     const bool keep = T >= tmin;
     kept = __builtin_amdgcn_ballot_w64(keep);
     taken = __builtin_amdgcn_ballot_w64(inq) & __builtin_amdgcn_ballot_w64(ina) & kept;
+    return keep ? wt : 0.0f;
+}
+
+// The same step with the contribution counted in the lane (n): no scalar
+// instruction waits on its comparisons.  An alpha outside the ellipse is -1, which
+// fails alpha >= alpha_min (never negative).
+__device__ __forceinline__ float lane_step(float q2, float opac, float& T, float qlim, float amin, float amax,
+                                           float tmin, uint32_t& n) {
+    const float al = __builtin_amdgcn_fmed3f(opac * __builtin_amdgcn_exp2f(q2), 0.0f, amax);
+    const float ai = q2 >= qlim ? al : -1.0f;
+    const bool cand = ai >= amin;
+    const float ae = cand ? ai : 0.0f;
+    const float wt = T * ae;
+    T = fmaf(-T, ae, T);
+    const bool keep = T >= tmin;
+    n += (cand & keep) ? 1u : 0u;
     return keep ? wt : 0.0f;
 }
 
