@@ -616,28 +616,33 @@ void radix_sort(uint32_t* keys, uint32_t* vals, uint32_t* keys_alt, uint32_t* va
 // Each view's items by depth, ties by Gaussian index; the order is view by
 // view, so that a view's records lie together (3.2 MB for 100k Gaussians, less
 // than an XCD's L2) for the random reads of the masks and the tile kernels.
-// Views of up to kViewSort items are sorted by one block each, in LDS and one
-// launch; larger ones in four passes over segments, the first of which forms
-// the keys itself.  us a call, one sort of the whole batch -> by view: 2k
+// Views of up to kViewSort items are sorted in LDS, kRun items a block; where a
+// view has several such runs, a second launch ranks each item among the others
+// (binary searches in the other runs, which L2 holds).  One block a view for
+// all its items left most of the chip idle: 9 views of 20000 items 77 -> 38 us.
+// Larger views take four passes over segments, the first of which forms the
+// keys itself.  us a call, one sort of the whole batch -> by view: 2k
 // Gaussians x 8 views 220 -> 149 (13 launches of the call become one); 500k x
 // 100 views 23371 -> 22795 (k_group_masks 1784 -> 1453 us, k_project 1508 ->
 // 1165: their reads hit L2), 100k x 50 views 1813 -> 1816.
 constexpr uint32_t kViewThreads = 1024, kViewWaves = kViewThreads / 64;
-constexpr uint32_t kViewSort = 24576;
+constexpr uint32_t kRun = 4096, kRuns = 6, kViewSort = kRun * kRuns;
 
-// IPT: items per thread at most.  The item's index within the view is 16 bits.
-// Only the bits in which the view's depths differ are sorted.
-template <int IPT>
-__global__ __launch_bounds__(kViewThreads) void k_sort_view(SortSource S, uint32_t* __restrict__ vals) {
-    constexpr uint32_t kCap = IPT * kViewThreads;
+// One run (blockIdx.y) of one view (blockIdx.x), kRun items at most.  Only the
+// bits in which the run's depths differ are sorted.  keys: the run's sorted
+// keys as well (views of several runs).
+__global__ __launch_bounds__(kViewThreads) void k_sort_view(SortSource S, uint32_t* __restrict__ vals,
+                                                            uint32_t* __restrict__ keys) {
+    constexpr uint32_t IPT = kRun / kViewThreads, kCap = kRun;
     __shared__ uint32_t skey[kCap];
     __shared__ uint16_t sidx[kCap];
     __shared__ uint16_t cnt[kViewWaves][256];
     __shared__ uint32_t wsum[kViewWaves];
     __shared__ uint32_t range[2];
     const ViewInfo& V = S.views[blockIdx.x];
-    const uint32_t n = V.n_gauss;
-    if (n == 0u) return;
+    const uint32_t first = blockIdx.y * kRun;
+    if (first >= V.n_gauss) return;
+    const uint32_t n = min(V.n_gauss - first, kRun);
     const uint32_t tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const uint32_t rounds = (n + kViewThreads - 1) / kViewThreads;  // uniform, <= IPT
     const uint32_t base = w * rounds * 64;                          // the wave's places
@@ -652,7 +657,7 @@ __global__ __launch_bounds__(kViewThreads) void k_sort_view(SortSource S, uint32
         if (it >= rounds) break;
         const uint32_t i = base + it * 64 + lane;
         id[it] = i;
-        kk[it] = i < n ? depth_key(S, V, (uint64_t)V.g_offset + i) : 0xFFFFFFFFu;
+        kk[it] = i < n ? depth_key(S, V, (uint64_t)V.g_offset + first + i) : 0xFFFFFFFFu;
         if (kk[it] != 0xFFFFFFFFu) {
             lo = min(lo, kk[it]);
             hi = max(hi, kk[it]);
@@ -749,8 +754,43 @@ __global__ __launch_bounds__(kViewThreads) void k_sort_view(SortSource S, uint32
     for (uint32_t it = 0; it < (uint32_t)IPT; ++it) {
         if (it >= rounds) break;
         const uint32_t i = base + it * 64 + lane;
-        if (i < n) vals[V.item_base + i] = V.item_base + id[it];
+        if (i < n) {
+            vals[V.item_base + first + i] = V.item_base + first + id[it];
+            if (keys) keys[V.item_base + first + i] = kk[it] == top ? 0xFFFFFFFFu : kk[it] + lo;
+        }
     }
+}
+
+// Places of a view's (blockIdx.x) sorted runs' items in the view's order: an
+// item's place in its run, plus the items of the other runs before it (equal keys
+// in an earlier run come first: the order of the items).
+__global__ __launch_bounds__(256) void k_merge_runs(const ViewInfo* __restrict__ views, const uint32_t* __restrict__ keys,
+                                                    const uint32_t* __restrict__ in, uint32_t* __restrict__ out) {
+    const ViewInfo& V = views[blockIdx.x];
+    const uint32_t n = V.n_gauss, i = blockIdx.y * 256 + threadIdx.x;
+    if (i >= n) return;
+    const uint32_t* k = keys + V.item_base;
+    const uint32_t key = k[i], run = i / kRun;
+    uint32_t at[kRuns];  // items of each run before this one
+#pragma unroll
+    for (uint32_t q = 0; q < kRuns; ++q) at[q] = 0u;
+    // all searches step together: at[q] items are known to come before
+#pragma unroll
+    for (uint32_t d = kRun; d >= 1u; d >>= 1) {
+#pragma unroll
+        for (uint32_t q = 0; q < kRuns; ++q) {
+            const uint32_t m = min(n > q * kRun ? n - q * kRun : 0u, kRun);  // the run's items
+            const uint32_t p = at[q] + d;
+            if (p <= m) {
+                const uint32_t x = k[q * kRun + p - 1u];
+                if (x < key || (x == key && q < run)) at[q] = p;
+            }
+        }
+    }
+    uint32_t place = i - run * kRun;
+#pragma unroll
+    for (uint32_t q = 0; q < kRuns; ++q) place += q == run ? 0u : at[q];
+    out[V.item_base + place] = in[V.item_base + i];
 }
 
 DepthSortShape depth_sort_shape(uint32_t max_n, uint64_t n_items) {
@@ -778,9 +818,13 @@ void launch_depth_sort(const ViewInfo* views, int n_views, uint32_t n_items, con
     src.znear = bp.znear;
     src.alpha_min = bp.alpha_min;
     if (d.in_lds) {
-        const dim3 grid((unsigned)n_views), block(kViewThreads);
-        if (max_n <= 4 * kViewThreads) hipLaunchKernelGGL(k_sort_view<4>, grid, block, 0, s, src, vals);
-        else hipLaunchKernelGGL(k_sort_view<(int)(kViewSort / kViewThreads)>, grid, block, 0, s, src, vals);
+        const unsigned runs = (max_n + kRun - 1) / kRun;
+        const dim3 grid((unsigned)n_views, runs), block(kViewThreads);
+        uint32_t* none = nullptr;
+        hipLaunchKernelGGL(k_sort_view, grid, block, 0, s, src, runs > 1 ? vals_alt : vals, runs > 1 ? keys : none);
+        if (runs > 1)
+            hipLaunchKernelGGL(k_merge_runs, dim3((unsigned)n_views, (max_n + 255) / 256), dim3(256), 0, s, views,
+                               keys, vals_alt, vals);
         return;
     }
     const uint32_t seg_tiles = (max_n + d.tile - 1) / d.tile;
