@@ -475,14 +475,19 @@ void launch_blend_adjoint(const TileLists& tl, const void* ypix, int ydtype, int
 // VS[j][g] = (V_gj, S_gj[0..C)) (per_view), or phi = Y0 and one summed slot
 // per Gaussian (L = 0).  One thread per (Gaussian, CH channels); FP64 sums.
 template <int L>
-constexpr int fold_rhs_channels() { return L >= 3 ? 2 : 4; }
+constexpr int fold_rhs_channels() { return L >= 3 ? 3 : 4; }
 
+// Views are taken four at a time, their visibilities loaded together (one after
+// the other, each view's loads waited for the last view's), and degree 3 takes
+// three channels a thread (two read every slot twice at C = 3).  300k Gaussians,
+// 40 views, degree 3: 197 -> 146 us.
 template <int L>
-__global__ void k_fold_rhs(const ViewInfo* __restrict__ views, int n_views,
+__global__ __launch_bounds__(128) void k_fold_rhs(const ViewInfo* __restrict__ views, int n_views,
                            const float* __restrict__ means, const float* __restrict__ VS,
                            int per_view, int64_t N, int C, float* __restrict__ out) {
     constexpr int NB = (L + 1) * (L + 1);
     constexpr int CH = fold_rhs_channels<L>();
+    constexpr int VB = 4;
     const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int c0 = blockIdx.y * CH;
     if (g >= N) return;
@@ -494,24 +499,35 @@ __global__ void k_fold_rhs(const ViewInfo* __restrict__ views, int n_views,
         for (int c = 0; c < CH; ++c) acc[m][c] = 0.0;
     const int nv = per_view ? n_views : 1;
     const float mx = means[3 * g], my = means[3 * g + 1], mz = means[3 * g + 2];
-    for (int v = 0; v < nv; ++v) {
-        const float* slot = VS + ((per_view ? views[v].vs_base : 0) + g) * stride;
-        if (slot[0] == 0.0f) continue;  // no contribution in this view
-        float phi[NB];
-        if (per_view) {
-            const ViewInfo& Vw = views[v];
-            const float dx = mx - (float)Vw.centre[0], dy = my - (float)Vw.centre[1],
-                        dz = mz - (float)Vw.centre[2];
-            const float inv = rsqrtf(dx * dx + dy * dy + dz * dz);
-            sh_eval<float, L>(dx * inv, dy * inv, dz * inv, phi);
-        } else {
-            sh_eval<float, L>(0.0f, 0.0f, 1.0f, phi);
+    for (int v0 = 0; v0 < nv; v0 += VB) {
+        float x[VB][CH], w[VB];
+#pragma unroll
+        for (int u = 0; u < VB; ++u) {
+            const int v = min(v0 + u, nv - 1);
+            const float* slot = VS + ((per_view ? views[v].vs_base : 0) + g) * stride;
+            w[u] = v0 + u < nv ? slot[0] : 0.0f;
+#pragma unroll
+            for (int c = 0; c < CH; ++c) x[u][c] = slot[1 + min(c0 + c, C - 1)];
         }
 #pragma unroll
-        for (int c = 0; c < CH; ++c) {
-            const double sc = (c0 + c < C) ? (double)slot[1 + c0 + c] : 0.0;
+        for (int u = 0; u < VB; ++u) {
+            if (w[u] == 0.0f) continue;  // no contribution in this view
+            float phi[NB];
+            if (per_view) {
+                const ViewInfo& Vw = views[v0 + u];
+                const float dx = mx - (float)Vw.centre[0], dy = my - (float)Vw.centre[1],
+                            dz = mz - (float)Vw.centre[2];
+                const float inv = rsqrtf(dx * dx + dy * dy + dz * dz);
+                sh_eval<float, L>(dx * inv, dy * inv, dz * inv, phi);
+            } else {
+                sh_eval<float, L>(0.0f, 0.0f, 1.0f, phi);
+            }
 #pragma unroll
-            for (int m = 0; m < NB; ++m) acc[m][c] = fma((double)phi[m], sc, acc[m][c]);
+            for (int c = 0; c < CH; ++c) {
+                const double sc = (double)x[u][c];
+#pragma unroll
+                for (int m = 0; m < NB; ++m) acc[m][c] = fma((double)phi[m], sc, acc[m][c]);
+            }
         }
     }
 #pragma unroll
