@@ -1421,14 +1421,12 @@ gsc_status gsc_colorize_refine(gsc_ctx* ctx, const float* means, const float* sc
         st = for_view_batches(ctx, all.data(), n_cams, means, opacities, N, bp, s,
                               [&](int v0, int nv, const Binned& bn) -> gsc_status {
             GSC_HIP(ctx->gamma.ensure(4 * (size_t)nv * (size_t)N * (size_t)C));
-            int max_px = 0;
-            for (int k = 0; k < nv; ++k) max_px = std::max(max_px, all[v0 + k].width * all[v0 + k].height);
             const TileLists tl = tile_lists(ctx, nv, bn);
             StageTimer t(ctx, s, GSC_STAGE_BLEND);
             launch_view_colors(ctx->views.as<ViewInfo>(), nv, N, means, coeffs, C, sh_deg,
                                ctx->gamma.as<float>(), s);
-            launch_render(tl, ctx->gamma.as<float>(), C, bp, ctx->img.as<float>(), d_pass_counter, s);
-            launch_residual(ctx->views.as<ViewInfo>(), nv, max_px, targets, tdtype, C, ctx->img.as<float>(), s);
+            launch_render(tl, ctx->gamma.as<float>(), C, bp, ctx->img.as<float>(), d_pass_counter, s,
+                          RenderResidual{targets, tdtype == GSC_BF16});
             uint32_t* queues = nullptr;
             if (tl.order != nullptr && (chunk & kChunkMfma)) {
                 GSC_HIP(ctx->queues.ensure(4 * (size_t)(kMaxC + 1)));

@@ -317,8 +317,13 @@ void launch_accumulate(const TileLists& tl, const void* targets, int tdtype, int
 void launch_view_colors(const ViewInfo* views, int n_views, int64_t N, const float* means,
                         const float* coeffs, int C, int sh_deg, float* gamma, hipStream_t s);
 
+// Targets to subtract a render from (y null: none).
+struct RenderResidual {
+    const void* y = nullptr;
+    int bf16 = 0;
+};
 void launch_render(const TileLists& tl, const float* gamma, int C, BlendParams bp, float* images,
-                   unsigned long long* counter, hipStream_t s);
+                   unsigned long long* counter, hipStream_t s, const RenderResidual& res = {});
 
 // Fold the per-view sums into the regularised normal equations and solve.
 // per_view: VS holds [n_views][N][C+1] (else [N][C+1] summed over views).
@@ -350,12 +355,6 @@ inline int refine_factor_words(int sh_deg) {
 void launch_refine_update(const ViewInfo* views, int n_views, const float* means, const float* VS,
                           int64_t N, int C, int sh_deg, const double* lam_nb, const double* factor,
                           const float* w, const uint8_t* status, float* coeffs, hipStream_t s);
-
-// Residual targets of the views of a batch, in place: img[row][c] =
-// y[row][c] - img[row][c] for every pixel of the n_views views (y float32
-// or bfloat16).
-void launch_residual(const ViewInfo* views, int n_views, int max_pixels, const void* y, int ydtype,
-                     int C, float* img, hipStream_t s);
 
 // Weights-only accumulate: V[slot] += sum_p w (stride 1; slots as in launch_accumulate).
 void launch_accumulate_weights(const TileLists& tl, bool per_view, BlendParams bp, float* V,

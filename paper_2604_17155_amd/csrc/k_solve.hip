@@ -871,29 +871,6 @@ void launch_refine_update(const ViewInfo* views, int n_views, const float* means
     }
 }
 
-// Residual targets in place over the pixels of a batch's views (grid y: view).
-__global__ __launch_bounds__(256) void k_residual(const ViewInfo* __restrict__ views, const void* __restrict__ y,
-                                                  int ydtype, int C, float* __restrict__ img) {
-    const ViewInfo& V = views[blockIdx.y];
-    const int64_t n = (int64_t)V.width * V.height * C;
-    const int64_t base = V.pixel_offset * (int64_t)C;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t e = base + i;
-        const float yv = ydtype == GSC_BF16 ? __uint_as_float((uint32_t)((const uint16_t*)y)[e] << 16)
-                                            : ((const float*)y)[e];
-        img[e] = yv - img[e];
-    }
-}
-
-void launch_residual(const ViewInfo* views, int n_views, int max_pixels, const void* y, int ydtype,
-                     int C, float* img, hipStream_t s) {
-    if (n_views <= 0 || max_pixels <= 0) return;
-    const int64_t per = (int64_t)max_pixels * C;
-    const unsigned bx = (unsigned)std::min<int64_t>((per + 255) / 256, 1024);
-    hipLaunchKernelGGL(k_residual, dim3(bx, (unsigned)n_views), dim3(256), 0, s, views, y, ydtype, C, img);
-}
-
 // L = 0 adjoint: A_g + w_g Lambda = w_g (Y0^2 + lambda_0).
 __global__ void k_adjoint_dc(const float* __restrict__ W, int64_t N, int C, double lam0,
                              const float* __restrict__ gc, const float* __restrict__ cin,
