@@ -549,7 +549,9 @@ gsc_status bin_views(gsc_ctx* ctx, const ViewInfo* all, int v0, int nv,
     if (ctx->opt.schedule != GSC_SCHEDULE_GRID) GSC_HIP(ctx->order.ensure(4 * tile_order_words((uint32_t)tiles)));
     // the buffer in which the sorted keys end comes last (its place takes the
     // bin lists of the allocation-free call)
-    const bool odd = ((gbits + 7) / 8) % 2 != 0;
+    uint64_t max_groups = 0;
+    for (int k = 0; k < nv; ++k) max_groups = std::max(max_groups, view_groups(all[v0 + k]));
+    const bool odd = group_sort_by_view(max_groups, gbits, nv, (uint32_t)pairs) || ((gbits + 7) / 8) % 2 != 0;
     GSC_HIP(ctx->pvals.ensure(4 * pairs + 4));
     GSC_HIP(ctx->pvals_alt.ensure(4 * pairs + 4));
     GSC_HIP((odd ? ctx->pkeys : ctx->pkeys_alt).ensure(4 * pairs + 4));
@@ -562,9 +564,9 @@ gsc_status bin_views(gsc_ctx* ctx, const ViewInfo* all, int v0, int nv,
     }
     StageTimer t(ctx, s, GSC_STAGE_TILE_SORT);
     bool in_alt = false;
-    radix_sort(ctx->pkeys.as<uint32_t>(), ctx->pvals.as<uint32_t>(), ctx->pkeys_alt.as<uint32_t>(),
-               ctx->pvals_alt.as<uint32_t>(), (uint32_t)pairs, gbits,
-               ctx->sort_scratch.as<uint32_t>(), s, nullptr, &in_alt);
+    launch_group_sort(dviews, nv, ni, max_groups, offsets, ctx->pkeys.as<uint32_t>(), ctx->pvals.as<uint32_t>(),
+                      ctx->pkeys_alt.as<uint32_t>(), ctx->pvals_alt.as<uint32_t>(), (uint32_t)pairs, gbits,
+                      ctx->sort_scratch.as<uint32_t>(), s, nullptr, &in_alt);
     GSC_LAUNCHED("group sort");
     if (in_alt) {  // the sorted pairs are in the alternate buffers: swap roles, no copy
         std::swap(ctx->pkeys, ctx->pkeys_alt);
@@ -776,6 +778,7 @@ struct gsc_plan {
         uint32_t n_items, n_tiles, n_groups;
         uint32_t group_cap, pair_cap;  // group pairs and bin pairs
         int group_bits;
+        uint64_t max_groups;  // of a view
         uint32_t max_n, uniform_n, sort_tiles;
         DepthSortShape dsort;
     };
@@ -865,6 +868,8 @@ void plan_number_views(gsc_plan* P) {
         b.n_groups = (uint32_t)groups;
         b.n_items = (uint32_t)items;
         b.group_bits = bits_for(groups + 1);
+        b.max_groups = 0;
+        for (int k = 0; k < b.nv; ++k) b.max_groups = std::max(b.max_groups, view_groups(P->views[b.v0 + k]));
     }
 }
 
@@ -919,9 +924,9 @@ gsc_status plan_bin_batch(gsc_plan* P, const gsc_plan::Batch& b, hipStream_t s) 
     {
         StageTimer t(ctx, s, GSC_STAGE_TILE_SORT);
         bool in_alt = false;
-        radix_sort(P->pkeys.as<uint32_t>(), P->pvals.as<uint32_t>(), P->pkeys_alt.as<uint32_t>(),
-                   P->pvals_alt.as<uint32_t>(), b.group_cap, b.group_bits,
-                   P->sort_scratch.as<uint32_t>(), s, d_live, &in_alt);
+        launch_group_sort(dv, b.nv, b.n_items, b.max_groups, offsets, P->pkeys.as<uint32_t>(), P->pvals.as<uint32_t>(),
+                          P->pkeys_alt.as<uint32_t>(), P->pvals_alt.as<uint32_t>(), b.group_cap, b.group_bits,
+                          P->sort_scratch.as<uint32_t>(), s, d_live, &in_alt);
         if (in_alt) {  // swap roles instead of copying; every run swaps alike
             std::swap(P->pkeys, P->pkeys_alt);
             std::swap(P->pvals, P->pvals_alt);

@@ -251,6 +251,14 @@ void launch_tile_order(const uint2* ranges, uint32_t n_bins, uint32_t* order, hi
 void radix_sort(uint32_t* keys, uint32_t* vals, uint32_t* keys_alt, uint32_t* vals_alt,
                 uint32_t n, int bits, uint32_t* scratch, hipStream_t s, const uint32_t* n_dev,
                 bool* result_in_alt);
+// The same for the group pairs of a batch's views (keys: global groups, `bits` of
+// them; offsets: the emission's places of the items; max_groups: of a view), view
+// by view where group_sort_by_view says so, which is one pass.
+bool group_sort_by_view(uint64_t max_groups, int bits, int n_views, uint32_t n);
+void launch_group_sort(const ViewInfo* views, int n_views, uint32_t n_items, uint64_t max_groups,
+                       const uint32_t* offsets, uint32_t* keys, uint32_t* vals, uint32_t* keys_alt,
+                       uint32_t* vals_alt, uint32_t n, int bits, uint32_t* scratch, hipStream_t s,
+                       const uint32_t* n_dev, bool* result_in_alt);
 
 // Accumulate variants ("chunks"): the channels per launch (launches =
 // ceil(C / channels)), plus kChunkMfma for the matrix-core forms: BF16

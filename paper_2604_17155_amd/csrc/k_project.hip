@@ -254,7 +254,8 @@ __global__ __launch_bounds__(256) void k_emit(const ViewInfo* __restrict__ views
                 });
             // The walk above and the one that counted are the same code on the
             // same record; should they ever disagree, unused slots get a group
-            // id past the last one, which sorts last and is ignored.
+            // id past the last one, which sorts last (of all, or of its view's) and
+            // is ignored.
             while (off < end) put(sentinel);
         }
     }
@@ -383,7 +384,7 @@ __global__ __launch_bounds__(256) void k_group_masks(GroupLists G, BlendParams b
             for (int q = 0; q < 16; ++q)
                 c[q] += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64((((q < 8 ? t.x : t.y) >> (4 * (q & 7))) & 1u) != 0u));
             // the next group among these 64 pairs, if any
-            const uint64_t later = __builtin_amdgcn_ballot_w64(key > g && key != 0xFFFFFFFFu);
+            const uint64_t later = __builtin_amdgcn_ballot_w64(key > g && key < G.n_groups);
             if (later == 0) break;  // uniform
             leave();
             g = (uint32_t)__builtin_amdgcn_readlane((int)key, __builtin_ctzll(later));
