@@ -298,7 +298,7 @@ gsc_status validate_options(const gsc_options* o) {
 
 // Automatic bin size.  32-pixel bins cut the (bin, Gaussian) pairs to sort
 // by ~2.5x once footprints span several 16-pixel tiles, at the price of a
-// coarser band cull in the blend; 16-pixel bins win for small footprints.
+// coarser block cull in the blend; 16-pixel bins win for small footprints.
 // The estimate of the footprint diameter is 6 sigma with sigma the mean axis
 // scale projected at the distance from each camera to the centroid.
 constexpr double kBin32Diameter = 24.0;  // pixels

@@ -308,7 +308,8 @@ inline bool split_sums(bool per_view, int tdtype, int C, int chunk) {
 // kChunkMfma | 16, 32 or 64 for BF16 targets; anything else picks
 // accumulate_chunk(C, tdtype)).  queues (device, one word per channel pass,
 // zeroed here by a fill kernel): persistent launches of kPersistentBlocks
-// blocks that take tiles from a counter; nullptr: one block per four tiles.
+// blocks that take tiles from a counter; nullptr: a block per kTileWaves tiles.
+// split_n: the slots of split sums (see sum_rows), 0: interleaved.
 // det (non-null): deterministic form.  VS holds 64-bit fixed-point words
 // (zero before the first launch); each tile's share is scaled by det->x
 // (visibility column) or det->y (channel columns), powers of two, and added

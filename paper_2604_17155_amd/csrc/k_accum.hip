@@ -36,7 +36,7 @@ __device__ __forceinline__ void vs_add(float* VS, float* p, float v, float scale
 
 // One tile, by one wave: blend its pixels front to back and add each
 // Gaussian's tile share of V and S (channels [c_off, c_off + CC) of C) to its
-// slot.  Returns the wave's accepted contributions (uniform).
+// slot.  Returns the accepted contributions of the lane's pixels.
 //
 // A pixel that stopped has T < t_min (outside the image it starts at
 // kOutsideT).  Blocks are skipped when the Gaussian's footprint misses them or

@@ -1,8 +1,8 @@
 // Device-wide exclusive scan and stable LSD radix sort (digits of up to 8 bits).
 //
-// The sort orders the (view, Gaussian) items by depth and then the emitted
-// (tile, item) pairs by tile.  Stability of every pass is what carries the
-// depth order (and the index tie-break) into each tile's list.
+// The sorts order each view's items by depth and then the emitted (group, item)
+// pairs by group of 4x4 bins.  Stability of every pass is what carries the depth
+// order (and the index tie-break) into each group's, and so each bin's, list.
 #include <algorithm>
 
 #include "gsc_internal.h"

@@ -264,7 +264,7 @@ __device__ __forceinline__ float uniform_in_vgpr(float x) {
 // alpha T (0 unless used); `taken` gets the wave's lanes that contributed,
 // built from one ballot per condition (each a compare the step makes
 // anyway); `kept` the lanes still live after the step (empty: every pixel of
-// the band has stopped and the band can be retired).
+// the block has stopped and the block can be retired).
 // Pixels outside the image start at kOutsideT (negative): T (1 - alpha)
 // stays negative and fails the test for any t_min >= 0.
 constexpr float kOutsideT = -1.0f;
