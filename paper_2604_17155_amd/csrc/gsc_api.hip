@@ -1319,7 +1319,6 @@ gsc_status gsc_colorize_noalloc(gsc_ctx* ctx, const float* means, const float* s
     if ((st = refuse_capture(s, "gsc_colorize_noalloc")) != GSC_OK) return st;
     memset(&ctx->stats, 0, sizeof(ctx->stats));
     ctx->stats_pending = false;
-    ctx->stats_pending = false;
     if (N == 0) return GSC_OK;
     std::lock_guard<std::mutex> lock(g_noalloc_mu);
     void* base = nullptr;
