@@ -96,9 +96,9 @@ MEASURED_TRAFFIC = {
     # HBM bytes per accumulate launch: FETCH_SIZE x 2 + WRITE_SIZE x 1 (the
     # factors a plain 256 MiB device copy gives), averaged over the launches
     # of one step; valid while the accumulate's sources hash to "sources"
-    "relight": {"bytes": 2.207e9, "sources": "4a382471bd57137b"},
-    "features": {"bytes": 2.362e10, "sources": "4a382471bd57137b"},
-    "batched": {"bytes": 7.689e9, "sources": "4a382471bd57137b"},
+    "relight": {"bytes": 1.09e+09, "sources": "a037dfafd9481a1b"},
+    "features": {"bytes": 2.159e+10, "sources": "a037dfafd9481a1b"},
+    "batched": {"bytes": 5.645e+09, "sources": "a037dfafd9481a1b"},
 }
 ACCUMULATE_SOURCES = ("paper_2604_17155_amd/csrc/k_accum.hip", "paper_2604_17155_amd/csrc/wave_ops.h",
                       "paper_2604_17155_amd/csrc/k_sort.hip",    # the tile order
