@@ -338,7 +338,7 @@ struct WalkLds {
     float4 ex[EX > 0 ? EX : 1][EX > 0 ? 64 : 1];
 };
 
-// Up to kWalkEntries entries, front to back.
+// Up to kWalkEntries entries, front to back (past n: the last one again, weight 0).
 template <int EX>
 struct WalkGroup {
     uint32_t item[kWalkEntries];     // their batch items (uniform)
@@ -400,10 +400,13 @@ __device__ __forceinline__ void walk_block(const TileGeom& tg, uint32_t kq, uint
             float2 c0[kWalkEntries];
             float4 c1[kWalkEntries];
             bool has[kWalkEntries];
+            uint32_t j = 0;
 #pragma unroll
             for (int u = 0; u < kWalkEntries; ++u) {
                 has[u] = todo != 0u;
-                const uint32_t j = has[u] ? (uint32_t)__builtin_ctzll(todo) : 0u;
+                // (a slot past the last entry repeats that entry with weight 0: its
+                // extra values may be infinite or NaN, and this one reaches the block)
+                j = has[u] ? (uint32_t)__builtin_ctzll(todo) : j;
                 todo &= todo - 1u;
                 g.item[u] = bcast_u(cur.item, j);
                 c0[u] = L.rec0[j];
