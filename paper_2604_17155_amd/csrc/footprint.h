@@ -20,7 +20,14 @@ __device__ inline float reach_q(float o, const BlendParams& bp) {
 }
 
 // The ellipse {q <= qmax} of a record, q = a (dx + b dy / a)^2 + cq dy^2 with
-// (dx, dy) the offset from the projected centre.
+// (dx, dy) the offset from the projected centre; all of it in the record's own
+// scale (-K times the conic and qmax), as the blend evaluates it.
+//
+// The determinant of a needle is a small difference of products (1e-5 of them at
+// 200 pixels sigma): each product's rounding error is added back by an fma, and the
+// coefficients are not rescaled first, so that the ellipse is the record's to a few
+// ulp.  Rescaled, with plain products, the row reach of 15% of needles of 100 to 200
+// pixels sigma, and 31% up to 400, fell short of the record's by up to 10 pixels.
 struct Ellipse {
     float bia;  // b / a
     float qa;   // qmax / a, widened by 1e-4 in the half width it gives
@@ -30,18 +37,18 @@ struct Ellipse {
 };
 __device__ inline bool make_ellipse(float4 r1, float qmax, Ellipse& e) {
 #pragma clang fp contract(off)
-    constexpr float kInvK = (float)(1.0 / kExp2Scale);
-    const float a = r1.x * kInvK, b = 0.5f * r1.y * kInvK, c = r1.z * kInvK;
-    const float det = a * c - b * b;
-    if (!(a > 0.0f && det > 0.0f && qmax > 0.0f)) return false;
+    const float a = -r1.x, b = -0.5f * r1.y, c = -r1.z, qm = qmax * (float)-kExp2Scale;
+    const float bb = b * b;
+    const float det = fmaf(a, c, -bb) - fmaf(b, b, -bb);
+    if (!(a > 0.0f && det > 0.0f && qm > 0.0f)) return false;
     const float ia = __builtin_amdgcn_rcpf(a), cq = det * ia;
     e.bia = b * ia;
-    e.qa = qmax * ia * 1.0002f;
+    e.qa = qm * ia * 1.0002f;
     e.ca = cq * ia * 1.0002f;
-    e.ry = __builtin_amdgcn_sqrtf(qmax * __builtin_amdgcn_rcpf(cq)) * 1.0001f + 0.01f;
+    e.ry = __builtin_amdgcn_sqrtf(qm * __builtin_amdgcn_rcpf(cq)) * 1.0001f + 0.01f;
     // dy = -sqrt(qmax / Sxx) Sxy with Sxx = c / det, Sxy = -b / det
     // (= sqrt(qmax / (c det)) b)
-    e.dyl = __builtin_amdgcn_sqrtf(qmax * __builtin_amdgcn_rcpf(c * det)) * b;
+    e.dyl = __builtin_amdgcn_sqrtf(qm * __builtin_amdgcn_rcpf(c * det)) * b;
     return true;
 }
 // Left and right edge over the rows [sa, sb] (row offsets from the centre) of
