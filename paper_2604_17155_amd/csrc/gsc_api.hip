@@ -149,6 +149,7 @@ struct gsc_ctx {
     int cache_bin = 16;
     uint32_t cache_tiles = 0;
     uint64_t cache_items = 0;
+    uint64_t cache_pairs_counted = 0;  // pairs_counted of the call that binned
     // device scratch
     DevBuf views, views_all, cov, keys, vals, keys_alt, vals_alt, rec,
         sort_scratch, pkeys, pvals, pkeys_alt, pvals_alt, granges, gfirst, gcounts, lists, ranges, vs, gamma, bbar, misc, order, queues,
@@ -663,6 +664,7 @@ gsc_status for_view_batches(gsc_ctx* ctx, const ViewInfo* all, int n_cams,
         ctx->cache_bin = ctx->bin;
         ctx->cache_tiles = last.n_tiles;
         ctx->cache_items = last.n_items;
+        ctx->cache_pairs_counted = ctx->pairs_counted;
     }
     return GSC_OK;
 }
@@ -699,7 +701,9 @@ gsc_status ensure_common(gsc_ctx* ctx, const float* means, const float* scales,
     if (!ctx->h_total) GSC_HIP(hipHostMalloc((void**)&ctx->h_total, 64));
     if (reuse) {  // bin size and packed geometry of the cached binning
         ctx->bin = ctx->cache_bin;
-        // (the bin pair count of the cached binning stays)
+        // (the cached binning's pairs: the device count stays, the counted part
+        // may have been an allocation-free call's since)
+        ctx->pairs_counted = ctx->cache_pairs_counted;
         launch_fill_u32(ctx->misc.as<uint32_t>(), 0u, 16, s);
         return GSC_OK;
     }
