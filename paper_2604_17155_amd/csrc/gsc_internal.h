@@ -232,7 +232,8 @@ void launch_tile_ranges(const uint32_t* sorted_keys, uint32_t n_pairs, uint32_t 
 
 void launch_fill_u32(uint32_t* p, uint32_t v, uint64_t n, hipStream_t s);
 
-// Exclusive scan of n uint32 values; total written to *total (device). Scratch
+// Exclusive scan of n uint32 values (sums stay at 2^32 - 1 from there on); total
+// written to *total (device). Scratch
 // must hold scan_scratch_words(n) words.
 size_t scan_scratch_words(uint64_t n);
 void launch_scan(const uint32_t* in, uint32_t* out, uint32_t n, uint32_t* total, uint32_t* scratch,

@@ -210,7 +210,8 @@ __global__ __launch_bounds__(256) void k_emit(const ViewInfo* __restrict__ views
     const uint32_t klast = min(k0 + blockDim.x, n_items) - 1;
     const uint32_t base = offsets[k0];
     const uint32_t end_all = offsets[klast] + counts[klast];
-    const bool staged = end_all - base <= kEmitStage;
+    // (offsets stay at 2^32 - 1 from there on, and an end past them wraps)
+    const bool staged = end_all >= base && end_all - base <= kEmitStage;
     const uint32_t k = k0 + threadIdx.x;
     const uint32_t cnt = k < n_items ? counts[k] : 0u;
     if (cnt != 0) {
@@ -261,10 +262,10 @@ __global__ __launch_bounds__(256) void k_emit(const ViewInfo* __restrict__ views
     }
     if (!staged) return;  // uniform over the block
     __syncthreads();
-    const uint32_t lim = min(end_all, max(cap, base));
-    for (uint32_t o = base + threadIdx.x; o < lim; o += blockDim.x) {
-        pair_keys[o] = skey[o - base];
-        pair_vals[o] = sval[o - base];
+    const uint32_t n = min(end_all, max(cap, base)) - base;
+    for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) {
+        pair_keys[base + i] = skey[i];
+        pair_vals[base + i] = sval[i];
     }
 }
 

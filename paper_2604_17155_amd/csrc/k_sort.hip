@@ -19,12 +19,17 @@ constexpr int kRsItems = 16;
 constexpr int kRsTile = kRsThreads * kRsItems;  // 8192: runs of ~32 keys per digit
 constexpr int kRsWaves = kRsThreads / 64;
 
+// Sums that stay at 2^32 - 1 instead of wrapping (one instruction, as the plain sum).
+// The pairs of a plan's run are not counted before they are placed; if its geometry
+// has grown until they pass 32 bits, offsets past the end have to stay past it.
+__device__ __forceinline__ uint32_t add_sat(uint32_t a, uint32_t b) { return __builtin_elementwise_add_sat(a, b); }
+
 __device__ inline uint32_t wave_inclusive_scan(uint32_t v) {
     int lane = threadIdx.x & 63;
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) {
         uint32_t o = __shfl_up(v, d, 64);
-        if (lane >= d) v += o;
+        if (lane >= d) v = add_sat(v, o);
     }
     return v;
 }
@@ -35,17 +40,19 @@ __device__ inline uint32_t block_exclusive_scan(uint32_t v, uint32_t* wsum, uint
     int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     uint32_t inc = wave_inclusive_scan(v);
     if (lane == 63) wsum[w] = inc;
+    uint32_t exc = __shfl_up(inc, 1, 64);
+    if (lane == 0) exc = 0u;
     __syncthreads();
     uint32_t off = 0, all = 0;
 #pragma unroll
     for (int k = 0; k < NT / 64; ++k) {
         uint32_t s = wsum[k];
-        if (k < w) off += s;
-        all += s;
+        if (k < w) off = add_sat(off, s);
+        all = add_sat(all, s);
     }
     *total = all;
     __syncthreads();
-    return off + inc - v;
+    return add_sat(off, exc);
 }
 // The kScanItems = 8 consecutive elements at base: two 16-byte loads when
 // they all lie below n and the array is 16-byte aligned, else one guarded
@@ -71,7 +78,7 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_reduce(const uint32_t* __
     scan_load8(in, base, n, x);
     uint32_t s = 0;
 #pragma unroll
-    for (int j = 0; j < kScanItems; ++j) s += x[j];
+    for (int j = 0; j < kScanItems; ++j) s = add_sat(s, x[j]);
     uint32_t tot;
     block_exclusive_scan(s, wsum, &tot);
     if (threadIdx.x == 0) bsums[blockIdx.x] = tot;
@@ -88,7 +95,7 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_down(const uint32_t* in, 
     uint32_t off = 0u;
     if (bsums && raw) {
         uint32_t part = 0u;
-        for (uint32_t i = threadIdx.x; i < blockIdx.x; i += kScanThreads) part += bsums[i];
+        for (uint32_t i = threadIdx.x; i < blockIdx.x; i += kScanThreads) part = add_sat(part, bsums[i]);
         block_exclusive_scan(part, wsum, &off);
     } else if (bsums) {
         off = bsums[blockIdx.x];
@@ -98,16 +105,16 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_down(const uint32_t* in, 
     scan_load8(in, base, n, x);
     uint32_t s = 0;
 #pragma unroll
-    for (int j = 0; j < kScanItems; ++j) s += x[j];
+    for (int j = 0; j < kScanItems; ++j) s = add_sat(s, x[j]);
     uint32_t tot;
     uint32_t pre = block_exclusive_scan(s, wsum, &tot);
-    pre += off;
+    pre = add_sat(off, pre);
     if (base + kScanItems <= n && (reinterpret_cast<uintptr_t>(out) & 15u) == 0) {
         uint32_t y[kScanItems];
 #pragma unroll
         for (int j = 0; j < kScanItems; ++j) {
             y[j] = pre;
-            pre += x[j];
+            pre = add_sat(pre, x[j]);
         }
         *reinterpret_cast<uint4*>(out + base) = make_uint4(y[0], y[1], y[2], y[3]);
         *reinterpret_cast<uint4*>(out + base + 4) = make_uint4(y[4], y[5], y[6], y[7]);
@@ -116,10 +123,10 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_down(const uint32_t* in, 
         for (int j = 0; j < kScanItems; ++j) {
             uint64_t idx = base + j;
             if (idx < n) out[idx] = pre;
-            pre += x[j];
+            pre = add_sat(pre, x[j]);
         }
     }
-    if (total && blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *total = off + tot;
+    if (total && blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *total = add_sat(off, tot);
 }
 
 size_t scan_scratch_words(uint64_t n) {
