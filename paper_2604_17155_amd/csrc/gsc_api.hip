@@ -559,7 +559,7 @@ gsc_status bin_views(gsc_ctx* ctx, const ViewInfo* all, int v0, int nv,
     GSC_HIP((odd ? ctx->pkeys_alt : ctx->pkeys).ensure(4 * pairs + 4));
     {
         StageTimer t(ctx, s, GSC_STAGE_EMIT);
-        launch_emit(dviews, nv, offsets, counts, rects, ctx->rec.as<float4>(), bp, ni, ng,
+        launch_emit(dviews, nv, offsets, counts, rects, ctx->rec.as<float4>(), bp, ni,
                     ctx->pkeys.as<uint32_t>(), ctx->pvals.as<uint32_t>(), ctx->bin, s);
         GSC_LAUNCHED("emit");
     }
@@ -921,7 +921,7 @@ gsc_status plan_bin_batch(gsc_plan* P, const gsc_plan::Batch& b, hipStream_t s) 
     {
         StageTimer t(ctx, s, GSC_STAGE_EMIT);
         launch_emit(dv, b.nv, offsets, counts, rects, P->rec.as<float4>(), P->bp, b.n_items,
-                    b.n_groups, P->pkeys.as<uint32_t>(), P->pvals.as<uint32_t>(), P->bin, s,
+                    P->pkeys.as<uint32_t>(), P->pvals.as<uint32_t>(), P->bin, s,
                     b.group_cap, d_drop);
         GSC_LAUNCHED("emit");
     }

@@ -139,11 +139,13 @@ void launch_project(const ViewInfo* views, int n_views, uint32_t n_items, const 
                     const float* geo, BlendParams bp, uint32_t* counts, uint32_t* rects, float4* rec,
                     int bin, hipStream_t s);
 
-// (group, depth rank) pairs of the depth-ordered records.  Pairs at offsets >=
-// cap are dropped and their items counted in *overflow (if given).
+// (group, depth rank) pairs of the depth-ordered records; a rank marked kVoidPair
+// reaches no bin.  Pairs at offsets >= cap are dropped and their items counted in
+// *overflow (if given).
+constexpr uint32_t kVoidPair = 1u << 31;
 void launch_emit(const ViewInfo* views, int n_views, const uint32_t* offsets, const uint32_t* counts,
                  const uint32_t* rects, const float4* rec, BlendParams bp,
-                 uint32_t n_items, uint32_t n_groups, uint32_t* pair_keys, uint32_t* pair_vals, int bin,
+                 uint32_t n_items, uint32_t* pair_keys, uint32_t* pair_vals, int bin,
                  hipStream_t s, uint32_t cap = 0xFFFFFFFFu, uint32_t* overflow = nullptr);
 
 // Pairs of (bin, item) over all items in any order (plan creation): adds to *out.

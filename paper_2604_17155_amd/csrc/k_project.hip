@@ -198,7 +198,7 @@ __global__ __launch_bounds__(256) void k_emit(const ViewInfo* __restrict__ views
                                               const uint32_t* __restrict__ counts,
                                               const uint32_t* __restrict__ rects,
                                               const float4* __restrict__ rec, BlendParams bp,
-                                              uint32_t n_items, uint32_t sentinel, uint32_t cap,
+                                              uint32_t n_items, uint32_t cap,
                                               uint32_t* __restrict__ overflow,
                                               uint32_t* __restrict__ pair_keys,
                                               uint32_t* __restrict__ pair_vals) {
@@ -224,14 +224,14 @@ __global__ __launch_bounds__(256) void k_emit(const ViewInfo* __restrict__ views
             if (overflow) atomicAdd(overflow, 1u);
             end = off < cap ? cap : off;
         }
-        auto put = [&](uint32_t key) {
+        auto put = [&](uint32_t key, uint32_t val) {
             if (off >= end) return;
             if (staged) {
                 skey[off - base] = key;
-                sval[off - base] = k;
+                sval[off - base] = val;
             } else {
                 pair_keys[off] = key;
-                pair_vals[off] = k;
+                pair_vals[off] = val;
             }
             ++off;
         };
@@ -240,7 +240,7 @@ __global__ __launch_bounds__(256) void k_emit(const ViewInfo* __restrict__ views
             uint32_t key = gbase + ((rect >> 9) & 0x1FFu) * gx + (rect & 0x1FFu);
             uint32_t c = 0;
             for (uint32_t i = 0; i < cnt; ++i) {
-                put(key + c);
+                put(key + c, k);
                 if (++c == w) {
                     c = 0;
                     key += gx;
@@ -251,13 +251,13 @@ __global__ __launch_bounds__(256) void k_emit(const ViewInfo* __restrict__ views
             Footprint f;
             if (make_footprint(r0, r1, reach_q(r1.w, bp), V.height, f))
                 footprint_groups<BIN>(f, V.width, [&](int gy, int a, int b) {
-                    for (int g = a; g <= b; ++g) put(gbase + (uint32_t)gy * gx + (uint32_t)g);
+                    for (int g = a; g <= b; ++g) put(gbase + (uint32_t)gy * gx + (uint32_t)g, k);
                 });
             // The walk above and the one that counted are the same code on the
-            // same record; should they ever disagree, unused slots get a group
-            // id past the last one, which sorts last (of all, or of its view's) and
-            // is ignored.
-            while (off < end) put(sentinel);
+            // same record; should they ever disagree, unused slots hold void pairs
+            // of the view's first group: every key names a group, and a void pair
+            // reaches none of its bins.
+            while (off < end) put(gbase, k | kVoidPair);
         }
     }
     if (!staged) return;  // uniform over the block
@@ -271,16 +271,16 @@ __global__ __launch_bounds__(256) void k_emit(const ViewInfo* __restrict__ views
 
 void launch_emit(const ViewInfo* views, int n_views, const uint32_t* offsets, const uint32_t* counts,
                  const uint32_t* rects, const float4* rec, BlendParams bp,
-                 uint32_t n_items, uint32_t n_groups, uint32_t* pair_keys, uint32_t* pair_vals, int bin,
+                 uint32_t n_items, uint32_t* pair_keys, uint32_t* pair_vals, int bin,
                  hipStream_t s, uint32_t cap, uint32_t* overflow) {
     if (n_items == 0) return;
     if (bin == 32)
         hipLaunchKernelGGL(k_emit<32>, dim3((n_items + 255) / 256), dim3(256), 0, s, views, n_views,
-                           offsets, counts, rects, rec, bp, n_items, n_groups, cap, overflow, pair_keys,
+                           offsets, counts, rects, rec, bp, n_items, cap, overflow, pair_keys,
                            pair_vals);
     else
         hipLaunchKernelGGL(k_emit<16>, dim3((n_items + 255) / 256), dim3(256), 0, s, views, n_views,
-                           offsets, counts, rects, rec, bp, n_items, n_groups, cap, overflow, pair_keys,
+                           offsets, counts, rects, rec, bp, n_items, cap, overflow, pair_keys,
                            pair_vals);
 }
 
@@ -321,6 +321,7 @@ __global__ __launch_bounds__(256) void k_group_masks(GroupLists G, BlendParams b
     const uint32_t n = live_pairs(G), begin = u * kWindow;
     if (begin >= n) return;  // whole wave
     const uint32_t end = min(begin + kWindow, n);
+    // (every pair's key names a group; a lane past the window's end has 0xFFFFFFFF)
     // the next 64 pairs' records are in flight while 64 are masked
     auto pair = [&](uint32_t b, uint32_t& key, uint32_t& k) {
         const bool in = b + lane < end;
@@ -330,7 +331,7 @@ __global__ __launch_bounds__(256) void k_group_masks(GroupLists G, BlendParams b
         key = in ? key : 0xFFFFFFFFu;
     };
     auto load = [&](uint32_t key, uint32_t k, float4& r0, float4& r1) {
-        const size_t at = 2 * (size_t)(key < G.n_groups ? k : 0u);
+        const size_t at = 2 * (size_t)(key < G.n_groups ? k & kItemMask : 0u);
         r0 = G.rec[at];
         r1 = G.rec[at + 1];
     };
@@ -374,7 +375,7 @@ __global__ __launch_bounds__(256) void k_group_masks(GroupLists G, BlendParams b
         for (;;) {
             const bool mine = key == g;
             Footprint f{};
-            const bool on = mine && g < G.n_groups && make_footprint(r0, r1, reach_q(r1.w, bp), H, f);
+            const bool on = mine && g < G.n_groups && !(k & kVoidPair) && make_footprint(r0, r1, reach_q(r1.w, bp), H, f);
             const uint2 m = group_masks<BIN>(on, f, gg.X0, gg.Y0, W);
             if (mine) {
                 G.mask_lo[b + lane] = m.x;

@@ -273,7 +273,7 @@ __device__ __forceinline__ uint32_t depth_key(const SortSource& S, const ViewInf
                                 __fmaf_rn(V.R[7], S.means[3 * g + 1], __fmaf_rn(V.R[8], S.means[3 * g + 2], V.t[2])));
     return (key > S.znear && S.opac[g] >= S.alpha_min) ? __float_as_uint(key) : 0xFFFFFFFFu;
 }
-// (a key past its view's groups, 0 .. mask - 1 there, goes last)
+// (a view's groups lie below mask; clamped, as the digit indexes LDS)
 __device__ __forceinline__ uint32_t sort_digit(const SortTile& T, uint32_t key, int shift, uint32_t mask) {
     return T.base != 0xFFFFFFFFu ? min(key - T.base, mask) : (key >> shift) & mask;
 }
@@ -706,7 +706,7 @@ void launch_group_sort(const ViewInfo* views, int n_views, uint32_t n_items, uin
         return;
     }
     uint32_t mask = 1u;
-    while (mask < max_groups) mask = 2u * mask + 1u;  // groups below it, and one value past them
+    while (mask < max_groups) mask = 2u * mask + 1u;  // the view's groups lie below it
     const uint32_t head = (uint32_t)((2 * (uint64_t)n_views + 2 + 63) / 64) * 64u;
     const uint32_t tiles = n / kRsTile + (uint32_t)n_views;
     hipLaunchKernelGGL(k_pair_segments, dim3(1), dim3(256), 0, s, views, n_views, n_items, offsets, n, n_dev,
