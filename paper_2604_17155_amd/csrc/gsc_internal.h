@@ -162,6 +162,7 @@ void launch_count_bins(const ViewInfo* views, int n_views, uint32_t n_items, con
 //     entries to totals[group] (zero before).
 //   launch_bin_ranges: with first[group] the exclusive scan of totals, the
 //     bins' ranges, and counts turned into each row's first list positions;
+//     puts the next group with pairs in the place of each group's ranges.x;
 //     adds *total to *sum (if given).
 //   launch_bin_lists: the bins' entries, depth rank | mask << kItemBits.
 // Positions past cap are cut off; the entries that lose one are counted in
@@ -175,7 +176,7 @@ struct GroupLists {
     int bin;
     uint32_t n_pairs;
     const uint32_t* n_dev;
-    const uint2* ranges;
+    uint2* ranges;
     const uint32_t* keys;
     const uint32_t* vals;
     const float4* rec;

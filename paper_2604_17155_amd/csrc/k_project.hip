@@ -409,7 +409,7 @@ void launch_group_masks(const GroupLists& g, BlendParams bp, hipStream_t s) {
     else hipLaunchKernelGGL(k_group_masks<16>, grid, block, 0, s, g, bp);
 }
 
-// One block per group; thread 16 j + f takes bin f of rows j, j + 16, ...
+// One block per group; thread 16 j + f takes bin f of the j-th sixteenth of its rows.
 template <int BIN>
 __global__ __launch_bounds__(256) void k_bin_ranges(GroupLists G, const uint32_t* __restrict__ first,
                                                     uint2* __restrict__ ranges, uint32_t cap,
@@ -450,6 +450,7 @@ __global__ __launch_bounds__(256) void k_bin_ranges(GroupLists G, const uint32_t
         run += c;
     }
     if (j != 0) return;
+    if (f == 0 && rows != 0u) G.ranges[g].x = rg.y < live_pairs(G) ? G.keys[rg.y] : G.n_groups;
     const GroupGeom gg = group_geom<BIN>(g, G.views, G.n_views);
     const ViewInfo& V = G.views[gg.view];
     const uint32_t bx = gg.bx + (f & 3u), by = gg.by + (f >> 2);
@@ -482,14 +483,12 @@ __global__ __launch_bounds__(256) void k_bin_lists(GroupLists G, uint32_t* __res
     const uint32_t end = min(begin + kWindow, n);
     uint32_t g = (uint32_t)__builtin_amdgcn_readfirstlane((int)G.first_group[u]);
     uint32_t at = begin;
-    // the group lists the window meets, one after the other
+    // the group lists the window meets, one after the other.  (Each names the next:
+    // stepping over the groups without pairs took a load apiece, one after the
+    // other: two splats in opposite corners of 16384x16384 pixels, 6.2 -> 0.49 ms.)
     while (at < end && g < G.n_groups) {
-        const uint2 rg = G.ranges[g];
+        const uint2 rg = G.ranges[g];  // the next group with pairs, the end of this one's
         const uint32_t stop = min(end, (uint32_t)__builtin_amdgcn_readfirstlane((int)rg.y));
-        if (__builtin_amdgcn_readfirstlane((int)rg.x) == __builtin_amdgcn_readfirstlane((int)rg.y) || stop <= at) {
-            ++g;  // a group without pairs
-            continue;
-        }
         uint32_t pos[16];
 #pragma unroll
         for (int f = 0; f < 16; ++f) pos[f] = G.counts[((size_t)u + g) * 16 + f];
@@ -524,8 +523,8 @@ __global__ __launch_bounds__(256) void k_bin_lists(GroupLists G, uint32_t* __res
             }
             __builtin_amdgcn_wave_barrier();  // the next 64 pairs overwrite the stage
         }
-        at = stop;
-        ++g;
+        at = max(at, stop);
+        g = (uint32_t)__builtin_amdgcn_readfirstlane((int)rg.x);
     }
 }
 
