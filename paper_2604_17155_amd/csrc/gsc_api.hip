@@ -535,11 +535,27 @@ gsc_status bin_views(gsc_ctx* ctx, const ViewInfo* all, int v0, int nv,
     GSC_HIP(hipStreamSynchronize(s));
     uint64_t pairs = *ctx->h_total;
     if (wide) memcpy(&pairs, reinterpret_cast<const char*>(ctx->h_total) + 8, 8);
-    // a group pair holds at least about one bin pair
-    if (pairs >= kMaxPairsPerBatch) {
-        if (nv > 1) return kSplit;
+    // A batch over its limit is split before its pairs take memory: where the group
+    // pairs alone pass it (a group pair holds one bin pair at least, but for a few
+    // corners of bounding boxes), and, for a limit that the caller set and sixteen
+    // bins a group pair would pass, by a count of the bin pairs.  (For the default
+    // limit the count, about what the masks of the same pairs cost, is left out: a
+    // batch of 2^27 to 2^31 group pairs is split after its lists are counted below.)
+    const uint64_t limit = batch_pair_limit(ctx->opt);
+    if (nv > 1 && pairs > limit) return kSplit;
+    if (pairs >= kMaxPairsPerBatch)
         return fail(GSC_ERR_CAPACITY, "one view produces %llu tile pairs (limit %llu)",
                     (unsigned long long)pairs, (unsigned long long)kMaxPairsPerBatch);
+    if (nv > 1 && ctx->opt.batch_pairs != 0 && 16 * pairs > limit) {
+        StageTimer t(ctx, s, GSC_STAGE_SCAN);
+        launch_fill_u32(reinterpret_cast<uint32_t*>(d_total64), 0u, 2, s);
+        launch_count_bins(dviews, nv, ni, counts, rects, ctx->rec.as<float4>(), bp, ctx->bin, d_total64, s);
+        GSC_LAUNCHED("bin count");
+        GSC_HIP(hipMemcpyAsync(ctx->h_total + 2, d_total64, 8, hipMemcpyDeviceToHost, s));
+        GSC_HIP(hipStreamSynchronize(s));
+        uint64_t bins = 0;
+        memcpy(&bins, ctx->h_total + 2, 8);
+        if (bins > limit) return kSplit;
     }
     const int gbits = bits_for(groups + 1);
     // per (window, group) row sixteen counts, then the windows' first groups
@@ -581,7 +597,7 @@ gsc_status bin_views(gsc_ctx* ctx, const ViewInfo* all, int v0, int nv,
                         ctx->gcounts.as<uint32_t>() + count_words, ctx->granges.as<uint32_t>() + 2 * groups};
     launch_group_masks(gl, bp, s);
     launch_scan(gl.totals, ctx->gfirst.as<uint32_t>(), ng, d_bins, ctx->sort_scratch.as<uint32_t>(), s);
-    const bool counted = ctx->no_alloc || 16 * pairs > std::min(kListsUncounted, batch_pair_limit(ctx->opt));
+    const bool counted = ctx->no_alloc || 16 * pairs > std::min(kListsUncounted, limit);
     if (counted) GSC_HIP(hipMemcpyAsync(ctx->h_total, d_bins, 4, hipMemcpyDeviceToHost, s));
     if (counted && 16 * pairs > 0xFFFFFFFFull) {  // the scan's total may have wrapped
         launch_fill_u32(reinterpret_cast<uint32_t*>(d_total64), 0u, 2, s);
@@ -607,7 +623,7 @@ gsc_status bin_views(gsc_ctx* ctx, const ViewInfo* all, int v0, int nv,
         GSC_HIP(ctx->no_alloc ? hipStreamSynchronize(s) : hipEventSynchronize(ctx->ev_read));
         bins = *ctx->h_total;
         if (16 * pairs > 0xFFFFFFFFull) memcpy(&bins, ctx->h_total + 2, 8);
-        if (bins > batch_pair_limit(ctx->opt) && nv > 1) return kSplit;
+        if (bins > limit && nv > 1) return kSplit;
         if (bins >= kMaxPairsPerBatch)
             return fail(GSC_ERR_CAPACITY, "one view produces %llu tile pairs (limit %llu)",
                         (unsigned long long)bins, (unsigned long long)kMaxPairsPerBatch);
