@@ -1322,12 +1322,15 @@ gsc_status gsc_colorize_noalloc(gsc_ctx* ctx, const float* means, const float* s
     if (n_cams > kNoallocMaxViews)
         return fail(GSC_ERR_CAPACITY, "gsc_colorize_noalloc takes at most %d cameras (got %d)",
                     kNoallocMaxViews, n_cams);
-    // what is known before binning: view tables, geometry records, per-item
-    // keys, counts and records, and the per-view sums
-    const uint64_t items = (uint64_t)N * (uint64_t)n_cams;
+    // what is known before binning: view tables, geometry records, the items of
+    // the first view batch (keys, values, their alternates, a record: 48 bytes
+    // each), the per-view sums and the fold's lists
+    const uint64_t batch = std::max<uint64_t>(1, batch_item_limit(ctx->opt) / (uint64_t)std::max<int64_t>(N, 1));
+    const uint64_t items = (uint64_t)N * std::min<uint64_t>((uint64_t)n_cams, batch);
     const uint64_t vs_words = (uint64_t)(sh_deg > 0 ? std::max(n_cams, 1) : 1) * (uint64_t)N * (uint64_t)(C + 1);
-    const uint64_t known = 2 * sizeof(ViewInfo) * (uint64_t)n_cams + 4ull * kGeoStride * (uint64_t)N +
-                           64ull * items + 4 * vs_words + (sh_deg > 0 ? 4ull * fold_obs_words(N, 0) : 0);
+    const uint64_t known = sizeof(ViewInfo) * (std::min<uint64_t>((uint64_t)n_cams, batch) + (sh_deg > 0 ? (uint64_t)n_cams : 0)) +
+                           4ull * kGeoStride * (uint64_t)N + 48ull * items + 4 * vs_words +
+                           (sh_deg > 0 ? 4ull * (uint64_t)fold_obs_words(N, n_cams) : 0);
     if (known > kNoallocScratchBytes)
         return fail(GSC_ERR_CAPACITY,
                     "gsc_colorize_noalloc: %llu Gaussians x %d views x %d channels need at least %llu "
