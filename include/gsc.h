@@ -161,11 +161,15 @@ typedef struct {
                          channels and a ones column in one block: C <= 15 for
                          BF16, C <= 7 for FP32 targets).  A code that does not
                          apply to the call falls back to the automatic choice.
+                         In launches of few 16x16 tiles the vector code that
+                         is the automatic choice for FP32 targets runs one
+                         wave per 8x8 pixel block, with 3, 7 or 15 channels
+                         per launch; other codes run as they say.
                          A tuned plan uses its own. */
     int32_t schedule;   /* order in which the blend + accumulate launch takes
                            its 16x16 tiles: GSC_SCHEDULE_AUTO (0),
-                           GSC_SCHEDULE_GRID (1: one wave per tile, in tile
-                           index order) or GSC_SCHEDULE_LONGEST_FIRST (2:
+                           GSC_SCHEDULE_GRID (1: one wave per tile, or per
+                           8x8 block of few tiles, in tile index order) or GSC_SCHEDULE_LONGEST_FIRST (2:
                            bins in decreasing octave of list length, tile
                            index order within an octave; the grid's blocks
                            map to tiles in that order, or, for the

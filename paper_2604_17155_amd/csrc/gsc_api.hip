@@ -899,9 +899,11 @@ gsc_status plan_accumulate(gsc_plan* P, const gsc_plan::Batch& b, const void* ta
     const TileLists tl{P->d_views.as<ViewInfo>() + b.v0, b.nv, b.n_tiles, P->bin, P->ranges.as<uint2>(),
                        P->lists.as<uint32_t>(), P->rec.as<float4>(), P->vals.as<uint32_t>(),
                        P->order.as<uint32_t>()};
+    chunk = resolve_chunk(chunk, P->C, tdtype);
+    StageTimer t(P->ctx, s, GSC_STAGE_BLEND, (uint32_t)accumulate_form(tl, P->C, chunk, false, persistent).launches);
     launch_accumulate(tl, targets, tdtype, P->C, P->per_view, P->bp, P->vs.as<float>(), d_counter, nullptr,
                       chunk, s, persistent ? P->queues.as<uint32_t>() : nullptr, nullptr,
-                      split_sums(P->per_view, tdtype, P->C, resolve_chunk(chunk, P->C, tdtype)) ? P->n_total : 0);
+                      split_sums(P->per_view, tdtype, P->C, chunk) ? P->n_total : 0);
     GSC_LAUNCHED("accumulate");
     return GSC_OK;
 }
@@ -1006,7 +1008,6 @@ gsc_status plan_run(gsc_plan* P, const void* targets, int tdtype, const double* 
     for (const auto& b : P->batches) {
         gsc_status st = plan_bin_batch(P, b, s);
         if (st != GSC_OK) return st;
-        StageTimer t(P->ctx, s, GSC_STAGE_BLEND);
         if ((st = plan_accumulate(P, b, targets, tdtype, chunk, P->acc_persistent, s)) != GSC_OK)
             return st;
     }
@@ -1190,7 +1191,6 @@ gsc_status colorize_core(gsc_ctx* ctx, const float* means, const float* scales,
     const bool split = split_sums(per_view, tdtype, C, chunk);
     st = for_view_batches_k(ctx, all, n_cams, means, opacities, N, bp, s, key, reuse,
                           [&](int v0, int nv, const Binned& bn) -> gsc_status {
-        StageTimer t(ctx, s, GSC_STAGE_BLEND, (uint32_t)accumulate_launches(C, chunk));
         (void)v0;
         // Tiles in the longest-first order: the vector form as a grid whose
         // blocks map to tiles through the order (the hardware dispatches
@@ -1202,6 +1202,7 @@ gsc_status colorize_core(gsc_ctx* ctx, const float* means, const float* scales,
             GSC_HIP(ctx->queues.ensure(4 * (size_t)(kMaxC + 1)));
             queues = ctx->queues.as<uint32_t>();
         }
+        StageTimer t(ctx, s, GSC_STAGE_BLEND, (uint32_t)accumulate_form(tl, C, chunk, det, queues != nullptr).launches);
         launch_accumulate(tl, targets, tdtype, C, per_view, bp, acc_vs, d_counter, x_cnt, chunk, s, queues,
                           det ? &dsc : nullptr, split ? N : 0);
         GSC_LAUNCHED("accumulate");
@@ -1507,12 +1508,13 @@ gsc_status gsc_render(gsc_ctx* ctx, const float* means, const float* scales, con
     st = for_view_batches_k(ctx, all.data(), n_cams, means, opacities, N, bp, s, &key, reuse,
                           [&](int v0, int nv, const Binned& bn) -> gsc_status {
         (void)v0;
-        StageTimer t(ctx, s, GSC_STAGE_BLEND, 1 + (uint32_t)((C + 3) / 4));
+        const TileLists tl = tile_lists(ctx, nv, bn);
+        StageTimer t(ctx, s, GSC_STAGE_BLEND, 1 + (uint32_t)render_launches(tl, C));
         GSC_HIP(ctx->gamma.ensure(4 * (size_t)nv * (size_t)std::max<int64_t>(N, 1) * (size_t)C));
         launch_view_colors(ctx->views.as<ViewInfo>(), nv, N, means, coeffs, C, sh_deg,
                            ctx->gamma.as<float>(), s);
         GSC_LAUNCHED("view colors");
-        launch_render(tile_lists(ctx, nv, bn), ctx->gamma.as<float>(), C, bp, images, d_counter, s);
+        launch_render(tl, ctx->gamma.as<float>(), C, bp, images, d_counter, s);
         GSC_LAUNCHED("render");
         return GSC_OK;
     });

@@ -272,16 +272,21 @@ void launch_group_sort(const ViewInfo* views, int n_views, uint32_t n_items, uin
 constexpr int kChunkMfma = 128;
 constexpr int kChunkPacked = kChunkMfma | 1;
 inline int chunk_channels(int chunk) { return chunk & (kChunkMfma - 1); }
-inline int accumulate_launches(int C, int chunk) {
-    if (chunk == kChunkPacked) return 1;
-    const int ch = chunk_channels(chunk);
-    return (C + ch - 1) / ch;
-}
 // Default variant for C channels of targets of type tdtype.
 int accumulate_chunk(int C, int tdtype);
 // `requested` if it is a valid variant that applies to C channels of type
 // tdtype, else the default.
 int resolve_chunk(int requested, int C, int tdtype);
+// What launch_accumulate makes of a resolved variant: the variant (deterministic
+// sums: of the vector form), whether it runs a wave per 8x8 block (few_tiles: the
+// default vector variant as a grid; other variants and the persistent grid run as
+// they were asked for), and the launches that take the channels.
+struct AccumulateForm {
+    int chunk;
+    bool blocks;
+    int launches;
+};
+AccumulateForm accumulate_form(const TileLists& tl, int C, int chunk, bool deterministic, bool persistent);
 
 // The sums of one slot: *(v + slot * v_stride) and the C floats at s + slot *
 // s_stride.  Interleaved slots of C + 1 floats, or (split_n slots) the S rows
@@ -335,6 +340,7 @@ struct RenderResidual {
     const void* y = nullptr;
     int bf16 = 0;
 };
+int render_launches(const TileLists& tl, int C);
 void launch_render(const TileLists& tl, const float* gamma, int C, BlendParams bp, float* images,
                    unsigned long long* counter, hipStream_t s, const RenderResidual& res = {});
 

@@ -1069,25 +1069,38 @@ bool accumulate_chunk_valid(int chunk, int tdtype) {
     return chunk == 1 || chunk == 2 || chunk == 3 || chunk == 4 || chunk == 8 || chunk == 16;
 }
 
+// Channels a launch of the form for few tiles takes (a power of two of values an
+// entry, with its weight).
+static int block_channels(int C) { return C <= 3 ? 3 : (C <= 7 ? 7 : 15); }
+
+AccumulateForm accumulate_form(const TileLists& tl, int C, int chunk, bool deterministic, bool persistent) {
+    if (deterministic && (chunk & kChunkMfma)) chunk = accumulate_chunk(C, GSC_F32);  // vector form only
+    const bool blocks = !deterministic && !persistent && few_tiles(tl) && chunk == accumulate_chunk(C, GSC_F32);
+    const int ch = blocks ? block_channels(C) : chunk_channels(chunk);
+    return AccumulateForm{chunk, blocks, chunk == kChunkPacked ? 1 : (C + ch - 1) / ch};
+}
+
 void launch_accumulate(const TileLists& tl, const void* targets, int tdtype, int C, bool per_view,
                        BlendParams bp, float* VS, unsigned long long* counter, uint32_t* gcount,
                        int chunk, hipStream_t s, uint32_t* queues, const float2* det, int64_t split_n) {
     if (tl.n_bins == 0) return;
-    chunk = resolve_chunk(chunk, C, tdtype);
-    if (det && (chunk & kChunkMfma)) chunk = accumulate_chunk(C, GSC_F32);  // vector form only
-    if (!det && few_tiles(tl) && !(chunk & kChunkMfma)) {
+    const AccumulateForm form = accumulate_form(tl, C, resolve_chunk(chunk, C, tdtype), det != nullptr, queues != nullptr);
+    chunk = form.chunk;
+    if (form.blocks) {
 #define GSC_ACCB(CCV)                                                                                    \
     do {                                                                                                 \
         if (tdtype == GSC_BF16) launch_acc_blocks<CCV, true>(tl, targets, C, per_view, bp, VS, counter, gcount, s); \
         else launch_acc_blocks<CCV, false>(tl, targets, C, per_view, bp, VS, counter, gcount, s);        \
     } while (0)
-        if (C <= 3) GSC_ACCB(3);
-        else if (C <= 7) GSC_ACCB(7);
-        else GSC_ACCB(15);
+        switch (block_channels(C)) {
+            case 3: GSC_ACCB(3); break;
+            case 7: GSC_ACCB(7); break;
+            default: GSC_ACCB(15); break;
+        }
 #undef GSC_ACCB
         return;
     }
-    if (queues) launch_fill_u32(queues, 0u, (uint64_t)accumulate_launches(C, chunk), s);
+    if (queues) launch_fill_u32(queues, 0u, (uint64_t)form.launches, s);
     if (chunk & kChunkMfma) {
         const SumRows rows = sum_rows(VS, C, split_n);
 #define GSC_ACCM(NB, YMV) \

@@ -371,16 +371,24 @@ __global__ __launch_bounds__(256) void k_render_blocks(
     if (c_off == 0 && lane == 0 && cnt) atomicAdd(counter, (unsigned long long)cnt);
 }
 
+// Channels a launch takes.
+static int render_channels(const TileLists& tl, int C) { return few_tiles(tl) && C > 4 ? 8 : 4; }
+int render_launches(const TileLists& tl, int C) {
+    const int ch = render_channels(tl, C);
+    return (C + ch - 1) / ch;
+}
+
 void launch_render(const TileLists& tl, const float* gamma, int C, BlendParams bp, float* images,
                    unsigned long long* counter, hipStream_t s, const RenderResidual& res) {
     if (tl.n_bins == 0) return;
     const uint32_t n_wt = wave_tiles(tl.n_bins, tl.bin);
+    const int step = render_channels(tl, C);
     if (few_tiles(tl)) {
 #define GSC_RENDERB(EXV, BINV)                                                                            \
     hipLaunchKernelGGL((k_render_blocks<EXV, BINV>), dim3(n_wt), dim3(256), 0, s, tl.views, tl.n_views,   \
                        n_wt, tl.ranges, tl.pair_vals, tl.rec, tl.items, gamma, C, c_off, bp, images,      \
                        counter, tl.order, res)
-        for (int c_off = 0; c_off < C; c_off += C <= 4 ? 4 : 8) {
+        for (int c_off = 0; c_off < C; c_off += step) {
             if (tl.bin == 32) {
                 if (C <= 4) GSC_RENDERB(1, 32); else GSC_RENDERB(2, 32);
             } else {
@@ -394,7 +402,7 @@ void launch_render(const TileLists& tl, const float* gamma, int C, BlendParams b
 #define GSC_RENDER(CCV, BINV)                                                                            \
     hipLaunchKernelGGL((k_render<CCV, BINV>), grid, block, 0, s, tl.views, tl.n_views, n_wt, tl.ranges, \
                        tl.pair_vals, tl.rec, tl.items, gamma, C, c_off, bp, images, counter, tl.order, res)
-    for (int c_off = 0; c_off < C; c_off += 4) {
+    for (int c_off = 0; c_off < C; c_off += step) {
         const bool three = C <= 3 && c_off == 0;
         if (tl.bin == 32) {
             if (three) GSC_RENDER(3, 32); else GSC_RENDER(4, 32);
