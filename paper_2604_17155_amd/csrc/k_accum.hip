@@ -415,20 +415,20 @@ __global__ __launch_bounds__(256) void k_accumulate_blocks(
     if (c_off == 0 && lane == 0 && cnt) atomicAdd(counter, (unsigned long long)cnt);
 }
 
+// One launch: channels [c_off, c_off + CC) of C.
 template <int CC, bool BF16>
-static void launch_acc_blocks(const TileLists& tl, const void* targets, int C, bool per_view, BlendParams bp,
-                              float* VS, unsigned long long* counter, uint32_t* gcount, hipStream_t s) {
+static void launch_acc_blocks(const TileLists& tl, const void* targets, int C, int c_off, bool per_view,
+                              BlendParams bp, float* VS, unsigned long long* counter, uint32_t* gcount,
+                              hipStream_t s) {
     const uint32_t n_wt = wave_tiles(tl.n_bins, tl.bin);
-    for (int c_off = 0; c_off < std::max(C, 1); c_off += std::max(CC, 1)) {
-        if (tl.bin == 32)
-            hipLaunchKernelGGL((k_accumulate_blocks<CC, BF16, 32>), dim3(n_wt), dim3(256), 0, s, tl.views,
-                               tl.n_views, n_wt, tl.ranges, tl.pair_vals, tl.rec, tl.items, targets, C, c_off,
-                               (int)per_view, bp, VS, counter, gcount, tl.order);
-        else
-            hipLaunchKernelGGL((k_accumulate_blocks<CC, BF16, 16>), dim3(n_wt), dim3(256), 0, s, tl.views,
-                               tl.n_views, n_wt, tl.ranges, tl.pair_vals, tl.rec, tl.items, targets, C, c_off,
-                               (int)per_view, bp, VS, counter, gcount, tl.order);
-    }
+    if (tl.bin == 32)
+        hipLaunchKernelGGL((k_accumulate_blocks<CC, BF16, 32>), dim3(n_wt), dim3(256), 0, s, tl.views,
+                           tl.n_views, n_wt, tl.ranges, tl.pair_vals, tl.rec, tl.items, targets, C, c_off,
+                           (int)per_view, bp, VS, counter, gcount, tl.order);
+    else
+        hipLaunchKernelGGL((k_accumulate_blocks<CC, BF16, 16>), dim3(n_wt), dim3(256), 0, s, tl.views,
+                           tl.n_views, n_wt, tl.ranges, tl.pair_vals, tl.rec, tl.items, targets, C, c_off,
+                           (int)per_view, bp, VS, counter, gcount, tl.order);
 }
 
 template <int CC, bool BF16, int BIN, bool DET = false>
@@ -1069,8 +1069,8 @@ bool accumulate_chunk_valid(int chunk, int tdtype) {
     return chunk == 1 || chunk == 2 || chunk == 3 || chunk == 4 || chunk == 8 || chunk == 16;
 }
 
-// Channels a launch of the form for few tiles takes (a power of two of values an
-// entry, with its weight).
+// Channels that the next launch of the form for few tiles takes of C that are left
+// (a power of two of values an entry, with its weight).
 static int block_channels(int C) { return C <= 3 ? 3 : (C <= 7 ? 7 : 15); }
 
 AccumulateForm accumulate_form(const TileLists& tl, int C, int chunk, bool deterministic, bool persistent) {
@@ -1089,13 +1089,19 @@ void launch_accumulate(const TileLists& tl, const void* targets, int tdtype, int
     if (form.blocks) {
 #define GSC_ACCB(CCV)                                                                                    \
     do {                                                                                                 \
-        if (tdtype == GSC_BF16) launch_acc_blocks<CCV, true>(tl, targets, C, per_view, bp, VS, counter, gcount, s); \
-        else launch_acc_blocks<CCV, false>(tl, targets, C, per_view, bp, VS, counter, gcount, s);        \
+        if (tdtype == GSC_BF16) launch_acc_blocks<CCV, true>(tl, targets, C, c_off, per_view, bp, VS, counter, gcount, s); \
+        else launch_acc_blocks<CCV, false>(tl, targets, C, c_off, per_view, bp, VS, counter, gcount, s); \
     } while (0)
-        switch (block_channels(C)) {
-            case 3: GSC_ACCB(3); break;
-            case 7: GSC_ACCB(7); break;
-            default: GSC_ACCB(15); break;
+        // (the last launch as narrow as the channels that are left: 16 channels of
+        // 4 views of 512x512, 100k splats, 641 us a call with two launches of 15,
+        // 569 with 15 and 3; the tile form, in one launch, 556, at 2 views 510
+        // against 394)
+        for (int c_off = 0; c_off < C; c_off += block_channels(C - c_off)) {
+            switch (block_channels(C - c_off)) {
+                case 3: GSC_ACCB(3); break;
+                case 7: GSC_ACCB(7); break;
+                default: GSC_ACCB(15); break;
+            }
         }
 #undef GSC_ACCB
         return;
@@ -1136,7 +1142,7 @@ void launch_accumulate_weights(const TileLists& tl, bool per_view, BlendParams b
                                unsigned long long* counter, hipStream_t s) {
     if (tl.n_bins == 0) return;
     if (few_tiles(tl)) {
-        launch_acc_blocks<0, false>(tl, nullptr, 0, per_view, bp, V, counter, nullptr, s);
+        launch_acc_blocks<0, false>(tl, nullptr, 0, 0, per_view, bp, V, counter, nullptr, s);
         return;
     }
     if (tl.bin == 32)
