@@ -435,9 +435,14 @@ TileLists tile_lists(const gsc_ctx* ctx, int nv, const Binned& bn) {
 inline uint64_t view_groups(const ViewInfo& v) { return (uint64_t)v.groups_x * (uint64_t)((v.tiles_y + 3) / 4); }
 
 // Bin pairs above which a batch's list buffer is sized by their count, a second
-// read-back (10-20 us): below, 16 bins for each group pair are allocated (at
-// most 512 MB; about a third of it is used).
-constexpr uint64_t kListsUncounted = 1ull << 27;
+// read-back: below, 16 bins for each group pair are allocated (at most 32 MB;
+// about a third of it is used).  The read-back shows in small calls alone, as the
+// bin ranges and the tile order run meanwhile: us a call without and with it, and
+// MiB of scratch, splats of 512x512 views (2k: 64x64; 20k: 256x256):
+//   1 x 2k 190 / 200, 8 / 10;   1 x 20k 221 / 225, 6 / 2;   1 x 100k 229 / 235, 30 / 20;
+//   4 x 100k 387 / 389, 90 / 56;   12 x 100k 608 / 605, 252 / 140;   25 x 100k 922 / 915,
+//   518 / 278.  16 bins a group pair are 2.4 M, 9.6 M and 30 M at 1, 4 and 12 x 100k.
+constexpr uint64_t kListsUncounted = 1ull << 23;
 
 // Project, depth-sort and list the views [v0, v0+nv) of `all`.  The batch's
 // ViewInfo table is uploaded to ctx->views (tile_base local to the batch).
