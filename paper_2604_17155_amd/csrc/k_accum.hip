@@ -861,7 +861,6 @@ __device__ __forceinline__ uint32_t accumulate_tile_wide(
     const int64_t slot_base = per_view ? V.vs_base : V.g_offset;
     const uint32_t n16 = lane & 15, q4 = lane >> 4;
     const int c = 16 * (int)wave + (int)n16;
-    const bool channels = 16 * (int)wave < C;  // uniform
 
     // targets: as in the form above (nearest pixel, last channel past the ends)
     bf16x8_t Y[8];
