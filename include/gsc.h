@@ -18,8 +18,8 @@
  *     is marked "host".  The library never frees or retains caller memory.
  *   - Work is enqueued on `stream` (a hipStream_t; NULL = the null stream).
  *     Calls that size their scratch from data (colorize, render and their
- *     adjoints) read one 4-byte count back from the device and therefore
- *     synchronise `stream` once per call; on a stream under graph capture
+ *     adjoints) read one or two pair counts back from the device for each
+ *     view batch and therefore synchronise `stream`; on a stream under graph capture
  *     they return GSC_ERR_NOT_CAPTURABLE without enqueueing anything.
  *   - Return value: GSC_OK or a negative gsc_status.  On failure
  *     gsc_last_error() returns a message for the calling thread.  Invalid
@@ -120,11 +120,11 @@ enum {
 
 /* Pipeline stages timed under GSC_FLAG_PROFILE (indices of gsc_stats.stage_ms). */
 enum {
-    GSC_STAGE_PROJECT = 0,    /* covariance, projection, footprint, depth key */
-    GSC_STAGE_DEPTH_SORT = 1, /* stable radix sort of (view, Gaussian) items by depth */
-    GSC_STAGE_SCAN = 2,       /* tile counts in depth order and their exclusive scan */
-    GSC_STAGE_EMIT = 3,       /* (tile, item) pair emission */
-    GSC_STAGE_TILE_SORT = 4,  /* stable radix sort of pairs by tile, tile ranges */
+    GSC_STAGE_PROJECT = 0,    /* projection, footprint, groups of bins reached */
+    GSC_STAGE_DEPTH_SORT = 1, /* depth keys and stable sort of each view's items by them */
+    GSC_STAGE_SCAN = 2,       /* exclusive scan of the group counts in depth order */
+    GSC_STAGE_EMIT = 3,       /* (group, item) pair emission */
+    GSC_STAGE_TILE_SORT = 4,  /* stable sort of pairs by group, bin lists, tile order */
     GSC_STAGE_BLEND = 5,      /* fused blend + accumulate (colorize) or blend + render */
     GSC_STAGE_SOLVE = 6,      /* fold into normal equations + Cholesky solve (or its adjoint) */
     GSC_STAGE_BLEND_ADJOINT = 7, /* backward: adjoint colours + two-pass blend adjoint */
@@ -294,8 +294,8 @@ gsc_status gsc_colorize_refine(gsc_ctx* ctx, const float* means, const float* sc
  * time the library is loaded until the process ends, and the host staging
  * of the camera tables held in static arrays.  No hipMalloc, hipFree or other
  * allocation happens in the call; the caller still passes every input and
- * output.  Like gsc_colorize it reads the tile-pair count back once, so it
- * synchronises `stream`.
+ * output.  Like gsc_colorize it reads pair counts back, so it synchronises
+ * `stream`.
  *   ctx supplies the options (GSC_FLAG_PROFILE and GSC_FLAG_REUSE_BINNING are
  *   ignored) and receives the statistics; its own scratch is not used.
  * Limits: at most 1024 cameras, and the whole call (geometry records,

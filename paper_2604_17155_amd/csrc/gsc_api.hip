@@ -1,6 +1,7 @@
 // C ABI: argument validation, context and scratch management, and the
-// per-call pipeline  project -> depth sort -> scan -> emit -> tile sort ->
-// tile ranges -> accumulate (per view batch) -> fold + solve.
+// per-call pipeline  depth sort -> project -> scan -> emit (group pairs) ->
+// group sort -> bin lists -> tile order -> accumulate (per view batch) ->
+// fold + solve.
 #include <math.h>
 #include <stdarg.h>
 #include <stdio.h>

@@ -217,7 +217,12 @@ inline uint32_t wave_tiles(uint32_t n_bins, int bin) { return bin == 32 ? 4u * n
 // 100k blob Gaussians, degree 3, 4 / 6 / 8 views of 512x512 (4096 / 6144 /
 // 8192 tiles): 573 / 633 / 668 against 523 / 652 / 734; an optimisation step
 // on 1 / 2 / 3 views of 640x640 (1600 / 3200 / 4800): 1996 / 2139 / 2287
-// against 1205 / 1757 / 2235.  32-pixel bins (larger footprints, whose entries
+// against 1205 / 1757 / 2235.  The same blobs, degree 0, 2 / 4 views (2048 / 4096
+// tiles): accumulate of 3 channels 342 / 394 against 278 / 409, of 15 502 / 545
+// against 315 / 465; render of 3 323 / 354 against 287 / 400; a render's adjoint
+// of 3 548 / 568 against 468 / 698, of 8 655 / 680 against 361 / 471.  (Short
+// lists favour blocks longer: 16 views of 250x250, 4096 tiles, accumulate of 3
+// 735 against 581.)  32-pixel bins (larger footprints, whose entries
 // meet all four blocks, and four times the gathers): one mask channel on
 // 480x320 / 640x480 / 2 x 640x480 (600 / 1200 / 2400 tiles): 253 / 260 / 268
 // against 239 / 279 / 355.

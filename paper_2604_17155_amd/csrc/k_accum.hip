@@ -95,9 +95,9 @@ __device__ __forceinline__ uint32_t accumulate_tile(
     const float ly[2] = {tile_offset_row(lane, 0), tile_offset_row(lane, 1)};
 
     // The list is walked in chunks of 64 entries.  A chunk's records are
-    // gathered at once, one entry per lane, and broadcast entry by entry with
-    // v_readlane; the next chunk's gather (and the pair values of the one
-    // after) are in flight while a chunk is blended.
+    // gathered at once, one entry per lane, and put in LDS, from which every
+    // lane reads an entry's; the next chunk's gather (and the pair values of the
+    // one after) are in flight while a chunk is blended.
     auto load_pv = [&](uint32_t b) -> uint32_t {
         return b + lane < rg.y ? pair_vals[b + lane] : 0u;
     };

@@ -368,8 +368,10 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_hist(SortSource S, uint32_t n
 constexpr uint32_t kStAgg = 1u << 30, kStInc = 1u << 31, kStVal = kStAgg - 1u;
 constexpr uint32_t kLookbackSpins = 1u << 22;
 constexpr int kScanned = 0, kRaw = 1, kOneSweep = 2;
-// (a segment's tiles; of a pass of few tiles in all, that many: one view of 300k
-// items in 147 tiles of 2048 keys 88 us for its five passes, in 37 of 8192 99)
+// (a segment's tiles; of a pass of few tiles in all, that many.  us of a depth sort
+// of one view, counters added up by the blocks / scanned: tiles of 2048 keys against
+// scanned ones of 8192: 98 tiles 58 / 82, 157 73 / 84, 196 81 / 85, 293 113 / 92;
+// tiles of 8192: 86 97 / 107, 135 113 / 114, 159 119 / 114; of two views, 160 98 / 112)
 constexpr uint32_t kRawTiles = 64, kRawPass = 160;
 
 template <int MODE, int ITEMS>
@@ -730,6 +732,9 @@ void launch_group_sort(const ViewInfo* views, int n_views, uint32_t n_items, uin
 // view has several such runs, a second launch ranks each item among the others
 // (binary searches in the other runs, which L2 holds).  One block a view for
 // all its items left most of the chip idle: 9 views of 20000 items 77 -> 38 us.
+// Six runs are where the forms meet, us of the sort in runs / segments at 24576 items:
+// 1 view 38 / 43, 4 40 / 44, 9 44 / 45, 50 89 / 89; 28000 items in more runs, each of
+// which every item searches, 48 / 42, 47 / 44, 52 / 46, 115 / 88.
 // Larger views take four passes over segments, the first of which forms the
 // keys itself.  us a call, one sort of the whole batch -> by view: 2k
 // Gaussians x 8 views 220 -> 149 (13 launches of the call become one); 500k x
