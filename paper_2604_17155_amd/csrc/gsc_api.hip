@@ -406,6 +406,21 @@ ViewInfo make_view(const gsc_camera& c, int j, int64_t N, int bin) {
     return v;
 }
 
+// The target rows of nv views as disjoint ranges [first, second), in order.
+std::vector<std::pair<int64_t, int64_t>> target_rows(const ViewInfo* views, int nv) {
+    std::vector<std::pair<int64_t, int64_t>> rows;
+    for (int k = 0; k < nv; ++k)
+        rows.push_back({views[k].pixel_offset, views[k].pixel_offset + (int64_t)views[k].width * views[k].height});
+    std::sort(rows.begin(), rows.end());
+    size_t n = 0;
+    for (const auto& r : rows) {
+        if (n > 0 && r.first <= rows[n - 1].second) rows[n - 1].second = std::max(rows[n - 1].second, r.second);
+        else rows[n++] = r;
+    }
+    rows.resize(n);
+    return rows;
+}
+
 int bits_for(uint64_t n) {
     int b = 0;
     while (b < 32 && (1ull << b) < n) ++b;
@@ -1459,8 +1474,14 @@ gsc_status gsc_colorize_refine(gsc_ctx* ctx, const float* means, const float* sc
             StageTimer t(ctx, s, GSC_STAGE_BLEND);
             launch_view_colors(ctx->views.as<ViewInfo>(), nv, N, means, coeffs, C, sh_deg,
                                ctx->gamma.as<float>(), s);
+            const RenderResidual res{targets, tdtype == GSC_BF16};
+            const bool fused = residual_in_render(tl, C);
             launch_render(tl, ctx->gamma.as<float>(), C, bp, ctx->img.as<float>(), d_pass_counter, s,
-                          RenderResidual{targets, tdtype == GSC_BF16});
+                          fused ? res : RenderResidual{});
+            // (views may share target rows: each row once)
+            if (!fused)
+                for (const auto& r : target_rows(all.data() + v0, nv))
+                    launch_residual(res, r.first * C, (r.second - r.first) * C, ctx->img.as<float>(), s);
             uint32_t* queues = nullptr;
             if (tl.order != nullptr && (chunk & kChunkMfma)) {
                 GSC_HIP(ctx->queues.ensure(4 * (size_t)(kMaxC + 1)));
@@ -1469,7 +1490,6 @@ gsc_status gsc_colorize_refine(gsc_ctx* ctx, const float* means, const float* sc
             launch_accumulate(tl, ctx->img.as<float>(), GSC_F32, C, per_view, bp, ctx->vs.as<float>(),
                               d_pass_counter, nullptr, chunk, s, queues);
             GSC_LAUNCHED("refinement pass");
-            (void)v0;
             return GSC_OK;
         }, &key, single, false);
         if (st != GSC_OK) return st;

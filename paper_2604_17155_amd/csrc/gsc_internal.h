@@ -346,6 +346,10 @@ struct RenderResidual {
     int bf16 = 0;
 };
 int render_launches(const TileLists& tl, int C);
+// Whether launch_render should form the residual; else launch_residual does, over n
+// values of the images from `first`.
+bool residual_in_render(const TileLists& tl, int C);
+void launch_residual(const RenderResidual& res, int64_t first, int64_t n, float* images, hipStream_t s);
 void launch_render(const TileLists& tl, const float* gamma, int C, BlendParams bp, float* images,
                    unsigned long long* counter, hipStream_t s, const RenderResidual& res = {});
 

@@ -191,7 +191,7 @@ void launch_view_adjoint(const ViewInfo* views, int n_views, int64_t N, const fl
 // written.  Same tile walk and blend decisions as accumulate_tile.
 // res.y non-null: images[row][c] = y[row][c] - the blend (the residual of a
 // refinement pass, without a pass of its own over targets and images: 34 us of
-// 5.2 M pixels).
+// 5.2 M pixels; see residual_in_render).
 __device__ __forceinline__ float pixel_out(const RenderResidual& res, int64_t at, float img) {
     if (res.y == nullptr) return img;  // uniform
     return (res.bf16 ? load_target<true>(res.y, at) : load_target<false>(res.y, at)) - img;
@@ -376,6 +376,28 @@ static int render_channels(const TileLists& tl, int C) { return few_tiles(tl) &&
 int render_launches(const TileLists& tl, int C) {
     const int ch = render_channels(tl, C);
     return (C + ch - 1) / ch;
+}
+
+// Each launch of a render would read its own channels of the targets, so every line
+// of them: the stores form the residual where one launch writes all channels.  us a
+// call with two passes, in the stores / by a pass: 20 views of 512x512, 100k splats, 4
+// channels 2442 / 2459, 8 (two launches) 3286 / 3346, 16 7491 / 6560, 64 bf16 34286 /
+// 25079; 18 views of 531x382, 700 splats, 4 767 / 777, 8 1126 / 977, 64 15310 / 6187.
+bool residual_in_render(const TileLists& tl, int C) { return render_launches(tl, C) == 1; }
+
+// images = y - images over n values from `first`.
+__global__ __launch_bounds__(256) void k_residual(const void* __restrict__ y, int bf16, int64_t first, int64_t n,
+                                                  float* __restrict__ images) {
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+        const int64_t e = first + i;
+        images[e] = (bf16 ? load_target<true>(y, e) : load_target<false>(y, e)) - images[e];
+    }
+}
+
+void launch_residual(const RenderResidual& res, int64_t first, int64_t n, float* images, hipStream_t s) {
+    if (n <= 0) return;
+    const unsigned blocks = (unsigned)std::min<int64_t>((n + 255) / 256, 16384);
+    hipLaunchKernelGGL(k_residual, dim3(blocks), dim3(256), 0, s, res.y, res.bf16, first, n, images);
 }
 
 void launch_render(const TileLists& tl, const float* gamma, int C, BlendParams bp, float* images,
