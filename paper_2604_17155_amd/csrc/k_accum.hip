@@ -51,6 +51,10 @@ __device__ __forceinline__ uint32_t accumulate_tile(
     float2* __restrict__ lrec0) {
     constexpr int CCA = CC > 0 ? CC : 1;
     const TileGeom tg = tile_geom<BIN>(tile, views, n_views);
+    uint2 rg = ranges[tg.bin];
+    rg.x = (uint32_t)__builtin_amdgcn_readfirstlane((int)rg.x);
+    rg.y = (uint32_t)__builtin_amdgcn_readfirstlane((int)rg.y);
+    if (rg.x >= rg.y) return 0;  // no entries: the tile's targets are not read
     const ViewInfo& V = views[tg.vloc];
     // view fields read once (plain values: the conditions below need no branch)
     const int vw = V.width, vh = V.height;
@@ -77,9 +81,6 @@ __device__ __forceinline__ uint32_t accumulate_tile(
         }
     }
     alive = (uint32_t)__builtin_amdgcn_readfirstlane((int)alive);
-    uint2 rg = ranges[tg.bin];
-    rg.x = (uint32_t)__builtin_amdgcn_readfirstlane((int)rg.x);
-    rg.y = (uint32_t)__builtin_amdgcn_readfirstlane((int)rg.y);
     uint32_t cnt = 0;  // contributions of the lane's pixels
     // item = V.item_base + g (g local to the view's scene)
     const int64_t item_base = V.item_base;
@@ -281,10 +282,12 @@ __device__ __forceinline__ uint32_t accumulate_tile(
 // tiles come in the order `order` gives (nullptr: tile index order).
 // Waves per SIMD the register allocation is held to: the weights alone and one
 // channel fit seven (72 registers), two and three channels six (80; held to
-// seven they spill 18 values, 1.43 -> 1.54 ms on 300k Gaussians, 40 views);
-// wider ones are left alone.
+// seven they spill 18 values, 1.43 -> 1.54 ms on 300k Gaussians, 40 views), sixteen
+// four (127; left alone it takes 170 and runs at two waves: a call of 16 FP32
+// channels, 100k splats, 20 views of 512x512 1411 -> 1148 us); four and eight are
+// left alone.
 template <int CC>
-constexpr int acc_waves_per_simd() { return CC <= 1 ? 7 : (CC <= 3 ? 6 : 1); }
+constexpr int acc_waves_per_simd() { return CC <= 1 ? 7 : (CC <= 3 ? 6 : (CC == 16 ? 4 : 1)); }
 
 template <int CC, bool BF16, int BIN, bool DET>
 __global__ __launch_bounds__(64 * kTileWaves) __attribute__((amdgpu_waves_per_eu(acc_waves_per_simd<CC>()))) void k_accumulate(
