@@ -580,9 +580,17 @@ gsc_status bin_views(gsc_ctx* ctx, const ViewInfo* all, int v0, int nv,
     }
     const int gbits = bits_for(groups + 1);
     // per (window, group) row sixteen counts, then the windows' first groups
-    const uint64_t count_words = group_count_words(pairs, groups);
-    GSC_HIP(ctx->gcounts.ensure(4 * (count_words + group_windows(pairs)) + 64));
     size_t pscr = radix_scratch_words((uint32_t)pairs);
+    uint32_t window = group_window(pairs, groups);
+    if (const Arena* a = ctx->gcounts.arena) {
+        // (wide windows where the scratch could run out: its rows cost up to 17 bytes
+        // a pair.  What follows takes at most 16 bytes a pair and 64 of lists.)
+        const uint64_t rest = 4 * (group_count_words(pairs, groups, window) + group_windows(pairs, window)) +
+                              4 * std::max(pscr, scr) + 4 * tile_order_words((uint32_t)tiles) + 80 * pairs + 4096;
+        if (a->used + rest > a->cap) window = kWindowMax;
+    }
+    const uint64_t count_words = group_count_words(pairs, groups, window);
+    GSC_HIP(ctx->gcounts.ensure(4 * (count_words + group_windows(pairs, window)) + 64));
     GSC_HIP(ctx->sort_scratch.ensure(4 * std::max(pscr, scr) + 256));
     if (ctx->opt.schedule != GSC_SCHEDULE_GRID) GSC_HIP(ctx->order.ensure(4 * tile_order_words((uint32_t)tiles)));
     // the buffer in which the sorted keys end comes last (its place takes the
@@ -612,7 +620,7 @@ gsc_status bin_views(gsc_ctx* ctx, const ViewInfo* all, int v0, int nv,
     }
     launch_fill_u32(ctx->granges.as<uint32_t>(), 0u, (uint64_t)3 * groups, s);
     launch_tile_ranges(ctx->pkeys.as<uint32_t>(), (uint32_t)pairs, ng, ctx->granges.as<uint2>(), s);
-    const GroupLists gl{dviews, nv, ng, ctx->bin, (uint32_t)pairs, nullptr, ctx->granges.as<uint2>(),
+    const GroupLists gl{dviews, nv, ng, ctx->bin, (uint32_t)pairs, window, nullptr, ctx->granges.as<uint2>(),
                         ctx->pkeys.as<uint32_t>(), ctx->pvals.as<uint32_t>(), ctx->rec.as<float4>(),
                         ctx->pkeys_alt.as<uint32_t>(), ctx->pvals_alt.as<uint32_t>(), ctx->gcounts.as<uint32_t>(),
                         ctx->gcounts.as<uint32_t>() + count_words, ctx->granges.as<uint32_t>() + 2 * groups};
@@ -977,10 +985,11 @@ gsc_status plan_bin_batch(gsc_plan* P, const gsc_plan::Batch& b, hipStream_t s) 
         launch_fill_u32(P->granges.as<uint32_t>(), 0u, (uint64_t)3 * b.n_groups, s);
         launch_tile_ranges(P->pkeys.as<uint32_t>(), b.group_cap, b.n_groups, P->granges.as<uint2>(), s,
                            d_live);
-        const GroupLists gl{dv, b.nv, b.n_groups, P->bin, b.group_cap, d_live, P->granges.as<uint2>(),
+        const uint32_t window = group_window(b.group_cap, b.n_groups);
+        const GroupLists gl{dv, b.nv, b.n_groups, P->bin, b.group_cap, window, d_live, P->granges.as<uint2>(),
                             P->pkeys.as<uint32_t>(), P->pvals.as<uint32_t>(), P->rec.as<float4>(),
                             P->pkeys_alt.as<uint32_t>(), P->pvals_alt.as<uint32_t>(), P->gcounts.as<uint32_t>(),
-                            P->gcounts.as<uint32_t>() + group_count_words(b.group_cap, b.n_groups),
+                            P->gcounts.as<uint32_t>() + group_count_words(b.group_cap, b.n_groups, window),
                             P->granges.as<uint32_t>() + 2 * (size_t)b.n_groups};
         launch_group_masks(gl, P->bp, s);
         launch_scan(gl.totals, P->gfirst.as<uint32_t>(), b.n_groups, nullptr, P->sort_scratch.as<uint32_t>(), s);
@@ -1841,7 +1850,9 @@ gsc_status gsc_plan_create(gsc_ctx* ctx, const gsc_scene* scenes, int32_t n_scen
         P->max_group_pairs = std::max(P->max_group_pairs, b.group_cap);
         P->max_pairs = std::max(P->max_pairs, b.pair_cap);
         P->max_groups = std::max(P->max_groups, b.n_groups);
-        part_words = std::max(part_words, (size_t)(group_count_words(b.group_cap, b.n_groups) + group_windows(b.group_cap)));
+        const uint32_t window = group_window(b.group_cap, b.n_groups);
+        part_words = std::max(part_words, (size_t)(group_count_words(b.group_cap, b.n_groups, window) +
+                                                   group_windows(b.group_cap, window)));
         P->max_tiles = std::max(P->max_tiles, b.n_tiles);
         P->items_total += b.n_items;
         P->pairs_total += b.pair_cap;

@@ -153,7 +153,7 @@ void launch_count_bins(const ViewInfo* views, int n_views, uint32_t n_items, con
                        const uint32_t* rects, const float4* rec, BlendParams bp, int bin, unsigned long long* out, hipStream_t s);
 
 // The lists of the groups of a view batch (sorted (group, rank) pairs), turned
-// into bin lists in three steps.  The pairs are taken in windows of kWindow,
+// into bin lists in three steps.  The pairs are taken in windows of `window`,
 // one per wave, whatever groups they hold, so that lists of any length spread
 // evenly.  Window u's pairs of group g have row u + g of `counts` (unique, as
 // both grow along the pairs).
@@ -168,13 +168,28 @@ void launch_count_bins(const ViewInfo* views, int n_views, uint32_t n_items, con
 // Positions past cap are cut off; the entries that lose one are counted in
 // *overflow (if given).  n_dev (optional): the live pair count, clamped to
 // n_pairs.
-constexpr uint32_t kWindow = 256;
+//
+// A wave takes the groups of its window one after the other, each at the price of
+// a dependent load or two, so the window shrinks (256 to 4, a power of two) until
+// there are as many windows as groups, or as many as the chip has places for
+// waves; the rows then at most double, and a window holds one or two groups.
+// us a call of 1 channel, windows of 256 / by this rule: 10 splats in 20 views of
+// 512x512 653 / 205, 100 splats 365 / 247, 1000 in 20 of 1024x1024 635 / 578; at
+// 100k splats the windows are 256 wide again (789 / 789).  2048 or 32768 windows
+// in place of 8192: within 2% from 1 to 100k splats in five sets of views.
+constexpr uint32_t kWindowMax = 256, kWindowMin = 4, kWindowsWanted = 8192;
+inline uint32_t group_window(uint64_t pairs, uint64_t groups) {
+    uint32_t w = kWindowMax;
+    while (w > kWindowMin && pairs < (uint64_t)w * (groups < kWindowsWanted ? groups : kWindowsWanted)) w /= 2;
+    return w;
+}
 struct GroupLists {
     const ViewInfo* views;
     int n_views;
     uint32_t n_groups;
     int bin;
     uint32_t n_pairs;
+    uint32_t window;  // group_window(n_pairs, n_groups), or kWindowMax to save memory
     const uint32_t* n_dev;
     uint2* ranges;
     const uint32_t* keys;
@@ -186,8 +201,10 @@ struct GroupLists {
     uint32_t* first_group;  // per window
     uint32_t* totals;
 };
-inline uint64_t group_windows(uint64_t pairs) { return (pairs + kWindow - 1) / kWindow; }
-inline uint64_t group_count_words(uint64_t pairs, uint64_t groups) { return 16 * (group_windows(pairs) + groups); }
+inline uint64_t group_windows(uint64_t pairs, uint32_t window) { return (pairs + window - 1) / window; }
+inline uint64_t group_count_words(uint64_t pairs, uint64_t groups, uint32_t window) {
+    return 16 * (group_windows(pairs, window) + groups);
+}
 void launch_group_masks(const GroupLists& g, BlendParams bp, hipStream_t s);
 void launch_bin_ranges(const GroupLists& g, const uint32_t* first, uint2* ranges, uint32_t cap,
                        const uint32_t* total, unsigned long long* sum, hipStream_t s);

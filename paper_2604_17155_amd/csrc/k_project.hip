@@ -286,23 +286,15 @@ void launch_emit(const ViewInfo* views, int n_views, const uint32_t* offsets, co
 
 namespace {
 
-// The view of a group and the group's origin.
-struct GroupGeom {
-    int view;
-    int X0, Y0;        // first pixel
-    uint32_t bx, by;   // first bin column and row
-};
-template <int BIN>
-__device__ inline GroupGeom group_geom(uint32_t g, const ViewInfo* __restrict__ views, int n_views) {
+// The view of a group.
+__device__ inline int group_view(uint32_t g, const ViewInfo* __restrict__ views, int n_views) {
     int lo = 0, hi = n_views - 1;
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
         if (views[mid].group_base <= g) lo = mid;
         else hi = mid - 1;
     }
-    const uint32_t local = g - views[lo].group_base, gx = (uint32_t)views[lo].groups_x;
-    const uint32_t cx = local % gx, cy = local / gx;
-    return GroupGeom{lo, (int)(cx << group_shift<BIN>()), (int)(cy << group_shift<BIN>()), 4 * cx, 4 * cy};
+    return lo;
 }
 
 __device__ inline uint32_t live_pairs(const GroupLists& G) { return G.n_dev ? min(G.n_pairs, *G.n_dev) : G.n_pairs; }
@@ -318,9 +310,9 @@ template <int BIN>
 __global__ __launch_bounds__(256) void k_group_masks(GroupLists G, BlendParams bp) {
     const uint32_t lane = threadIdx.x & 63;
     const uint32_t u = (uint32_t)__builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
-    const uint32_t n = live_pairs(G), begin = u * kWindow;
+    const uint32_t n = live_pairs(G), begin = u * G.window;
     if (begin >= n) return;  // whole wave
-    const uint32_t end = min(begin + kWindow, n);
+    const uint32_t end = min(begin + G.window, n);
     // (every pair's key names a group; a lane past the window's end has 0xFFFFFFFF)
     // the next 64 pairs' records are in flight while 64 are masked
     auto pair = [&](uint32_t b, uint32_t& key, uint32_t& k) {
@@ -345,13 +337,22 @@ __global__ __launch_bounds__(256) void k_group_masks(GroupLists G, BlendParams b
     uint32_t c[16];  // its entries per bin (uniform)
 #pragma unroll
     for (int q = 0; q < 16; ++q) c[q] = 0u;
-    GroupGeom gg{};
-    int W = 1, H = 1;
+    int W = 1, H = 1, X0 = 0, Y0 = 0;
+    uint32_t base = 0, gx = 1, next = 0;  // the current view's first group, columns; the next view's first group
     auto enter = [&]() {
         if (g >= G.n_groups) return;
-        gg = group_geom<BIN>(g, G.views, G.n_views);
-        W = G.views[gg.view].width;
-        H = G.views[gg.view].height;
+        if (g >= next) {
+            const int v = group_view(g, G.views, G.n_views);
+            const ViewInfo& V = G.views[v];
+            W = V.width;
+            H = V.height;
+            base = V.group_base;
+            gx = (uint32_t)V.groups_x;
+            next = v + 1 < G.n_views ? G.views[v + 1].group_base : G.n_groups;
+        }
+        const uint32_t local = g - base, row = local / gx;
+        X0 = (int)((local - row * gx) << group_shift<BIN>());
+        Y0 = (int)(row << group_shift<BIN>());
     };
     auto leave = [&]() {  // writes the group's row
         if (g >= G.n_groups) return;
@@ -376,7 +377,7 @@ __global__ __launch_bounds__(256) void k_group_masks(GroupLists G, BlendParams b
             const bool mine = key == g;
             Footprint f{};
             const bool on = mine && g < G.n_groups && !(k & kVoidPair) && make_footprint(r0, r1, reach_q(r1.w, bp), H, f);
-            const uint2 m = group_masks<BIN>(on, f, gg.X0, gg.Y0, W);
+            const uint2 m = group_masks<BIN>(on, f, X0, Y0, W);
             if (mine) {
                 G.mask_lo[b + lane] = m.x;
                 G.mask_hi[b + lane] = m.y;
@@ -404,7 +405,7 @@ __global__ __launch_bounds__(256) void k_group_masks(GroupLists G, BlendParams b
 
 void launch_group_masks(const GroupLists& g, BlendParams bp, hipStream_t s) {
     if (g.n_groups == 0 || g.n_pairs == 0) return;
-    const dim3 grid((unsigned)((group_windows(g.n_pairs) + 3) / 4)), block(256);
+    const dim3 grid((unsigned)((group_windows(g.n_pairs, g.window) + 3) / 4)), block(256);
     if (g.bin == 32) hipLaunchKernelGGL(k_group_masks<32>, grid, block, 0, s, g, bp);
     else hipLaunchKernelGGL(k_group_masks<16>, grid, block, 0, s, g, bp);
 }
@@ -419,7 +420,7 @@ __global__ __launch_bounds__(256) void k_bin_ranges(GroupLists G, const uint32_t
     const uint32_t g = blockIdx.x, f = threadIdx.x & 15u, j = threadIdx.x >> 4;
     if (g == 0 && threadIdx.x == 0 && sum) atomicAdd(sum, (unsigned long long)*total);
     const uint2 rg = G.ranges[g];
-    const uint32_t u0 = rg.x / kWindow, rows = rg.x < rg.y ? (rg.y - 1) / kWindow - u0 + 1 : 0u;
+    const uint32_t u0 = rg.x / G.window, rows = rg.x < rg.y ? (rg.y - 1) / G.window - u0 + 1 : 0u;
     uint32_t* cnt = G.counts + ((size_t)u0 + g) * 16 + f;
     // thread j takes `per` consecutive rows
     const uint32_t per = (rows + 15u) / 16u, p0 = min(j * per, rows), p1 = min(p0 + per, rows);
@@ -451,9 +452,9 @@ __global__ __launch_bounds__(256) void k_bin_ranges(GroupLists G, const uint32_t
     }
     if (j != 0) return;
     if (f == 0 && rows != 0u) G.ranges[g].x = rg.y < live_pairs(G) ? G.keys[rg.y] : G.n_groups;
-    const GroupGeom gg = group_geom<BIN>(g, G.views, G.n_views);
-    const ViewInfo& V = G.views[gg.view];
-    const uint32_t bx = gg.bx + (f & 3u), by = gg.by + (f >> 2);
+    const ViewInfo& V = G.views[group_view(g, G.views, G.n_views)];
+    const uint32_t local = g - V.group_base, row = local / (uint32_t)V.groups_x;
+    const uint32_t bx = 4 * (local - row * (uint32_t)V.groups_x) + (f & 3u), by = 4 * row + (f >> 2);
     if (bx < (uint32_t)V.tiles_x && by < (uint32_t)V.tiles_y)
         ranges[V.tile_base + by * (uint32_t)V.tiles_x + bx] = make_uint2(min(start, cap), min(start + tot, cap));
 }
@@ -478,9 +479,9 @@ __global__ __launch_bounds__(256) void k_bin_lists(GroupLists G, uint32_t* __res
     __shared__ uint2 stage[4][1024];
     const uint32_t lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const uint32_t u = (uint32_t)__builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + w));
-    const uint32_t n = live_pairs(G), begin = u * kWindow;
+    const uint32_t n = live_pairs(G), begin = u * G.window;
     if (begin >= n) return;  // whole wave (no block barrier below)
-    const uint32_t end = min(begin + kWindow, n);
+    const uint32_t end = min(begin + G.window, n);
     uint32_t g = (uint32_t)__builtin_amdgcn_readfirstlane((int)G.first_group[u]);
     uint32_t at = begin;
     // the group lists the window meets, one after the other.  (Each names the next:
@@ -530,7 +531,7 @@ __global__ __launch_bounds__(256) void k_bin_lists(GroupLists G, uint32_t* __res
 
 void launch_bin_lists(const GroupLists& g, uint32_t* lists, uint32_t cap, uint32_t* overflow, hipStream_t s) {
     if (g.n_groups == 0 || g.n_pairs == 0) return;
-    const dim3 grid((unsigned)((group_windows(g.n_pairs) + 3) / 4)), block(256);
+    const dim3 grid((unsigned)((group_windows(g.n_pairs, g.window) + 3) / 4)), block(256);
     if (cap != 0xFFFFFFFFu) hipLaunchKernelGGL(k_bin_lists<true>, grid, block, 0, s, g, lists, cap, overflow);
     else hipLaunchKernelGGL(k_bin_lists<false>, grid, block, 0, s, g, lists, cap, overflow);
 }
