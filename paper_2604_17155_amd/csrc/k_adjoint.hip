@@ -48,17 +48,23 @@ __device__ __forceinline__ float quotient(float a, float d) {
 // linear in the channels, so chunk launches add their shares of dL/do; the
 // first chunk also carries -delta.
 // The forms of up to three channels are held to seven waves per SIMD (72
-// registers), as the forward accumulate (both adjoints 4.53 ms; six 4.58).
+// registers), as the forward accumulate (both adjoints 4.53 ms; six 4.58).  Of
+// four channels six (five with dL/dy), of eight four (20 views of 800x800, 100k
+// splats, eight channels and dL/dy, bins of 32: 1912 us at three, 1691 at four).
+//
+// A tile without entries reads no pixel values: of a few splats they were most of
+// the traffic (10 splats, 20 views of 1024x1024, 16 channels, dL/do alone: 617 ->
+// 70 us; 466 splats, 38 of 570x962, 3 channels with dL/dy: 306 -> 197).
 //
 // Bound by vector issue, as the forward walks: 300k Gaussians, 40 views of
 // 800x800, degree 3, 3 channels: colorize 3.78 -> 2.32 ms, render 3.73 -> 2.20
 // (before: a live flag per pixel carried through every step, the compiler's
 // division, one wave reduction and one atomic per entry).
-template <int CC>
-constexpr int adj_waves_per_simd() { return CC >= 1 && CC <= 3 ? 7 : 1; }
+template <int CC, bool GY>
+constexpr int adj_waves_per_simd() { return CC <= 3 ? 7 : (CC == 4 ? (GY ? 5 : 6) : (CC == 8 ? 4 : 1)); }
 
 template <int CC, bool BF16, bool GY, int BIN>
-__global__ __launch_bounds__(64 * kTileWaves) __attribute__((amdgpu_waves_per_eu(adj_waves_per_simd<CC>()))) void k_blend_adjoint(
+__global__ __launch_bounds__(64 * kTileWaves) __attribute__((amdgpu_waves_per_eu(adj_waves_per_simd<CC, GY>()))) void k_blend_adjoint(
     const ViewInfo* __restrict__ views, int n_views, uint32_t n_wt, const uint2* __restrict__ ranges,
     const uint32_t* __restrict__ pair_vals,
     const float4* __restrict__ rec, const uint32_t* __restrict__ items, const void* __restrict__ ypix, int C, int c_off,
@@ -76,6 +82,12 @@ __global__ __launch_bounds__(64 * kTileWaves) __attribute__((amdgpu_waves_per_eu
     if (wi >= n_wt) return;  // whole wave
     const uint32_t wt = queued_tile<BIN>(wi, order);  // blocks start in index order
     const TileGeom tg = tile_geom<BIN>(wt, views, n_views);
+    uint2 rg = ranges[tg.bin];
+    rg.x = (uint32_t)__builtin_amdgcn_readfirstlane((int)rg.x);
+    rg.y = (uint32_t)__builtin_amdgcn_readfirstlane((int)rg.y);
+    // (the pixels of a tile without entries are not read)
+    const bool grads = grad_o != nullptr && rg.x < rg.y;
+    if (!GY && !grads) return;
     const ViewInfo& V = views[tg.vloc];
     const int stride = C + 1;
     const bool first_chunk = c_off == 0;
@@ -101,11 +113,8 @@ __global__ __launch_bounds__(64 * kTileWaves) __attribute__((amdgpu_waves_per_eu
         const int64_t row = V.pixel_offset + (int64_t)iy * V.width + ix;
 #pragma unroll
         for (int c = 0; c < CC; ++c)
-            yv[k][c] = (inside[k] && grad_o && c_off + c < C) ? load_target<BF16>(ypix, row * C + c_off + c) : 0.0f;
+            yv[k][c] = (inside[k] && grads && c_off + c < C) ? load_target<BF16>(ypix, row * C + c_off + c) : 0.0f;
     }
-    uint2 rg = ranges[tg.bin];
-    rg.x = (uint32_t)__builtin_amdgcn_readfirstlane((int)rg.x);
-    rg.y = (uint32_t)__builtin_amdgcn_readfirstlane((int)rg.y);
 
     // Both passes walk the list the same way, so that they take the same
     // decisions.  A chunk of 64 entries is gathered at once, one entry per
@@ -229,7 +238,7 @@ __global__ __launch_bounds__(64 * kTileWaves) __attribute__((amdgpu_waves_per_eu
                 if (c_off + c < C) grad_y[row * C + c_off + c] = gy[k][c];
         }
     }
-    if (grad_o == nullptr) return;
+    if (!grads) return;
 
     // ---- pass 2: dL/dalpha per entry, reduced to dL/do per Gaussian -------
     // The step is pixel_step's, with the transmittance before the entry kept; a
@@ -292,6 +301,11 @@ __global__ __launch_bounds__(256) void k_blend_adjoint_blocks(
     const uint32_t wi = xcd_block(blockIdx.x, gridDim.x);
     if (wi >= n_tiles) return;
     const TileGeom tg = tile_geom<BIN>(queued_tile<BIN>(wi, order), views, n_views);
+    uint2 rg = ranges[tg.bin];
+    rg.x = (uint32_t)__builtin_amdgcn_readfirstlane((int)rg.x);
+    rg.y = (uint32_t)__builtin_amdgcn_readfirstlane((int)rg.y);
+    const bool grads = grad_o != nullptr && rg.x < rg.y;  // (as above)
+    if (!GY && !grads) return;
     const ViewInfo& V = views[tg.vloc];
     const int ix = tg.x0 + block_px(lane, (int)kq), iy = tg.y0 + block_py(lane, (int)kq);
     const bool inside = (ix < V.width) & (iy < V.height);
@@ -303,10 +317,7 @@ __global__ __launch_bounds__(256) void k_blend_adjoint_blocks(
     float yv[CC];
 #pragma unroll
     for (int c = 0; c < CC; ++c)
-        yv[c] = (inside && grad_o && c_off + c < C) ? load_target<BF16>(ypix, row * C + c_off + c) : 0.0f;
-    uint2 rg = ranges[tg.bin];
-    rg.x = (uint32_t)__builtin_amdgcn_readfirstlane((int)rg.x);
-    rg.y = (uint32_t)__builtin_amdgcn_readfirstlane((int)rg.y);
+        yv[c] = (inside && grads && c_off + c < C) ? load_target<BF16>(ypix, row * C + c_off + c) : 0.0f;
     const float tmin = uniform_in_vgpr(bp.t_min), amax = uniform_in_vgpr(bp.alpha_max);
     // an entry's adjoint colours, then delta (the first channel chunk carries it)
     auto load_ex = [&](bool own, uint32_t item, float4 (&ex)[EX]) {
@@ -359,7 +370,7 @@ __global__ __launch_bounds__(256) void k_blend_adjoint_blocks(
                 if (c_off + c < C) grad_y[row * C + c_off + c] = gy[c];
         }
     }
-    if (grad_o == nullptr) return;
+    if (!grads) return;
     // pass 2: dL/dalpha per entry, reduced to dL/do per Gaussian
     double P = 0.0;
     T = inside ? 1.0f : kOutsideT;
