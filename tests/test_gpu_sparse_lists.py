@@ -1,4 +1,4 @@
-"""Few splats in many groups of bins: a window of 256 pairs then spans whole views of
+"""Few splats in many groups of bins: a window of group pairs then spans whole views of
 groups without any.  The lists against the oracle, and the time of two splats far
 apart against two close together (the walk of a window must not pass over the groups
 between them one by one)."""
