@@ -21,8 +21,13 @@ namespace gsc {
 // kAdjoint) are an order more than the result if every item reads its own.  So
 // a thread owns a Gaussian and takes its views kTermViews at a time: the
 // block's coefficients go to LDS once, by coalesced loads of the caller's own
-// layout, and one LDS read serves kTermViews items.  Where the channels do not
-// fit, they are staged a few at a time for each set of views.
+// layout, and one LDS read serves kTermViews items.  Where the coefficients of a
+// block's threads' Gaussians do not fit, it takes fewer of them (down to four, 64
+// channels at L = 3) and several threads each, which share the views: the staging
+// stays one coalesced pass (a few channels at a time for each set of views, in
+// 12-byte pieces of 124-byte rows: 94k Gaussians, 34 views, L = 3, kAdjoint, 31
+// channels 8143 -> 810 us, 64 channels 17881 -> 1500; a thread an item 3222 and
+// 7454).
 // 300k Gaussians, 40 views, L = 3, C = 3: kColours 373 -> 117 us, kRenderAdjoint
 // 384 -> 111, kAdjoint 749 -> 211, and two or four transposes of the
 // coefficients (27-157 us) gone (before, a thread an item reading transposed
@@ -30,35 +35,23 @@ namespace gsc {
 enum TermMode { kColours, kRenderAdjoint, kAdjoint };
 constexpr int kTermBlock = 128, kTermViews = 4;
 constexpr int kTermLoads = 8;  // loads in flight a thread while staging
-// coefficients of one Gaussian in LDS at a time: 96 x 129 floats, three blocks a CU
-constexpr int kTermStage = 96;
+constexpr size_t kTermStage = 96 * (kTermBlock + 1);  // floats of LDS: three blocks a CU
 
-// Channels c0 .. c0+cw of the block's Gaussians: dst[(m * cw + c) * (kTermBlock + 1) + t].
-template <int NB>
-__device__ __forceinline__ void stage_terms(const float* __restrict__ src, int64_t g0, int n, int C, int c0,
-                                            int cw, float* dst) {
-    const int per = NB * cw;
+// The coefficients of n Gaussians from g0 (`per` each, contiguous):
+// dst[k * ld + t], the k-th of Gaussian g0 + t.
+__device__ __forceinline__ void stage_terms(const float* __restrict__ src, int64_t g0, int n, int per, int ld,
+                                            float* dst) {
     const int dq = kTermBlock / per, dr = kTermBlock - dq * per;
     int t = (int)threadIdx.x / per, k = (int)threadIdx.x - t * per;
-    if (cw == C) {  // contiguous
-        const float* from = src + g0 * per;
-        const int total = n * per;
-        for (int i0 = (int)threadIdx.x; i0 < total; i0 += kTermBlock * kTermLoads) {
-            float x[kTermLoads];
+    const float* from = src + g0 * per;
+    const int total = n * per;
+    for (int i0 = (int)threadIdx.x; i0 < total; i0 += kTermBlock * kTermLoads) {
+        float x[kTermLoads];
 #pragma unroll
-            for (int u = 0; u < kTermLoads; ++u) x[u] = from[min(i0 + u * kTermBlock, total - 1)];
+        for (int u = 0; u < kTermLoads; ++u) x[u] = from[min(i0 + u * kTermBlock, total - 1)];
 #pragma unroll
-            for (int u = 0; u < kTermLoads; ++u) {
-                if (i0 + u * kTermBlock < total) dst[k * (kTermBlock + 1) + t] = x[u];
-                t += dq;
-                k += dr;
-                if (k >= per) k -= per, ++t;
-            }
-        }
-    } else {
-        while (t < n) {
-            const int m = k / cw, c = k - m * cw;
-            dst[k * (kTermBlock + 1) + t] = src[(g0 + t) * (int64_t)(NB * C) + m * C + c0 + c];
+        for (int u = 0; u < kTermLoads; ++u) {
+            if (i0 + u * kTermBlock < total) dst[k * ld + t] = x[u];
             t += dq;
             k += dr;
             if (k >= per) k -= per, ++t;
@@ -66,19 +59,21 @@ __device__ __forceinline__ void stage_terms(const float* __restrict__ src, int64
     }
 }
 
-template <int L, int MODE>
+// GB Gaussians a block (a power of two; 0: `gaussians`), kTermBlock / GB threads each.
+template <int L, int MODE, int GB>
 __global__ __launch_bounds__(kTermBlock) void k_view_terms(
-    const ViewInfo* __restrict__ views, int n_views, int views_per_row, int64_t N,
+    const ViewInfo* __restrict__ views, int n_views, int views_per_row, int64_t N, int gaussians,
     const float* __restrict__ means, const float* __restrict__ coeffs, const float* __restrict__ bbar,
-    const float* __restrict__ rho, int C, int cw, float* __restrict__ out) {
+    const float* __restrict__ rho, int C, float* __restrict__ out) {
     constexpr int NB = (L + 1) * (L + 1);
-    constexpr int LD = kTermBlock + 1;
     extern __shared__ float stage[];
-    float* sc = stage;                  // c_g
-    float* sb = stage + NB * cw * LD;   // Bbar_g
-    const int64_t g0 = (int64_t)blockIdx.x * kTermBlock;
-    const int n = (int)min((int64_t)kTermBlock, N - g0);
-    const int t = (int)threadIdx.x;
+    const int gb = GB != 0 ? GB : gaussians, ld = gb + 1;
+    float* sc = stage;               // c_g
+    float* sb = stage + NB * C * ld; // Bbar_g
+    const int64_t g0 = (int64_t)blockIdx.x * gb;
+    const int n = (int)min((int64_t)gb, N - g0);
+    const int slots = kTermBlock / gb, slot = GB == kTermBlock ? 0 : (int)threadIdx.x / gb;  // (uniform: scalar loads)
+    const int t = GB == kTermBlock ? (int)threadIdx.x : (int)threadIdx.x & (gb - 1);
     const int64_t g = g0 + t;
     const bool own = t < n;
     const double px = own ? (double)means[3 * g] : 0.0, py = own ? (double)means[3 * g + 1] : 0.0,
@@ -86,54 +81,54 @@ __global__ __launch_bounds__(kTermBlock) void k_view_terms(
     const double rg = (MODE == kAdjoint && own) ? (double)rho[g] : 0.0;
     const int v_first = (int)blockIdx.y * views_per_row, v_end = min(n_views, v_first + views_per_row);
     const int stride = MODE == kColours ? C : C + 1;
-    for (int vb = v_first; vb < v_end; vb += kTermViews) {
-        float phi[kTermViews][NB];
-        float* dst[kTermViews];
-        double delta[kTermViews];
+    stage_terms(coeffs, g0, n, NB * C, ld, sc);
+    if constexpr (MODE == kAdjoint) stage_terms(bbar, g0, n, NB * C, ld, sb);
+    __syncthreads();
+    // VT views of the thread, from v on, `slots` apart
+    auto terms = [&](int v, auto vt) {
+        constexpr int VT = decltype(vt)::value;
+        float phi[VT][NB];
+        float* dst[VT];
+        double delta[VT];
 #pragma unroll
-        for (int j = 0; j < kTermViews; ++j) {
-            const ViewInfo& V = views[min(vb + j, v_end - 1)];
+        for (int j = 0; j < VT; ++j) {
+            const ViewInfo& V = views[min(v + j * slots, v_end - 1)];
             const int64_t k = g - V.g_offset;
-            const bool in = own && vb + j < v_end && k >= 0 && k < (int64_t)V.n_gauss;
+            const bool in = own && v + j * slots < v_end && k >= 0 && k < (int64_t)V.n_gauss;
             dst[j] = in ? out + ((int64_t)V.item_base + k) * stride : nullptr;
             const double dx = px - V.centre[0], dy = py - V.centre[1], dz = pz - V.centre[2];
             const double inv = 1.0 / sqrt(dx * dx + dy * dy + dz * dz);
             sh_eval<float, L>((float)(dx * inv), (float)(dy * inv), (float)(dz * inv), phi[j]);
             delta[j] = rg;
         }
-        for (int c0 = 0; c0 < C; c0 += cw) {
-            const int w = min(cw, C - c0);
-            if (vb == v_first || cw < C) {  // uniform over the block
-                __syncthreads();
-                stage_terms<NB>(coeffs, g0, n, C, c0, w, sc);
-                if constexpr (MODE == kAdjoint) stage_terms<NB>(bbar, g0, n, C, c0, w, sb);
-                __syncthreads();
+        for (int c = 0; c < C; ++c) {
+            float a[VT] = {}, b[VT] = {};
+#pragma unroll
+            for (int m = 0; m < NB; ++m) {
+                const float x = sc[(m * C + c) * ld + t];
+#pragma unroll
+                for (int j = 0; j < VT; ++j) a[j] = fmaf(x, phi[j][m], a[j]);
+                if constexpr (MODE == kAdjoint) {
+                    const float y = sb[(m * C + c) * ld + t];
+#pragma unroll
+                    for (int j = 0; j < VT; ++j) b[j] = fmaf(y, phi[j][m], b[j]);
+                }
             }
-            for (int c = 0; c < w; ++c) {
-                float a[kTermViews] = {}, b[kTermViews] = {};
 #pragma unroll
-                for (int m = 0; m < NB; ++m) {
-                    const float x = sc[(m * w + c) * LD + t];
-#pragma unroll
-                    for (int j = 0; j < kTermViews; ++j) a[j] = fmaf(x, phi[j][m], a[j]);
-                    if constexpr (MODE == kAdjoint) {
-                        const float y = sb[(m * w + c) * LD + t];
-#pragma unroll
-                        for (int j = 0; j < kTermViews; ++j) b[j] = fmaf(y, phi[j][m], b[j]);
-                    }
-                }
-#pragma unroll
-                for (int j = 0; j < kTermViews; ++j) {
-                    if constexpr (MODE == kAdjoint) delta[j] += (double)a[j] * (double)b[j];
-                    if (dst[j]) dst[j][c0 + c] = MODE == kAdjoint ? b[j] : a[j];
-                }
+            for (int j = 0; j < VT; ++j) {
+                if constexpr (MODE == kAdjoint) delta[j] += (double)a[j] * (double)b[j];
+                if (dst[j]) dst[j][c] = MODE == kAdjoint ? b[j] : a[j];
             }
         }
         if constexpr (MODE != kColours) {
 #pragma unroll
-            for (int j = 0; j < kTermViews; ++j)
+            for (int j = 0; j < VT; ++j)
                 if (dst[j]) dst[j][C] = MODE == kAdjoint ? (float)delta[j] : 0.0f;
         }
+    };
+    for (int vb = v_first; vb < v_end; vb += kTermViews * slots) {
+        if (v_end - vb > slots) terms(vb + slot, std::integral_constant<int, kTermViews>{});
+        else terms(vb + slot, std::integral_constant<int, 1>{});
     }
 }
 
@@ -142,20 +137,23 @@ namespace {
 template <int L, int MODE>
 void launch_terms(const ViewInfo* views, int n_views, int64_t N, const float* means, const float* coeffs,
                   const float* bbar, const float* rho, int C, float* out, hipStream_t s) {
-    constexpr int NB = (L + 1) * (L + 1);
-    const int sets = MODE == kAdjoint ? 2 : 1;
-    const int cw = std::min(C, kTermStage / (NB * sets));
-    const int64_t gx = (N + kTermBlock - 1) / kTermBlock;
+    const size_t per = (size_t)((L + 1) * (L + 1)) * (size_t)C * (MODE == kAdjoint ? 2 : 1);
+    int gb = kTermBlock;  // (64 channels of degree 3, two sets: four)
+    while (gb > 1 && per * (size_t)(gb + 1) > kTermStage) gb /= 2;
+    const int64_t gx = (N + gb - 1) / gb;
     // views split over grid rows where the Gaussians alone give under 4096
     // blocks (two waves each: eight a SIMD).  Each row stages the coefficients
     // again: 2344 blocks by 40 views take 117 us in one row, 127 in five
-    const int sets_of_views = (n_views + kTermViews - 1) / kTermViews;
+    const int set = kTermViews * (kTermBlock / gb), sets_of_views = (n_views + set - 1) / set;
     const int64_t rows = std::min<int64_t>(std::max<int64_t>(4096 / gx, 1), sets_of_views);
-    const int per_row = (int)((sets_of_views + rows - 1) / rows) * kTermViews;
+    const int per_row = (int)((sets_of_views + rows - 1) / rows) * set;
     dim3 grid((unsigned)gx, (unsigned)((n_views + per_row - 1) / per_row)), block(kTermBlock);
-    const size_t lds = sizeof(float) * (size_t)(sets * NB * cw) * (kTermBlock + 1);
-    hipLaunchKernelGGL((k_view_terms<L, MODE>), grid, block, lds, s, views, n_views, per_row, N, means, coeffs,
-                       bbar, rho, C, cw, out);
+#define GSC_TERMS(GBV)                                                                                    \
+    hipLaunchKernelGGL((k_view_terms<L, MODE, GBV>), grid, block, sizeof(float) * per * (size_t)(gb + 1), s, \
+                       views, n_views, per_row, N, gb, means, coeffs, bbar, rho, C, out)
+    if (gb == kTermBlock) GSC_TERMS(kTermBlock);
+    else GSC_TERMS(0);
+#undef GSC_TERMS
 }
 
 template <int MODE>
