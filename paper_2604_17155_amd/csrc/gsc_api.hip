@@ -1627,12 +1627,14 @@ gsc_status gsc_colorize_backward(gsc_ctx* ctx, const float* means, const float* 
     // 3. per view batch: adjoint colours, then the two-pass blend adjoint
     auto body = [&](int v0, int nv, const Binned& bn) -> gsc_status {
         (void)v0;
-        GSC_HIP(ctx->gamma.ensure(4 * (size_t)nv * (size_t)N * (size_t)(C + 1)));
+        const TileLists tl = tile_lists(ctx, nv, bn);
+        const int width = adjoint_channels(tl, C);
+        GSC_HIP(ctx->gamma.ensure(4 * (size_t)nv * (size_t)N * (size_t)beta_stride(C, width)));
         StageTimer t(ctx, s, GSC_STAGE_BLEND_ADJOINT);
-        launch_view_adjoint(ctx->views.as<ViewInfo>(), nv, N, means, coeffs, d_bbar, d_rho, C, sh_deg,
+        launch_view_adjoint(ctx->views.as<ViewInfo>(), nv, N, means, coeffs, d_bbar, d_rho, C, width, sh_deg,
                             ctx->gamma.as<float>(), s);
         GSC_LAUNCHED("view adjoint");
-        launch_blend_adjoint(tile_lists(ctx, nv, bn), targets, tdtype, C, ctx->gamma.as<float>(), bp,
+        launch_blend_adjoint(tl, targets, tdtype, C, ctx->gamma.as<float>(), bp,
                              grad_targets, grad_opacities, s);
         GSC_LAUNCHED("blend adjoint");
         return GSC_OK;
@@ -1696,12 +1698,14 @@ gsc_status gsc_render_backward(gsc_ctx* ctx, const float* means, const float* sc
             GSC_LAUNCHED("accumulate");
         }
         if (grad_opacities) {
-            GSC_HIP(ctx->gamma.ensure(4 * (size_t)nv * (size_t)N * (size_t)(C + 1)));
+            const TileLists tl = tile_lists(ctx, nv, bn);
+            const int width = adjoint_channels(tl, C);
+            GSC_HIP(ctx->gamma.ensure(4 * (size_t)nv * (size_t)N * (size_t)beta_stride(C, width)));
             StageTimer t(ctx, s, GSC_STAGE_BLEND_ADJOINT);
-            launch_view_adjoint(ctx->views.as<ViewInfo>(), nv, N, means, coeffs, nullptr, nullptr, C, sh_deg,
+            launch_view_adjoint(ctx->views.as<ViewInfo>(), nv, N, means, coeffs, nullptr, nullptr, C, width, sh_deg,
                                 ctx->gamma.as<float>(), s);
             GSC_LAUNCHED("view colours");
-            launch_blend_adjoint(tile_lists(ctx, nv, bn), grad_images, GSC_F32, C, ctx->gamma.as<float>(), bp,
+            launch_blend_adjoint(tl, grad_images, GSC_F32, C, ctx->gamma.as<float>(), bp,
                                  nullptr, grad_opacities, s);
             GSC_LAUNCHED("blend adjoint");
         }

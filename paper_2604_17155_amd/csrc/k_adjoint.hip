@@ -47,8 +47,8 @@ __device__ __forceinline__ float quotient(float a, float d) {
 }  // namespace
 
 // CC: channels of this launch (chunk [c_off, c_off + CC) of C).  dL/dw is
-// linear in the channels, so chunk launches add their shares of dL/do; the
-// first chunk also carries -delta.
+// linear in the channels, so chunk launches add their shares of dL/do, each with
+// its channels' part of delta.
 // The forms of up to three channels are held to seven waves per SIMD (72
 // registers), as the forward accumulate (both adjoints 4.53 ms; six 4.58).  Of
 // four channels six (five with dL/dy), of eight four (20 views of 800x800, 100k
@@ -91,8 +91,7 @@ __global__ __launch_bounds__(64 * kTileWaves) __attribute__((amdgpu_waves_per_eu
     const bool grads = grad_o != nullptr && rg.x < rg.y;
     if (!GY && !grads) return;
     const ViewInfo& V = views[tg.vloc];
-    const int stride = C + 1;
-    const bool first_chunk = c_off == 0;
+    const int stride = beta_stride(C, CC), part = C + c_off / CC;
     // dL/do of an entry goes to Gaussian g_offset + (item - item_base), the
     // item being named by the entry's record
     const int64_t g_shift = V.g_offset - (int64_t)V.item_base;
@@ -149,7 +148,7 @@ __global__ __launch_bounds__(64 * kTileWaves) __attribute__((amdgpu_waves_per_eu
             float RB[CC];
 #pragma unroll
             for (int c = 0; c < CC; ++c) RB[c] = (own && c_off + c < C) ? bl[c_off + c] : 0.0f;
-            const float RD = (own && first_chunk) ? -bl[C] : 0.0f;
+            const float RD = own ? -bl[part] : 0.0f;
             const uint32_t BL = own ? (entry_blocks<BIN>(pv, R0, R1, bp) & alive) : 0u;
             uint64_t todo = __builtin_amdgcn_ballot_w64(BL != 0u);
             srec1[w][lane] = R1;
@@ -313,21 +312,20 @@ __global__ __launch_bounds__(256) void k_blend_adjoint_blocks(
     const bool inside = (ix < V.width) & (iy < V.height);
     if (__builtin_amdgcn_ballot_w64(inside) == 0) return;  // whole wave
     const int64_t row = V.pixel_offset + (int64_t)iy * V.width + ix;
-    const int stride = C + 1;
-    const bool first_chunk = c_off == 0;
+    const int stride = beta_stride(C, CC), part = C + c_off / CC;
     const int64_t g_shift = V.g_offset - (int64_t)V.item_base;
     float yv[CC];
 #pragma unroll
     for (int c = 0; c < CC; ++c)
         yv[c] = (inside && grads && c_off + c < C) ? load_target<BF16>(ypix, row * C + c_off + c) : 0.0f;
     const float tmin = uniform_in_vgpr(bp.t_min), amax = uniform_in_vgpr(bp.alpha_max);
-    // an entry's adjoint colours, then delta (the first channel chunk carries it)
+    // an entry's adjoint colours, then the launch's part of delta
     auto load_ex = [&](bool own, uint32_t item, float4 (&ex)[EX]) {
         const float* bl = beta + (int64_t)item * stride;
         float v[4 * EX];
 #pragma unroll
         for (int c = 0; c < CC; ++c) v[c] = (own && c_off + c < C) ? bl[c_off + c] : 0.0f;
-        v[CC] = (own && first_chunk) ? bl[C] : 0.0f;
+        v[CC] = own ? bl[part] : 0.0f;
 #pragma unroll
         for (int x = 0; x < EX; ++x) ex[x] = make_float4(v[4 * x], v[4 * x + 1], v[4 * x + 2], v[4 * x + 3]);
     };
@@ -454,17 +452,23 @@ static void launch_badj_cc(const TileLists& tl, const void* ypix, int ydtype, in
 #undef GSC_BADJ
 }
 
+int adjoint_channels(const TileLists& tl, int C) {
+    if (few_tiles(tl)) return C <= 3 ? 3 : (C <= 7 ? 7 : 15);
+    return accumulate_chunk(C, GSC_F32);  // vector-lane channel chunks
+}
+
 template <bool GY>
 static void launch_badj(const TileLists& tl, const void* ypix, int ydtype, int C, const float* beta,
                         BlendParams bp, float* grad_y, float* grad_o, hipStream_t s) {
+    const int width = adjoint_channels(tl, C);
     if (few_tiles(tl)) {
-        if (C <= 3) launch_badj_blocks<1, GY>(tl, ypix, ydtype, C, beta, bp, grad_y, grad_o, s);
-        else if (C <= 7) launch_badj_blocks<2, GY>(tl, ypix, ydtype, C, beta, bp, grad_y, grad_o, s);
+        if (width == 3) launch_badj_blocks<1, GY>(tl, ypix, ydtype, C, beta, bp, grad_y, grad_o, s);
+        else if (width == 7) launch_badj_blocks<2, GY>(tl, ypix, ydtype, C, beta, bp, grad_y, grad_o, s);
         else launch_badj_blocks<4, GY>(tl, ypix, ydtype, C, beta, bp, grad_y, grad_o, s);
         return;
     }
 #define GSC_BA(CCV) launch_badj_cc<CCV, GY>(tl, ypix, ydtype, C, beta, bp, grad_y, grad_o, s)
-    switch (accumulate_chunk(C, GSC_F32)) {  // vector-lane channel chunks
+    switch (width) {
         case 1: GSC_BA(1); break;
         case 2: GSC_BA(2); break;
         case 3: GSC_BA(3); break;

@@ -12,9 +12,10 @@ namespace gsc {
 // Per-item terms of the blends, from the SH coefficients (batch item i is view
 // v's Gaussian g, items in their own order, phi = phi(dir_gv)):
 //   kColours        out[i*C + c]       = sum_m c_g[m][c] phi_m
-//   kRenderAdjoint  out[i*(C+1) + c]   the same, and 0 at C (delta of a render)
-//   kAdjoint        out[i*(C+1) + c]   = beta_c = sum_m Bbar_g[m][c] phi_m, and
-//                   out[i*(C+1) + C]   = delta = rho_g + sum_c beta_c (c_g^T phi)_c
+//   kRenderAdjoint  out[i*B + c]       the same, and 0 from C on (delta of a render)
+//   kAdjoint        out[i*B + c]       = beta_c = sum_m Bbar_g[m][c] phi_m, and
+//                   out[i*B + C + p]   = sum_c beta_c (c_g^T phi)_c over the p-th `width`
+//                   channels, plus rho_g for p = 0 (B = beta_stride(C, width))
 //
 // Bound by the writes (12-16 bytes an item at C = 3) and the FP64 direction;
 // the coefficients (108 bytes a Gaussian at L = 2, C = 3, twice that for
@@ -64,7 +65,7 @@ template <int L, int MODE, int GB>
 __global__ __launch_bounds__(kTermBlock) void k_view_terms(
     const ViewInfo* __restrict__ views, int n_views, int views_per_row, int64_t N, int gaussians,
     const float* __restrict__ means, const float* __restrict__ coeffs, const float* __restrict__ bbar,
-    const float* __restrict__ rho, int C, float* __restrict__ out) {
+    const float* __restrict__ rho, int C, int width, float* __restrict__ out) {
     constexpr int NB = (L + 1) * (L + 1);
     extern __shared__ float stage[];
     const int gb = GB != 0 ? GB : gaussians, ld = gb + 1;
@@ -80,7 +81,7 @@ __global__ __launch_bounds__(kTermBlock) void k_view_terms(
                  pz = own ? (double)means[3 * g + 2] : 0.0;
     const double rg = (MODE == kAdjoint && own) ? (double)rho[g] : 0.0;
     const int v_first = (int)blockIdx.y * views_per_row, v_end = min(n_views, v_first + views_per_row);
-    const int stride = MODE == kColours ? C : C + 1;
+    const int stride = MODE == kColours ? C : beta_stride(C, width);
     stage_terms(coeffs, g0, n, NB * C, ld, sc);
     if constexpr (MODE == kAdjoint) stage_terms(bbar, g0, n, NB * C, ld, sb);
     __syncthreads();
@@ -101,6 +102,7 @@ __global__ __launch_bounds__(kTermBlock) void k_view_terms(
             sh_eval<float, L>((float)(dx * inv), (float)(dy * inv), (float)(dz * inv), phi[j]);
             delta[j] = rg;
         }
+        int end = min(width, C), part = C;  // of the channels that share a delta
         for (int c = 0; c < C; ++c) {
             float a[VT] = {}, b[VT] = {};
 #pragma unroll
@@ -119,11 +121,16 @@ __global__ __launch_bounds__(kTermBlock) void k_view_terms(
                 if constexpr (MODE == kAdjoint) delta[j] += (double)a[j] * (double)b[j];
                 if (dst[j]) dst[j][c] = MODE == kAdjoint ? b[j] : a[j];
             }
-        }
-        if constexpr (MODE != kColours) {
+            if constexpr (MODE != kColours) {
+                if (c + 1 != end) continue;  // uniform
 #pragma unroll
-            for (int j = 0; j < VT; ++j)
-                if (dst[j]) dst[j][C] = MODE == kAdjoint ? (float)delta[j] : 0.0f;
+                for (int j = 0; j < VT; ++j) {
+                    if (dst[j]) dst[j][part] = MODE == kAdjoint ? (float)delta[j] : 0.0f;
+                    delta[j] = 0.0;
+                }
+                end = min(end + width, C);
+                ++part;
+            }
         }
     };
     for (int vb = v_first; vb < v_end; vb += kTermViews * slots) {
@@ -136,7 +143,7 @@ namespace {
 
 template <int L, int MODE>
 void launch_terms(const ViewInfo* views, int n_views, int64_t N, const float* means, const float* coeffs,
-                  const float* bbar, const float* rho, int C, float* out, hipStream_t s) {
+                  const float* bbar, const float* rho, int C, int width, float* out, hipStream_t s) {
     const size_t per = (size_t)((L + 1) * (L + 1)) * (size_t)C * (MODE == kAdjoint ? 2 : 1);
     int gb = kTermBlock;  // (64 channels of degree 3, two sets: four)
     while (gb > 1 && per * (size_t)(gb + 1) > kTermStage) gb /= 2;
@@ -150,7 +157,7 @@ void launch_terms(const ViewInfo* views, int n_views, int64_t N, const float* me
     dim3 grid((unsigned)gx, (unsigned)((n_views + per_row - 1) / per_row)), block(kTermBlock);
 #define GSC_TERMS(GBV)                                                                                    \
     hipLaunchKernelGGL((k_view_terms<L, MODE, GBV>), grid, block, sizeof(float) * per * (size_t)(gb + 1), s, \
-                       views, n_views, per_row, N, gb, means, coeffs, bbar, rho, C, out)
+                       views, n_views, per_row, N, gb, means, coeffs, bbar, rho, C, width, out)
     if (gb == kTermBlock) GSC_TERMS(kTermBlock);
     else GSC_TERMS(0);
 #undef GSC_TERMS
@@ -158,14 +165,14 @@ void launch_terms(const ViewInfo* views, int n_views, int64_t N, const float* me
 
 template <int MODE>
 void launch_terms_deg(int sh_deg, const ViewInfo* views, int n_views, int64_t N, const float* means,
-                      const float* coeffs, const float* bbar, const float* rho, int C, float* out,
+                      const float* coeffs, const float* bbar, const float* rho, int C, int width, float* out,
                       hipStream_t s) {
     if (N <= 0 || n_views <= 0) return;
     switch (sh_deg) {
-        case 0: launch_terms<0, MODE>(views, n_views, N, means, coeffs, bbar, rho, C, out, s); break;
-        case 1: launch_terms<1, MODE>(views, n_views, N, means, coeffs, bbar, rho, C, out, s); break;
-        case 2: launch_terms<2, MODE>(views, n_views, N, means, coeffs, bbar, rho, C, out, s); break;
-        default: launch_terms<3, MODE>(views, n_views, N, means, coeffs, bbar, rho, C, out, s); break;
+        case 0: launch_terms<0, MODE>(views, n_views, N, means, coeffs, bbar, rho, C, width, out, s); break;
+        case 1: launch_terms<1, MODE>(views, n_views, N, means, coeffs, bbar, rho, C, width, out, s); break;
+        case 2: launch_terms<2, MODE>(views, n_views, N, means, coeffs, bbar, rho, C, width, out, s); break;
+        default: launch_terms<3, MODE>(views, n_views, N, means, coeffs, bbar, rho, C, width, out, s); break;
     }
 }
 
@@ -173,16 +180,16 @@ void launch_terms_deg(int sh_deg, const ViewInfo* views, int n_views, int64_t N,
 
 void launch_view_colors(const ViewInfo* views, int n_views, int64_t N, const float* means,
                         const float* coeffs, int C, int sh_deg, float* gamma, hipStream_t s) {
-    launch_terms_deg<kColours>(sh_deg, views, n_views, N, means, coeffs, nullptr, nullptr, C, gamma, s);
+    launch_terms_deg<kColours>(sh_deg, views, n_views, N, means, coeffs, nullptr, nullptr, C, C, gamma, s);
 }
 
 void launch_view_adjoint(const ViewInfo* views, int n_views, int64_t N, const float* means,
-                         const float* coeffs, const float* bbar, const float* rho, int C, int sh_deg,
-                         float* beta, hipStream_t s) {
+                         const float* coeffs, const float* bbar, const float* rho, int C, int width,
+                         int sh_deg, float* beta, hipStream_t s) {
     if (bbar == nullptr)
-        launch_terms_deg<kRenderAdjoint>(sh_deg, views, n_views, N, means, coeffs, nullptr, nullptr, C, beta, s);
+        launch_terms_deg<kRenderAdjoint>(sh_deg, views, n_views, N, means, coeffs, nullptr, nullptr, C, width, beta, s);
     else
-        launch_terms_deg<kAdjoint>(sh_deg, views, n_views, N, means, coeffs, bbar, rho, C, beta, s);
+        launch_terms_deg<kAdjoint>(sh_deg, views, n_views, N, means, coeffs, bbar, rho, C, width, beta, s);
 }
 
 // images[row][c] = sum_g w_gp * gamma_gv[c]; every pixel of every tile is
