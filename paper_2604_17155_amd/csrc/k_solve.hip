@@ -626,10 +626,30 @@ __global__ __launch_bounds__(64) void k_fold_solve(const ViewInfo* __restrict__ 
 // Gaussian is observed when some view gave it weight.  Its views' weights are
 // loaded eight at a time (independent loads in flight together); the views
 // that gave it weight become its bits in `seen`.  Unobserved ones get their
-// outputs here (zeros; GSC_G_UNOBSERVED, w = 0); the observed ones are put into
-// one of kObsClasses classes by their number of views, most first, counted per
-// block and class, and listed class by class.
+// outputs here (zeros, a wave a row; GSC_G_UNOBSERVED, w = 0); the observed ones are
+// put into one of kObsClasses classes by their number of views, most first, counted
+// per block and class, and listed class by class.
 constexpr int kObsClasses = 64;
+
+// Past kObsSerial views the bits come from a launch of their own, a thread for 16
+// views of a Gaussian: a block of 1024 alone waits for its views one group of loads
+// after the other.  Fold and solve, 3 channels, us one launch / two: 4290 Gaussians
+// 166 views 106 / 61, 100k 40 views 60 / 55, 500 40 views 35 / 29, 20k 24 views
+// 31 / 31, 500 17 views 23 / 25.
+constexpr int kObsSerial = 24;
+__global__ __launch_bounds__(256) void k_obs_seen(const float* __restrict__ VS, int n_views, int64_t N, int stride,
+                                                  uint16_t* __restrict__ seen) {
+    const int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (g >= N) return;
+    const int v0 = 16 * (int)blockIdx.y;
+    float x[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) x[u] = v0 + u < n_views ? VS[((int64_t)(v0 + u) * N + g) * stride] : 0.0f;
+    uint32_t bits = 0;
+#pragma unroll
+    for (int u = 0; u < 16; ++u) bits |= (uint32_t)(x[u] > 0.0f) << u;
+    seen[g * (int64_t)gridDim.y + blockIdx.y] = (uint16_t)bits;  // (the lowest views first)
+}
 
 __global__ __launch_bounds__(1024) void k_obs_count(const float* __restrict__ VS, int n_views, int64_t N,
                                                     int stride, int64_t row, float* __restrict__ coeffs,
@@ -639,20 +659,23 @@ __global__ __launch_bounds__(1024) void k_obs_count(const float* __restrict__ VS
     if (threadIdx.x < (unsigned)kObsClasses) cnt[threadIdx.x] = 0u;
     __syncthreads();
     const int64_t g = (int64_t)blockIdx.x * 1024 + threadIdx.x;
+    uint32_t n = 0;
     if (g < N) {
         const int words = (n_views + 63) / 64;
-        uint32_t n = 0;
         for (int w = 0; w < words; ++w) {
             uint64_t bits = 0;
-            const int v1 = min(n_views, 64 * w + 64);
-            for (int v0 = 64 * w; v0 < v1; v0 += 8) {
-                float x[8];
+            if (n_views > kObsSerial) {  // uniform
+                bits = obs.seen[g * (int64_t)words + w];
+            } else {
+                for (int v0 = 0; v0 < n_views; v0 += 8) {
+                    float x[8];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) x[u] = v0 + u < v1 ? VS[((int64_t)(v0 + u) * N + g) * stride] : 0.0f;
+                    for (int u = 0; u < 8; ++u) x[u] = v0 + u < n_views ? VS[((int64_t)(v0 + u) * N + g) * stride] : 0.0f;
 #pragma unroll
-                for (int u = 0; u < 8; ++u) bits |= (uint64_t)(x[u] > 0.0f) << ((v0 + u) & 63);
+                    for (int u = 0; u < 8; ++u) bits |= (uint64_t)(x[u] > 0.0f) << (v0 + u);
+                }
+                obs.seen[g] = bits;
             }
-            obs.seen[g * (int64_t)words + w] = bits;
             n += (uint32_t)__popcll(bits);
         }
         uint8_t cls = 255;
@@ -660,12 +683,25 @@ __global__ __launch_bounds__(1024) void k_obs_count(const float* __restrict__ VS
             cls = (uint8_t)(kObsClasses - 1 - min((int)((uint64_t)n * kObsClasses / (uint64_t)(n_views + 1)), kObsClasses - 1));
             atomicAdd(&cnt[cls], 1u);
         } else {
-            for (int64_t i = 0; i < row; ++i) coeffs[g * row + i] = 0.0f;
             if (status) status[g] = GSC_G_UNOBSERVED;
             if (wout) wout[g] = 0.0f;
             if (rho) rho[g] = 0.0f;
         }
         obs.cls[g] = cls;
+    }
+    // Rows of zeros: short ones by their threads, others by the wave, one after the
+    // other (a thread a row stores 4 bytes of 64 lines at a time: 250k rows of 1024
+    // floats 2096 -> 747 us with the solve, of 27 76 -> 50; of 12 42 and 40, but 19
+    // and 21 of 5k).
+    const bool none = g < N && n == 0u;
+    if (row < 16) {
+        for (int64_t i = 0; none && i < row; ++i) coeffs[g * row + i] = 0.0f;
+    } else {
+        const int lane = (int)threadIdx.x & 63;
+        for (uint64_t m = __builtin_amdgcn_ballot_w64(none); m != 0; m &= m - 1) {
+            float* out = coeffs + (g - lane + __builtin_ctzll(m)) * row;
+            for (int64_t i = lane; i < row; i += 64) out[i] = 0.0f;
+        }
     }
     __syncthreads();
     if (threadIdx.x < (unsigned)kObsClasses) obs.counts[(size_t)threadIdx.x * gridDim.x + blockIdx.x] = cnt[threadIdx.x];
@@ -707,6 +743,9 @@ static ObsList launch_obs_list(const float* VS, int n_views, int64_t N, int stri
     uint32_t* total = scr + scan_scratch_words((uint64_t)kObsClasses * nblk);
     o.n_list = total;
     o.cls = reinterpret_cast<uint8_t*>(total + 2);
+    if (n_views > kObsSerial)
+        hipLaunchKernelGGL(k_obs_seen, dim3((unsigned)((N + 255) / 256), (unsigned)(4 * words)), dim3(256), 0, s, VS,
+                           n_views, N, stride, reinterpret_cast<uint16_t*>(o.seen));
     hipLaunchKernelGGL(k_obs_count, dim3(nblk), dim3(1024), 0, s, VS, n_views, N, stride, row, coeffs, status, wout,
                        rho, o);
     launch_scan(o.counts, o.counts, kObsClasses * nblk, total, scr, s);
