@@ -922,6 +922,15 @@ void plan_number_views(gsc_plan* P) {
     }
 }
 
+// Whether an untuned plan's accumulate takes its tiles from a queue: the form of 33 to
+// 64 channels past one round of its blocks.  us a launch, grid / queue, 64 channels:
+// 20 views of 512x512, 20k splats 838 / 621, 100k 1044 / 807; 20 of 960x540, 500k
+// 2334 / 1491; 100 of 128x128 (6400 tiles), 5000 409 / 419; 4 of 256x256 (1024) 210 /
+// 225.  (The others are faster as a grid, 32 channels of 500k splats 2262 / 2555.)
+bool plan_queue(const gsc_plan* P, int chunk) {
+    return chunk_channels(chunk) == 64 && wave_tiles(P->max_tiles, P->bin) > kPersistentBlocks;
+}
+
 gsc_status plan_accumulate(gsc_plan* P, const gsc_plan::Batch& b, const void* targets, int tdtype,
                            int chunk, bool persistent, hipStream_t s) {
     unsigned long long* d_counter = reinterpret_cast<unsigned long long*>(P->misc.p);
@@ -1034,15 +1043,14 @@ gsc_status plan_run(gsc_plan* P, const void* targets, int tdtype, const double* 
     launch_fill_u32(P->vs.as<uint32_t>(), 0u, P->vs_slots * (uint64_t)(P->C + 1), s);
     launch_cov3d(P->means, P->opac, P->scales, P->quats, P->cov.as<float>(), P->n_total, s);
     GSC_LAUNCHED("cov3d");
-    const int chunk = P->acc_chunk ? P->acc_chunk : P->ctx->opt.accumulate_variant;
+    const int chunk = resolve_chunk(P->acc_chunk ? P->acc_chunk : P->ctx->opt.accumulate_variant, P->C, tdtype);
+    const bool queue = P->acc_chunk ? P->acc_persistent : plan_queue(P, chunk);
     for (const auto& b : P->batches) {
         gsc_status st = plan_bin_batch(P, b, s);
         if (st != GSC_OK) return st;
-        if ((st = plan_accumulate(P, b, targets, tdtype, chunk, P->acc_persistent, s)) != GSC_OK)
-            return st;
+        if ((st = plan_accumulate(P, b, targets, tdtype, chunk, queue, s)) != GSC_OK) return st;
     }
-    return plan_solve(P, split_sums(P->per_view, tdtype, P->C, resolve_chunk(chunk, P->C, tdtype)), lam, coeffs,
-                      status, s);
+    return plan_solve(P, split_sums(P->per_view, tdtype, P->C, chunk), lam, coeffs, status, s);
 }
 
 }  // namespace
@@ -1924,12 +1932,12 @@ gsc_status gsc_plan_autotune(gsc_plan* plan, const void* targets, int32_t tdtype
     std::vector<int> pool;
     if (plan->C <= (tdtype == GSC_BF16 ? 15 : 7)) pool.push_back(kChunkPacked);
     if (tdtype == GSC_BF16)  // matrix-core forms up to the channels needed
-        for (int ch : {16, 32, 64})
-            if (ch < plan->C + 16) pool.push_back(kChunkMfma | ch);
+        for (int ch : {16, 32, 64})  // (64 is the default past 32)
+            if (ch < plan->C + 16 || (ch == 64 && plan->C > 32)) pool.push_back(kChunkMfma | ch);
     for (int c : {accumulate_chunk(plan->C, GSC_F32), 16, 8, 4}) pool.push_back(c);
     for (int c : pool)
         if (std::find(chunks.begin(), chunks.end(), c) == chunks.end() &&
-            chunk_channels(c) <= std::max(4, plan->C + ((c & kChunkMfma) ? 15 : 0)))
+            chunk_channels(c) <= std::max(4, plan->C + ((c & kChunkMfma) ? 31 : 0)))
             chunks.push_back(c);
     std::vector<int> cand;  // chunk | persistent << 8
     for (int c : chunks)
@@ -2006,9 +2014,10 @@ gsc_status gsc_plan_get_info(gsc_plan* plan, gsc_plan_info* out) {
     out->items = plan->items_total;
     out->pair_capacity = plan->pairs_total;
     out->bin_size = plan->bin;
-    const int chosen = plan->acc_chunk ? plan->acc_chunk : plan->ctx->opt.accumulate_variant;
-    out->accumulate_variant = resolve_chunk(chosen, plan->C, plan->last_tdtype) |
-                              (plan->acc_persistent ? 256 : 0);
+    const int chosen = resolve_chunk(plan->acc_chunk ? plan->acc_chunk : plan->ctx->opt.accumulate_variant, plan->C,
+                                     plan->last_tdtype);
+    const bool queue = plan->acc_chunk ? plan->acc_persistent : plan_queue(plan, chosen);
+    out->accumulate_variant = chosen | (queue ? 256 : 0);
     for (int i = 0; i < 8; ++i) {
         out->tuned_variant[i] = plan->tune_variant[i];
         out->tuned_ms[i] = plan->tune_ms[i];
