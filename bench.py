@@ -96,13 +96,16 @@ MEASURED_TRAFFIC = {
     # HBM bytes per accumulate launch: FETCH_SIZE x 2 + WRITE_SIZE x 1 (the
     # factors a plain 256 MiB device copy gives), averaged over the launches
     # of one step; valid while the accumulate's sources hash to "sources"
-    "relight": {"bytes": 1.09e+09, "sources": "a037dfafd9481a1b"},
-    "features": {"bytes": 2.159e+10, "sources": "a037dfafd9481a1b"},
-    "batched": {"bytes": 5.645e+09, "sources": "a037dfafd9481a1b"},
+    "relight": {"bytes": 1.043e+09, "sources": "42ca999b67275e96"},
+    "features": {"bytes": 2.130e+10, "sources": "42ca999b67275e96"},
+    "batched": {"bytes": 5.645e+09, "sources": "42ca999b67275e96"},
 }
-ACCUMULATE_SOURCES = ("paper_2604_17155_amd/csrc/k_accum.hip", "paper_2604_17155_amd/csrc/wave_ops.h",
-                      "paper_2604_17155_amd/csrc/k_sort.hip",    # the tile order
-                      "paper_2604_17155_amd/csrc/gsc_api.hip")   # the launch shape
+ACCUMULATE_SOURCES = tuple("paper_2604_17155_amd/csrc/" + f for f in (
+    "k_accum.hip", "wave_ops.h", "footprint.h",
+    "k_project.hip",       # the lists
+    "k_sort.hip",          # the tile order
+    "gsc_internal.h",      # the rules of forms and shapes
+    "gsc_api.hip"))        # the launch shape
 
 
 def accumulate_sources_digest() -> str:
